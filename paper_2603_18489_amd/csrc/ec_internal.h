@@ -223,8 +223,10 @@ int vocab_reduce_parts(int V);
 // logits [n_rows, V] with row stride ld -> partials [n_rows][vocab_reduce_parts(V)]
 void launch_vocab_reduce(const float* logits, int n_rows, int V, size_t ld, float4* partials,
                          hipStream_t s);
-// partials -> stats [n_rows] (token id as float, confidence, entropy, max logit)
-void launch_row_stats(const float4* partials, int nparts, int n_rows, float4* stats, hipStream_t s);
+// logits -> stats [n_rows] (token id as float, confidence, entropy, max logit); partials: scratch for
+// n_rows * vocab_reduce_parts(V) tuples
+void launch_row_stats(const float* logits, int n_rows, int V, size_t ld, float4* partials,
+                      float4* stats, hipStream_t s);
 void launch_decide(const DecideArgs& a, int B, hipStream_t s);
 void launch_init_state(int* x, uint8_t* masked, int* hist, DevState* st, const int* prompt_dev,
                        int P, int N, int mask_id, hipStream_t s);

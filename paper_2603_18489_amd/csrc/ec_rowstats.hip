@@ -31,8 +31,7 @@ int check_args(const float* logits, int rows, int vocab, size_t ld, float* stats
 int run(const float* logits, int rows, int vocab, size_t ld, float* stats, float4* partials,
         hipStream_t s) {
   if (rows == 0) return EC_OK;
-  launch_vocab_reduce(logits, rows, vocab, ld, partials, s);
-  launch_row_stats(partials, vocab_reduce_parts(vocab), rows, (float4*)stats, s);
+  launch_row_stats(logits, rows, vocab, ld, partials, (float4*)stats, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return rs_fail(EC_ERR_HIP, std::string("row statistics kernels: ") + hipGetErrorString(e));
   return EC_OK;

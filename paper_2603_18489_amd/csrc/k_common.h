@@ -58,6 +58,32 @@ __device__ __forceinline__ float other_row(float x) {
   return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
 }
 
+// ---- whole-wave reductions without LDS: four DPP exchanges inside each row of 16 lanes (xor 1,
+// xor 2, mirror of 8, mirror of 16), then the two lane swaps.  Every lane ends with the same bits.
+template <int CTRL> __device__ __forceinline__ int dpp_i(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_f(float x) {
+  return __int_as_float(dpp_i<CTRL>(__float_as_int(x)));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v += dpp_f<0xB1>(v); v += dpp_f<0x4E>(v); v += dpp_f<0x141>(v); v += dpp_f<0x140>(v);
+  v += other_row(v);
+  return v + other_half(v);
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = fmaxf(v, dpp_f<0xB1>(v)); v = fmaxf(v, dpp_f<0x4E>(v));
+  v = fmaxf(v, dpp_f<0x141>(v)); v = fmaxf(v, dpp_f<0x140>(v));
+  v = fmaxf(v, other_row(v));
+  return fmaxf(v, other_half(v));
+}
+__device__ __forceinline__ int wave_min_dpp(int v) {
+  v = min(v, dpp_i<0xB1>(v)); v = min(v, dpp_i<0x4E>(v));
+  v = min(v, dpp_i<0x141>(v)); v = min(v, dpp_i<0x140>(v));
+  v = min(v, __float_as_int(other_row(__int_as_float(v))));
+  return min(v, __float_as_int(other_half(__int_as_float(v))));
+}
+
 template <typename T> __device__ __forceinline__ float load_f32(const T* p);
 template <> __device__ __forceinline__ float load_f32<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float load_f32<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }

@@ -33,22 +33,49 @@ __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
   return r;
 }
 
-__device__ __forceinline__ void vt_push(VTuple& v, float z, int idx) {
-  if (z == -INFINITY) return;  // probability 0 contributes 0 (0 ln 0 := 0)
-  if (z > v.m) {  // new maximum: re-base what was accumulated so far
-    if (v.s != 0.f) {
-      float d = v.m - z, e = expf(d);
-      v.t = e * (v.t + d * v.s);
-      v.s = v.s * e;
+// Tuple of NE * 64 consecutive logits held by one wave (lane l: elements first + 64 u + l, -inf for
+// those past the end).  The maximum and its lowest index come first, so every logit then costs one
+// exponential and no branch.  A logit of -inf has probability 0 and contributes 0 (0 ln 0 := 0); a
+// NaN makes the sums NaN.  All lanes return the same tuple.
+template <int NE>
+__device__ __forceinline__ VTuple vt_of_wave(const float (&z)[NE], int first) {
+  const int lane = threadIdx.x & 63;
+  float m = z[0];
+#pragma unroll
+  for (int u = 1; u < NE; ++u) m = fmaxf(m, z[u]);
+  VTuple v;
+  v.m = wave_max_dpp(fmaxf(m, -INFINITY));   // (a lane of NaNs must not hand one on)
+  if (!(fabsf(v.m) < INFINITY)) {
+    // Nothing finite (all -inf or NaN), or a +inf: not a distribution, unless the +inf is alone.
+    int n_inf = 0, n_other = 0;
+    v.idx = INT_MAX;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      const bool top = z[u] == INFINITY;
+      n_inf += top;
+      n_other += !top && z[u] != -INFINITY;
+      if (top) v.idx = min(v.idx, first + u * 64 + lane);
     }
-    v.m = z;
-    v.idx = idx;
-    v.s += 1.f;
-  } else {
-    float d = z - v.m, e = expf(d);
-    v.s += e;
-    v.t += e * d;
+    v.idx = wave_min_dpp(v.idx);
+    n_inf = (int)wave_sum_dpp((float)n_inf);
+    n_other = (int)wave_sum_dpp((float)n_other);
+    v.s = n_other > 0 || n_inf > 1 ? __builtin_nanf("") : (float)n_inf;
+    v.t = n_other > 0 || n_inf > 1 ? __builtin_nanf("") : 0.f;
+    return v;
   }
+  int u_first = NE;
+  float s = 0.f, t = 0.f;
+#pragma unroll
+  for (int u = NE - 1; u >= 0; --u) {
+    u_first = z[u] == v.m ? u : u_first;
+    const float d = z[u] - v.m, e = expf(d);
+    s += e;
+    t = fmaf(e, fmaxf(d, -1e30f), t);        // (-inf: e = 0; a NaN is in e)
+  }
+  v.idx = wave_min_dpp(u_first < NE ? first + u_first * 64 + lane : INT_MAX);
+  v.s = wave_sum_dpp(s);
+  v.t = wave_sum_dpp(t);
+  return v;
 }
 
 __device__ __forceinline__ VTuple vt_shfl_down(const VTuple& v, int o) {
@@ -60,15 +87,6 @@ __device__ __forceinline__ VTuple vt_shfl_down(const VTuple& v, int o) {
   return r;
 }
 
-// xor-shuffle of a whole tuple
-__device__ __forceinline__ VTuple vt_shfl_xor(const VTuple& v, int o) {
-  VTuple r;
-  r.m = __shfl_xor(v.m, o, 64);
-  r.idx = __shfl_xor(v.idx, o, 64);
-  r.s = __shfl_xor(v.s, o, 64);
-  r.t = __shfl_xor(v.t, o, 64);
-  return r;
-}
 __device__ __forceinline__ float4 vt_pack(const VTuple& v) {
   return make_float4(v.m, __int_as_float(v.idx), v.s, v.t);
 }

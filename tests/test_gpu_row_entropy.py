@@ -62,3 +62,32 @@ def test_row_entropy_closed_forms():
     assert s[3, 0] == 123 and s[3, 1] == 1.0 and s[3, 2] == 0.0
     # deterministic: the same input gives the same bits
     assert np.array_equal(s, ec.row_entropy(z).cpu().numpy())
+
+
+@pytest.mark.parametrize("rows,V,pad", [(1, 2047, 0), (3, 2048, 1), (2, 2049, 0), (5, 16383, 3),
+                                        (128, 16384, 0), (4, 16385, 0), (2, 163839, 1)])
+def test_row_entropy_part_edges_and_values_without_a_distribution(rows, V, pad):
+    """Part boundaries (2048 logits), both sides of the one-launch limit (16384 logits), rows that
+    start at any 4-byte address; -inf, NaN and +inf logits.  Bounds as above: float32 sums."""
+    rng = np.random.default_rng(V)
+    z = (rng.standard_normal((rows, V)) * 6.0).astype(np.float32)
+    z[0, 1::2] = -np.inf                      # probability 0
+    z[-1, V - 1] = z[-1].max() + 2.0          # the maximum in the last part's tail
+    buf = torch.zeros((rows, V + pad), dtype=torch.float32, device="cuda")
+    zt = buf[:, :V]
+    zt.copy_(torch.from_numpy(z))
+    got = ec.row_entropy(zt).cpu().numpy().astype(np.float64)
+    ref = oracle_stats(z)
+    assert np.array_equal(got[:, 0], ref[:, 0]) and np.array_equal(got[:, 3], ref[:, 3])
+    assert np.abs(got[:, 1] / ref[:, 1] - 1.0).max() <= 4e-6
+    assert np.abs(got[:, 2] - ref[:, 2]).max() <= 4e-6 * math.log(V)
+    zt[0, 5] = float("nan")                   # a NaN: NaN statistics, the others untouched
+    s = ec.row_entropy(zt).cpu().numpy()
+    assert np.isnan(s[0, 1]) and (rows == 1 or np.array_equal(s[1:], got[1:].astype(np.float32)))
+    zt[0, :] = float("nan")                   # no maximum at all: no token either
+    s = ec.row_entropy(zt).cpu().numpy()
+    assert np.isnan(s[0, 1]) and not 0 <= s[0, 0] < V
+    zt[0, :] = -float("inf")                  # one +inf among -inf: certain
+    zt[0, V // 2] = float("inf")
+    s = ec.row_entropy(zt).cpu().numpy()
+    assert s[0, 0] == V // 2 and s[0, 1] == 1.0 and s[0, 2] == 0.0
