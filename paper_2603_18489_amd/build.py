@@ -25,7 +25,7 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-MFMA_SOURCES = ["k_gemm_bf16.hip", "k_attn_mfma.hip"]
+MFMA_SOURCES = ["k_gemm_bf16.hip", "k_attn_mfma.hip", "k_gemm_f32.hip", "k_attn.hip"]
 
 
 def check_no_masked_mfma(hipcc: str) -> None:

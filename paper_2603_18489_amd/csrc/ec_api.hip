@@ -52,7 +52,7 @@ struct Buffers {
   char* kv;  // [L][2] planes; a plane holds every sequence's [Hkv][keys][hd] slabs, storage type
   size_t kv_plane;  // elements per plane
   // activations
-  float* h; void* u; float* qkv; void* q; void* attn; float* gu; void* act; void* u_lm;
+  float* h; void* u; float* qkv; void* q; void* attn; void* act; void* u_lm;
   float* logits; float4* partials;
   // bf16 only: row sums of squares [2L+1][kSumSlots][sumsq_stride] (44.20 fixed point), packed matrices
   unsigned long long* sumsq; int sumsq_stride;
@@ -129,7 +129,6 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.qkv = c.take<float>(R * (nq + 2 * nkv));
   b.q = c.take<char>(R * nq * es);
   b.attn = c.take<char>(R * nq * es);
-  b.gu = c.take<float>(m.dtype == EC_F32 ? R * 2 * m.d_ffn : 1);
   b.act = c.take<char>(R * m.d_ffn * es);
   b.u_lm = c.take<char>(BL16 * m.d_model * es);
   b.logits = c.take<float>(BL * m.vocab);
@@ -414,40 +413,42 @@ int forward_f32(ec_ctx* c, int mode, int M, int n_mb) {
   Buffers& b = c->b;
   hipStream_t s = c->stream;
   const int d = m.d_model, F = m.d_ffn, hd = m.head_dim, T = c->g.T[0];
-  const int nq = m.n_heads * hd, nkv = m.n_kv_heads * hd, nqkv = nq + 2 * nkv;
+  const int nq = m.n_heads * hd, nkv = m.n_kv_heads * hd;
   const int* rows = (mode == EC_FULL) ? nullptr : b.rows_partial;
   const int* lm_sel = (mode == EC_FULL) ? b.mb_pos : b.mb_idx;
-  float* u = (float*)b.u; float* q = (float*)b.q; float* attn = (float*)b.attn;
-  float* act = (float*)b.act; float* u_lm = (float*)b.u_lm;
+  float* q = (float*)b.q; float* attn = (float*)b.attn; float* act = (float*)b.act;
   auto W = [](const void* p) { return (const float*)p; };
+  auto gemm = [&](const float* A, const int* sel, int n_rows, const void* w0, int N, int K,
+                  const void* gain, float* C, int ldc) {
+    F32Gemm g{};
+    g.A = A; g.sel = sel; g.M = n_rows; g.N = N; g.K = K; g.W[0] = W(w0); g.gain = W(gain);
+    g.eps = m.rms_eps; g.scale = m.logit_scale; g.C = C; g.ldc = ldc;
+    g.rows = rows; g.cs = b.rope_cs; g.Hq = m.n_heads; g.Hkv = m.n_kv_heads; g.hd = hd;
+    return g;
+  };
 
   { Scope p(c, EC_K_EMBED); launch_embed_f32(W(c->w.tok_emb), b.x, rows, M, d, m.vocab, b.h, s); }
   for (int l = 0; l < m.n_layers; ++l) {
     float* kc = (float*)kv_ptr(c, l, 0); float* vc = (float*)kv_ptr(c, l, 1);
-    { Scope p(c, EC_K_NORM);
-      launch_rmsnorm_f32(b.h, nullptr, M, d, W(c->attn_norm[l]), m.rms_eps, u, s); }
     { Scope p(c, EC_K_QKV);
-      launch_gemm_f32(u, W(c->wq[l]), b.qkv, nqkv, M, nq, d, 0, 1.f, s);
-      launch_gemm_f32(u, W(c->wk[l]), b.qkv + nq, nqkv, M, nkv, d, 0, 1.f, s);
-      launch_gemm_f32(u, W(c->wv[l]), b.qkv + nq + nkv, nqkv, M, nkv, d, 0, 1.f, s); }
-    { Scope p(c, EC_K_ROPE_KV);
-      launch_rope_scatter_f32(b.qkv, rows, M, m.n_heads, m.n_kv_heads, hd, b.rope_cs, q, kc, vc, s); }
+      F32Gemm g = gemm(b.h, nullptr, M, c->wq[l], nq + 2 * nkv, d, c->attn_norm[l], q, nq);
+      g.W[1] = W(c->wk[l]); g.W[2] = W(c->wv[l]); g.kc = kc; g.vc = vc;
+      launch_gemm_f32(F32_QKV, g, s); }
     { Scope p(c, EC_K_ATTN);
       launch_attention_f32(q, kc, vc, M, T, m.n_heads, m.n_kv_heads, hd, attn, s); }
-    { Scope p(c, EC_K_OPROJ); launch_gemm_f32(attn, W(c->wo[l]), b.h, d, M, d, nq, 1, 1.f, s); }
-    { Scope p(c, EC_K_NORM);
-      launch_rmsnorm_f32(b.h, nullptr, M, d, W(c->mlp_norm[l]), m.rms_eps, u, s); }
+    { Scope p(c, EC_K_OPROJ);
+      launch_gemm_f32(F32_RESID, gemm(attn, nullptr, M, c->wo[l], d, nq, nullptr, b.h, d), s); }
     { Scope p(c, EC_K_GATEUP);
-      launch_gemm_f32(u, W(c->w_gate[l]), b.gu, 2 * F, M, F, d, 0, 1.f, s);
-      launch_gemm_f32(u, W(c->w_up[l]), b.gu + F, 2 * F, M, F, d, 0, 1.f, s); }
-    { Scope p(c, EC_K_SWIGLU); launch_swiglu_f32(b.gu, M, F, act, s); }
-    { Scope p(c, EC_K_DOWN); launch_gemm_f32(act, W(c->w_down[l]), b.h, d, M, d, F, 1, 1.f, s); }
+      F32Gemm g = gemm(b.h, nullptr, M, c->w_gate[l], F, d, c->mlp_norm[l], act, F);
+      g.W[1] = W(c->w_up[l]);
+      launch_gemm_f32(F32_SWIGLU, g, s); }
+    { Scope p(c, EC_K_DOWN);
+      launch_gemm_f32(F32_RESID, gemm(act, nullptr, M, c->w_down[l], d, F, nullptr, b.h, d), s); }
   }
   // logits only for the block's masked rows
-  { Scope p(c, EC_K_NORM);
-    launch_rmsnorm_f32(b.h, lm_sel, n_mb, d, W(c->w.final_norm), m.rms_eps, u_lm, s); }
   { Scope p(c, EC_K_LMHEAD);
-    launch_gemm_f32(u_lm, W(c->w.lm_head), b.logits, m.vocab, n_mb, m.vocab, d, 0, m.logit_scale, s); }
+    launch_gemm_f32(F32_LOGITS, gemm(b.h, lm_sel, n_mb, c->w.lm_head, m.vocab, d,
+                                     c->w.final_norm, b.logits, m.vocab), s); }
   return EC_OK;
 }
 

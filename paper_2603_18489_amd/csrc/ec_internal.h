@@ -93,18 +93,24 @@ void set_global_error(const char* msg);
 // float32 path
 void launch_embed_f32(const float* emb, const int* x, const int* rows, int M, int d, int vocab,
                       float* h, hipStream_t s);
-// out row r = rmsnorm(h row sel[r] (or r)) * gain
-void launch_rmsnorm_f32(const float* h, const int* sel, int M, int d, const float* gain, float eps,
-                        float* out, hipStream_t s);
 void launch_rope_table(float2* cs, int T, int hd, float base, hipStream_t s);
-// caches row-major [T, Hkv*hd]
-void launch_rope_scatter_f32(const float* qkv, const int* rows, int M, int Hq, int Hkv, int hd,
-                             const float2* cs, float* q_out, float* kcache, float* vcache,
-                             hipStream_t s);
-void launch_swiglu_f32(const float* gu, int M, int F, float* act, hipStream_t s);
-// C[M,N] (ldc) = scale * A[M,K] W[N,K]^T, or C += ... when accumulate.
-void launch_gemm_f32(const float* A, const float* W, float* C, int ldc, int M, int N, int K,
-                     int accumulate, float scale, hipStream_t s);
+// The float32 GEMMs (k_gemm_f32.hip).  Everything but F32_RESID normalises its operand's rows.
+enum { F32_QKV = 0, F32_RESID = 1, F32_SWIGLU = 2, F32_LOGITS = 3 };
+struct F32Gemm {
+  const float* A;                 // [.., K] row-major
+  const int* sel;                 // nullable: activation row m is row sel[m] of A
+  int M, N, K;                    // (N: output features; F32_SWIGLU of one of the two matrices)
+  const float* W[3];              // row-major [.., K]: one matrix, or gate and up, or q, k and v
+  const float* gain; float eps;   // the norm of A's rows (not F32_RESID)
+  float scale;                    // F32_LOGITS
+  float* C; int ldc;              // (F32_QKV: the query rows, [M, Hq*hd])
+  const int* rows;                // F32_QKV, nullable: position of each row (else its index)
+  const float2* cs;               // F32_QKV: RoPE table
+  int Hq, Hkv, hd;                // F32_QKV
+  float *kc, *vc;                 // F32_QKV: caches, row-major [T, Hkv*hd]
+  int nt;                         // (filled in by the launcher)
+};
+void launch_gemm_f32(int epi, F32Gemm g, hipStream_t s);
 void launch_attention_f32(const float* q, const float* kc, const float* vc, int M, int T, int Hq,
                           int Hkv, int hd, float* out, hipStream_t s);
 

@@ -1,5 +1,5 @@
 // Small memory-bound kernels around the GEMMs.
-//  float32 path: embedding gather, RMSNorm, RoPE + KV-cache scatter, SwiGLU (row-major tensors).
+//  float32 path: embedding gather.
 //  bf16 path:    the step prologue (row list, embedding gather fused with the first norm's
 //                operand), the one-time re-tiling of the matrices, and the un-tiling of a cache
 //                layer for debug read-back.  Everything else of that path lives in the GEMM
@@ -101,33 +101,6 @@ void launch_step_prologue_bf16(const StepLists& L, const bf16_t* emb, int d, con
 }
 
 // ---------------------------------------------------------------------------------------------
-// RMSNorm (float32 path): u = h * rsqrt(mean(h^2) + eps) * g
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float* __restrict__ h,
-                                                          const int* __restrict__ sel, int d,
-                                                          const float* __restrict__ gain,
-                                                          float eps, float* __restrict__ outp) {
-  __shared__ float red[4];
-  int r = blockIdx.x;
-  const float* src = h + (size_t)(sel ? sel[r] : r) * d;
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < d; c += 256) {
-    float v = src[c];
-    ss += v * v;
-  }
-  ss = block_sum<4>(ss, red);
-  float rstd = 1.0f / sqrtf(ss / (float)d + eps);
-  float* out = outp + (size_t)r * d;
-  for (int c = threadIdx.x; c < d; c += 256) out[c] = src[c] * rstd * gain[c];
-}
-
-void launch_rmsnorm_f32(const float* h, const int* sel, int M, int d, const float* gain, float eps,
-                        float* out, hipStream_t s) {
-  if (M <= 0) return;
-  rmsnorm_f32_kernel<<<M, 256, 0, s>>>(h, sel, d, gain, eps, out);
-}
-
-// ---------------------------------------------------------------------------------------------
 // RoPE table: cs[pos][j] = (cos, sin)(pos * base^(-2j/hd)), evaluated in double once per context.
 // ---------------------------------------------------------------------------------------------
 __global__ void rope_table_kernel(float2* __restrict__ cs, int T, int half, int hd, double base) {
@@ -142,60 +115,6 @@ __global__ void rope_table_kernel(float2* __restrict__ cs, int T, int half, int 
 void launch_rope_table(float2* cs, int T, int hd, float base, hipStream_t s) {
   int n = T * (hd / 2);
   rope_table_kernel<<<(n + 255) / 256, 256, 0, s>>>(cs, T, hd / 2, hd, (double)base);
-}
-
-// ---------------------------------------------------------------------------------------------
-// RoPE + KV scatter (float32 path): from the projected row [q | k | v] rotate q and k by the
-// row's absolute position, write q to the query buffer and k, v into the cache row `pos`.
-// The cache holds post-RoPE keys.  One block per row; one full cache row per (row, K/V).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void rope_scatter_f32_kernel(
-    const float* __restrict__ qkv, const int* __restrict__ rows, int Hq, int Hkv, int hd,
-    const float2* __restrict__ cs, float* __restrict__ q_out, float* __restrict__ kcache,
-    float* __restrict__ vcache) {
-  int r = blockIdx.x;
-  int pos = rows ? rows[r] : r;
-  int half = hd / 2;
-  int nq = Hq * hd, nkv = Hkv * hd;
-  const float* row = qkv + (size_t)r * (nq + 2 * nkv);
-  const float2* csr = cs + (size_t)pos * half;
-  for (int idx = threadIdx.x; idx < (Hq + Hkv) * half; idx += 256) {
-    int head = idx / half, j = idx - head * half;
-    float a = row[head * hd + j], b = row[head * hd + j + half];
-    float2 c = csr[j];
-    float ra = a * c.x - b * c.y, rb = b * c.x + a * c.y;
-    float* dst = head < Hq ? q_out + (size_t)r * nq + head * hd + j
-                           : kcache + (size_t)pos * nkv + (head - Hq) * hd + j;
-    dst[0] = ra;
-    dst[half] = rb;
-  }
-  const float* vrow = row + nq + nkv;
-  float* vdst = vcache + (size_t)pos * nkv;
-  for (int c = threadIdx.x; c < nkv; c += 256) vdst[c] = vrow[c];
-}
-
-void launch_rope_scatter_f32(const float* qkv, const int* rows, int M, int Hq, int Hkv, int hd,
-                             const float2* cs, float* q_out, float* kcache, float* vcache,
-                             hipStream_t s) {
-  if (M <= 0) return;
-  rope_scatter_f32_kernel<<<M, 256, 0, s>>>(qkv, rows, Hq, Hkv, hd, cs, q_out, kcache, vcache);
-}
-
-// ---------------------------------------------------------------------------------------------
-// SwiGLU (float32 path): act = silu(gate) * up with gu = [gate | up] ([M, 2F]).
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void swiglu_f32_kernel(const float* __restrict__ gu, int F,
-                                                         float* __restrict__ act) {
-  int r = blockIdx.y;
-  int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= F) return;
-  float g = gu[(size_t)r * 2 * F + c], u = gu[(size_t)r * 2 * F + F + c];
-  act[(size_t)r * F + c] = g / (1.0f + expf(-g)) * u;
-}
-
-void launch_swiglu_f32(const float* gu, int M, int F, float* act, hipStream_t s) {
-  if (M <= 0) return;
-  swiglu_f32_kernel<<<dim3((F + 255) / 256, M), 256, 0, s>>>(gu, F, act);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -509,3 +509,38 @@ def test_rows_of_nan_logits_are_reported_and_nothing_leaves_its_buffers(dtype, b
     s = (run_teacher_forced(cfg, good, dec, prompts[0], TOL[dtype], max_steps=4) if batch == 1 else
          run_teacher_forced_batch(cfg, good, dec, prompts, TOL[dtype], max_steps=4))
     assert s["steps"] == 4
+
+
+@pytest.mark.parametrize("hq,hkv,hd,d,f,vocab,P,shift", [
+    (2, 1, 64, 136, 200, 1003, 19, 0),     # K = 136 and 200: half-filled last k-chunks, odd tile counts
+    (3, 3, 128, 264, 1032, 4099, 40, 0),   # K just above 256: eight waves to a block
+    (8, 2, 64, 512, 1032, 515, 300, 0),    # many tiles: four to a block, both k-lengths
+    (2, 2, 64, 72, 8, 2, 1, 0),            # one tile, the smallest vocabulary
+    (4, 2, 64, 256, 520, 777, 30, 1),      # weights that start at any element
+])
+def test_f32_gemm_edges(hq, hkv, hd, d, f, vocab, P, shift):
+    """The float32 kernels at the edges of their tiles, k-chunks and dispatch rules."""
+    cfg = small_cfg("f32", hq, hkv, hd, d=d, f=f, vocab=vocab, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 61, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=21, block=8, k_recent=3, tokens_per_step=2, tau=1e9)
+    prompt = ec_inputs.make_prompt(max(vocab, 98), P, 4) % vocab
+    st = eco.eco_init(eco.OracleModel(cfg, w), dec, prompt)
+    dw = ec.weights_to_device(cfg, w)
+    if shift:
+        import torch
+
+        def moved(t):
+            buf = torch.empty(t.numel() + shift, dtype=t.dtype, device=t.device)
+            return buf[shift:].view(t.shape).copy_(t)
+        dw = {k: [moved(t) for t in v] if isinstance(v, list) else moved(v) for k, v in dw.items()}
+    g = ec.EntropyCache(cfg, dw, dec, prompt)
+    g.keep_logits(True)
+    for i in range(4):
+        r = eco.eco_step(st, eco.FULL if i in (0, 2) else eco.PARTIAL)
+        g.step_forced(r["mode"], r["positions"], r["tokens"])
+        z = g.debug_read(ec.EC_DBG_LOGITS, count=len(r["Mb"]))
+        assert relerr(z, r["logits"]) < 1e-5, (i, relerr(z, r["logits"]))
+        for l in range(cfg.n_layers):
+            assert relerr(g.debug_read(ec.EC_DBG_KCACHE, l), st.Kc[l]) < 1e-5
+            assert relerr(g.debug_read(ec.EC_DBG_VCACHE, l), st.Vc[l]) < 1e-5
+    g.close()
