@@ -875,25 +875,35 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 
 // (With the plain store epilogue of a K split, blocks of at most 192 x 192 fit two to a CU: the
 // register count is pinned to the 128 VGPRs that allows.  The fused epilogues need more.)
-// PIPE: the fragments of k-step k+1 are read from LDS into a second register set while the
-// MFMAs of k-step k run.  Without it every k-step is a burst of LDS reads (all waves at once,
-// right after the barrier, matrix cores idle) followed by a burst of MFMAs.
-template <int EPI, int WM, int WN, int WTM, int WTN, bool PIPE>
-constexpr int tiled8_waves_per_eu() {
-  // four-wave blocks: two to a CU (256 registers each) unless the read-ahead needs more
-  return WM * WN == 4 ? (PIPE ? 1 : 2) : (EPI == EPI_PARTIAL && WTM * WTN <= 18 ? 4 : 2);
-}
-template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool PIPE, bool WS>
+//
+// ROLL: the fragments of k-step k+1 are read from LDS while the MFMAs of k-step k run, a few after
+// each row of them: a weight fragment goes back to the registers its last MFMA has just freed, the
+// activation fragments and the last weight fragment have a second set.  Reads and MFMAs of a
+// k-step one after the other leave the matrix cores idle for the reads (96 KiB at 128 B a clock
+// for 192 x 384) and all of a step's reads ahead of its MFMAs hold up the issue of the latter.  What
+// is left at 192 x 384 is mostly the delivery of the operands from L2: without the loads (on
+// whatever the LDS holds) the gate/up launch below takes 89 us, with all of them hitting in L2 125.
+// us per launch on MI355X at 768 rows, d 4096, F 12288:
+//   gate/up  192 x 384        141 -> 127     q k v  192 x 192            89 -> 84
+//   O, down  192 x 256 x 4 K   55 -> 52 (mean of the two; the read-ahead of whole k-steps before)
+template <int EPI, int WTM, int WTN>
+constexpr bool tiled8_roll() { return EPI != EPI_PARTIAL || WTM * WTN > 18; }
+template <int EPI, int WTM, int WTN>
+constexpr int tiled8_waves_per_eu() { return tiled8_roll<EPI, WTM, WTN>() ? 2 : 4; }
+
+template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool WS>
 __global__ __launch_bounds__(WM * WN * 64)
-__attribute__((amdgpu_waves_per_eu(tiled8_waves_per_eu<EPI, WM, WN, WTM, WTN, PIPE>(),
-                                   tiled8_waves_per_eu<EPI, WM, WN, WTM, WTN, PIPE>())))
+__attribute__((amdgpu_waves_per_eu(tiled8_waves_per_eu<EPI, WTM, WTN>(),
+                                   tiled8_waves_per_eu<EPI, WTM, WTN>())))
 void gemm_bf16_tiled8_kernel(
     const u32x4* __restrict__ Ap, const u32x4* __restrict__ Wp, int total_nt, int KB_all, int MT,
     GemmEpi e) {
   constexpr int NW = WM * WN, BMT = WM * WTM, BNT = WN * WTN, NF = BMT + BNT;
-  constexpr int LF = (NF + NW - 1) / NW;  // loads per wave and stage (all waves issue LF)
+  constexpr int LF = (NF + NW - 1) / NW;  // loads per stage of the waves with wave < NF - (LF-1)*NW,
+                                          // one less for the others
   static_assert(LF * NSTAGE <= 63, "vmcnt counts at most 63 outstanding loads");
-  extern __shared__ u32x4 lds[];  // [NSTAGE][NF][64] + one dump fragment
+  static_assert(WTN > 1, "the rolling reads need two weight fragments a wave");
+  extern __shared__ u32x4 lds[];  // [NSTAGE][NF][64]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int bx, by;
   tiled_block_xy(bx, by);
@@ -905,40 +915,37 @@ void gemm_bf16_tiled8_kernel(
 
   // Fragment f of the block (0..BMT-1 activations, BMT.. weights) is loaded by wave f % NW.
   // A fragment outside the matrix streams fragment 0 instead (valid memory); what it produces
-  // lands in rows / columns that are never stored.  Slots past NF go to the dump fragment, so
-  // that every wave has the same number of loads in flight (the vmcnt arithmetic needs that).
-  const u32x4* src[LF];
-  size_t stride[LF];  // u32x4 per k-step
-  int dst[LF];        // fragment slot within a stage, or -1 = dump
+  // lands in rows / columns that are never stored.  The addresses are wave-uniform.
+  const char* src[LF];
+  size_t step[LF];  // bytes per k-step
+  const bool more = wave < NF - (LF - 1) * NW;
 #pragma unroll
-  for (int i = 0; i < LF; ++i) {
-    int f = wave + NW * i;
-    src[i] = Ap + lane;
-    stride[i] = (size_t)MT * 64;
-    dst[i] = f < NF ? f : -1;
-    if (f < BMT) {
-      int mt = mt0 + f;
-      if (mt < MT) src[i] = Ap + (size_t)mt * 64 + lane;
-    } else if (f < NF) {
-      int nt = nt0 + (f - BMT);
-      if (nt < total_nt) {
-        src[i] = Wp + packed_w_frag(nt, 0, KB_all, e.w_grp) * 64 + lane;
-        stride[i] = (size_t)e.w_grp * 64;
-      }
-    }
-    src[i] += (size_t)kb_first * stride[i];
+  for (int l = 0; l < LF; ++l) {
+    const int f = wave + NW * l;
+    const int mt = f < BMT && mt0 + f < MT ? mt0 + f : 0;
+    const int nt = f >= BMT && f < NF && nt0 + f - BMT < total_nt ? nt0 + f - BMT : 0;
+    step[l] = (f < BMT ? (size_t)MT : (size_t)e.w_grp) * 1024;
+    src[l] = (f < BMT ? (const char*)Ap + (size_t)mt * 1024
+                      : (const char*)Wp + packed_w_frag(nt, 0, KB_all, e.w_grp) * 1024) +
+             kb_first * step[l];
   }
-  auto issue = [&](int kb) {  // k-step kb (clamped) -> stage kb % NSTAGE
-    const int kbc = min(kb, KB - 1), stage = kb % NSTAGE;
-#pragma unroll
-    for (int i = 0; i < LF; ++i) {
-      u32x4* slot = dst[i] >= 0 ? lds + ((size_t)stage * NF + dst[i]) * 64
-                                : lds + (size_t)NSTAGE * NF * 64;
-      __builtin_amdgcn_global_load_lds(
-          (const void __attribute__((address_space(1)))*)(src[i] + (size_t)kbc * stride[i]),
-          (void __attribute__((address_space(3)))*)slot, 16, 0, 0);
-    }
-  };
+  const unsigned voff = lane * 16;
+  int fill = 0, slot_w = 0;  // k-step requested next (its operands are those of the last one once
+                             // the range is through), and the slot it goes to
+#define EC_T8_LOAD(L)                                                                        \
+  __builtin_amdgcn_global_load_lds(                                                          \
+      (const void __attribute__((address_space(1)))*)(src[L] + voff),                        \
+      (void __attribute__((address_space(3)))*)(lds + ((size_t)slot_w * NF + wave + NW * (L)) * 64), 16, 0, 0);
+#define EC_T8_ISSUE(LO, HI)                                                                  \
+  _Pragma("unroll") for (int l = (LO); l < (HI); ++l) {                                      \
+    if (NF % NW == 0 || l < LF - 1) { EC_T8_LOAD(l) }                                        \
+    else if (more) { EC_T8_LOAD(l) }                                                         \
+    src[l] += fill + 1 < KB ? step[l] : 0;                                                   \
+  }
+#define EC_T8_FILLED ++fill; slot_w = slot_w == NSTAGE - 1 ? 0 : slot_w + 1;
+  // waits until at most the loads of the newest STEPS k-steps of this wave are in flight
+#define EC_T8_WAIT(STEPS)                                                                    \
+  if (NF % NW == 0 || more) wait_vmcnt<LF*(STEPS)>(); else wait_vmcnt<(LF - 1)*(STEPS)>();
 
   f32x4 acc[WTN][WTM];
 #pragma unroll
@@ -946,15 +953,16 @@ void gemm_bf16_tiled8_kernel(
 #pragma unroll
     for (int j = 0; j < WTM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  if constexpr (!PIPE) {
+  int slot_r = 0;
+  if constexpr (!tiled8_roll<EPI, WTM, WTN>()) {
 #pragma unroll
-    for (int sgl = 0; sgl < NSTAGE - 1; ++sgl) issue(sgl);
+    for (int sgl = 0; sgl < NSTAGE - 1; ++sgl) { EC_T8_ISSUE(0, LF) EC_T8_FILLED }
     for (int kb = 0; kb < KB; ++kb) {
-      // this wave's loads of k-step kb have landed once at most LF*(NSTAGE-2) newer ones remain
-      wait_vmcnt<LF*(NSTAGE - 2)>();
-      block_barrier_nofence();  // ... and so have everyone else's; the stage read last iteration is free
-      issue(kb + NSTAGE - 1);
-      const u32x4* st = lds + (size_t)(kb % NSTAGE) * NF * 64;
+      EC_T8_WAIT(NSTAGE - 2)    // this wave's loads of k-step kb have landed
+      block_barrier_nofence();  // ... and so have everyone else's; the slot read last iteration is free
+      EC_T8_ISSUE(0, LF) EC_T8_FILLED
+      const u32x4* st = lds + (size_t)slot_r * NF * 64;
+      slot_r = slot_r == NSTAGE - 1 ? 0 : slot_r + 1;
       bf16x8 af[WTM], wf[WTN];
 #pragma unroll
       for (int j = 0; j < WTM; ++j) af[j] = v4_as_bf16x8(st[(wm * WTM + j) * 64 + lane]);
@@ -968,52 +976,62 @@ void gemm_bf16_tiled8_kernel(
     }
   } else {
     // All NSTAGE slots are kept in flight.  Step k: this wave has finished reading slot k (its
-    // fragments sit in one register set) and its loads of k-step k+1 have landed; after the
-    // barrier that holds for every wave, so slot k is refilled with k-step k + NSTAGE, the
-    // fragments of k+1 go to the other register set, and the MFMAs of k run over those reads.
-    bf16x8 afa[WTM], wfa[WTN], afb[WTM], wfb[WTN];
-#define EC_T8_READ(AF, WF, KB_)                                                              \
+    // fragments sit in registers) and its loads of k-step k+1 have landed; after the barrier that
+    // holds for every wave, so slot k is refilled with k-step k + NSTAGE while slot k+1 is read.
+    bf16x8 afa[WTM], afb[WTM], wf[WTN - 1], wla, wlb;
+#define EC_T8_WF(I, WL) ((I) < WTN - 1 ? wf[(I) < WTN - 1 ? (I) : 0] : WL)
+#define EC_T8_STEP(AF, WL, AFN, WLN)                                                         \
   {                                                                                          \
-    const u32x4* st_ = lds + (size_t)((KB_) % NSTAGE) * NF * 64;                             \
-    _Pragma("unroll") for (int j = 0; j < WTM; ++j)                                          \
-        AF[j] = v4_as_bf16x8(st_[(wm * WTM + j) * 64 + lane]);                               \
-    _Pragma("unroll") for (int i = 0; i < WTN; ++i)                                          \
-        WF[i] = v4_as_bf16x8(st_[(BMT + wn * WTN + i) * 64 + lane]);                         \
-  }
-#define EC_T8_MMA(AF, WF)                                                                    \
-  _Pragma("unroll") for (int i = 0; i < WTN; ++i)                                            \
-    _Pragma("unroll") for (int j = 0; j < WTM; ++j)                                          \
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WF[i], AF[j], acc[i][j], 0, 0, 0);
-#define EC_T8_STEP(AF, WF, AFN, WFN, KB_)                                                    \
-  {                                                                                          \
-    wait_vmcnt<LF*(NSTAGE - 2)>();  /* own loads of KB_+1 have landed */                     \
-    block_barrier_nofence();        /* and slot KB_ is in registers, for every wave */       \
-    issue((KB_) + NSTAGE);                                                                   \
-    EC_T8_READ(AFN, WFN, (KB_) + 1)                                                          \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
-    EC_T8_MMA(AF, WF)                                                                        \
-    __builtin_amdgcn_sched_barrier(0);                                                       \
+    EC_T8_WAIT(NSTAGE - 2)                                                                   \
+    block_barrier_nofence();                                                                 \
+    slot_r = slot_r == NSTAGE - 1 ? 0 : slot_r + 1;                                          \
+    const u32x4* sa_ = lds + ((size_t)slot_r * NF + wm * WTM) * 64 + lane;                   \
+    const u32x4* sw_ = lds + ((size_t)slot_r * NF + BMT + wn * WTN) * 64 + lane;             \
+    _Pragma("unroll") for (int i = 0; i < WTN; ++i) {                                        \
+      _Pragma("unroll") for (int j = 0; j < WTM; ++j)                                        \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(EC_T8_WF(i, WL), AF[j],          \
+                                                            acc[i][j], 0, 0, 0);             \
+      __builtin_amdgcn_sched_barrier(0);                                                     \
+      if (i < WTN - 1) {                                                                     \
+        if (i == 0) WLN = v4_as_bf16x8(sw_[(WTN - 1) * 64]);                                 \
+        _Pragma("unroll")                                                                    \
+        for (int j = i * WTM / (WTN - 1); j < (i + 1) * WTM / (WTN - 1); ++j)                \
+          AFN[j] = v4_as_bf16x8(sa_[j * 64]);                                                \
+        wf[i < WTN - 1 ? i : 0] = v4_as_bf16x8(sw_[i * 64]);                                 \
+      }                                                                                      \
+      EC_T8_ISSUE(i * LF / WTN, (i + 1) * LF / WTN)                                          \
+      __builtin_amdgcn_sched_barrier(0);                                                     \
+    }                                                                                        \
+    EC_T8_FILLED                                                                             \
   }
 #pragma unroll
-    for (int sgl = 0; sgl < NSTAGE; ++sgl) issue(sgl);
-    wait_vmcnt<LF*(NSTAGE - 1)>();
+    for (int sgl = 0; sgl < NSTAGE; ++sgl) { EC_T8_ISSUE(0, LF) EC_T8_FILLED }
+    EC_T8_WAIT(NSTAGE - 1)
     block_barrier_nofence();
-    EC_T8_READ(afa, wfa, 0)
-    for (int kb = 0; kb < KB; kb += 2) {
-      EC_T8_STEP(afa, wfa, afb, wfb, kb)
-      // an odd trip count runs one surplus step on a clamped (repeated) k-step: its activation
-      // fragments are zeroed so that it adds nothing
-      if (kb + 1 >= KB) {
 #pragma unroll
-        for (int j = 0; j < WTM; ++j) afb[j] = v4_as_bf16x8((u32x4){0u, 0u, 0u, 0u});
-      }
-      EC_T8_STEP(afb, wfb, afa, wfa, kb + 1)
+    for (int j = 0; j < WTM; ++j) afa[j] = v4_as_bf16x8(lds[(wm * WTM + j) * 64 + lane]);
+#pragma unroll
+    for (int i = 0; i < WTN - 1; ++i) wf[i] = v4_as_bf16x8(lds[(BMT + wn * WTN + i) * 64 + lane]);
+    wla = v4_as_bf16x8(lds[(BMT + wn * WTN + WTN - 1) * 64 + lane]);
+    for (int kb = 0; kb + 1 < KB; kb += 2) {
+      EC_T8_STEP(afa, wla, afb, wlb)
+      EC_T8_STEP(afb, wlb, afa, wla)
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (KB & 1) {  // (an odd trip count: the last k-step's fragments are in the first set)
+#pragma unroll
+      for (int i = 0; i < WTN; ++i)
+#pragma unroll
+        for (int j = 0; j < WTM; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(EC_T8_WF(i, wla), afa[j], acc[i][j], 0, 0, 0);
+    }
 #undef EC_T8_STEP
-#undef EC_T8_MMA
-#undef EC_T8_READ
+#undef EC_T8_WF
   }
+#undef EC_T8_WAIT
+#undef EC_T8_FILLED
+#undef EC_T8_ISSUE
+#undef EC_T8_LOAD
   wait_vmcnt<0>();  // drain the clamped tail loads before the LDS goes away
 
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
@@ -1022,12 +1040,12 @@ void gemm_bf16_tiled8_kernel(
                                                    blockIdx.z);
 }
 
-template <int EPI, bool WS, int WM, int WN, int WTM, int WTN, int NSTAGE, bool PIPE = false>
+template <int EPI, bool WS, int WM, int WN, int WTM, int WTN, int NSTAGE>
 static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
                             const GemmEpi& e, hipStream_t s, int ksplit) {
   constexpr int NF = WM * WTM + WN * WTN;
-  const size_t smem = ((size_t)NSTAGE * NF + 1) * 1024;
-  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, PIPE, WS>;
+  const size_t smem = (size_t)NSTAGE * NF * 1024;
+  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS>;
   static bool attr_set = false;
   if (!attr_set && smem > 48 * 1024) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1039,19 +1057,26 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 }
 
 // Second half of a K-split residual GEMM: h += sum over the splits (fixed order), then what
-// EPI_RESID does: next operand bf16(h * gain) and the row's sum of squares.
+// EPI_RESID does: next operand bf16(h * gain) and the row's sum of squares.  Bound by its bytes:
+// every load is requested before the first is used.  768 rows of 4096 in four pieces:
+// 82 MB in 16.3 us (5.0 TB/s, what a large copy reaches).
 // grid (ceil(d / 1024), M), 256 threads, 4 columns per thread.
-__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e, int ksplit) {
+template <int KSPLIT>
+__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
   __shared__ float red[4];
   const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
   float part = 0.f;
   if (n < e.d) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int z = 0; z < ksplit; ++z) {
-      float4 p = *(const float4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
-    part = epi_resid(e, m, n >> 4, (n >> 2) & 3, (f32x4){v.x, v.y, v.z, v.w});
+    f32x4 p[KSPLIT];
+#pragma unroll
+    for (int z = 0; z < KSPLIT; ++z)
+      p[z] = *(const f32x4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
+    const float4 h = *(const float4*)(e.h + (size_t)m * e.d + n);
+    const u32x2 g4 = *(const u32x2*)(e.gain_next + n);
+    f32x4 v = p[0];
+#pragma unroll
+    for (int z = 1; z < KSPLIT; ++z) v += p[z];
+    part = epi_resid_pre(e, m, n >> 4, (n >> 2) & 3, v, h, g4);
   }
   part = block_sum<4>(part, red);
   if (threadIdx.x == 0) {
@@ -1075,10 +1100,12 @@ struct TilePick { int tile, ksplit; };
 constexpr int kNumTiles = 8;
 static const int kTileM[kNumTiles] = {12, 12, 12, 12, 12, 12, 8, 6};
 static const int kTileN[kNumTiles] = {24, 16, 12, 8, 12, 8, 8, 8};
-static const float kTileUsAlone[kNumTiles] = {0.98f, 0.71f, 0.54f, 0.46f, 0.64f, 0.55f, 0.53f, 0.41f};
-static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.90f, 0.75f, 0.f, 0.f, 0.f, 0.f};
+static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.41f};
+static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.93f, 0.75f, 0.f, 0.f, 0.f, 0.f};
 
-static TilePick pick_tile(int MT, int total_nt, int KB, int max_ksplit, int M, int N) {
+// epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
+// cache stores of q k v, the residual stream's read and write; partial products are plain stores.
+static TilePick pick_tile(int MT, int total_nt, int KB, int max_ksplit, int M, int N, float epi_us) {
   TilePick best{1, 1};
   float best_t = 1e30f;
   for (int i = 0; i < kNumTiles; ++i) {
@@ -1088,7 +1115,8 @@ static TilePick pick_tile(int MT, int total_nt, int KB, int max_ksplit, int M, i
       const float ksteps = (float)((KB + ks - 1) / ks);
       const long pairs = (kTileUsPair[i] > 0.f && ks > 1) ? per_cu / 2 : 0;
       const long singles = per_cu - 2 * pairs;
-      float t = ksteps * (pairs * kTileUsPair[i] + singles * kTileUsAlone[i]) + 5.0f * (pairs + singles);
+      const float edge = 5.0f + (ks > 1 ? 0.02f : epi_us) * kTileM[i] * kTileN[i];
+      float t = ksteps * (pairs * kTileUsPair[i] + singles * kTileUsAlone[i]) + edge * (pairs + singles);
       if (ks > 1) t += 2.5f + (float)M * N * (ks + 4) * 4.0f / 5.0e6f;  // finish kernel
       if (t < best_t) { best_t = t; best = TilePick{i, ks}; }
     }
@@ -1103,7 +1131,7 @@ static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int
                                  const GemmEpi& e, hipStream_t s, int tile, int ksplit) {
   switch (tile) {
     case 0: launch_tiled8_t<EPI, WS, 2, 4, 6, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 1: launch_tiled8_t<EPI, WS, 2, 4, 6, 4, 3, true>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
+    case 1: launch_tiled8_t<EPI, WS, 2, 4, 6, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
     case 2: launch_tiled8_t<EPI, WS, 2, 4, 6, 3, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
     case 3: launch_tiled8_t<EPI, WS, 2, 4, 6, 2, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
     case 4: launch_tiled4_t<EPI, 6, 6, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
@@ -1118,6 +1146,15 @@ static void launch_tiled_pick(const bf16_t* Ap, int MT, const bf16_t* Wp, int to
                               const GemmEpi& e, hipStream_t s, int tile, int ksplit) {
   if (e.wscale) launch_tiled_pick_ws<EPI, true>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
   else launch_tiled_pick_ws<EPI, false>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
+}
+
+static void launch_resid_finish(const GemmEpi& e, int ksplit, int N, hipStream_t s) {
+  const dim3 grid((N + 1023) / 1024, e.M);
+  switch (ksplit) {
+    case 2: resid_finish_kernel<2><<<grid, 256, 0, s>>>(e); break;
+    case 3: resid_finish_kernel<3><<<grid, 256, 0, s>>>(e); break;
+    default: resid_finish_kernel<4><<<grid, 256, 0, s>>>(e); break;
+  }
 }
 
 template <int EPI>
@@ -1151,10 +1188,11 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
     // the tiled kernel reads its activation rows in place (no gather) and walks every m-tile of
     // the buffer; rows from e.M on are dropped in the epilogue
     const int max_ks = (EPI == EPI_RESID && e.partial) ? e.max_ksplit : 1;
-    TilePick tp = pick_tile(MT_src, total_nt, KB, max_ks, e.M, N);
+    const float epi_us = EPI == EPI_QKV || EPI == EPI_RESID ? 0.064f : 0.f;
+    TilePick tp = pick_tile(MT_src, total_nt, KB, max_ks, e.M, N, epi_us);
     if (tp.ksplit > 1) {
       launch_tiled_pick<EPI_PARTIAL>(Ap, MT_src, Wp, total_nt, KB, e, s, tp.tile, tp.ksplit);
-      resid_finish_kernel<<<dim3((N + 1023) / 1024, e.M), 256, 0, s>>>(e, tp.ksplit);
+      launch_resid_finish(e, tp.ksplit, N, s);
     } else {
       launch_tiled_pick<EPI>(Ap, MT_src, Wp, total_nt, KB, e, s, tp.tile, 1);
     }

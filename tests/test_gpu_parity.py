@@ -544,3 +544,19 @@ def test_f32_gemm_edges(hq, hkv, hd, d, f, vocab, P, shift):
             assert relerr(g.debug_read(ec.EC_DBG_KCACHE, l), st.Kc[l]) < 1e-5
             assert relerr(g.debug_read(ec.EC_DBG_VCACHE, l), st.Vc[l]) < 1e-5
     g.close()
+
+
+@pytest.mark.parametrize("hq,hkv,hd,d,f,P", [
+    (4, 2, 64, 288, 12320, 760),    # 9 k-steps, an odd number; 1540 weight tiles
+    (4, 4, 64, 32, 4128, 900),      # a single k-step; 129 k-steps for 2 weight tiles
+    (8, 8, 128, 1056, 6176, 1400),  # 33 and 193 k-steps, uneven K ranges, ragged row and column tiles
+])
+def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P):
+    """The many-row GEMMs at odd and tiny numbers of k-steps, with tiles that the matrices do not
+    fill."""
+    cfg = small_cfg("bf16", hq, hkv, hd, d=d, f=f, vocab=512, scale=4.0)
+    w = ec_inputs.make_weights(cfg, 67, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=11, block=4, k_recent=2, tokens_per_step=1, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 6), TOL["bf16"], max_steps=2)
+    print(s)
+    assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
