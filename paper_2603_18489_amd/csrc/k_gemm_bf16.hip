@@ -223,7 +223,9 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // the compiler could treat as divergent
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nt0 = blockIdx.x * NTW;
-  const int kb_lo = (wave * KB) / KS, kb_hi = ((wave + 1) * KB) / KS;
+  // blockIdx.y picks one of gridDim.y contiguous K ranges (EPI_PARTIAL; otherwise gridDim.y = 1)
+  const int kr_lo = (int)((blockIdx.y * KB) / gridDim.y), kr_n = (int)(((blockIdx.y + 1) * KB) / gridDim.y) - kr_lo;
+  const int kb_lo = kr_lo + (wave * kr_n) / KS, kb_hi = kr_lo + ((wave + 1) * kr_n) / KS;
 
   // a tile past the end streams tile 0 instead (valid memory) and is dropped at the store
   const int grp = e.w_grp;
@@ -397,7 +399,6 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
     return (f32x4){s.x, s.y, s.z, s.w};
   };
 
-  static_assert(EPI != EPI_PARTIAL, "K-split partial products are a tiled-kernel epilogue");
   if constexpr (EPI == EPI_LOGITS) {
     // Logits of the block's NTW*16 columns, and their reduction.  A row's 16 columns of one tile
     // sit in the 4 lanes l, l^16, l^32, l^48 (4 columns each): maximum and lowest index holding
@@ -457,23 +458,64 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
         part = o < KS * 64 ? epi_resid_pre(e, m, vt, q4, v, pre_h, pre_g) : epi_resid(e, m, vt, q4, v);
       epi_add_sumsq(e, m, mvalid, part);
     } else if (mvalid && vt < total_nt) {
-      if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
+      if constexpr (EPI == EPI_PARTIAL)
+        *(float4*)(e.partial + ((size_t)blockIdx.y * e.M + m) * e.d + vt * 16 + q4 * 4) =
+            make_float4(v[0], v[1], v[2], v[3]);
+      else if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
       else epi_qkv(e, m, vt, q4, v, rstd_s[m]);
     }
   }
 }
 
+// Second half of a K-split residual GEMM: h += sum over the splits (fixed order), then what
+// EPI_RESID does: next operand bf16(h * gain) and the row's sum of squares.  Bound by its bytes:
+// every load is requested before the first is used.  768 rows of 4096 in four pieces:
+// 82 MB in 16.3 us (5.0 TB/s, what a large copy reaches).
+// grid (ceil(d / 1024), M), 256 threads, 4 columns per thread.
+template <int KSPLIT>
+__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
+  __shared__ float red[4];
+  const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
+  float part = 0.f;
+  if (n < e.d) {
+    f32x4 p[KSPLIT];
+#pragma unroll
+    for (int z = 0; z < KSPLIT; ++z)
+      p[z] = *(const f32x4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
+    const float4 h = *(const float4*)(e.h + (size_t)m * e.d + n);
+    const u32x2 g4 = *(const u32x2*)(e.gain_next + n);
+    f32x4 v = p[0];
+#pragma unroll
+    for (int z = 1; z < KSPLIT; ++z) v += p[z];
+    part = epi_resid_pre(e, m, n >> 4, (n >> 2) & 3, v, h, g4);
+  }
+  part = block_sum<4>(part, red);
+  if (threadIdx.x == 0) {
+    unsigned long long fx = sumsq_to_fixed<58>(part);
+    if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)(blockIdx.x & (kSumSlots - 1)) * e.sum_stride + m), fx);
+  }
+}
+
+static void launch_resid_finish(const GemmEpi& e, int ksplit, int N, hipStream_t s) {
+  const dim3 grid((N + 1023) / 1024, e.M);
+  switch (ksplit) {
+    case 2: resid_finish_kernel<2><<<grid, 256, 0, s>>>(e); break;
+    case 3: resid_finish_kernel<3><<<grid, 256, 0, s>>>(e); break;
+    default: resid_finish_kernel<4><<<grid, 256, 0, s>>>(e); break;
+  }
+}
+
 template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false>
 static void launch_skinny_t(const bf16_t* Ap, int MT_src, const void* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s) {
-  int grid = (total_nt + NTW - 1) / NTW;
+                            const GemmEpi& e, hipStream_t s, int ksplit = 1) {
+  dim3 grid((total_nt + NTW - 1) / NTW, ksplit);
   size_t smem = (size_t)KS * NTW * MT * 64 * sizeof(float4) + MT * 16 * sizeof(float);
   if (EPI == EPI_LOGITS) smem += (size_t)NTW * MT * 16 * sizeof(float4);  // per-tile row tuples
   if (W8) smem += NTW * 16 * sizeof(float);                               // weight scales
   if (smem > 48 * 1024) {
     static bool once = false;
     if (!once) {
-      hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8>,
+      (void)hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       once = true;
     }
@@ -497,6 +539,19 @@ int skinny_tiles_per_block(int epi, int total_nt) {
   return total_nt >= 2 * 256 ? 2 : 1;
 }
 
+// A residual GEMM has only d_model / 16 weight tiles, one to a block, and every block pulls the
+// whole [rows, K] operand beside its 16 rows of weights: 1.2 MB beside 0.4 at 48 rows of 12288.  Four
+// neighbouring tiles and a quarter of K to a block pull a quarter of that; the partial products
+// are summed by resid_finish_kernel (4.8 us and the gap before it).  us on MI355X, whole K -> split
+// and finish, d 4096:
+//   3 row tiles  K 12288  30.5 -> 21.3 + 4.8   (e4m3 23.5 -> 15.4 + 4.0)   K 4096  11.2 ->  8.2 + 4.8
+//   6 row tiles  K 12288  44.4 -> 27.0 + 5.1                               K 4096  16.6 -> 11.0 + 5.1
+// which is a gain of about MT * K * 2.4e-4 - 5.5 us.  Two tiles and half of K: 23 and 33 at K 12288.
+constexpr int kSkinnySplit = 4;
+static bool skinny_splits(int MT, int K, const GemmEpi& e) {
+  return e.partial && e.max_ksplit >= kSkinnySplit && (long)MT * K >= 23000;
+}
+
 // e4m3 weights: KB counts 64-wide k-steps; fewer steps per register set, because a step holds
 // two activation fragments per m-tile
 template <int EPI, int MT>
@@ -505,6 +560,13 @@ static void launch_skinny_mt_w8(const bf16_t* Ap, int MT_src, const void* Wq, in
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
+    if constexpr (MT > 1) {
+      if (skinny_splits(MT, KB * 64, e)) {
+        launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s, kSkinnySplit);
+        launch_resid_finish(e, kSkinnySplit, total_nt * 16, s);
+        return;
+      }
+    }
     launch_skinny_t<EPI, MT, 1, 8, (MT > 3 ? 1 : 2), true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else {
     constexpr int U6 = MT > 2 ? 1 : 2, U8 = MT > 3 ? 1 : 2;
@@ -523,6 +585,13 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, (MT > 2 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
+    if constexpr (MT > 1) {
+      if (skinny_splits(MT, KB * 32, e)) {
+        launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s, kSkinnySplit);
+        launch_resid_finish(e, kSkinnySplit, total_nt * 16, s);
+        return;
+      }
+    }
     launch_skinny_t<EPI, MT, 1, 8, 2>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else {
     // (five or six m-tiles: one k-step per register set where two would not fit 256 registers)
@@ -1056,35 +1125,6 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
   kern<<<grid, WM * WN * 64, smem, s>>>((const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT, e);
 }
 
-// Second half of a K-split residual GEMM: h += sum over the splits (fixed order), then what
-// EPI_RESID does: next operand bf16(h * gain) and the row's sum of squares.  Bound by its bytes:
-// every load is requested before the first is used.  768 rows of 4096 in four pieces:
-// 82 MB in 16.3 us (5.0 TB/s, what a large copy reaches).
-// grid (ceil(d / 1024), M), 256 threads, 4 columns per thread.
-template <int KSPLIT>
-__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
-  __shared__ float red[4];
-  const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
-  float part = 0.f;
-  if (n < e.d) {
-    f32x4 p[KSPLIT];
-#pragma unroll
-    for (int z = 0; z < KSPLIT; ++z)
-      p[z] = *(const f32x4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
-    const float4 h = *(const float4*)(e.h + (size_t)m * e.d + n);
-    const u32x2 g4 = *(const u32x2*)(e.gain_next + n);
-    f32x4 v = p[0];
-#pragma unroll
-    for (int z = 1; z < KSPLIT; ++z) v += p[z];
-    part = epi_resid_pre(e, m, n >> 4, (n >> 2) & 3, v, h, g4);
-  }
-  part = block_sum<4>(part, red);
-  if (threadIdx.x == 0) {
-    unsigned long long fx = sumsq_to_fixed<58>(part);
-    if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)(blockIdx.x & (kSumSlots - 1)) * e.sum_stride + m), fx);
-  }
-}
-
 // Block shapes of the tiled kernels (rows x weight rows) and what one k-step costs on MI355X
 // with all 256 CUs busy (us, measured): alone on its CU, and - for the shapes small enough that
 // two blocks share a CU's LDS and registers - per k-step of such a pair.
@@ -1146,15 +1186,6 @@ static void launch_tiled_pick(const bf16_t* Ap, int MT, const bf16_t* Wp, int to
                               const GemmEpi& e, hipStream_t s, int tile, int ksplit) {
   if (e.wscale) launch_tiled_pick_ws<EPI, true>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
   else launch_tiled_pick_ws<EPI, false>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
-}
-
-static void launch_resid_finish(const GemmEpi& e, int ksplit, int N, hipStream_t s) {
-  const dim3 grid((N + 1023) / 1024, e.M);
-  switch (ksplit) {
-    case 2: resid_finish_kernel<2><<<grid, 256, 0, s>>>(e); break;
-    case 3: resid_finish_kernel<3><<<grid, 256, 0, s>>>(e); break;
-    default: resid_finish_kernel<4><<<grid, 256, 0, s>>>(e); break;
-  }
 }
 
 template <int EPI>

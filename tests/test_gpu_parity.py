@@ -560,3 +560,20 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P):
     s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 6), TOL["bf16"], max_steps=2)
     print(s)
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
+
+
+@pytest.mark.parametrize("dtype,hq,d,f,block,k", [
+    ("bf16", 4, 288, 11520, 24, 2),   # 2 row tiles x 11520: the shortest split down projection there
+    ("bf16", 4, 288, 7680, 40, 8),    # 3 row tiles; 18 weight tiles in groups of four
+    ("bf16", 8, 512, 4608, 70, 20),   # 6 row tiles
+    ("fp8w", 4, 320, 7744, 40, 8),    # e4m3 codes, 121 k-steps over four ranges of four waves
+    ("fp8w", 4, 256, 4672, 70, 25),
+])
+def test_partial_step_with_split_down_projection(dtype, hq, d, f, block, k):
+    """Few-row steps whose down projection is split along K over blocks."""
+    cfg = small_cfg(dtype, hq, 2, 64, d=d, f=f, vocab=512, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 71, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=2 * block, block=block, k_recent=k, tokens_per_step=4, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 30, 6), TOL[dtype], max_steps=6)
+    print(s)
+    assert s["modes"][eco.PARTIAL] == 5 and s["rows_stat"] > 0
