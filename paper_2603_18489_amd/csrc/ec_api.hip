@@ -44,7 +44,7 @@ struct Buffers {
   // sequence state, sequence after sequence: x / masked / rows_partial / prompt by positions,
   // the others with the fixed stride named in DecideArgs
   int* x; uint8_t* masked; int* hist; DevState* st; int* mb_pos; int* rows_partial; int* mb_idx;
-  float* row_stats; StepOut* out; int* forced_pos; int* forced_tok; int* prompt;
+  float* row_stats; int* prompt;
   // the step's row list (bf16 path)
   SeqDesc* seqs; int4* rowinfo; int4* tileinfo; int* lm_sel;
   int4* pairs;  // (row tile, sequence) visits of the few-row sequences, [rmax/16 + B]
@@ -116,11 +116,13 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.x = c.take<int>(g.xtot); b.masked = c.take<uint8_t>(g.xtot); b.hist = c.take<int>((size_t)B * N);
   b.st = c.take<DevState>(B); b.mb_pos = c.take<int>(BL); b.rows_partial = c.take<int>(g.xtot);
   b.mb_idx = c.take<int>(BL); b.row_stats = c.take<float>(BL * 4);
-  b.out = c.take<StepOut>(B); b.forced_pos = c.take<int>((size_t)B * EC_MAX_N);
-  b.forced_tok = c.take<int>((size_t)B * EC_MAX_N); b.prompt = c.take<int>(g.ptot);
-  b.seqs = c.take<SeqDesc>(B); b.rowinfo = c.take<int4>(R); b.tileinfo = c.take<int4>(R / 16);
+  b.prompt = c.take<int>(g.ptot);
+  // the sequence table and, right behind it, [B sequence entries][visits]: one upload for both
+  static_assert(sizeof(SeqDesc) % sizeof(int4) == 0, "pairs follow seqs");
+  char* tab = c.take<char>((size_t)B * sizeof(SeqDesc) + (R / 16 + 2 * B) * sizeof(int4));
+  b.seqs = (SeqDesc*)tab; b.pairs = tab ? (int4*)(tab + (size_t)B * sizeof(SeqDesc)) : nullptr;
+  b.rowinfo = c.take<int4>(R); b.tileinfo = c.take<int4>(R / 16);
   b.lm_sel = c.take<int>(BL);
-  b.pairs = c.take<int4>(R / 16 + 2 * B);   // [B sequence entries][visits]
   b.rope_cs = c.take<float2>((size_t)g.tmax * (m.head_dim / 2));
   b.kv_plane = g.kv_plane;
   b.kv = c.take<char>((size_t)m.n_layers * 2 * g.kv_plane * es);
@@ -133,7 +135,7 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.u_lm = c.take<char>(BL16 * m.d_model * es);
   b.logits = c.take<float>(BL * m.vocab);
   {  // partial tuples of the vocabulary reduction: from the LM-head epilogue or from vocab_reduce
-    const size_t np_fused = bf16_path(m.dtype) ? (size_t)lm_head_parts(m.vocab) : 0;
+    const size_t np_fused = bf16_path(m.dtype) ? (size_t)lm_head_parts(m.vocab) : (size_t)(m.vocab + 15) / 16;
     const size_t np_plain = (size_t)vocab_reduce_parts(m.vocab);
     b.partials = c.take<float4>(BL * (np_fused > np_plain ? np_fused : np_plain));
   }
@@ -237,9 +239,10 @@ struct ec_ctx {
   StepOut* host_out = nullptr;   // pinned [B]: the decision kernel writes its results here
   StepOut* host_out_dev = nullptr;  // the same memory as the device addresses it
   int serial = 0;                   // number of the last decision launch (StepOut::serial)
-  int* host_stage = nullptr;     // pinned: prompts / forced lists on their way to the device
-  SeqDesc* host_seqs = nullptr;  // pinned [B]
-  int4* host_pairs = nullptr;    // pinned [rmax/16 + B]
+  int* host_stage = nullptr;     // pinned: prompts on their way to the device, forced lists
+  int* host_stage_dev = nullptr; // (the same memory as the device addresses it)
+  SeqDesc* host_seqs = nullptr;  // pinned [B] ...
+  int4* host_pairs = nullptr;    // ... and behind it [rmax/16 + 2B] (Buffers: seqs, pairs)
   // host mirror of the scalar state, per sequence
   int steps_run = 0;
   std::vector<int> next_mode, has_full, done, n_mb, n_rows_partial;
@@ -313,7 +316,7 @@ void fill_decide_args(ec_ctx* c, DecideArgs& a) {
   a.seqs = c->B == 1 ? nullptr : c->b.seqs;
   a.seq0 = c->host_seqs[0];
   a.partials = c->b.partials; a.nparts = c->step_nparts;
-  a.forced_pos = c->b.forced_pos; a.forced_tok = c->b.forced_tok;
+  a.forced_pos = c->host_stage_dev; a.forced_tok = c->host_stage_dev + (size_t)c->B * EC_MAX_N;
   a.x = c->b.x; a.masked = c->b.masked; a.hist = c->b.hist; a.st = c->b.st;
   a.mb_pos = c->b.mb_pos; a.rows_partial = c->b.rows_partial; a.mb_idx = c->b.mb_idx;
   a.row_stats = c->b.row_stats; a.out = c->host_out_dev;
@@ -447,8 +450,10 @@ int forward_f32(ec_ctx* c, int mode, int M, int n_mb) {
   }
   // logits only for the block's masked rows
   { Scope p(c, EC_K_LMHEAD);
-    launch_gemm_f32(F32_LOGITS, gemm(b.h, lm_sel, n_mb, c->w.lm_head, m.vocab, d,
-                                     c->w.final_norm, b.logits, m.vocab), s); }
+    F32Gemm g = gemm(b.h, lm_sel, n_mb, c->w.lm_head, m.vocab, d, c->w.final_norm, b.logits, m.vocab);
+    g.vparts = b.partials;
+    c->fused_reduce = true;
+    c->step_nparts = launch_gemm_f32(F32_LOGITS, g, s); }
   return EC_OK;
 }
 
@@ -616,17 +621,10 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
     }
   sp.single = sp.n_full + sp.n_partial == 1;
   sp.R = (sp.R + 15) / 16 * 16;
-  if (!sp.single && sp.npairs > 0)
-    EC_HIP(c, hipMemcpyAsync(c->b.pairs, c->host_pairs, (size_t)(B + sp.npairs) * sizeof(int4),
+  if (B > 1) {
+    const size_t npairs = !sp.single && sp.npairs > 0 ? B + sp.npairs : 0;
+    EC_HIP(c, hipMemcpyAsync(c->b.seqs, c->host_seqs, B * sizeof(SeqDesc) + npairs * sizeof(int4),
                              hipMemcpyHostToDevice, c->stream));
-  if (B > 1)
-    EC_HIP(c, hipMemcpyAsync(c->b.seqs, c->host_seqs, (size_t)B * sizeof(SeqDesc),
-                             hipMemcpyHostToDevice, c->stream));
-  if (forced_n) {
-    EC_HIP(c, hipMemcpyAsync(c->b.forced_pos, c->host_stage, (size_t)B * EC_MAX_N * sizeof(int),
-                             hipMemcpyHostToDevice, c->stream));
-    EC_HIP(c, hipMemcpyAsync(c->b.forced_tok, c->host_stage + (size_t)B * EC_MAX_N,
-                             (size_t)B * EC_MAX_N * sizeof(int), hipMemcpyHostToDevice, c->stream));
   }
   // ---- forward, vocabulary reduction, decision ---------------------------------------------------
   c->fused_reduce = false; c->step_nparts = vocab_reduce_parts(c->m.vocab); c->logits_stored = true;
@@ -656,13 +654,6 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
   c->rows_recomputed += sp.rows;
   c->full_steps += sp.n_full;
   c->partial_steps += sp.n_partial;
-  std::vector<DevState> st;
-  if (forced_n) {
-    // the flags follow the committed tokens; the device computed them, mirror them from its state
-    st.resize(B);
-    EC_HIP(c, hipStreamSynchronize(c->stream));
-    EC_HIP(c, hipMemcpy(st.data(), c->b.st, (size_t)B * sizeof(DevState), hipMemcpyDeviceToHost));
-  }
   int all_done = 1;
   foff = 0;
   for (int b = 0; b < B; ++b) {
@@ -683,7 +674,7 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
     if (fn >= 0) {
       for (int i = 0; i < fn; ++i) mh[fpos[f0 + i]] = 0;
       c->tokens += fn;
-      c->next_mode[b] = st[b].skip ? EC_PARTIAL : EC_FULL;
+      c->next_mode[b] = o.skip ? EC_PARTIAL : EC_FULL;   // (the flag follows the committed tokens)
     } else {
       for (int i = 0; i < o.r.n_unmasked; ++i) mh[o.r.positions[i]] = 0;
       c->tokens += o.r.n_unmasked;
@@ -810,7 +801,6 @@ static int init_impl(ec_ctx** out, const ec_model_cfg* model, const ec_weights* 
     if (c->host_out) (void)hipHostFree(c->host_out);
     if (c->host_stage) (void)hipHostFree(c->host_stage);
     if (c->host_seqs) (void)hipHostFree(c->host_seqs);
-    if (c->host_pairs) (void)hipHostFree(c->host_pairs);
     delete c;
     return fail(nullptr, code, msg);
   };
@@ -820,12 +810,14 @@ static int init_impl(ec_ctx** out, const ec_model_cfg* model, const ec_weights* 
   if (e != hipSuccess) return bail(EC_ERR_HIP, std::string("hipHostGetDevicePointer: ") + hipGetErrorString(e));
   memset(c->host_out, 0, (size_t)B * sizeof(StepOut));
   size_t stage = (g.ptot > (size_t)2 * B * EC_MAX_N ? g.ptot : (size_t)2 * B * EC_MAX_N) * sizeof(int);
-  e = hipHostMalloc((void**)&c->host_stage, stage, hipHostMallocDefault);
+  e = hipHostMalloc((void**)&c->host_stage, stage, hipHostMallocCoherent);
   if (e != hipSuccess) return bail(EC_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-  e = hipHostMalloc((void**)&c->host_seqs, (size_t)B * sizeof(SeqDesc), hipHostMallocDefault);
+  e = hipHostGetDevicePointer((void**)&c->host_stage_dev, c->host_stage, 0);
+  if (e != hipSuccess) return bail(EC_ERR_HIP, std::string("hipHostGetDevicePointer: ") + hipGetErrorString(e));
+  e = hipHostMalloc((void**)&c->host_seqs, (size_t)B * sizeof(SeqDesc) + (g.rmax / 16 + 2 * B) * sizeof(int4),
+                    hipHostMallocDefault);
   if (e != hipSuccess) return bail(EC_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-  e = hipHostMalloc((void**)&c->host_pairs, (g.rmax / 16 + 2 * B) * sizeof(int4), hipHostMallocDefault);
-  if (e != hipSuccess) return bail(EC_ERR_HIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
+  c->host_pairs = (int4*)(c->host_seqs + B);
 
   // one-time device set-up: RoPE table, re-tiled bf16 matrices, finite padding keys
   launch_rope_table(c->b.rope_cs, g.tmax, c->m.head_dim, c->m.rope_base, c->stream);
@@ -1035,7 +1027,6 @@ void ec_destroy(ec_ctx* ctx) {
   if (ctx->host_out) (void)hipHostFree(ctx->host_out);
   if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);
   if (ctx->host_seqs) (void)hipHostFree(ctx->host_seqs);
-  if (ctx->host_pairs) (void)hipHostFree(ctx->host_pairs);
   delete ctx;
 }
 

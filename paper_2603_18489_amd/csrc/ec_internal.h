@@ -47,7 +47,8 @@ struct StepOut {
   int next_n_rows_partial;
   int serial;   // the launch's DecideArgs::serial once everything above has been written
   int nonfinite;  // 1: some block row had no finite maximum logit (its token was forced to 0)
-  int pad[4];
+  int skip;       // the context's flag: 1 = next EC_AUTO step is PARTIAL
+  int pad[3];
 };
 
 // Arguments of the decision kernel: one block per sequence.  The pointers are those of sequence
@@ -63,8 +64,8 @@ struct DecideArgs {
   int mode_run;
   int n_rows_run;
   int forced_n;            // -1: commit the step's own choice
-  const int* forced_pos;   // device, stride EC_MAX_N
-  const int* forced_tok;   // device, stride EC_MAX_N
+  const int* forced_pos;   // pinned host memory, stride EC_MAX_N: read where it is, no copy ahead
+  const int* forced_tok;   // of the step (stride EC_MAX_N)
   int init_only;           // 1: no decode, only build the lists of the first step
   // sequence state
   int* x;                  // [T] (x_off)
@@ -108,9 +109,11 @@ struct F32Gemm {
   const float2* cs;               // F32_QKV: RoPE table
   int Hq, Hkv, hd;                // F32_QKV
   float *kc, *vc;                 // F32_QKV: caches, row-major [T, Hkv*hd]
+  float4* vparts;                 // F32_LOGITS: [row][column blocks] partial tuples (k_vtuple.h)
   int nt;                         // (filled in by the launcher)
 };
-void launch_gemm_f32(int epi, F32Gemm g, hipStream_t s);
+// returns the number of column blocks (at most one per 16 output features)
+int launch_gemm_f32(int epi, F32Gemm g, hipStream_t s);
 void launch_attention_f32(const float* q, const float* kc, const float* vc, int M, int T, int Hq,
                           int Hkv, int hd, float* out, hipStream_t s);
 

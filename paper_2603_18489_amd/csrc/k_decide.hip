@@ -114,23 +114,34 @@ void launch_row_stats(const float* logits, int n_rows, int V, size_t ld, float4*
 // ---- block-wide integer helpers (kDecideThreads threads) --------------------------------------
 constexpr int kDecideThreads = 1024, kDecideWaves = kDecideThreads / 64;
 
-// Exclusive prefix of a 0/1 flag over the block; returns the prefix, *total gets the block sum.
-__device__ __forceinline__ int block_excl_scan_flag(int flag, int* scratch, int* total) {
-  unsigned long long ball = __ballot(flag);
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int pre = __popcll(ball & ((1ull << lane) - 1ull));
+// Exclusive prefixes of up to four 0/1 flags over the block and their totals, one exchange for all
+// of them (each count fits 16 bits).  `scratch` may be written again after the next barrier.
+template <int NF>
+__device__ __forceinline__ void block_excl_scan_flags(const bool (&flag)[NF], unsigned long long* scratch,
+                                                      int (&prefix)[NF], int (&total)[NF]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  unsigned long long mine = 0;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const unsigned long long ball = __ballot(flag[f]);
+    prefix[f] = __popcll(ball & below);
+    mine |= (unsigned long long)__popcll(ball) << (16 * f);
+  }
+  if (lane == 0) scratch[w] = mine;
   __syncthreads();
-  if (lane == 0) scratch[w] = __popcll(ball);
-  __syncthreads();
-  int off = 0, tot = 0;
+  unsigned long long off = 0, tot = 0;
 #pragma unroll
   for (int i = 0; i < kDecideWaves; ++i) {
-    const int c = scratch[i];
+    const unsigned long long c = scratch[i];
     off += i < w ? c : 0;
     tot += c;
   }
-  *total = tot;
-  return off + pre;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    prefix[f] += (int)((off >> (16 * f)) & 0xffff);
+    total[f] = (int)((tot >> (16 * f)) & 0xffff);
+  }
 }
 
 // The quantity the threshold is applied to, accumulated over the newly decoded tokens: their
@@ -153,7 +164,12 @@ __device__ __forceinline__ bool gate_skips(float v, float tau, int metric) {
 // decide: one block of kDecideThreads threads per sequence.  Everything the block reads from
 // memory (state, history, mask set, the rows' partial tuples, the caller's forced tokens) is
 // requested up front; from then on it works in LDS and registers, so the kernel's latency is two
-// memory round trips plus arithmetic.
+// memory round trips plus a chain of barriers and exchanges, which is kept short: one exponential to
+// merge a half wave's tuples, no barrier to find the k-th largest history value (up to 512 slots)
+// or the current block, one to compact the three row lists.  The forced lists are read where the
+// host left them and the flag goes back with the result, so a forced step adds no copies.
+// On MI355X a step of the float32 model of 128 positions spends 11.3 us here (15.7 with a barrier
+// per bisection step and per scan), a 2-layer bf16 model's forced step 83 us in all (133).
 // dynamic LDS: int hist[N4] | uint8 masked[N4], N4 = N rounded up to 4
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
@@ -171,11 +187,12 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     a.P = sd.P; a.T = sd.T;
   }
   __shared__ int s_tok[EC_MAX_BLOCK], s_pos[EC_MAX_BLOCK];
-  __shared__ float s_conf[EC_MAX_BLOCK], s_H[EC_MAX_BLOCK];
+  __shared__ __align__(16) float s_conf[EC_MAX_BLOCK];
+  __shared__ float s_H[EC_MAX_BLOCK];
   __shared__ int s_badrow[EC_MAX_BLOCK];  // 1: the row's logits had no finite maximum / sums
   __shared__ int s_sel[EC_MAX_N];    // block rows of the step's own choice, most confident first
   __shared__ int s_frow[EC_MAX_N];   // block rows of the caller's positions (-1: not in the block)
-  __shared__ int scratch[kDecideWaves];
+  __shared__ unsigned long long scratch[2][kDecideWaves];
   __shared__ float sh_f[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int P = a.P, N = a.N;
@@ -192,15 +209,16 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
   int f_pos = -1, f_tok = -1;
   if (!a.init_only) {
     if (tid < a.n_mb) s_pos[tid] = a.mb_pos[tid];
+    else if (tid < EC_MAX_BLOCK) s_conf[tid] = -1.f;   // ranks behind every row
     if (tid < a.forced_n) { f_pos = a.forced_pos[tid]; f_tok = a.forced_tok[tid]; }
   }
   const int t = st.t;
+  int bad_rows = 0;
 
   if (!a.init_only) {
     // ---- merge the vocabulary partials of each block row (fixed order) ----------------------
     // Half a wave per row, 32 rows at a time: lane l of the half merges parts l, l + 32, ... in
-    // that order (sixteen loads in flight), then the 32 tuples are merged pairwise down to the
-    // half's first lane.
+    // that order (sixteen loads in flight), then the 32 tuples are merged at once.
     for (int row0 = 0; row0 < a.n_mb; row0 += 2 * kDecideWaves) {
       const int row = row0 + wave * 2 + (lane >> 5), l32 = lane & 31;
       const bool live = row < a.n_mb;
@@ -239,8 +257,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
           if (ok[u] && d == 0.f && pi < v.idx) v.idx = pi;       // lowest index among equal maxima
         }
       }
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) v = vt_merge(v, vt_shfl_down(v, o));
+      v = vt_merge_half(v);
       if (live && l32 == 0) {
         float conf, H;
         vt_finish(v, conf, H);
@@ -274,9 +291,13 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     int rank = EC_MAX_BLOCK;
     if (is_row) {
       rank = 0;
-      for (int r = 0; r < a.n_mb; ++r) {
-        const float c = s_conf[r];
-        rank += (c > my_conf || (c == my_conf && r < tid)) ? 1 : 0;
+#pragma unroll 4
+      for (int r = 0; r < a.n_mb; r += 4) {   // (four rows a read; those past the end hold -1)
+        const float4 c4 = *(const float4*)(s_conf + r);
+        const float c[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          rank += (c[i] > my_conf || (c[i] == my_conf && r + i < tid)) ? 1 : 0;
       }
       if (rank < n) {
         s_sel[rank] = tid;
@@ -310,7 +331,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
       s_msk[c_pos - P] = 0;
       s_hist[c_pos - P] = t;
     }
-    __syncthreads();
+    bad_rows = __syncthreads_or(is_row && s_badrow[tid]);
     if (tid == 0) {
       // gate values, accumulated in the order of the lists (the entropy sum is order-sensitive)
       GateAcc own = gate_init(a.gate_metric);
@@ -343,12 +364,24 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     int kth = INT_MIN;
     if (a.k_recent > 0) {
       int lo = 1, hi = t, found = INT_MIN;
+      // (up to 512 slots every wave counts for itself, eight to a lane, without a barrier)
+      constexpr int HL = 8;
+      int hv[HL];
+      if (N <= 64 * HL) {
+#pragma unroll
+        for (int u = 0; u < HL; ++u) hv[u] = u * 64 + lane < N ? s_hist[u * 64 + lane] : INT_MIN;
+      }
       while (lo <= hi) {  // uniform across the block
         const int mid = (lo + hi) >> 1;
         int c = 0;
-        for (int base = 0; base < N; base += kDecideThreads) {  // uniform trip count
-          const int i = base + tid;
-          c += __syncthreads_count(i < N && s_hist[i] >= mid);
+        if (N <= 64 * HL) {
+#pragma unroll
+          for (int u = 0; u < HL; ++u) c += __popcll(__ballot(hv[u] >= mid));
+        } else {
+          for (int base = 0; base < N; base += kDecideThreads) {  // uniform trip count
+            const int i = base + tid;
+            c += __syncthreads_count(i < N && s_hist[i] >= mid);
+          }
         }
         if (c >= a.k_recent) { found = mid; lo = mid + 1; } else { hi = mid - 1; }
       }
@@ -369,10 +402,9 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
   const bool sliding = a.schedule == EC_SCHED_SLIDING;
   int blk = st.blk;
   if (!sliding) {
-    while (blk < nblocks) {  // uniform: every thread evaluates the same counts
-      const int lo = blk * a.block, hi = min(N, lo + a.block);
-      const int i = lo + tid;   // block <= EC_MAX_BLOCK <= threads
-      if (__syncthreads_count(i < hi && s_msk[i]) > 0) break;
+    while (blk < nblocks) {  // uniform: every wave looks at the whole block (at most 128 slots)
+      const int lo = blk * a.block + lane, hi = min(N, (blk + 1) * a.block);
+      if (__ballot((lo < hi && s_msk[lo]) || (lo + 64 < hi && s_msk[lo + 64]))) break;
       ++blk;
     }
     st.blk = blk;
@@ -382,34 +414,33 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
   // ---- row lists of the next step: M and M u R, ascending ---------------------------------------
   // M = the masked rows of the current block, or (sliding window) the first `block` masked slots
   const int blo = blk * a.block, bhi = min(N, blo + a.block);   // in generation slots
-  int n_rows = 0, n_mb = 0, n_recent = 0, masked_seen = 0;
-  for (int base = 0; base < N; base += kDecideThreads) {
+  int n_rows = 0, n_mb = 0, n_recent = 0, masked_seen = 0, buf = 0;
+  for (int base = 0; base < N; base += kDecideThreads, buf ^= 1) {
     const int i = base + tid, pos = P + i;
-    int inM = 0, inR = 0, msk = 0;
+    bool inM = false, inR = false, msk = false;
     if (i < N) {
-      msk = s_msk[i] ? 1 : 0;
-      inM = (!sliding && !st.done && i >= blo && i < bhi && msk) ? 1 : 0;
+      msk = s_msk[i] != 0;
+      inM = !sliding && !st.done && i >= blo && i < bhi && msk;
       const int h = s_hist[i];
-      inR = (!a.init_only && h != INT_MIN && h >= tauR) ? 1 : 0;
+      inR = !a.init_only && h != INT_MIN && h >= tauR;
     }
     if (sliding) {
-      int tot_msk;
-      int pre_msk = block_excl_scan_flag(msk, scratch, &tot_msk);
-      inM = (msk && masked_seen + pre_msk < a.block) ? 1 : 0;
-      masked_seen += tot_msk;
+      int pre[1], tot[1];
+      block_excl_scan_flags<1>({msk}, scratch[buf], pre, tot);
+      inM = msk && masked_seen + pre[0] < a.block;
+      masked_seen += tot[0];
+      buf ^= 1;
     }
-    int tot_any, tot_m;
-    int pre_any = block_excl_scan_flag(inM | inR, scratch, &tot_any);
-    int pre_m = block_excl_scan_flag(inM, scratch, &tot_m);
-    const int tot_r = __syncthreads_count(inR);
-    if (inM | inR) a.rows_partial[n_rows + pre_any] = pos;
+    int pre[3], tot[3];
+    block_excl_scan_flags<3>({inM || inR, inM, inR}, scratch[buf], pre, tot);
+    if (inM || inR) a.rows_partial[n_rows + pre[0]] = pos;
     if (inM) {
-      a.mb_pos[n_mb + pre_m] = pos;
-      a.mb_idx[n_mb + pre_m] = n_rows + pre_any;
+      a.mb_pos[n_mb + pre[1]] = pos;
+      a.mb_idx[n_mb + pre[1]] = n_rows + pre[0];
     }
-    n_rows += tot_any;
-    n_mb += tot_m;
-    n_recent += tot_r;
+    n_rows += tot[0];
+    n_mb += tot[1];
+    n_recent += tot[2];
   }
   if (sliding) st.done = (n_mb == 0);
   if (tid == 0) {
@@ -432,10 +463,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     // The result sits in pinned host memory.  The other threads' entries were stored before the
     // barriers above; this fence orders them and the fields above before the serial number, so
     // a host that sees the number sees the whole result.
-    int bad = 0;
-    if (!a.init_only)
-      for (int r = 0; r < a.n_mb; ++r) bad |= s_badrow[r];
-    o.nonfinite = bad;
+    o.nonfinite = bad_rows;
+    o.skip = st.skip;
     __threadfence_system();
     __hip_atomic_store(&o.serial, a.serial, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }

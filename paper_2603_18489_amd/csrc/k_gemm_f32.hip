@@ -19,13 +19,15 @@
 //               rotation pair meets in lanes l and l + 32; v tiles are in natural order.
 //   F32_RESID   h += result
 //   F32_SWIGLU  x 1/rms, silu(gate) * up (8 gate rows and their 8 up rows share a tile)
-//   F32_LOGITS  x 1/rms x logit scale
+//   F32_LOGITS  x 1/rms x logit scale -> logits, and the block's columns of every row reduced to one
+//               (max, argmax, sum e, sum e (z - max)) tuple for the decision kernel
 //
 // On MI355X the 64-step generation of the smallest model (2 layers, d 256, feed-forward 768,
 // vocabulary 4096, 128 positions) takes 5.8 ms, 5 launches per layer; 41 ms with 64 x 64 tiles of
 // scalar loads (8 blocks for N = 256, 30 - 43 us a launch) and norm, rotation and SwiGLU as kernels
 // of their own.
 #include "ec_internal.h"
+#include "k_vtuple.h"
 
 namespace ec {
 
@@ -40,6 +42,7 @@ __global__ __launch_bounds__(KS * 64) void gemm_f32_kernel(F32Gemm g) {
   constexpr int U = 4;
   __shared__ float4 red[KS][TN * TM][64];
   __shared__ float ssq[KS][TM * 16];
+  __shared__ float4 tup[TN][TM * 16];   // F32_LOGITS
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, q4 = lane >> 4;
   const int nt0 = blockIdx.x * TN, mt0 = blockIdx.y * TM;
@@ -182,12 +185,41 @@ __global__ __launch_bounds__(KS * 64) void gemm_f32_kernel(F32Gemm g) {
         *h = o;
       }
     } else {
-      const float x[4] = {v.x, v.y, v.z, v.w};
+      // A row's 16 columns of the tile sit in lanes l, l^16, l^32, l^48, four each; columns past the
+      // vocabulary (any number; rows start anywhere) have probability 0.
+      const int n = vt * 16 + q4 * 4;
+      float z[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {   // (the vocabulary is any number: rows start anywhere)
-        const int n = vt * 16 + q4 * 4 + r;
-        if (valid && n < g.N) g.C[(size_t)m * g.ldc + n] = x[r];
+      for (int r = 0; r < 4; ++r) {
+        if (vt >= g.nt || n + r >= g.N) z[r] = -INFINITY;
+        else if (m < g.M) g.C[(size_t)m * g.ldc + n + r] = z[r];
       }
+      float mx = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+      mx = fmaxf(mx, other_row(mx));
+      mx = fmaxf(mx, other_half(mx));
+      int idx = z[0] == mx ? n : z[1] == mx ? n + 1 : z[2] == mx ? n + 2 : z[3] == mx ? n + 3 : INT_MAX;
+      idx = min(idx, __float_as_int(other_row(__int_as_float(idx))));
+      idx = min(idx, __float_as_int(other_half(__int_as_float(idx))));
+      float s4 = 0.f, t4 = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float d = z[r] - mx, ex = z[r] == -INFINITY ? 0.f : expf(d);
+        s4 += ex;
+        t4 += z[r] == -INFINITY ? 0.f : ex * d;
+      }
+      s4 += other_row(s4); t4 += other_row(t4);
+      s4 += other_half(s4); t4 += other_half(t4);
+      if (q4 == 0) tup[i][j * 16 + r16] = make_float4(mx, __int_as_float(idx), s4, t4);
+    }
+  }
+  if constexpr (EPI == F32_LOGITS) {
+    __syncthreads();
+    const int m = mt0 * 16 + (int)threadIdx.x;
+    if (threadIdx.x < TM * 16 && m < g.M) {
+      VTuple t = vt_unpack(tup[0][threadIdx.x]);
+#pragma unroll
+      for (int i = 1; i < TN; ++i) t = vt_merge(t, vt_unpack(tup[i][threadIdx.x]));
+      g.vparts[(size_t)m * gridDim.x + blockIdx.x] = vt_pack(t);
     }
   }
 }
@@ -207,26 +239,27 @@ static void launch_f32_t(const F32Gemm& g, hipStream_t s) {
 //   gate/up  K  512, 3456 tiles   1x1 8 waves 33.2   2x2 4 waves 21.4       2x2 8 waves 22.0
 //   O, down  K 1536,  576 tiles   1x1 8 waves 13.6   2x2 4 waves 15.8       2x2 8 waves 12.0
 template <int EPI>
-static void launch_f32(const F32Gemm& g, bool vec, hipStream_t s) {
+static int launch_f32(const F32Gemm& g, bool vec, hipStream_t s) {
   const bool few = (long)g.nt * ((g.M + 15) / 16) <= 512, short_k = g.K <= 256;
   if (!vec) launch_f32_t<EPI, 1, 8, false>(g, s);
   else if (few && short_k) launch_f32_t<EPI, 1, 4, true>(g, s);
   else if (few) launch_f32_t<EPI, 1, 8, true>(g, s);
   else if (short_k) launch_f32_t<EPI, 2, 4, true>(g, s);
   else launch_f32_t<EPI, 2, 8, true>(g, s);
+  return vec && !few ? (g.nt + 1) / 2 : g.nt;
 }
 
-void launch_gemm_f32(int epi, F32Gemm g, hipStream_t s) {
-  if (g.M <= 0) return;
+int launch_gemm_f32(int epi, F32Gemm g, hipStream_t s) {
+  if (g.M <= 0) return 0;
   g.nt = epi == F32_QKV ? (g.Hq + 2 * g.Hkv) * (g.hd / 16)
        : epi == F32_SWIGLU ? g.N / 8 : (g.N + 15) / 16;
   // the caller's tensors may start at any element; the workspace is aligned
   const bool vec = (((uintptr_t)g.W[0] | (uintptr_t)g.W[1] | (uintptr_t)g.W[2] | (uintptr_t)g.gain) & 15) == 0;
   switch (epi) {
-    case F32_QKV: launch_f32<F32_QKV>(g, vec, s); break;
-    case F32_RESID: launch_f32<F32_RESID>(g, vec, s); break;
-    case F32_SWIGLU: launch_f32<F32_SWIGLU>(g, vec, s); break;
-    default: launch_f32<F32_LOGITS>(g, vec, s); break;
+    case F32_QKV: return launch_f32<F32_QKV>(g, vec, s);
+    case F32_RESID: return launch_f32<F32_RESID>(g, vec, s);
+    case F32_SWIGLU: return launch_f32<F32_SWIGLU>(g, vec, s);
+    default: return launch_f32<F32_LOGITS>(g, vec, s);
   }
 }
 

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <limits.h>
 
+#include "k_common.h"
+
 namespace ec {
 
 struct VTuple {
@@ -87,6 +89,26 @@ __device__ __forceinline__ VTuple vt_shfl_down(const VTuple& v, int o) {
   return r;
 }
 
+// The 32 tuples of a half wave merged at once: every lane re-bases its own to the common maximum
+// (one exponential), then the sums go through lane exchanges.  All lanes of the half return the result.
+__device__ __forceinline__ VTuple vt_merge_half(const VTuple& v) {
+  VTuple r;
+  float m = v.m;
+  m = fmaxf(m, dpp_f<0xB1>(m)); m = fmaxf(m, dpp_f<0x4E>(m));
+  m = fmaxf(m, dpp_f<0x141>(m)); m = fmaxf(m, dpp_f<0x140>(m));
+  r.m = fmaxf(m, other_row(m));
+  int idx = v.s != 0.f && v.m == r.m ? v.idx : INT_MAX;
+  idx = min(idx, dpp_i<0xB1>(idx)); idx = min(idx, dpp_i<0x4E>(idx));
+  idx = min(idx, dpp_i<0x141>(idx)); idx = min(idx, dpp_i<0x140>(idx));
+  r.idx = min(idx, __float_as_int(other_row(__int_as_float(idx))));
+  const float d = v.m - r.m, e = expf(d);
+  float s = v.s != 0.f ? v.s * e : 0.f, t = v.s != 0.f ? e * (v.t + d * v.s) : 0.f;
+  s += dpp_f<0xB1>(s); s += dpp_f<0x4E>(s); s += dpp_f<0x141>(s); s += dpp_f<0x140>(s);
+  t += dpp_f<0xB1>(t); t += dpp_f<0x4E>(t); t += dpp_f<0x141>(t); t += dpp_f<0x140>(t);
+  r.s = s + other_row(s);
+  r.t = t + other_row(t);
+  return r;
+}
 __device__ __forceinline__ float4 vt_pack(const VTuple& v) {
   return make_float4(v.m, __int_as_float(v.idx), v.s, v.t);
 }

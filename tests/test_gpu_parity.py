@@ -577,3 +577,32 @@ def test_partial_step_with_split_down_projection(dtype, hq, d, f, block, k):
     s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 30, 6), TOL[dtype], max_steps=6)
     print(s)
     assert s["modes"][eco.PARTIAL] == 5 and s["rows_stat"] > 0
+
+
+@pytest.mark.parametrize("N,block,k,n,sliding", [
+    (512, 128, 30, 30, 0),     # the most slots the waves count for themselves, the largest block
+    (513, 100, 3, 32, 1),      # one more; sliding window
+    (1100, 65, 64, 32, 0),     # more slots than threads
+    (1030, 7, 0, 7, 1),        # nothing recent; two rounds of the row lists
+])
+def test_decision_bookkeeping_sizes(N, block, k, n, sliding):
+    """Row sets, history and flags over whole generations whose slot counts cross the decision
+    kernel's limits (bit-exact against the oracle, teacher forced)."""
+    cfg = small_cfg("f32", 2, 1, 64, d=64, f=64, vocab=300, layers=1, scale=6.0)
+    w = ec_inputs.make_weights(cfg, 73, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=N, block=block, k_recent=k, tokens_per_step=n, tau=1e9,
+                              schedule=sliding)
+    prompt = ec_inputs.make_prompt(cfg.vocab, 3, 6)
+    st = eco.eco_init(eco.OracleModel(cfg, w), dec, prompt)
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, prompt)
+    while not st.done:
+        r = eco.eco_step(st, eco.AUTO, keep_logits=False)
+        q = g.step_forced(r["mode"], r["positions"], r["tokens"])
+        assert q["done"] == st.done and q["n_block_rows"] == len(r["Mb"]) and q["n_query_rows"] == len(r["S"])
+        assert q["n_recent_next"] == len(r["R"])
+        if not st.done:
+            rows = sorted(set(eco.current_block_masked(st).tolist()) | set(r["R"]))
+            assert g.debug_read(ec.EC_DBG_ROWS, count=len(rows)).tolist() == rows
+    assert np.array_equal(g.debug_read(ec.EC_DBG_X), st.x.astype(np.int32))
+    assert g.debug_read(ec.EC_DBG_HIST).tolist() == [int(h) for h in st.hist]
+    g.close()
