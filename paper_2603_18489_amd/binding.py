@@ -191,26 +191,36 @@ def weights_to_device(cfg, w: Dict[str, object], device="cuda:0") -> Dict[str, o
     return out
 
 
+def _raw_stream(torch, stream) -> int:
+    """hipStream_t of `stream`, or of the current device's current stream (looked up without making
+    a stream object: 0.4 us instead of 2.7, in a call of about 8)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def row_entropy(logits, stream=None):
     """ec_row_entropy on a float32 CUDA tensor [rows, vocab] (row stride = logits.stride(0)):
     returns a float32 CUDA tensor [rows, 4] (token, confidence, entropy, max logit).  The
-    workspace is a torch allocation; the call is enqueued on `stream` (default: current)."""
+    workspace is a torch allocation.  Without `stream` the call is ordered on the current stream
+    like any torch operation; with one it is enqueued there and waited for."""
     import torch
-    lib = load_library()
+    lib = _lib or load_library()
     rows, vocab = logits.shape
     assert logits.dtype == torch.float32 and logits.stride(1) == 1
     stats = torch.empty((rows, 4), dtype=torch.float32, device=logits.device)
     if rows == 0:
         return stats         # (an empty tensor has no address to hand over)
     need = lib.ec_row_entropy_workspace_bytes(rows, vocab)
+    # (result and workspace belong to the current stream: on that one the allocator hands their memory
+    # on behind this call only; another stream has to be done with the workspace on return)
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=logits.device)
-    st = stream if stream is not None else torch.cuda.current_stream()
-    rc = lib.ec_row_entropy(C.c_void_p(logits.data_ptr()), rows, vocab,
-                            logits.stride(0) if rows > 1 else vocab, C.c_void_p(stats.data_ptr()),
-                            C.c_void_p(ws.data_ptr()), need, C.c_void_p(st.cuda_stream))
+    rc = lib.ec_row_entropy(logits.data_ptr(), rows, vocab, logits.stride(0) if rows > 1 else vocab,
+                            stats.data_ptr(), ws.data_ptr(), need, _raw_stream(torch, stream))
     if rc != EC_OK:
         raise EcError(rc, lib.ec_last_error(None).decode())
-    st.synchronize()     # the workspace is released on return
+    if stream is not None:
+        stream.synchronize()
     return stats
 
 
@@ -218,14 +228,13 @@ def row_entropy_noalloc(logits, stats, stream=None):
     """ec_row_entropy_noalloc: `stats` is a caller-provided float32 CUDA tensor [rows, 4]; the
     call itself allocates nothing.  Enqueued on `stream` (default: current), not synchronised."""
     import torch
-    lib = load_library()
+    lib = _lib or load_library()
     rows, vocab = logits.shape
     assert logits.dtype == torch.float32 and logits.stride(1) == 1
     assert stats.dtype == torch.float32 and stats.is_contiguous() and stats.shape == (rows, 4)
-    st = stream if stream is not None else torch.cuda.current_stream()
-    rc = lib.ec_row_entropy_noalloc(C.c_void_p(logits.data_ptr()), rows, vocab,
-                                    logits.stride(0) if rows > 1 else vocab,
-                                    C.c_void_p(stats.data_ptr()), C.c_void_p(st.cuda_stream))
+    rc = lib.ec_row_entropy_noalloc(logits.data_ptr(), rows, vocab,
+                                    logits.stride(0) if rows > 1 else vocab, stats.data_ptr(),
+                                    _raw_stream(torch, stream))
     if rc != EC_OK:
         raise EcError(rc, lib.ec_last_error(None).decode())
 

@@ -91,3 +91,21 @@ def test_row_entropy_part_edges_and_values_without_a_distribution(rows, V, pad):
     zt[0, V // 2] = float("inf")
     s = ec.row_entropy(zt).cpu().numpy()
     assert s[0, 0] == V // 2 and s[0, 1] == 1.0 and s[0, 2] == 0.0
+
+
+def test_row_entropy_streams():
+    """The default stream, a current side stream and an explicit one give the same bits, also when
+    the workspace's memory is handed on to later work right behind the call."""
+    z = torch.randn((64, 40000), dtype=torch.float32, device="cuda") * 4.0
+    ref = ec.row_entropy(z).cpu().numpy()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        got = []
+        for _ in range(4):
+            got.append(ec.row_entropy(z))
+            torch.empty(ec.load_library().ec_row_entropy_workspace_bytes(64, 40000),
+                        dtype=torch.uint8, device="cuda").fill_(255)
+        got = [g.cpu().numpy() for g in got]
+    explicit = ec.row_entropy(z, stream=side).cpu().numpy()
+    assert all(np.array_equal(g, ref) for g in got) and np.array_equal(explicit, ref)
