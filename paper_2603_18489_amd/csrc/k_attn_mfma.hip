@@ -8,10 +8,21 @@
 //   S^T[keys x queries] = K . Q^T          (2 key tiles x HD/32 MFMAs, K fragments straight from
 //                                            the cache, Q fragments held in registers)
 //   online softmax down the key axis        (a lane owns 8 consecutive keys of one query; the
-//                                            other 24 are 2 xor-shuffles away)
+//                                            other 24 are 2 lane swaps away)
 //   O^T[hd x queries] += V^T . P^T          (HD/16 MFMAs; the lane's 8 probabilities ARE the
 //                                            B operand, V^T fragments straight from the cache)
 // Every operand load is a coalesced 1 KiB fragment in the cache's own layout.
+//
+// With many rows the softmax arithmetic bounds the kernels (two waves per SIMD, 16 MFMAs to a chunk
+// and tile): bare exp2 instructions (arguments at most 8; what underflows is far below a bf16
+// probability), row sums kept per lane, and a reference that moves only when it has to take a chunk
+// from 180 vector instructions to 70.  us per launch on MI355X, before -> now:
+//   768 rows x 768 keys x 32 heads          29.1 -> 22.8
+//   1280 x 1280 x 28 heads on 4 kv heads    69.0 -> 49.9
+//   16 x (1536 x 1536) x 32 heads           1038 -> 770 (0.80 PFLOP/s)
+// (Maxima in inline assembly are not an option: nothing there waits for the MFMAs' results.)
+// Reading the next chunk's K and this one's V from the ring during the softmax gained 3 % with two
+// tiles a wave and cost the one-tile kernels their second block per compute unit (50 -> 64).
 //
 // Two kernels:
 //   split   (few query rows, partial step): a block owns one query tile of one kv head and its
@@ -35,8 +46,24 @@ __device__ __forceinline__ bf16x8 u4_as_bf16x8(uint4 v) {
   return c.b;
 }
 
+__device__ __forceinline__ float max_of_swap16(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float max_of_swap32(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// a query's sum over its four lanes
+__device__ __forceinline__ float sum_of_lanes4(float x) {
+  x += other_row(x);
+  return x + other_half(x);
+}
+
 // One 32-key chunk for one 16-query tile: S^T = K Q^T, online softmax down the keys, O^T += V^T P^T.
-// kf / vf: the chunk's K and V^T fragments; qf: the tile's Q fragments; the lane owns query
+// l_run: the lane's part of the softmax denominator.  kf / vf: the chunk's K and V^T fragments; qf: the tile's Q fragments; the lane owns query
 // (lane & 15) and keys key0 .. key0+7.  mask_tail (wave-uniform): keys >= T are padding.
 template <int HB, int HT>
 __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const bf16x8 (&vf)[HT],
@@ -61,21 +88,17 @@ __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const
   }
   float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])),
                    fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-  // (lane swaps in the vector ALU: the cross-lane path through LDS costs four round trips here)
-  mx = fmaxf(mx, other_row(mx));
-  mx = fmaxf(mx, other_half(mx));
-  const float m_new = fmaxf(m_run, mx * scale_log2e);  // scale > 0: max commutes with it
-  float rs = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sv[e] = exp2f(fmaf(sv[e], scale_log2e, -m_new));
-    rs += sv[e];
-  }
-  rs += other_row(rs);
-  rs += other_half(rs);
-  // the accumulators are rescaled only when some query of the wave saw a new maximum
-  if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-    const float alpha = exp2f(m_run - m_new);  // 0 on the first chunk, 1 where nothing changed
+  // (the two halves a lane swap returns hold the value and its partner's: their maximum is both's)
+  mx = max_of_swap16(mx);
+  mx = max_of_swap32(mx) * scale_log2e;  // scale > 0: max commutes with it
+  // The reference of the exponentials only moves when some query of the wave exceeds it by more than
+  // 2^8: probabilities are then up to 2^8 instead of 1, with the same relative precision in bf16
+  // and in the float32 sums, and the accumulators are rescaled once or twice per tile instead of
+  // in nearly every chunk.
+  if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.0f) != 0) {
+    const float m_new = fmaxf(m_run, mx);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first chunk
+    m_run = m_new;
     l_run *= alpha;
 #pragma unroll
     for (int h = 0; h < HT; ++h) {
@@ -84,8 +107,12 @@ __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const
       acc[h] = a;
     }
   }
-  l_run += rs;
-  m_run = m_new;
+  // (the lane's own 8 keys: the query's four lanes are added up once, at the end)
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    sv[e] = __builtin_amdgcn_exp2f(fmaf(sv[e], scale_log2e, -m_run));
+    l_run += sv[e];
+  }
   uint4 pu = make_uint4(pack2_bf16(sv[0], sv[1]), pack2_bf16(sv[2], sv[3]),
                         pack2_bf16(sv[4], sv[5]), pack2_bf16(sv[6], sv[7]));
   const bf16x8 pf = u4_as_bf16x8(pu);
@@ -239,6 +266,7 @@ __global__ __launch_bounds__(512) void attn_mfma_split_kernel(
   // Every wave parks (m, l, O) in LDS; after one barrier wave w combines the NW copies of hd tile
   // w (and w + NW, ...) in wave order, normalises and stores it.
   constexpr int SLOT = HT * 64 + 32;  // float4 per wave: O tiles + (m, l) pairs
+  l_run = sum_of_lanes4(l_run);
   {
     float4* slot = lds + (size_t)wave * SLOT;
 #pragma unroll
@@ -259,7 +287,7 @@ __global__ __launch_bounds__(512) void attn_mfma_split_kernel(
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     float2 ml = ((const float2*)(lds + (size_t)w * SLOT + HT * 64))[lane];
-    wgt[w] = ml.y > 0.f ? exp2f(wgt[w] - m_all) : 0.f;  // a wave without keys has weight 0
+    wgt[w] = ml.y > 0.f ? __builtin_amdgcn_exp2f(wgt[w] - m_all) : 0.f;  // a wave without keys has weight 0
     l_all += ml.y * wgt[w];
   }
   const int nz = gridDim.z;
@@ -313,7 +341,7 @@ __global__ __launch_bounds__(512) void attn_mfma_split_kernel(
     for (int z = 0; z < nz; ++z) {
       const float* pz = base + (size_t)z * PSLOT;
       const float2 ml = ld_agent(pz + HT * 256 + lane * 2);
-      const float wz = ml.y > 0.f ? exp2f(ml.x - m_fin) : 0.f;
+      const float wz = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - m_fin) : 0.f;
       const float2 a = ld_agent(pz + (h * 64 + lane) * 4), b = ld_agent(pz + (h * 64 + lane) * 4 + 2);
       l_fin += ml.y * wz;
       o.x += a.x * wz; o.y += a.y * wz; o.z += b.x * wz; o.w += b.y * wz;
@@ -458,8 +486,8 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_shared_kernel(
 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
+    const float inv = 1.0f / sum_of_lanes4(l_run[t]);
     if (qrow[t] >= R) continue;
-    float inv = 1.0f / l_run[t];
 #pragma unroll
     for (int h = 0; h < HT; ++h) {
       f32x4 a = acc[t][h];

@@ -606,3 +606,18 @@ def test_decision_bookkeeping_sizes(N, block, k, n, sliding):
     assert np.array_equal(g.debug_read(ec.EC_DBG_X), st.x.astype(np.int32))
     assert g.debug_read(ec.EC_DBG_HIST).tolist() == [int(h) for h in st.hist]
     g.close()
+
+
+@pytest.mark.parametrize("P,gain", [(230, 1.0), (230, 12.0), (2120, 6.0)])
+def test_attention_scores_that_keep_growing(P, gain):
+    """Keys whose scores grow along the context, slowly and fast, so that the softmax reference stays,
+    moves now and then, and moves often (full and partial steps, key slices over blocks)."""
+    cfg = small_cfg("bf16", 4, 2, 64, layers=1, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 79, gain_jitter=0.1)
+    # sharper scores: larger queries (the attention norm's gain also scales k and v, both sides see it)
+    from tests.gpu_harness import bf16_bits_to_f32
+    w["wq"][0] = ec_inputs.f32_to_bf16_bits(bf16_bits_to_f32(w["wq"][0]) * np.float32(gain))
+    dec = ec_inputs.DecodeCfg(gen_len=24, block=16, k_recent=2, tokens_per_step=2, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 7), TOL["bf16"], max_steps=4)
+    print(s)
+    assert s["tokens_exact"] > 0
