@@ -31,7 +31,7 @@
 //     activation fragments come from L2.  The KS partial tiles are summed in LDS in a fixed
 //     order, then the epilogue runs on the sums.
 //   tiled (M > 96): block tile chosen per shape so that the grid fills the 256 CUs.  4 waves:
-//     LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384): operands
+//     LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384, 256x256): operands
 //     loaded from global memory directly into a 3-stage LDS ring.
 #include "ec_internal.h"
 #include "k_vtuple.h"
@@ -1128,8 +1128,16 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // Block shapes of the tiled kernels (rows x weight rows) and what one k-step costs on MI355X
 // with all 256 CUs busy (us, measured): alone on its CU, and - for the shapes small enough that
 // two blocks share a CU's LDS and registers - per k-step of such a pair.
-//   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128
+//   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128   8: 192 x 320   9: 256 x 256
 //   4 waves: 4: 192 x 192   5: 192 x 128   6: 128 x 128   7: 96 x 128
+// What a whole launch loses most by is its last round: shapes 8 and 9 are there for the sizes at which
+// the others leave compute units or rows idle.  us per launch, best of 0 - 7 -> with 8 and 9:
+//   544 rows   gate/up  4096 -> 2 x 12288  192 blocks of 0, 231 of 8             122 -> 107
+//   512 rows   LM head  4096 -> 126464     990 of 0 in 576 rows, 988 of 9        543 -> 481
+//   1280 rows  gate/up  3584 -> 2 x 18944  693 of 0, 740 of 9 (in three rounds)  344 -> 314
+//   1280 rows  down     18944 -> 3584      3 x 70 of 0, 3 x 84 of 8              187 -> 161
+//   3552 rows  O + down                    209 of 0, 247 of 8                    480 -> 436
+//   24576 rows O + down                    2048 of 1, 1536 of 9                  2965 -> 2717
 // Two waves per SIMD overlap one wave's LDS reads and barrier waits with the other's MFMAs, four
 // (two 8-wave blocks) do so better still.  The wider the block the fewer operand bytes per flop
 // cross L2 and LDS.  A grid that does not fill the 256 CUs in whole rounds wastes the
@@ -1137,11 +1145,11 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // a small second kernel sums.  Two blocks to a CU need the 128-register kernels, which only the
 // plain store epilogue of a K split fits.
 struct TilePick { int tile, ksplit; };
-constexpr int kNumTiles = 8;
-static const int kTileM[kNumTiles] = {12, 12, 12, 12, 12, 12, 8, 6};
-static const int kTileN[kNumTiles] = {24, 16, 12, 8, 12, 8, 8, 8};
-static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.41f};
-static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.93f, 0.75f, 0.f, 0.f, 0.f, 0.f};
+constexpr int kNumTiles = 10;
+static const int kTileM[kNumTiles] = {12, 12, 12, 12, 12, 12, 8, 6, 12, 16};
+static const int kTileN[kNumTiles] = {24, 16, 12, 8, 12, 8, 8, 8, 20, 16};
+static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.41f, 0.78f, 0.80f};
+static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.93f, 0.75f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
 // epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
 // cache stores of q k v, the residual stream's read and write; partial products are plain stores.
@@ -1177,7 +1185,9 @@ static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int
     case 4: launch_tiled4_t<EPI, 6, 6, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
     case 5: launch_tiled4_t<EPI, 6, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
     case 6: launch_tiled4_t<EPI, 4, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    default: launch_tiled4_t<EPI, 3, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
+    case 7: launch_tiled4_t<EPI, 3, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
+    case 8: launch_tiled8_t<EPI, WS, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
+    default: launch_tiled8_t<EPI, WS, 2, 4, 8, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
   }
 }
 

@@ -550,6 +550,8 @@ def test_f32_gemm_edges(hq, hkv, hd, d, f, vocab, P, shift):
     (4, 2, 64, 288, 12320, 760),    # 9 k-steps, an odd number; 1540 weight tiles
     (4, 4, 64, 32, 4128, 900),      # a single k-step; 129 k-steps for 2 weight tiles
     (8, 8, 128, 1056, 6176, 1400),  # 33 and 193 k-steps, uneven K ranges, ragged row and column tiles
+    (4, 4, 64, 96, 12224, 520),     # gate/up in 192 x 320 blocks, the last row and column block ragged
+    (4, 4, 64, 96, 8192, 760),      # gate/up in 256 x 256 blocks, the last of four row blocks 3 rows
 ])
 def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P):
     """The many-row GEMMs at odd and tiny numbers of k-steps, with tiles that the matrices do not
