@@ -14,7 +14,7 @@
 // Every operand load is a coalesced 1 KiB fragment in the cache's own layout.
 //
 // With many rows the softmax arithmetic bounds the kernels (two waves per SIMD, 16 MFMAs to a chunk
-// and tile): bare exp2 instructions (arguments at most 8; what underflows is far below a bf16
+// and tile): bare exp2 instructions (arguments at most 10; what underflows is far below a bf16
 // probability), row sums kept per lane, and a reference that moves only when it has to take a chunk
 // from 180 vector instructions to 70.  us per launch on MI355X, before -> now:
 //   768 rows x 768 keys x 32 heads          29.1 -> 22.8
@@ -92,10 +92,10 @@ __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const
   mx = max_of_swap16(mx);
   mx = max_of_swap32(mx) * scale_log2e;  // scale > 0: max commutes with it
   // The reference of the exponentials only moves when some query of the wave exceeds it by more than
-  // 2^8: probabilities are then up to 2^8 instead of 1, with the same relative precision in bf16
+  // 2^10: probabilities are then up to 2^10 instead of 1, with the same relative precision in bf16
   // and in the float32 sums, and the accumulators are rescaled once or twice per tile instead of
   // in nearly every chunk.
-  if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.0f) != 0) {
+  if (__builtin_amdgcn_ballot_w64(mx > m_run + 10.0f) != 0) {
     const float m_new = fmaxf(m_run, mx);
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first chunk
     m_run = m_new;
