@@ -205,6 +205,16 @@ def row_entropy(logits, stream=None):
     workspace is a torch allocation.  Without `stream` the call is ordered on the current stream
     like any torch operation; with one it is enqueued there and waited for."""
     import torch
+    if stream is not None:
+        # Result and workspace come from the pool of the stream that the kernels run on: the current
+        # stream's pool may hand out the workspace of an earlier call whose kernels are still pending.
+        here = torch.cuda.current_stream()
+        with torch.cuda.stream(stream):
+            stats = row_entropy(logits)
+        stream.synchronize()
+        if stats.shape[0] and stream != here:
+            stats.record_stream(here)    # the caller goes on with it there
+        return stats
     lib = _lib or load_library()
     rows, vocab = logits.shape
     assert logits.dtype == torch.float32 and logits.stride(1) == 1
@@ -212,15 +222,12 @@ def row_entropy(logits, stream=None):
     if rows == 0:
         return stats         # (an empty tensor has no address to hand over)
     need = lib.ec_row_entropy_workspace_bytes(rows, vocab)
-    # (result and workspace belong to the current stream: on that one the allocator hands their memory
-    # on behind this call only; another stream has to be done with the workspace on return)
+    # (both belong to the current stream: the allocator hands their memory on behind this call only)
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=logits.device)
     rc = lib.ec_row_entropy(logits.data_ptr(), rows, vocab, logits.stride(0) if rows > 1 else vocab,
-                            stats.data_ptr(), ws.data_ptr(), need, _raw_stream(torch, stream))
+                            stats.data_ptr(), ws.data_ptr(), need, _raw_stream(torch, None))
     if rc != EC_OK:
         raise EcError(rc, lib.ec_last_error(None).decode())
-    if stream is not None:
-        stream.synchronize()
     return stats
 
 

@@ -109,3 +109,31 @@ def test_row_entropy_streams():
         got = [g.cpu().numpy() for g in got]
     explicit = ec.row_entropy(z, stream=side).cpu().numpy()
     assert all(np.array_equal(g, ref) for g in got) and np.array_equal(explicit, ref)
+
+
+@pytest.mark.parametrize("side_first", [False, True])
+def test_row_entropy_calls_on_two_streams_at_once(side_first):
+    """A call on the current stream, still pending, and a call on another stream with logits of its own:
+    each gives the bits it gives alone.  (More than 16384 logits: the two-launch form, whose partial
+    tuples live in the workspace.)"""
+    R, V = 128, 163840
+    a = torch.randn((R, V), dtype=torch.float32, device="cuda") * 4.0
+    b = torch.randn((R, V), dtype=torch.float32, device="cuda") * 8.0
+    ref_a, ref_b = ec.row_entropy(a).cpu().numpy(), ec.row_entropy(b).cpu().numpy()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(4):
+        busy = [torch.mul(a, 1.0) for _ in range(3)]      # the current stream is behind
+        if side_first:
+            got_b = ec.row_entropy(b, stream=side)
+            got_a = ec.row_entropy(a)
+        else:
+            got_a = ec.row_entropy(a)
+            got_b = ec.row_entropy(b, stream=side)
+        late = got_b * 1.0                                # used on the current stream, then given back
+        del got_b
+        more = ec.row_entropy(a, stream=side)
+        assert np.array_equal(got_a.cpu().numpy(), ref_a)
+        assert np.array_equal(late.cpu().numpy(), ref_b)
+        assert np.array_equal(more.cpu().numpy(), ref_a)
+        del busy
