@@ -205,6 +205,10 @@ def row_entropy(logits, stream=None):
     workspace is a torch allocation.  Without `stream` the call is ordered on the current stream
     like any torch operation; with one it is enqueued there and waited for."""
     import torch
+    dev = logits.get_device()
+    if 0 <= dev != torch.cuda.current_device():   # (the kernels run where the logits are)
+        with torch.cuda.device(dev):
+            return row_entropy(logits, stream)
     if stream is not None:
         # Result and workspace come from the pool of the stream that the kernels run on: the current
         # stream's pool may hand out the workspace of an earlier call whose kernels are still pending.
@@ -235,6 +239,10 @@ def row_entropy_noalloc(logits, stats, stream=None):
     """ec_row_entropy_noalloc: `stats` is a caller-provided float32 CUDA tensor [rows, 4]; the
     call itself allocates nothing.  Enqueued on `stream` (default: current), not synchronised."""
     import torch
+    dev = logits.get_device()
+    if 0 <= dev != torch.cuda.current_device():
+        with torch.cuda.device(dev):
+            return row_entropy_noalloc(logits, stats, stream)
     lib = _lib or load_library()
     rows, vocab = logits.shape
     assert logits.dtype == torch.float32 and logits.stride(1) == 1

@@ -107,3 +107,23 @@ def test_the_workspace_belongs_to_the_stream_that_uses_it(torch):
     assert side.waited == 1 and torch.current[0] is here
     # the caller goes on with the result on its own stream
     assert r is torch.launches[1][0] and r.recorded == [here]
+
+
+def test_logits_on_a_device_that_is_not_current(torch):
+    """The kernels run on the device of the logits, on that device's current stream: the one that result
+    and workspace belong to."""
+    z = Tensor(torch, (64, 40000), "float32", 1)
+    r = binding.row_entropy(z)
+    stats, ws, raw, dev = torch.launches.pop()
+    assert (raw, dev) == (1001, 1) and r is stats
+    assert stats.owner.cuda_stream == ws.owner.cuda_stream == raw
+    binding.row_entropy_noalloc(z, r)
+    assert torch.launches.pop()[2:] == (1001, 1)
+    side = Stream(8, 1)
+    r = binding.row_entropy(z, stream=side)
+    stats, ws, raw, dev = torch.launches.pop()
+    assert (raw, dev) == (8, 1) and stats.owner is ws.owner is side and r.recorded == [torch.current[1]]
+    binding.row_entropy_noalloc(z, r, stream=side)
+    assert torch.launches.pop()[2:] == (8, 1)
+    assert torch.dev == 0
+
