@@ -127,3 +127,10 @@ def test_logits_on_a_device_that_is_not_current(torch):
     assert torch.launches.pop()[2:] == (8, 1)
     assert torch.dev == 0
 
+
+
+def test_current_stream_without_the_short_lookup(torch):
+    """torch's undocumented lookup of the current stream is used only where it exists."""
+    del torch._C._cuda_getCurrentRawStream
+    binding.row_entropy(Tensor(torch, (2, 100), "float32", 0))
+    assert torch.launches.pop()[2] == 1000
