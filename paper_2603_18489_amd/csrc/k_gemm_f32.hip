@@ -238,15 +238,20 @@ static void launch_f32_t(const F32Gemm& g, hipStream_t s) {
 //   gate/up  K  256,  768 tiles   1x1 4 waves  7.2            8 waves 10.6  2x2 4 waves  6.5
 //   gate/up  K  512, 3456 tiles   1x1 8 waves 33.2   2x2 4 waves 21.4       2x2 8 waves 22.0
 //   O, down  K 1536,  576 tiles   1x1 8 waves 13.6   2x2 4 waves 15.8       2x2 8 waves 12.0
+// Weights that are not 16-byte aligned are read by single elements and take the same two block
+// shapes, eight waves each; LM head and decision at 128 rows, four tiles instead of one to a block:
+// K 256, vocabulary 126464: 690 -> 404; K 512, 151936: 1230 -> 667 (half the tuples to merge, too).
 template <int EPI>
 static int launch_f32(const F32Gemm& g, bool vec, hipStream_t s) {
   const bool few = (long)g.nt * ((g.M + 15) / 16) <= 512, short_k = g.K <= 256;
-  if (!vec) launch_f32_t<EPI, 1, 8, false>(g, s);
-  else if (few && short_k) launch_f32_t<EPI, 1, 4, true>(g, s);
+  if (!vec) {
+    if (few) launch_f32_t<EPI, 1, 8, false>(g, s);
+    else launch_f32_t<EPI, 2, 8, false>(g, s);
+  } else if (few && short_k) launch_f32_t<EPI, 1, 4, true>(g, s);
   else if (few) launch_f32_t<EPI, 1, 8, true>(g, s);
   else if (short_k) launch_f32_t<EPI, 2, 4, true>(g, s);
   else launch_f32_t<EPI, 2, 8, true>(g, s);
-  return vec && !few ? (g.nt + 1) / 2 : g.nt;
+  return few ? g.nt : (g.nt + 1) / 2;
 }
 
 int launch_gemm_f32(int epi, F32Gemm g, hipStream_t s) {

@@ -517,6 +517,7 @@ def test_rows_of_nan_logits_are_reported_and_nothing_leaves_its_buffers(dtype, b
     (8, 2, 64, 512, 1032, 515, 300, 0),    # many tiles: four to a block, both k-lengths
     (2, 2, 64, 72, 8, 2, 1, 0),            # one tile, the smallest vocabulary
     (4, 2, 64, 256, 520, 777, 30, 1),      # weights that start at any element
+    (8, 2, 64, 264, 1032, 4115, 300, 3),   # ... and many tiles of them
 ])
 def test_f32_gemm_edges(hq, hkv, hd, d, f, vocab, P, shift):
     """The float32 kernels at the edges of their tiles, k-chunks and dispatch rules."""
