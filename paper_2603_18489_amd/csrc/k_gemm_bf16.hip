@@ -223,8 +223,13 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // the compiler could treat as divergent
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nt0 = blockIdx.x * NTW;
-  // blockIdx.y picks one of gridDim.y contiguous K ranges (EPI_PARTIAL; otherwise gridDim.y = 1)
-  const int kr_lo = (int)((blockIdx.y * KB) / gridDim.y), kr_n = (int)(((blockIdx.y + 1) * KB) / gridDim.y) - kr_lo;
+  // EPI_PARTIAL: blockIdx.y picks one of gridDim.y contiguous K ranges.  (The others are not charged the
+  // division and the load of the grid's size ahead of their first operand: about 0.4 us a launch.)
+  int kr_lo = 0, kr_n = KB;
+  if constexpr (EPI == EPI_PARTIAL) {
+    kr_lo = (int)((blockIdx.y * KB) / gridDim.y);
+    kr_n = (int)(((blockIdx.y + 1) * KB) / gridDim.y) - kr_lo;
+  }
   const int kb_lo = kr_lo + (wave * kr_n) / KS, kb_hi = kr_lo + ((wave + 1) * kr_n) / KS;
 
   // a tile past the end streams tile 0 instead (valid memory) and is dropped at the store
