@@ -127,15 +127,17 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.kv_plane = g.kv_plane;
   b.kv = c.take<char>((size_t)m.n_layers * 2 * g.kv_plane * es);
   b.h = c.take<float>(R * m.d_model);
-  b.u = c.take<char>(R * m.d_model * es);
-  b.qkv = c.take<float>(R * (nq + 2 * nkv));
+  // (the float32 GEMMs norm, gather and rotate on the way: no operand rows in memory)
+  const bool bf16 = bf16_path(m.dtype);
+  b.u = bf16 ? c.take<char>(R * m.d_model * es) : nullptr;
+  b.qkv = bf16 ? c.take<float>(R * (nq + 2 * nkv)) : nullptr;
   b.q = c.take<char>(R * nq * es);
   b.attn = c.take<char>(R * nq * es);
   b.act = c.take<char>(R * m.d_ffn * es);
-  b.u_lm = c.take<char>(BL16 * m.d_model * es);
+  b.u_lm = bf16 ? c.take<char>(BL16 * m.d_model * es) : nullptr;
   b.logits = c.take<float>(BL * m.vocab);
   {  // partial tuples of the vocabulary reduction: from the LM-head epilogue or from vocab_reduce
-    const size_t np_fused = bf16_path(m.dtype) ? (size_t)lm_head_parts(m.vocab) : (size_t)(m.vocab + 15) / 16;
+    const size_t np_fused = bf16 ? (size_t)lm_head_parts(m.vocab) : (size_t)(m.vocab + 15) / 16;
     const size_t np_plain = (size_t)vocab_reduce_parts(m.vocab);
     b.partials = c.take<float4>(BL * (np_fused > np_plain ? np_fused : np_plain));
   }
@@ -144,7 +146,7 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.sumsq = nullptr;
   b.ksplit_part = nullptr; b.ksplit_floats = 0; b.attn_tickets = nullptr;
   b.sumsq_stride = (int)R;
-  if (bf16_path(m.dtype)) {
+  if (bf16) {
     b.sumsq = c.take<unsigned long long>((size_t)(2 * m.n_layers + 1) * kSumSlots * R);
     b.ksplit_floats = (size_t)kMaxKSplit * R * m.d_model;
     b.ksplit_part = c.take<float>(b.ksplit_floats);

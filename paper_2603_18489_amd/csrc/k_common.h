@@ -162,11 +162,6 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 // Sum over a block of NW waves; every thread gets the result.  `scratch` holds NW floats.
 template <int NW> __device__ __forceinline__ float block_sum(float v, float* scratch) {
   v = wave_sum(v);
@@ -177,17 +172,6 @@ template <int NW> __device__ __forceinline__ float block_sum(float v, float* scr
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NW; ++i) s += scratch[i];
-  return s;
-}
-template <int NW> __device__ __forceinline__ float block_max(float v, float* scratch) {
-  v = wave_max(v);
-  int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[w] = v;
-  __syncthreads();
-  float s = scratch[0];
-#pragma unroll
-  for (int i = 1; i < NW; ++i) s = fmaxf(s, scratch[i]);
   return s;
 }
 
