@@ -169,7 +169,9 @@ typedef struct {
 } ec_gen_stats;
 
 /* Kernel classes for ec_profile_*: names follow the paper's wall-clock breakdown (attention
- * with rotary embeddings, feed-forward, KV-cache update, decision, remaining operations). */
+ * with rotary embeddings, feed-forward, KV-cache update, decision, remaining operations).
+ * EC_K_NORM, EC_K_ROPE_KV and EC_K_SWIGLU stay 0: that work runs inside the matrix kernels, under
+ * the class of the product it belongs to. */
 enum {
   EC_K_EMBED = 0, EC_K_NORM, EC_K_QKV, EC_K_ROPE_KV, EC_K_ATTN, EC_K_OPROJ, EC_K_GATEUP,
   EC_K_SWIGLU, EC_K_DOWN, EC_K_LMHEAD, EC_K_VOCAB_REDUCE, EC_K_DECIDE, EC_K_COUNT
@@ -273,6 +275,14 @@ int ec_debug_keep_logits(ec_ctx *ctx, int on);
  * store its logits is EC_ERR_STATE. */
 int ec_debug_read(ec_ctx *ctx, int what, int layer, void *host_dst, size_t bytes); /* sequence 0 */
 int ec_debug_read_seq(ec_ctx *ctx, int seq, int what, int layer, void *host_dst, size_t bytes);
+
+/* Which block of output a many-row matrix product of a bfloat16 or e4m3 model is cut into (test and
+ * diagnosis aid; pure host computation): shape = {rows of a block, output features of a block, ranges
+ * that K is split into}.  product: EC_K_QKV, EC_K_OPROJ, EC_K_GATEUP, EC_K_DOWN or EC_K_LMHEAD; rows: the
+ * rows it works on, list_rows: the row list's length with its padding (>= rows).  Errors: EC_ERR_ARG,
+ * also for a float32 model and for products of so few rows that they stream their weights instead. */
+int ec_debug_block_shape(const ec_model_cfg *model, int product, int32_t list_rows, int32_t rows,
+                         int32_t shape[3] /*HOST*/);
 
 /* The O(V) reduction behind the method's decision (Eq. 1 and the complexity discussion of the
  * Method section) as a call of its own, for logits that already sit on the device: for each row

@@ -31,7 +31,7 @@ KERNEL_CLASS_NAMES = ["embed", "norm", "qkv", "rope_kv", "attn", "oproj", "gateu
 
 EXPORTS = ["ec_workspace_bytes", "ec_init", "ec_reset", "ec_step", "ec_step_forced", "ec_debug_keep_logits",
            "ec_step_forced_batch", "ec_generate", "ec_profile_enable", "ec_profile_read",
-           "ec_debug_read", "ec_debug_read_seq", "ec_destroy", "ec_strerror", "ec_last_error",
+           "ec_debug_read", "ec_debug_read_seq", "ec_debug_block_shape", "ec_destroy", "ec_strerror", "ec_last_error",
            "ec_row_entropy_workspace_bytes", "ec_row_entropy", "ec_row_entropy_noalloc"]
 
 
@@ -126,6 +126,9 @@ def load_library() -> C.CDLL:
     lib.ec_debug_read.argtypes = [vp, C.c_int, C.c_int, vp, C.c_size_t]
     lib.ec_debug_read_seq.restype = C.c_int
     lib.ec_debug_read_seq.argtypes = [vp, C.c_int, C.c_int, C.c_int, vp, C.c_size_t]
+    lib.ec_debug_block_shape.restype = C.c_int
+    lib.ec_debug_block_shape.argtypes = [C.POINTER(ec_model_cfg), C.c_int, C.c_int32, C.c_int32,
+                                         C.POINTER(C.c_int32 * 3)]
     lib.ec_row_entropy_workspace_bytes.restype = C.c_size_t
     lib.ec_row_entropy_workspace_bytes.argtypes = [C.c_int32, C.c_int32]
     lib.ec_row_entropy.restype = C.c_int
@@ -189,6 +192,15 @@ def weights_to_device(cfg, w: Dict[str, object], device="cuda:0") -> Dict[str, o
         else:
             out[k] = [up(x) for x in v] if isinstance(v, list) else up(v)
     return out
+
+
+def block_shape(cfg, product: int, list_rows: int, rows: int):
+    """ec_debug_block_shape: (rows, output features, K ranges) of the blocks of a many-row product."""
+    mc, shape = model_cfg_struct(cfg), (C.c_int32 * 3)()
+    rc = load_library().ec_debug_block_shape(C.byref(mc), product, list_rows, rows, C.byref(shape))
+    if rc != EC_OK:
+        raise EcError(rc, load_library().ec_last_error(None).decode())
+    return tuple(shape)
 
 
 def _raw_stream(torch, stream) -> int:

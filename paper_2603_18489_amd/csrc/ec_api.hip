@@ -1018,6 +1018,26 @@ int ec_debug_keep_logits(ec_ctx* ctx, int on) {
   return EC_OK;
 }
 
+int ec_debug_block_shape(const ec_model_cfg* m, int product, int32_t list_rows, int32_t rows,
+                         int32_t shape[3]) {
+  if (!m || !shape) return fail(nullptr, EC_ERR_ARG, "model and shape must not be NULL");
+  if (!bf16_path(m->dtype)) return fail(nullptr, EC_ERR_ARG, "float32 models have no such blocks");
+  if (rows < 1 || list_rows < rows) return fail(nullptr, EC_ERR_ARG, "rows must be in [1, list_rows]");
+  const int nq = m->n_heads * m->head_dim, nkv = m->n_kv_heads * m->head_dim;
+  int epi, N, K = m->d_model;
+  switch (product) {
+    case EC_K_QKV: epi = EPI_QKV; N = nq + 2 * nkv; break;
+    case EC_K_OPROJ: epi = EPI_RESID; N = m->d_model; K = nq; break;
+    case EC_K_GATEUP: epi = EPI_SWIGLU; N = 2 * m->d_ffn; break;
+    case EC_K_DOWN: epi = EPI_RESID; N = m->d_model; K = m->d_ffn; break;
+    case EC_K_LMHEAD: epi = EPI_LOGITS; N = m->vocab; break;
+    default: return fail(nullptr, EC_ERR_ARG, "product is not a matrix product");
+  }
+  if (!gemm_bf16_block_shape(epi, list_rows, rows, N, K, kMaxKSplit, shape))
+    return fail(nullptr, EC_ERR_ARG, "so few rows stream their weights");
+  return EC_OK;
+}
+
 int ec_debug_read(ec_ctx* ctx, int what, int layer, void* host_dst, size_t bytes) {
   return ec_debug_read_seq(ctx, 0, what, layer, host_dst, bytes);
 }

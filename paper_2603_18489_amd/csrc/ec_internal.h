@@ -202,6 +202,9 @@ void launch_unpack_cache(const bf16_t* packed, int is_v, int T, int Tpad, int Hk
 // weight-streaming kernels (few rows) read it instead of Wp.
 void launch_gemm_bf16(int epi, const bf16_t* Ap, int M_src, const bf16_t* Wp, const void* Wq,
                       int N, int K, const GemmEpi& e, hipStream_t s);
+// the block (rows, output features, K ranges) that launch_gemm_bf16 picks for these sizes; false where
+// it streams the weights (few rows)
+bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, int max_ksplit, int shape[3]);
 // e4m3 source: Wq receives the codes as 1 KiB fragment pairs (64 k per weight tile and step),
 // Wp the same values as bf16 fragments (exact); either may be NULL.  mode / hd / grp / row0 as
 // launch_repack_weight.

@@ -1158,7 +1158,8 @@ static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.93f, 0.75f, 0.f, 0.f, 0
 
 // epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
 // cache stores of q k v, the residual stream's read and write; partial products are plain stores.
-static TilePick pick_tile(int MT, int total_nt, int KB, int max_ksplit, int M, int N, float epi_us) {
+static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit, int M, int N) {
+  const float epi_us = epi == EPI_QKV || epi == EPI_RESID ? 0.064f : 0.f;
   TilePick best{1, 1};
   float best_t = 1e30f;
   for (int i = 0; i < kNumTiles; ++i) {
@@ -1203,11 +1204,21 @@ static void launch_tiled_pick(const bf16_t* Ap, int MT, const bf16_t* Wp, int to
   else launch_tiled_pick_ws<EPI, false>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
 }
 
+// row tiles up to which a product goes to the weight-streaming kernels (gathered LM-head rows: 64 at most)
+static bool streams_weights(int epi, int MT) { return MT <= (epi == EPI_LOGITS ? 4 : 6); }
+
+bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, int max_ksplit, int shape[3]) {
+  if (streams_weights(epi, (M + 15) / 16)) return false;
+  const TilePick tp = pick_tile(epi, (M_src + 15) / 16, N / 16, K / 32, epi == EPI_RESID ? max_ksplit : 1, M, N);
+  shape[0] = kTileM[tp.tile] * 16; shape[1] = kTileN[tp.tile] * 16; shape[2] = tp.ksplit;
+  return true;
+}
+
 template <int EPI>
 static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void* Wq, int N, int K,
                        const GemmEpi& e, hipStream_t s) {
   const int total_nt = N / 16, KB = K / 32, MT = (e.M + 15) / 16, MT_src = (M_src + 15) / 16;
-  if (Wq && MT <= 6 && !(EPI == EPI_LOGITS && MT > 4)) {  // weight streaming from e4m3 codes
+  if (Wq && streams_weights(EPI, MT)) {  // weight streaming from e4m3 codes
     switch (MT) {
       case 1: launch_skinny_mt_w8<EPI, 1>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
       case 2: launch_skinny_mt_w8<EPI, 2>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
@@ -1221,7 +1232,7 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
   // Up to 96 rows (a block of 32 plus the paper's default budget of 64 recent tokens) the GEMMs
   // are weight-streaming: 3.7 ms a step at 64 rows, 4.5 ms at 96, against 7.8 ms through the
   // tiled kernels.
-  if (MT <= 6 && !(EPI == EPI_LOGITS && MT > 4)) {  // (gathered LM-head rows: 64 at most)
+  if (streams_weights(EPI, MT)) {
     switch (MT) {
       case 1: launch_skinny_mt<EPI, 1>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
       case 2: launch_skinny_mt<EPI, 2>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
@@ -1234,8 +1245,7 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
     // the tiled kernel reads its activation rows in place (no gather) and walks every m-tile of
     // the buffer; rows from e.M on are dropped in the epilogue
     const int max_ks = (EPI == EPI_RESID && e.partial) ? e.max_ksplit : 1;
-    const float epi_us = EPI == EPI_QKV || EPI == EPI_RESID ? 0.064f : 0.f;
-    TilePick tp = pick_tile(MT_src, total_nt, KB, max_ks, e.M, N, epi_us);
+    TilePick tp = pick_tile(EPI, MT_src, total_nt, KB, max_ks, e.M, N);
     if (tp.ksplit > 1) {
       launch_tiled_pick<EPI_PARTIAL>(Ap, MT_src, Wp, total_nt, KB, e, s, tp.tile, tp.ksplit);
       launch_resid_finish(e, tp.ksplit, N, s);

@@ -205,3 +205,21 @@ def test_row_entropy_argument_errors_without_gpu(lib):
     assert call(z, 32, 126464, 126464, st, ws, need - 256, None) == ec.EC_ERR_WORKSPACE
     assert len(lib.ec_strerror(ec.EC_ERR_HOST_MEMORY)) > 0
     assert len(lib.ec_strerror(ec.EC_ERR_NONFINITE)) > 0
+
+
+def test_block_shape_query(lib):
+    mc, _, wl = _cfgs("llada8b_l2")
+    shape = (C.c_int32 * 3)()
+    q = lambda *a: lib.ec_debug_block_shape(*a, C.byref(shape))
+    for product in (ec.EC_K_QKV, ec.EC_K_OPROJ, ec.EC_K_GATEUP, ec.EC_K_DOWN, ec.EC_K_LMHEAD):
+        for rows in (97, 768, 24576):
+            assert q(C.byref(mc), product, (rows + 255) // 256 * 256, rows) == ec.EC_OK
+            assert shape[0] % 16 == 0 and shape[1] % 16 == 0 and 1 <= shape[2] <= 4
+            assert shape[2] == 1 or product in (ec.EC_K_OPROJ, ec.EC_K_DOWN)   # only residual products split K
+    assert q(None, ec.EC_K_QKV, 768, 768) == ec.EC_ERR_ARG
+    assert lib.ec_debug_block_shape(C.byref(mc), ec.EC_K_QKV, 768, 768, None) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), ec.EC_K_ATTN, 768, 768) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), ec.EC_K_QKV, 767, 768) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), ec.EC_K_QKV, 96, 96) == ec.EC_ERR_ARG      # weight-streaming kernels
+    f32, _, _ = _cfgs("tiny_f32")
+    assert q(C.byref(f32), ec.EC_K_QKV, 768, 768) == ec.EC_ERR_ARG

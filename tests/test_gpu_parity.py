@@ -23,6 +23,11 @@ def small_cfg(dtype, hq=4, hkv=4, hd=64, d=256, f=768, vocab=4096, layers=2, sca
                               rope_base=10000.0, logit_scale=scale, dtype=dtype)
 
 
+def block_shape(cfg, product, T):
+    """blocks of a product over the T rows of one sequence's full step (its list is padded to 256)"""
+    return ec.block_shape(cfg, product, (T + 255) // 256 * 256, T)
+
+
 def test_tiny_f32_whole_generation():
     wl = ec_inputs.WORKLOADS["tiny_f32"]
     cfg = wl.model.replace(logit_scale=16.0)      # both modes occur (about half the steps FULL)
@@ -547,22 +552,70 @@ def test_f32_gemm_edges(hq, hkv, hd, d, f, vocab, P, shift):
     g.close()
 
 
-@pytest.mark.parametrize("hq,hkv,hd,d,f,P", [
-    (4, 2, 64, 288, 12320, 760),    # 9 k-steps, an odd number; 1540 weight tiles
-    (4, 4, 64, 32, 4128, 900),      # a single k-step; 129 k-steps for 2 weight tiles
-    (8, 8, 128, 1056, 6176, 1400),  # 33 and 193 k-steps, uneven K ranges, ragged row and column tiles
-    (4, 4, 64, 96, 12224, 520),     # gate/up in 192 x 320 blocks, the last row and column block ragged
-    (4, 4, 64, 96, 8192, 760),      # gate/up in 256 x 256 blocks, the last of four row blocks 3 rows
+@pytest.mark.parametrize("hq,hkv,hd,d,f,P,gate_up", [
+    (4, 2, 64, 288, 12320, 760, None),    # 9 k-steps, an odd number; 1540 weight tiles
+    (4, 4, 64, 32, 4128, 900, None),      # a single k-step; 129 k-steps for 2 weight tiles
+    (8, 8, 128, 1056, 6176, 1400, None),  # 33 and 193 k-steps, uneven K ranges, ragged row and column tiles
+    (4, 4, 64, 96, 9152, 520, (192, 320, 1)),   # the last row and column block ragged
+    (4, 4, 64, 96, 8192, 760, (256, 256, 1)),   # the last of four row blocks 3 rows
 ])
-def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P):
+def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     """The many-row GEMMs at odd and tiny numbers of k-steps, with tiles that the matrices do not
     fill."""
     cfg = small_cfg("bf16", hq, hkv, hd, d=d, f=f, vocab=512, scale=4.0)
     w = ec_inputs.make_weights(cfg, 67, gain_jitter=0.1)
     dec = ec_inputs.DecodeCfg(gen_len=11, block=4, k_recent=2, tokens_per_step=1, tau=1e9)
+    if gate_up:
+        assert block_shape(cfg, ec.EC_K_GATEUP, P + 11) == gate_up
     s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 6), TOL["bf16"], max_steps=2)
     print(s)
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,hd,d,f,P,blocks", [
+    # q/k/v with rotation and cache stores, the last row and column block ragged
+    ("bf16", 32, 32, 128, 96, 256, 760, {"QKV": (192, 320, 1)}),
+    ("bf16", 32, 32, 128, 96, 256, 1089, {"QKV": (256, 256, 1)}),
+    ("fp8w", 32, 32, 128, 128, 256, 760, {"QKV": (192, 320, 1)}),
+    ("fp8w", 32, 32, 128, 128, 256, 1089, {"QKV": (256, 256, 1)}),
+    # gate/up with row scales
+    ("fp8w", 4, 4, 64, 128, 6016, 760, {"GATEUP": (192, 320, 1)}),
+    ("fp8w", 4, 4, 64, 128, 8128, 760, {"GATEUP": (256, 256, 1)}),
+    # residual products, K whole and split (partial products, finish)
+    ("bf16", 4, 4, 64, 4640, 64, 2538, {"OPROJ": (192, 320, 1), "DOWN": (192, 320, 1)}),
+    ("fp8w", 4, 4, 64, 4672, 64, 2538, {"OPROJ": (192, 320, 1), "DOWN": (192, 320, 1)}),
+    ("bf16", 4, 4, 64, 6176, 64, 2538, {"OPROJ": (256, 256, 1), "DOWN": (256, 256, 1)}),
+    ("fp8w", 4, 4, 64, 6208, 64, 2538, {"OPROJ": (256, 256, 1), "DOWN": (256, 256, 1)}),
+    ("bf16", 4, 4, 64, 4128, 4096, 520, {"DOWN": (192, 320, 4)}),
+    ("fp8w", 4, 4, 64, 4160, 4096, 520, {"DOWN": (192, 320, 4)}),
+    ("bf16", 4, 4, 64, 4128, 6176, 1089, {"DOWN": (256, 256, 3)}),
+    ("fp8w", 4, 4, 64, 4160, 6208, 1089, {"DOWN": (256, 256, 3)}),
+])
+def test_widest_tiled_blocks(dtype, hq, hkv, hd, d, f, P, blocks):
+    """Blocks of 192 x 320 and 256 x 256 under every epilogue, with and without row scales, at sizes that
+    leave the last blocks ragged.  The sizes are those at which the kernels pick these blocks."""
+    cfg = small_cfg(dtype, hq, hkv, hd, d=d, f=f, vocab=512, layers=1, scale=4.0)
+    for product, shape in blocks.items():
+        assert block_shape(cfg, getattr(ec, "EC_K_" + product), P + 11) == shape, product
+    w = ec_inputs.make_weights(cfg, 83, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=11, block=4, k_recent=2, tokens_per_step=1, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 6), TOL[dtype], max_steps=2)
+    print(s)
+    assert s["rows_stat"] > 0
+
+
+@pytest.mark.parametrize("dtype,vocab,shape", [("bf16", 32752, (256, 256, 1)), ("fp8w", 32752, (256, 256, 1)),
+                                               ("bf16", 26224, (192, 320, 1)), ("fp8w", 26224, (192, 320, 1))])
+def test_widest_tiled_blocks_lm_head(dtype, vocab, shape):
+    """The same for the LM head of four sequences with 128 masked positions each."""
+    cfg = small_cfg(dtype, 4, 2, 64, d=128, f=256, vocab=vocab, layers=1, scale=8.0)
+    dec = ec_inputs.DecodeCfg(batch=4, gen_len=128, block=128, k_recent=2, tokens_per_step=1, tau=1e9)
+    assert ec.block_shape(cfg, ec.EC_K_LMHEAD, 512, 512) == shape
+    w = ec_inputs.make_weights(cfg, 89, gain_jitter=0.1)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, 5 + b, 6 + b) for b in range(4)]
+    s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL[dtype], max_steps=1)
+    print(s)
+    assert s["rows_stat"] > 0
 
 
 @pytest.mark.parametrize("dtype,hq,d,f,block,k", [
