@@ -13,13 +13,12 @@
 //                                            B operand, V^T fragments straight from the cache)
 // Every operand load is a coalesced 1 KiB fragment in the cache's own layout.
 //
-// With many rows the softmax arithmetic bounds the kernels (two waves per SIMD, 16 MFMAs to a chunk
-// and tile): bare exp2 instructions (arguments at most 10; what underflows is far below a bf16
-// probability), row sums kept per lane, and a reference that moves only when it has to take a chunk
-// from 180 vector instructions to 70.  us per launch on MI355X, before -> now:
-//   768 rows x 768 keys x 32 heads          29.1 -> 22.8
-//   1280 x 1280 x 28 heads on 4 kv heads    69.0 -> 49.9
-//   16 x (1536 x 1536) x 32 heads           1038 -> 770 (0.80 PFLOP/s)
+// With many rows the softmax arithmetic bounds the kernels (two waves per SIMD, 17 MFMAs to a chunk
+// and tile): bare exp2 instructions (arguments at most 0; what underflows is far below a bf16
+// probability) and row sums on the matrix cores.  us per launch on MI355X, before -> now:
+//   768 rows x 768 keys x 32 heads          28.3 -> 25.2
+//   1280 x 1280 x 28 heads on 4 kv heads    66.5 -> 57.0
+//   16 x (1536 x 1536) x 32 heads           1033 -> 820 (0.75 PFLOP/s)
 // (Maxima in inline assembly are not an option: nothing there waits for the MFMAs' results.)
 // Reading the next chunk's K and this one's V from the ring during the softmax gained 3 % with two
 // tiles a wave and cost the one-tile kernels their second block per compute unit (50 -> 64).
@@ -56,19 +55,38 @@ __device__ __forceinline__ float max_of_swap32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// a query's sum over its four lanes
-__device__ __forceinline__ float sum_of_lanes4(float x) {
-  x += other_row(x);
-  return x + other_half(x);
+// The softmax denominator adds up the very bf16 probabilities that multiply V, so that their rounding
+// cancels in the quotient: the weights of a query sum to one.  With every register in use (the split
+// kernel: 256 and 9 spilled with the other form) in the vector ALU, the lane's own 8 keys, its query's
+// four lanes added up at the end; where the vector ALU is the bound (the shared kernel: 5 % less time)
+// as a product of P^T with ones, complete in every lane.
+__device__ __forceinline__ void add_probs(float& l, const uint4& pu, const bf16x8&) {
+  const unsigned u[4] = {pu.x, pu.y, pu.z, pu.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) l += __uint_as_float(u[e] << 16) + __uint_as_float(u[e] & 0xffff0000u);
 }
+__device__ __forceinline__ void add_probs(f32x4& l, const uint4&, const bf16x8& pf) {
+  constexpr unsigned kOnes = 0x3f803f80u;   // two bf16 ones
+  l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u4_as_bf16x8(make_uint4(kOnes, kOnes, kOnes, kOnes)), pf, l, 0, 0, 0);
+}
+__device__ __forceinline__ float scaled(float l, float f) { return l * f; }
+__device__ __forceinline__ f32x4 scaled(f32x4 v, float f) {
+  v[0] *= f; v[1] *= f; v[2] *= f; v[3] *= f;
+  return v;
+}
+__device__ __forceinline__ float denominator(float l) {
+  l += other_row(l);
+  return l + other_half(l);
+}
+__device__ __forceinline__ float denominator(const f32x4& l) { return l[0]; }
 
 // One 32-key chunk for one 16-query tile: S^T = K Q^T, online softmax down the keys, O^T += V^T P^T.
-// l_run: the lane's part of the softmax denominator.  kf / vf: the chunk's K and V^T fragments; qf: the tile's Q fragments; the lane owns query
+// kf / vf: the chunk's K and V^T fragments; qf: the tile's Q fragments; the lane owns query
 // (lane & 15) and keys key0 .. key0+7.  mask_tail (wave-uniform): keys >= T are padding.
-template <int HB, int HT>
+template <int HB, int HT, typename Denom>
 __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const bf16x8 (&vf)[HT],
                                                 const bf16x8 (&qf)[HB], f32x4 (&acc)[HT],
-                                                float& m_run, float& l_run, float scale_log2e,
+                                                float& m_run, Denom& l_run, float scale_log2e,
                                                 int key0, int T, bool mask_tail) {
   f32x4 s2[2];
 #pragma unroll
@@ -91,31 +109,23 @@ __device__ __forceinline__ void attn_chunk_tile(const bf16x8 (&kf)[2][HB], const
   // (the two halves a lane swap returns hold the value and its partner's: their maximum is both's)
   mx = max_of_swap16(mx);
   mx = max_of_swap32(mx) * scale_log2e;  // scale > 0: max commutes with it
-  // The reference of the exponentials only moves when some query of the wave exceeds it by more than
-  // 2^10: probabilities are then up to 2^10 instead of 1, with the same relative precision in bf16
-  // and in the float32 sums, and the accumulators are rescaled once or twice per tile instead of
-  // in nearly every chunk.
-  if (__builtin_amdgcn_ballot_w64(mx > m_run + 10.0f) != 0) {
+  // The reference of the exponentials is the running maximum, so that the largest probability is 1 and
+  // has no rounding.  (One that lags behind by up to 2^10 saves a tenth of the full-step kernel and adds
+  // up to 1 % to the error of a layer whose queries look at a few keys each.)
+  if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
     const float m_new = fmaxf(m_run, mx);
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first chunk
     m_run = m_new;
-    l_run *= alpha;
+    l_run = scaled(l_run, alpha);
 #pragma unroll
-    for (int h = 0; h < HT; ++h) {
-      f32x4 a = acc[h];
-      a[0] *= alpha; a[1] *= alpha; a[2] *= alpha; a[3] *= alpha;
-      acc[h] = a;
-    }
+    for (int h = 0; h < HT; ++h) acc[h] = scaled(acc[h], alpha);
   }
-  // (the lane's own 8 keys: the query's four lanes are added up once, at the end)
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sv[e] = __builtin_amdgcn_exp2f(fmaf(sv[e], scale_log2e, -m_run));
-    l_run += sv[e];
-  }
+  for (int e = 0; e < 8; ++e) sv[e] = __builtin_amdgcn_exp2f(fmaf(sv[e], scale_log2e, -m_run));
   uint4 pu = make_uint4(pack2_bf16(sv[0], sv[1]), pack2_bf16(sv[2], sv[3]),
                         pack2_bf16(sv[4], sv[5]), pack2_bf16(sv[6], sv[7]));
   const bf16x8 pf = u4_as_bf16x8(pu);
+  add_probs(l_run, pu, pf);
 #pragma unroll
   for (int h = 0; h < HT; ++h)
     acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[h], pf, acc[h], 0, 0, 0);
@@ -266,7 +276,6 @@ __global__ __launch_bounds__(512) void attn_mfma_split_kernel(
   // Every wave parks (m, l, O) in LDS; after one barrier wave w combines the NW copies of hd tile
   // w (and w + NW, ...) in wave order, normalises and stores it.
   constexpr int SLOT = HT * 64 + 32;  // float4 per wave: O tiles + (m, l) pairs
-  l_run = sum_of_lanes4(l_run);
   {
     float4* slot = lds + (size_t)wave * SLOT;
 #pragma unroll
@@ -274,7 +283,7 @@ __global__ __launch_bounds__(512) void attn_mfma_split_kernel(
       f32x4 a = acc[h];
       slot[h * 64 + lane] = make_float4(a[0], a[1], a[2], a[3]);
     }
-    ((float2*)(slot + HT * 64))[lane] = make_float2(m_run, l_run);
+    ((float2*)(slot + HT * 64))[lane] = make_float2(m_run, denominator(l_run));
   }
   __syncthreads();
   float wgt[NW], m_all = -INFINITY, l_all = 0.f;
@@ -449,11 +458,12 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_shared_kernel(
     }
   }
   f32x4 acc[QT][HT];
-  float m_run[QT], l_run[QT];
+  float m_run[QT];
+  f32x4 l_run[QT];
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     m_run[t] = -INFINITY;
-    l_run[t] = 0.f;
+    l_run[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int h = 0; h < HT; ++h) acc[t][h] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
@@ -486,7 +496,7 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_shared_kernel(
 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    const float inv = 1.0f / sum_of_lanes4(l_run[t]);
+    const float inv = 1.0f / denominator(l_run[t]);
     if (qrow[t] >= R) continue;
 #pragma unroll
     for (int h = 0; h < HT; ++h) {

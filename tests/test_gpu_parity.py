@@ -666,8 +666,8 @@ def test_decision_bookkeeping_sizes(N, block, k, n, sliding):
 
 @pytest.mark.parametrize("P,gain", [(230, 1.0), (230, 12.0), (2120, 6.0)])
 def test_attention_scores_that_keep_growing(P, gain):
-    """Keys whose scores grow along the context, slowly and fast, so that the softmax reference stays,
-    moves now and then, and moves often (full and partial steps, key slices over blocks)."""
+    """Keys whose scores grow along the context, slowly and fast, so that the running maximum moves now
+    and then, and often (full and partial steps, key slices over blocks)."""
     cfg = small_cfg("bf16", 4, 2, 64, layers=1, scale=8.0)
     w = ec_inputs.make_weights(cfg, 79, gain_jitter=0.1)
     # sharper scores: larger queries (the attention norm's gain also scales k and v, both sides see it)
@@ -677,3 +677,33 @@ def test_attention_scores_that_keep_growing(P, gain):
     s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 7), TOL["bf16"], max_steps=4)
     print(s)
     assert s["tokens_exact"] > 0
+
+
+@pytest.mark.parametrize("hq,hkv,hd,P,batch", [
+    (4, 2, 64, 70, 1), (4, 4, 128, 900, 1), (8, 2, 128, 2600, 1),   # one visit, key slices over blocks
+    (16, 4, 64, 300, 16),                                           # a batch: one block per (sequence, head)
+])
+@pytest.mark.parametrize("gain", [4.0, 30.0, 300.0])
+def test_attention_weights_sum_to_one(hq, hkv, hd, P, batch, gain):
+    """With one and the same embedding for every token all values are equal, and attention returns that
+    value whatever the scores are: the weights' sum is one to float32 rounding (at most T + 32 roundings
+    of 2^-24, far inside half a bf16 step), so the logits are those of a model with zero queries, bit
+    for bit.  (A denominator of unrounded probabilities misses the value by up to 2^-9.)"""
+    from tests.gpu_harness import bf16_bits_to_f32
+    cfg = small_cfg("bf16", hq, hkv, hd, layers=1, scale=8.0, vocab=512)
+    w = ec_inputs.make_weights(cfg, 97, gain_jitter=0.1)
+    w["tok_emb"][:] = w["tok_emb"][0]
+    dec = ec_inputs.DecodeCfg(batch=batch, gen_len=48, block=20, k_recent=2, tokens_per_step=1, tau=1e9)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, P + b, 7) for b in range(batch)]
+    got = []
+    for c in (0.0, gain):
+        wc = dict(w, wq=[ec_inputs.f32_to_bf16_bits(bf16_bits_to_f32(w["wq"][0]) * np.float32(c))])
+        g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, wc), dec, prompts if batch > 1 else prompts[0])
+        g.keep_logits(True)
+        z = []
+        for mode in (ec.EC_FULL, ec.EC_PARTIAL):
+            g.step_forced_batch([mode] * batch, [[]] * batch, [[]] * batch)
+            z += [g.debug_read(ec.EC_DBG_LOGITS, seq=b) for b in range(batch)]
+        g.close()
+        got.append(np.stack(z))
+    assert np.array_equal(got[0], got[1])
