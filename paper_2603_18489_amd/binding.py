@@ -203,14 +203,14 @@ def block_shape(cfg, product: int, list_rows: int, rows: int):
     return tuple(shape)
 
 
-def _raw_stream(torch, stream) -> int:
-    """hipStream_t of `stream`, or of the current device's current stream (where torch has the lookup
-    that makes no stream object: 0.4 us instead of 2.7, in a call of about 8)."""
+def _raw_stream(torch, stream, device: int) -> int:
+    """hipStream_t of `stream`, or of `device`'s current stream (where torch has the lookup that makes
+    no stream object: 0.4 us instead of 2.7, in a call of about 8)."""
     if stream is None:
         lookup = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         if lookup is not None:
-            return lookup(torch.cuda.current_device())
-        stream = torch.cuda.current_stream()
+            return lookup(device)
+        stream = torch.cuda.current_stream(device)
     return stream.cuda_stream
 
 
@@ -220,8 +220,8 @@ def row_entropy(logits, stream=None):
     workspace is a torch allocation.  Without `stream` the call is ordered on the current stream
     like any torch operation; with one it is enqueued there and waited for."""
     import torch
-    dev = logits.get_device()
-    if 0 <= dev != torch.cuda.current_device():   # (the kernels run where the logits are)
+    dev, current = logits.get_device(), torch.cuda.current_device()
+    if 0 <= dev != current:   # (the kernels run where the logits are)
         with torch.cuda.device(dev):
             return row_entropy(logits, stream)
     if stream is not None:
@@ -244,7 +244,7 @@ def row_entropy(logits, stream=None):
     # (both belong to the current stream: the allocator hands their memory on behind this call only)
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=logits.device)
     rc = lib.ec_row_entropy(logits.data_ptr(), rows, vocab, logits.stride(0) if rows > 1 else vocab,
-                            stats.data_ptr(), ws.data_ptr(), need, _raw_stream(torch, None))
+                            stats.data_ptr(), ws.data_ptr(), need, _raw_stream(torch, None, current))
     if rc != EC_OK:
         raise EcError(rc, lib.ec_last_error(None).decode())
     return stats
@@ -254,8 +254,8 @@ def row_entropy_noalloc(logits, stats, stream=None):
     """ec_row_entropy_noalloc: `stats` is a caller-provided float32 CUDA tensor [rows, 4]; the
     call itself allocates nothing.  Enqueued on `stream` (default: current), not synchronised."""
     import torch
-    dev = logits.get_device()
-    if 0 <= dev != torch.cuda.current_device():
+    dev, current = logits.get_device(), torch.cuda.current_device()
+    if 0 <= dev != current:
         with torch.cuda.device(dev):
             return row_entropy_noalloc(logits, stats, stream)
     lib = _lib or load_library()
@@ -264,7 +264,7 @@ def row_entropy_noalloc(logits, stats, stream=None):
     assert stats.dtype == torch.float32 and stats.is_contiguous() and stats.shape == (rows, 4)
     rc = lib.ec_row_entropy_noalloc(logits.data_ptr(), rows, vocab,
                                     logits.stride(0) if rows > 1 else vocab, stats.data_ptr(),
-                                    _raw_stream(torch, stream))
+                                    _raw_stream(torch, stream, current))
     if rc != EC_OK:
         raise EcError(rc, lib.ec_last_error(None).decode())
 
