@@ -38,7 +38,8 @@ __device__ __forceinline__ VTuple vocab_part(const float* __restrict__ z, int V,
 
 // grid (ceil(parts / 4), rows): one wave per partial tuple.  Bound by the logits' bytes.  On
 // MI355X at 128 rows of 126464 logits (64.7 MB) a call of ec_row_entropy_noalloc takes
-// 18.3 us (3.5 TB/s); 95 us when each thread branched on every new maximum and one thread merged a row.
+// 18.0 us (3.6 TB/s), 19.1 with logits that are not in the last-level cache; 71 and 84 us when each
+// thread branched on every new maximum and one thread merged a row.
 __global__ __launch_bounds__(256) void vocab_reduce_kernel(const float* __restrict__ logits, int V,
                                                            size_t ld, int nparts,
                                                            float4* __restrict__ partials) {
@@ -168,8 +169,10 @@ __device__ __forceinline__ bool gate_skips(float v, float tau, int metric) {
 // merge a half wave's tuples, no barrier to find the k-th largest history value (up to 512 slots)
 // or the current block, one to compact the three row lists.  The forced lists are read where the
 // host left them and the flag goes back with the result, so a forced step adds no copies.
-// On MI355X a step of the float32 model of 128 positions spends 11.3 us here (15.7 with a barrier
-// per bisection step and per scan), a 2-layer bf16 model's forced step 83 us in all (133).
+// On MI355X a step of the float32 model of 128 positions and 4096 tokens spends 11.3 us here (15.7 with
+// a barrier per bisection step and per scan), a 2-layer bf16 model's forced step 81 us in all (132).
+// With the 988 tuples a row of a 126464-token vocabulary it is 15.4 us: 32 rows' tuples, 0.5 MB, come
+// through one compute unit.
 // dynamic LDS: int hist[N4] | uint8 masked[N4], N4 = N rounded up to 4
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {

@@ -552,6 +552,12 @@ int skinny_tiles_per_block(int epi, int total_nt) {
 //   3 row tiles  K 12288  30.5 -> 21.3 + 4.8   (e4m3 23.5 -> 15.4 + 4.0)   K 4096  11.2 ->  8.2 + 4.8
 //   6 row tiles  K 12288  44.4 -> 27.0 + 5.1                               K 4096  16.6 -> 11.0 + 5.1
 // which is a gain of about MT * K * 2.4e-4 - 5.5 us.  Two tiles and half of K: 23 and 33 at K 12288.
+// The line holds at every width, since a block's bytes do not depend on it and the few blocks of a narrow
+// matrix leave as much of the chip idle split or not.  us of a down projection with its finish, by
+// events, just above the line (MT K 23808 - 24576, 2 to 6 row tiles) and at 3 row tiles of 12288:
+//   d  128   17.1 -> 14.9, 22.7 -> 18.5     d 2048   20.4 -> 18.3, 28.0 -> 23.5
+//   d  512   18.7 -> 15.5, 26.1 -> 19.7     d 4096   23.8 -> 21.1, 32.0 -> 26.5 (6 x 3968: 20.1 -> 20.3)
+//   d 1024   19.5 -> 16.1, 26.7 -> 20.3     d 8192   38.7 -> 32.8, 56.8 -> 44.1
 constexpr int kSkinnySplit = 4;
 static bool skinny_splits(int MT, int K, const GemmEpi& e) {
   return e.partial && e.max_ksplit >= kSkinnySplit && (long)MT * K >= 23000;
