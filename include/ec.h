@@ -269,6 +269,13 @@ int ec_profile_read(ec_ctx *ctx, ec_profile *out);
  * more than 64 block rows over the batch materialise their logits anyway.)  Errors: EC_ERR_ARG. */
 int ec_debug_keep_logits(ec_ctx *ctx, int on);
 
+/* The products that divide K over blocks let these meet and exchange partial sums.  polls: how often a
+ * block looks for the others before it leaves its share to the last of them (the default is in the
+ * tens of milliseconds); apart != 0: the blocks are taken to run on different XCDs, which makes them
+ * write their caches back.  Results are bit-identical whatever is set; for tests.
+ * Errors: EC_ERR_ARG (polls < 0). */
+int ec_debug_meeting(ec_ctx *ctx, int32_t polls, int apart);
+
 /* Copies internal state of one sequence to the host (synchronises the stream; test and
  * diagnosis aid, not part of the method).  bytes must not exceed the size of the item
  * (EC_ERR_ARG otherwise); the copy is truncated to bytes.  EC_DBG_LOGITS of a step that did not

@@ -31,7 +31,7 @@ KERNEL_CLASS_NAMES = ["embed", "norm", "qkv", "rope_kv", "attn", "oproj", "gateu
 
 EXPORTS = ["ec_workspace_bytes", "ec_init", "ec_reset", "ec_step", "ec_step_forced", "ec_debug_keep_logits",
            "ec_step_forced_batch", "ec_generate", "ec_profile_enable", "ec_profile_read",
-           "ec_debug_read", "ec_debug_read_seq", "ec_debug_block_shape", "ec_destroy", "ec_strerror", "ec_last_error",
+           "ec_debug_read", "ec_debug_read_seq", "ec_debug_block_shape", "ec_debug_meeting", "ec_destroy", "ec_strerror", "ec_last_error",
            "ec_row_entropy_workspace_bytes", "ec_row_entropy", "ec_row_entropy_noalloc"]
 
 
@@ -122,6 +122,8 @@ def load_library() -> C.CDLL:
     lib.ec_profile_read.argtypes = [vp, C.POINTER(ec_profile)]
     lib.ec_debug_keep_logits.restype = C.c_int
     lib.ec_debug_keep_logits.argtypes = [vp, C.c_int]
+    lib.ec_debug_meeting.restype = C.c_int
+    lib.ec_debug_meeting.argtypes = [vp, C.c_int32, C.c_int]
     lib.ec_debug_read.restype = C.c_int
     lib.ec_debug_read.argtypes = [vp, C.c_int, C.c_int, vp, C.c_size_t]
     lib.ec_debug_read_seq.restype = C.c_int
@@ -363,6 +365,10 @@ class EntropyCache:
     def keep_logits(self, on: bool = True):
         """Makes the following steps store their logits so that EC_DBG_LOGITS can read them."""
         self._check(self.lib.ec_debug_keep_logits(self.ctx, int(on)))
+
+    def debug_meeting(self, polls: int, apart: bool = False):
+        """Blocks that share a tile wait this many polls for each other; apart: as if on different XCDs."""
+        self._check(self.lib.ec_debug_meeting(self.ctx, polls, int(apart)))
 
     def profile_enable(self, on: bool):
         self._check(self.lib.ec_profile_enable(self.ctx, int(on)))

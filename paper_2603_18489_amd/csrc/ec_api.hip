@@ -56,9 +56,10 @@ struct Buffers {
   float* logits; float4* partials;
   // bf16 only: row sums of squares [2L+1][kSumSlots][sumsq_stride] (44.20 fixed point), packed matrices
   unsigned long long* sumsq; int sumsq_stride;
-  float* ksplit_part;  // [kMaxKSplit][T][d] partial products of K-split residual GEMMs; between
-                       // them, the key slices of the partial-step attention
+  float* ksplit_part;  // pieces of K-split residual GEMMs; between them, the key slices of the
+                       // partial-step attention
   size_t ksplit_floats;
+  int4* meet;          // MeetSlots of the step's residual GEMMs, [2L][kMeetSlots]
   int* attn_tickets;   // [256] arrival counters of the key slices, zero between launches
   std::vector<PackedLayer> pl; bf16_t* lm_head_p;
   uint8_t* lm_head_q = nullptr; float* lm_head_s = nullptr;  // EC_FP8W
@@ -144,11 +145,12 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   b.pl.clear();
   b.lm_head_p = nullptr;
   b.sumsq = nullptr;
-  b.ksplit_part = nullptr; b.ksplit_floats = 0; b.attn_tickets = nullptr;
+  b.ksplit_part = nullptr; b.ksplit_floats = 0; b.attn_tickets = nullptr; b.meet = nullptr;
   b.sumsq_stride = (int)R;
   if (bf16) {
     b.sumsq = c.take<unsigned long long>((size_t)(2 * m.n_layers + 1) * kSumSlots * R);
-    b.ksplit_floats = (size_t)kMaxKSplit * R * m.d_model;
+    b.ksplit_floats = meet_piece_floats(R, m.d_model);
+    b.meet = c.take<int4>((size_t)2 * m.n_layers * kMeetSlots);
     b.ksplit_part = c.take<float>(b.ksplit_floats);
     b.attn_tickets = c.take<int>(256);
     b.pl.resize(m.n_layers);
@@ -259,6 +261,7 @@ struct ec_ctx {
   bool fused_reduce = false;
   int step_nparts = 0;
   // profiling
+  int meet_limit = 20000, meet_apart = 0;   // GemmEpi; ec_debug_meeting
   bool prof_on = false;
   std::vector<ProfEvent> prof_pool;
   size_t prof_used = 0;
@@ -474,6 +477,12 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
   bf16_t* u = (bf16_t*)b.u; bf16_t* q = (bf16_t*)b.q; bf16_t* attn = (bf16_t*)b.attn;
   bf16_t* act = (bf16_t*)b.act;
   auto G = [](const void* p) { return (const bf16_t*)p; };
+  // operands of a residual GEMM's K split; i: its number in the step
+  auto splits = [&](GemmEpi& e, int i) {
+    e.partial = b.ksplit_part; e.partial_floats = b.ksplit_floats;
+    e.meet = (MeetSlot*)(b.meet + (size_t)i * kMeetSlots);
+    e.meet_limit = c->meet_limit; e.meet_apart = c->meet_apart;
+  };
   auto sums = [&](int i) { return b.sumsq + (size_t)i * kSumSlots * b.sumsq_stride; };
 
   { Scope p(c, EC_K_EMBED);
@@ -481,6 +490,7 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
     sl.seqs = c->B == 1 ? nullptr : b.seqs; sl.seq0 = c->host_seqs[0]; sl.B = c->B; sl.R = R; sl.n_lm = sp.n_lm; sl.x = b.x;
     sl.rows_partial = b.rows_partial; sl.mb_pos = b.mb_pos; sl.mb_idx = b.mb_idx;
     sl.vocab = m.vocab;
+    sl.meet = b.meet; sl.n_meet = 2 * L * kMeetSlots;
     sl.block = c->d.block; sl.rowinfo = b.rowinfo; sl.tileinfo = b.tileinfo; sl.lm_sel = b.lm_sel;
     launch_step_prologue_bf16(sl, G(c->w.tok_emb), d, G(c->attn_norm[0]), b.h, u, b.sumsq,
                               (2 * L + 1) * kSumSlots, b.sumsq_stride, s); }
@@ -501,7 +511,7 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
     { Scope p(c, EC_K_OPROJ);
       GemmEpi e{}; e.M = M; e.MT = MT; e.h = b.h; e.d = d; e.gain_next = G(c->mlp_norm[l]);
       e.a_next = u; e.sumsq_out = sums(2 * l + 1); e.sum_stride = b.sumsq_stride;
-      e.partial = b.ksplit_part; e.max_ksplit = kMaxKSplit;
+      splits(e, 2 * l);
       e.w_grp = skinny_tiles_per_block(EPI_RESID, d / 16); e.wscale = b.pl[l].so;
       launch_gemm_bf16(EPI_RESID, attn, R, b.pl[l].wo, b.pl[l].qo, d, nq, e, s); }
     { Scope p(c, EC_K_GATEUP);
@@ -513,7 +523,7 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
       GemmEpi e{}; e.M = M; e.MT = MT; e.h = b.h; e.d = d;
       e.gain_next = G(l + 1 < L ? c->attn_norm[l + 1] : c->w.final_norm);
       e.a_next = u; e.sumsq_out = sums(2 * l + 2); e.sum_stride = b.sumsq_stride;
-      e.partial = b.ksplit_part; e.max_ksplit = kMaxKSplit;
+      splits(e, 2 * l + 1);
       e.w_grp = skinny_tiles_per_block(EPI_RESID, d / 16); e.wscale = b.pl[l].sd;
       launch_gemm_bf16(EPI_RESID, act, R, b.pl[l].wd, b.pl[l].qd, d, F, e, s); }
   }
@@ -1018,6 +1028,13 @@ int ec_debug_keep_logits(ec_ctx* ctx, int on) {
   return EC_OK;
 }
 
+int ec_debug_meeting(ec_ctx* ctx, int32_t polls, int apart) {
+  if (!ctx) return fail(nullptr, EC_ERR_ARG, "ctx is NULL");
+  if (polls < 0) return fail(ctx, EC_ERR_ARG, "polls must be >= 0");
+  ctx->meet_limit = polls; ctx->meet_apart = apart != 0;
+  return EC_OK;
+}
+
 int ec_debug_block_shape(const ec_model_cfg* m, int product, int32_t list_rows, int32_t rows,
                          int32_t shape[3]) {
   if (!m || !shape) return fail(nullptr, EC_ERR_ARG, "model and shape must not be NULL");
@@ -1033,7 +1050,7 @@ int ec_debug_block_shape(const ec_model_cfg* m, int product, int32_t list_rows, 
     case EC_K_LMHEAD: epi = EPI_LOGITS; N = m->vocab; break;
     default: return fail(nullptr, EC_ERR_ARG, "product is not a matrix product");
   }
-  if (!gemm_bf16_block_shape(epi, list_rows, rows, N, K, kMaxKSplit, shape))
+  if (!gemm_bf16_block_shape(epi, list_rows, rows, N, K, meet_piece_floats(list_rows, N), shape))
     return fail(nullptr, EC_ERR_ARG, "so few rows stream their weights");
   return EC_OK;
 }

@@ -118,13 +118,23 @@ void launch_attention_f32(const float* q, const float* kc, const float* vc, int 
                           int Hkv, int hd, float* out, hipStream_t s);
 
 // bf16 path
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_PARTIAL = 4 };
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 constexpr int kMaxKSplit = 4;
+constexpr int kMeetSlots = 256;  // groups of blocks per launch that can exchange pieces of a K split
 // A row's sum of squares is accumulated by many blocks at once.  Atomics on one address
 // serialise, so each row has kSumSlots counters (a block adds to the one its index selects) and
 // the reader adds them up; integer addition keeps the total independent of the order.
 constexpr int kSumSlots = 8;
 enum { REPACK_PLAIN = 0, REPACK_ROPE_HALVES = 1, REPACK_LO8 = 2, REPACK_HI8 = 3 };
+
+struct MeetSlot;   // k_meet.h
+constexpr size_t kMeetSlotBytes = 16;
+// floats that hold the pieces of any K split of a residual product with at most `rows` rows (whole tiles of 16)
+// and d outputs: four ranges of the padded product, and never more than a block of 256 x 320 for every compute unit
+inline size_t meet_piece_floats(size_t rows, size_t d) {
+  const size_t all = 4 * (rows + 256) * (d + 384), most = 256 * 256 * 320;
+  return all < most ? all : most;
+}
 
 // What a GEMM epilogue needs (k_gemm_bf16.hip).  Row sums of squares are 44.20 fixed point.
 struct GemmEpi {
@@ -144,7 +154,9 @@ struct GemmEpi {
   float4* vparts;                 // EPI_LOGITS, skinny kernel: [row][blocks] partial tuples of
                                   // the vocabulary reduction (k_vtuple.h), one per block
   float* h; int d;                // EPI_RESID: residual stream [M, d]
-  float* partial; int max_ksplit; // nullable: room for [max_ksplit][M][d] fp32 partial products
+  float* partial; size_t partial_floats;  // EPI_RESID, nullable: room for the pieces of a K split
+  MeetSlot* meet;                 // nullable: [kMeetSlots], zero, this launch's own (k_meet.h)
+  int meet_limit, meet_apart;     // polls before a block stops waiting; blocks taken as on different XCDs
   const bf16_t* gain_next;        // gain of the norm that follows
   bf16_t* a_next;                 // packed bf16(h * gain_next)
   unsigned long long* sumsq_out;  // [kSumSlots][sum_stride], accumulated with integer atomics
@@ -174,6 +186,7 @@ struct StepLists {
   const int* mb_idx;            // stride block
   int block;
   int4* rowinfo; int4* tileinfo; int* lm_sel;
+  int4* meet; int n_meet;       // the step's MeetSlots: zeroed (as int4)
 };
 void launch_step_prologue_bf16(const StepLists& L, const bf16_t* emb, int d, const bf16_t* gain,
                                float* h, bf16_t* a_out, unsigned long long* sumsq, int nbuf,
@@ -204,7 +217,7 @@ void launch_gemm_bf16(int epi, const bf16_t* Ap, int M_src, const bf16_t* Wp, co
                       int N, int K, const GemmEpi& e, hipStream_t s);
 // the block (rows, output features, K ranges) that launch_gemm_bf16 picks for these sizes; false where
 // it streams the weights (few rows)
-bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, int max_ksplit, int shape[3]);
+bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, size_t piece_floats, int shape[3]);
 // e4m3 source: Wq receives the codes as 1 KiB fragment pairs (64 k per weight tile and step),
 // Wp the same values as bf16 fragments (exact); either may be NULL.  mode / hd / grp / row0 as
 // launch_repack_weight.

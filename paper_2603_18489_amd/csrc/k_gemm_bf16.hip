@@ -34,6 +34,7 @@
 //     LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384, 256x256): operands
 //     loaded from global memory directly into a 3-stage LDS ring.
 #include "ec_internal.h"
+#include "k_meet.h"
 #include "k_vtuple.h"
 
 namespace ec {
@@ -204,6 +205,36 @@ __device__ __forceinline__ void epi_qkv(const GemmEpi& e, int m, int vt, int q4,
   }
 }
 
+// Which tile and range of K a block works on where K is split over Z blocks, on a one-dimensional grid.  An XCD
+// gets a run of whole tiles, the Z blocks of a tile one after the other, so that they run at the same time
+// and meet in one L2.  If the XCDs' runs, up to a tile of different length, fit its 32 compute units, the
+// grid has room for the longest on each (meet_grid) and the blocks it has too many find no tile: false.
+// Otherwise the grid is Z blocks a tile, and what is left over on the XCDs (up to Z - 1 blocks each) makes up
+// the last tiles, whose blocks have to fence.
+template <int Z>
+__device__ __forceinline__ bool meet_place(int tiles, int& tile, int& z) {
+  const int n = gridDim.x, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  if (n != tiles * Z) {
+    tile = xcd * tiles / 8 + j / Z;
+    z = j % Z;
+    return tile < (xcd + 1) * tiles / 8;
+  }
+  const int few = n >> 3, more = n & 7;   // blocks of an XCD: few + 1 on the first `more` of them
+  const int q = (few + (xcd < more)) / Z, above = min(xcd, more), below = xcd - above;
+  int at = (above * ((few + 1) / Z) + below * (few / Z)) * Z + j;
+  if (j >= q * Z) {
+    const int whole = (more * ((few + 1) / Z) + (8 - more) * (few / Z)) * Z;
+    at = whole + above * ((few + 1) % Z) + below * (few % Z) + j - q * Z;
+  }
+  tile = at / Z;
+  z = at - tile * Z;
+  return true;
+}
+static int meet_grid(int tiles, int Z) {
+  const int longest = (tiles + 7) / 8 * Z;
+  return longest <= 32 ? 8 * longest : tiles * Z;
+}
+
 // ---------------------------------------------------------------------------------------------
 // skinny: grid = ceil(n-tiles / NTW) blocks of KS*64 threads
 // ---------------------------------------------------------------------------------------------
@@ -211,7 +242,10 @@ __device__ __forceinline__ void epi_qkv(const GemmEpi& e, int m, int vt, int q4,
 // 64 k per weight tile and k-step; a lane's 16 bytes are turned into two bf16 MFMA operands in
 // registers (exact), so a k-step is two MFMAs per (weight tile, m-tile) on two activation
 // fragments, KB counts 64-wide steps, and the per-row scales multiply the K-reduced sums.
-template <int EPI, int MT, int NTW, int KS, int U, bool W8 = false>
+// Z > 1: K is also divided over Z blocks, which exchange the sums of each other's shares of
+// the (tile, m-tile) units and finish their own (k_meet.h).  A block then owns Z times the weight tiles
+// and pulls a Z-th of the activations.
+template <int EPI, int MT, int NTW, int KS, int U, bool W8 = false, int Z = 1>
 __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* __restrict__ Ap,
                                                                    const u32x4* __restrict__ Wp,
                                                                    int total_nt, int KB,
@@ -222,13 +256,15 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // provably wave-uniform: MFMA ignores the EXEC mask, so it must never sit under a condition
   // the compiler could treat as divergent
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nt0 = blockIdx.x * NTW;
-  // EPI_PARTIAL: blockIdx.y picks one of gridDim.y contiguous K ranges.  (The others are not charged the
-  // division and the load of the grid's size ahead of their first operand: about 0.4 us a launch.)
+  int bx = blockIdx.x, bz = 0;
+  if constexpr (Z > 1) {
+    if (!meet_place<Z>((total_nt + NTW - 1) / NTW, bx, bz)) return;
+  }
+  const int nt0 = bx * NTW;
   int kr_lo = 0, kr_n = KB;
-  if constexpr (EPI == EPI_PARTIAL) {
-    kr_lo = (int)((blockIdx.y * KB) / gridDim.y);
-    kr_n = (int)(((blockIdx.y + 1) * KB) / gridDim.y) - kr_lo;
+  if constexpr (Z > 1) {
+    kr_lo = bz * KB / Z;
+    kr_n = (bz + 1) * KB / Z - kr_lo;
   }
   const int kb_lo = kr_lo + (wave * kr_n) / KS, kb_hi = kr_lo + ((wave + 1) * kr_n) / KS;
 
@@ -311,12 +347,14 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // still counts outstanding loads exactly.
   // Epilogue operands of the thread's first output unit are fetched here too: the residual
   // stream and gains (EPI_RESID) so that the epilogue does not start with a round trip to memory.
-  constexpr int UNITS = NTW * MT * 64;  // whole waves: the wave's 64 lanes share (tile, m-tile)
+  constexpr int NU = NTW * MT, UNITS = NU * 64;  // whole waves: the wave's 64 lanes share (tile, m-tile)
+  // Z > 1: the block of range z finishes units z NU / Z .. (z + 1) NU / Z - 1
+  const int u_lo = bz * NU / Z, u_hi = (bz + 1) * NU / Z;
   float4 pre_h = make_float4(0.f, 0.f, 0.f, 0.f);
   u32x2 pre_g = {0u, 0u};
   if constexpr (EPI == EPI_RESID) {
-    const int o = threadIdx.x < UNITS ? threadIdx.x : 0;
-    const int l = o & 63, unit = o >> 6, iu = unit / MT, j = unit - iu * MT;
+    const int unit = u_lo + wave < u_hi ? u_lo + wave : u_lo;
+    const int l = lane, iu = unit / MT, j = unit - iu * MT;
     const int m = j * 16 + (l & 15), vt = nt0 + iu;
     const int mm = m < e.M ? m : 0, n = (vt < total_nt ? vt : 0) * 16 + (l >> 4) * 4;
     pre_h = *(const float4*)(e.h + (size_t)mm * e.d + n);
@@ -451,81 +489,72 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
     }
     return;
   }
-  for (int o = threadIdx.x; o < UNITS; o += KS * 64) {
-    const int l = o & 63, unit = o >> 6, iu = unit / MT, j = unit - iu * MT;
-    const int m = j * 16 + (l & 15), q4 = l >> 4;
+  // the epilogue on the sums of one unit
+  auto finish = [&](int unit, f32x4 v, bool pre) {
+    const int iu = unit / MT, j = unit - iu * MT, q4 = lane >> 4;
+    const int m = j * 16 + (lane & 15), vt = nt0 + iu;
     const bool mvalid = m < e.M;
-    const int vt = nt0 + iu;
-    f32x4 v = ksum((iu * MT + j) * 64 + l, iu, q4);
     if constexpr (EPI == EPI_RESID) {
       float part = 0.f;
       if (mvalid && vt < total_nt)
-        part = o < KS * 64 ? epi_resid_pre(e, m, vt, q4, v, pre_h, pre_g) : epi_resid(e, m, vt, q4, v);
+        part = pre ? epi_resid_pre(e, m, vt, q4, v, pre_h, pre_g) : epi_resid(e, m, vt, q4, v);
       epi_add_sumsq(e, m, mvalid, part);
     } else if (mvalid && vt < total_nt) {
-      if constexpr (EPI == EPI_PARTIAL)
-        *(float4*)(e.partial + ((size_t)blockIdx.y * e.M + m) * e.d + vt * 16 + q4 * 4) =
-            make_float4(v[0], v[1], v[2], v[3]);
-      else if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
+      if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
       else epi_qkv(e, m, vt, q4, v, rstd_s[m]);
+    }
+  };
+  if constexpr (Z == 1) {
+    for (int unit = wave; unit < NU; unit += KS) finish(unit, ksum(unit * 64 + lane, unit / MT, lane >> 4), unit == wave);
+  } else {
+    const int z = bz;
+    f32x4* mine = (f32x4*)e.partial + ((size_t)bx * Z + z) * UNITS + lane;
+    const f32x4* all = (const f32x4*)e.partial + (size_t)bx * Z * UNITS + lane;
+    for (int unit = wave; unit < NU; unit += KS)
+      if (unit < u_lo || unit >= u_hi) mine[unit * 64] = ksum(unit * 64 + lane, unit / MT, lane >> 4);
+    unsigned shares = meet_blocks(e.meet + bx, Z, z, e.meet_limit, e.meet_apart, [&] {
+      for (int unit = u_lo + wave; unit < u_hi; unit += KS) mine[unit * 64] = ksum(unit * 64 + lane, unit / MT, lane >> 4);
+    });
+    constexpr int MU = ((NU + Z - 1) / Z + KS - 1) / KS;  // units of a share to a wave
+    while (shares) {
+      const int sh = __builtin_ctz(shares), lo = sh * NU / Z + wave, hi = (sh + 1) * NU / Z;
+      shares &= shares - 1;
+      f32x4 p[MU][Z];   // every piece is requested before the first is used
+#pragma unroll
+      for (int i = 0; i < MU; ++i)
+#pragma unroll
+        for (int y = 0; y < Z; ++y)
+          if (y != z) p[i][y] = all[((size_t)y * NU + (lo + i * KS < hi ? lo + i * KS : hi - 1)) * 64];
+#pragma unroll
+      for (int i = 0; i < MU; ++i) {
+        const int unit = lo + i * KS;
+        if (unit >= hi) break;
+        const f32x4 own = ksum(unit * 64 + lane, unit / MT, lane >> 4);
+        f32x4 v = z == 0 ? own : p[i][0];
+#pragma unroll
+        for (int y = 1; y < Z; ++y) v += y == z ? own : p[i][y];
+        finish(unit, v, i == 0 && sh == z);
+      }
     }
   }
 }
 
-// Second half of a K-split residual GEMM: h += sum over the splits (fixed order), then what
-// EPI_RESID does: next operand bf16(h * gain) and the row's sum of squares.  Bound by its bytes:
-// every load is requested before the first is used.  768 rows of 4096 in four pieces:
-// 82 MB in 16.3 us (5.0 TB/s, what a large copy reaches).
-// grid (ceil(d / 1024), M), 256 threads, 4 columns per thread.
-template <int KSPLIT>
-__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
-  __shared__ float red[4];
-  const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
-  float part = 0.f;
-  if (n < e.d) {
-    f32x4 p[KSPLIT];
-#pragma unroll
-    for (int z = 0; z < KSPLIT; ++z)
-      p[z] = *(const f32x4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
-    const float4 h = *(const float4*)(e.h + (size_t)m * e.d + n);
-    const u32x2 g4 = *(const u32x2*)(e.gain_next + n);
-    f32x4 v = p[0];
-#pragma unroll
-    for (int z = 1; z < KSPLIT; ++z) v += p[z];
-    part = epi_resid_pre(e, m, n >> 4, (n >> 2) & 3, v, h, g4);
-  }
-  part = block_sum<4>(part, red);
-  if (threadIdx.x == 0) {
-    unsigned long long fx = sumsq_to_fixed<58>(part);
-    if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)(blockIdx.x & (kSumSlots - 1)) * e.sum_stride + m), fx);
-  }
-}
-
-static void launch_resid_finish(const GemmEpi& e, int ksplit, int N, hipStream_t s) {
-  const dim3 grid((N + 1023) / 1024, e.M);
-  switch (ksplit) {
-    case 2: resid_finish_kernel<2><<<grid, 256, 0, s>>>(e); break;
-    case 3: resid_finish_kernel<3><<<grid, 256, 0, s>>>(e); break;
-    default: resid_finish_kernel<4><<<grid, 256, 0, s>>>(e); break;
-  }
-}
-
-template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false>
+template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false, int Z = 1>
 static void launch_skinny_t(const bf16_t* Ap, int MT_src, const void* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s, int ksplit = 1) {
-  dim3 grid((total_nt + NTW - 1) / NTW, ksplit);
+                            const GemmEpi& e, hipStream_t s) {
+  const int groups = (total_nt + NTW - 1) / NTW, grid = Z > 1 ? meet_grid(groups, Z) : groups;
   size_t smem = (size_t)KS * NTW * MT * 64 * sizeof(float4) + MT * 16 * sizeof(float);
   if (EPI == EPI_LOGITS) smem += (size_t)NTW * MT * 16 * sizeof(float4);  // per-tile row tuples
   if (W8) smem += NTW * 16 * sizeof(float);                               // weight scales
   if (smem > 48 * 1024) {
     static bool once = false;
     if (!once) {
-      (void)hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8>,
+      (void)hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8, Z>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       once = true;
     }
   }
-  gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8><<<grid, KS * 64, smem, s>>>(
+  gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8, Z><<<grid, KS * 64, smem, s>>>(
       (const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT_src, e);
 }
 
@@ -546,21 +575,23 @@ int skinny_tiles_per_block(int epi, int total_nt) {
 
 // A residual GEMM has only d_model / 16 weight tiles, one to a block, and every block pulls the
 // whole [rows, K] operand beside its 16 rows of weights: 1.2 MB beside 0.4 at 48 rows of 12288.  Four
-// neighbouring tiles and a quarter of K to a block pull a quarter of that; the partial products
-// are summed by resid_finish_kernel (4.8 us and the gap before it).  us on MI355X, whole K -> split
-// and finish, d 4096:
-//   3 row tiles  K 12288  30.5 -> 21.3 + 4.8   (e4m3 23.5 -> 15.4 + 4.0)   K 4096  11.2 ->  8.2 + 4.8
-//   6 row tiles  K 12288  44.4 -> 27.0 + 5.1                               K 4096  16.6 -> 11.0 + 5.1
-// which is a gain of about MT * K * 2.4e-4 - 5.5 us.  Two tiles and half of K: 23 and 33 at K 12288.
-// The line holds at every width, since a block's bytes do not depend on it and the few blocks of a narrow
-// matrix leave as much of the chip idle split or not.  us of a down projection with its finish, by
-// events, just above the line (MT K 23808 - 24576, 2 to 6 row tiles) and at 3 row tiles of 12288:
-//   d  128   17.1 -> 14.9, 22.7 -> 18.5     d 2048   20.4 -> 18.3, 28.0 -> 23.5
-//   d  512   18.7 -> 15.5, 26.1 -> 19.7     d 4096   23.8 -> 21.1, 32.0 -> 26.5 (6 x 3968: 20.1 -> 20.3)
-//   d 1024   19.5 -> 16.1, 26.7 -> 20.3     d 8192   38.7 -> 32.8, 56.8 -> 44.1
+// neighbouring tiles and a quarter of K to a block pull a quarter of that; the meeting of the four
+// blocks costs about 2 us.  us on MI355X with weights from memory, whole K -> split, d 4096:
+//   row tiles   K 4096         K 8192         K 12288        K 18944        e4m3: K 4096, 12288
+//       1     8.7 -> 10.5   14.9 -> 16.6   19.9 -> 20.6   28.9 -> 28.1     6.9 ->  8.1  14.1 -> 13.1
+//       2    10.5 -> 11.3   17.5 -> 17.6   25.0 -> 21.9   36.9 -> 29.9     8.5 ->  8.9  18.9 -> 14.4
+//       3    11.5 -> 11.7   19.2 -> 17.9   27.8 -> 22.6   41.4 -> 31.0     9.5 ->  9.9  21.8 -> 15.7
+//       4    13.6 -> 12.5   23.2 -> 19.1   33.8 -> 24.2   51.6 -> 34.2    11.4 -> 10.6  26.9 -> 17.8
+//       6    16.3 -> 14.8   28.5 -> 21.5   42.3 -> 27.7   66.0 -> 38.9    14.7 -> 13.1  36.1 -> 22.4
+// so the line lies at MT * K = 16000.  (Two tiles and half of K lie in between; the wider products gain
+// nothing from a split: q k v 20.9 -> 21.3, gate/up 33.8 -> 38.9 at 3 row tiles.)  It holds at every width, since a
+// block's bytes do not depend on it: d 1024, 3 row tiles, K 12288 24.6 -> 17.4.
 constexpr int kSkinnySplit = 4;
-static bool skinny_splits(int MT, int K, const GemmEpi& e) {
-  return e.partial && e.max_ksplit >= kSkinnySplit && (long)MT * K >= 23000;
+static int max_ksplit(int epi, const GemmEpi& e);
+static bool skinny_splits(int MT, int total_nt, int K, const GemmEpi& e) {
+  return max_ksplit(EPI_RESID, e) >= kSkinnySplit && (total_nt + kSkinnySplit - 1) / kSkinnySplit <= kMeetSlots &&
+         (size_t)(total_nt + kSkinnySplit - 1) / kSkinnySplit * kSkinnySplit * kSkinnySplit * MT * 256 <= e.partial_floats &&
+         (long)MT * K >= 16000;
 }
 
 // e4m3 weights: KB counts 64-wide k-steps; fewer steps per register set, because a step holds
@@ -571,12 +602,9 @@ static void launch_skinny_mt_w8(const bf16_t* Ap, int MT_src, const void* Wq, in
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
-    if constexpr (MT > 1) {
-      if (skinny_splits(MT, KB * 64, e)) {
-        launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s, kSkinnySplit);
-        launch_resid_finish(e, kSkinnySplit, total_nt * 16, s);
-        return;
-      }
+    if (skinny_splits(MT, total_nt, KB * 64, e)) {
+      launch_skinny_t<EPI, MT, kSkinnySplit, 4, 1, true, kSkinnySplit>(Ap, MT_src, Wq, total_nt, KB, e, s);
+      return;
     }
     launch_skinny_t<EPI, MT, 1, 8, (MT > 3 ? 1 : 2), true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else {
@@ -596,12 +624,9 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, (MT > 2 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
-    if constexpr (MT > 1) {
-      if (skinny_splits(MT, KB * 32, e)) {
-        launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s, kSkinnySplit);
-        launch_resid_finish(e, kSkinnySplit, total_nt * 16, s);
-        return;
-      }
+    if (skinny_splits(MT, total_nt, KB * 32, e)) {
+      launch_skinny_t<EPI, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 2), false, kSkinnySplit>(Ap, MT_src, Wp, total_nt, KB, e, s);
+      return;
     }
     launch_skinny_t<EPI, MT, 1, 8, 2>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else {
@@ -720,8 +745,7 @@ __device__ __forceinline__ void tiled_epilogue_qkv(const GemmEpi& e, f32x4 (&acc
 
 template <int EPI, int WTM, int WTN, bool PIPE = true>
 __device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WTN][WTM],
-                                               int mt_base, int nt_base, int total_nt, int lane,
-                                               int kz) {
+                                               int mt_base, int nt_base, int total_nt, int lane) {
   if constexpr (EPI == EPI_QKV && PIPE) {
     tiled_epilogue_qkv<WTM, WTN>(e, acc, mt_base, nt_base, total_nt, lane);
     return;
@@ -741,33 +765,13 @@ __device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WT
   for (int j = 0; j < WTM; ++j) {
     const int m = (mt_base + j) * 16 + (lane & 15);
     const bool mvalid = m < e.M;
-    if constexpr (EPI == EPI_RESID) {
-      float part = 0.f;
-#pragma unroll
-      for (int i = 0; i < WTN; ++i) {
-        int vt = nt_base + i;
-        if (mvalid && vt < total_nt) part += epi_resid(e, m, vt, q4, acc[i][j]);
-      }
-      epi_add_sumsq(e, m, mvalid, part);
-    } else if constexpr (EPI == EPI_LOGITS) {
+    if constexpr (EPI == EPI_LOGITS) {
       if (mvalid) {
         const float rs = rsj[j];
 #pragma unroll
         for (int i = 0; i < WTN; ++i) {
           int vt = nt_base + i;
           if (vt < total_nt) epi_logits(e, m, vt, q4, acc[i][j], rs);
-        }
-      }
-    } else if constexpr (EPI == EPI_PARTIAL) {
-      if (mvalid) {
-#pragma unroll
-        for (int i = 0; i < WTN; ++i) {
-          int vt = nt_base + i;
-          if (vt < total_nt) {
-            f32x4 v = acc[i][j];
-            *(float4*)(e.partial + ((size_t)kz * e.M + m) * e.d + vt * 16 + q4 * 4) =
-                make_float4(v[0], v[1], v[2], v[3]);
-          }
         }
       }
     } else {
@@ -787,6 +791,155 @@ __device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WT
         }
       }
     }
+  }
+}
+
+// Residual epilogue of Z blocks that hold the same tile for Z ranges of K (k_meet.h).  The tile's fragments
+// are shared out by their number in the wave, WTM * i + j: every wave stores those of the other blocks'
+// shares (1 KiB each, as the registers hold them), and after the meeting adds the others' pieces to its
+// own share in the order of the ranges and finishes it.  Rows' sums of squares go through LDS (`sums`: the
+// block's WN x rows floats), one addition to memory per row and share.
+// Against partial products and a second kernel that reads them all back (768 rows, d 4096, 192 x 256 x 4):
+// O 46.7 -> 38.1 us, down 89 -> 80; of that 14 us are the exchange and the residual stream's read and write.
+template <int WM, int WN, int WTM, int WTN, int Z>
+__device__ __forceinline__ void tiled_meet_resid(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt0,
+                                                 int nt0, int total_nt, int wave, int lane, int tile,
+                                                 int z, float* sums) {
+  constexpr int NFR = WTN * WTM, NO = (NFR + Z - 1) / Z, ROWS = WM * WTM * 16;
+  const int wm = wave / WN, wn = wave % WN, q4 = lane >> 4;
+  const size_t per_range = (size_t)WM * WN * NFR * 64;
+  f32x4* pieces = (f32x4*)e.partial + (size_t)tile * Z * per_range + (size_t)wave * NFR * 64 + lane;
+  const int rows_j = (e.M + 15) / 16 - mt0 - wm * WTM;   // row tiles of the wave that hold rows: no exchange beyond
+  // (the share's ranges are known per z at compile time: the accumulators need constant indices)
+  f32x4 own[NO];
+#pragma unroll
+  for (int y = 0; y < Z; ++y)
+    if (y == z) {
+#pragma unroll
+      for (int f = 0; f < NFR; ++f) {
+        if (f >= y * NFR / Z && f < (y + 1) * NFR / Z) own[f - y * NFR / Z] = acc[f / WTM][f % WTM];
+        else if (f % WTM < rows_j) pieces[y * per_range + f * 64] = acc[f / WTM][f % WTM];
+      }
+      if ((y + 1) * NFR / Z - y * NFR / Z < NO) own[NO - 1] = own[0];  // (a share one fragment short)
+    }
+  // The share is finished NB fragments at a time, every load of a batch ahead of its first use; the first
+  // batch's residual stream and gains are on their way while the blocks meet.
+  constexpr int NB = NO < 28 / Z ? NO : 28 / Z;
+  float4 h[NB];
+  u32x2 g[NB];
+  auto row_of = [&](int f) { return (mt0 + wm * WTM + f % WTM) * 16 + (lane & 15); };
+  auto tile_of = [&](int f) { return nt0 + wn * WTN + f / WTM; };
+  auto fetch_h = [&](int first, int hi) {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int f = min(first + k, hi - 1), m = min(row_of(f), e.M - 1), n = min(tile_of(f), total_nt - 1) * 16 + q4 * 4;
+      h[k] = *(const float4*)(e.h + (size_t)m * e.d + n);
+      g[k] = *(const u32x2*)(e.gain_next + n);
+    }
+  };
+  fetch_h(z * NFR / Z, (z + 1) * NFR / Z);
+  unsigned shares = meet_blocks(e.meet + tile, Z, z, e.meet_limit, e.meet_apart, [&] {
+    const int lo = z * NFR / Z, n = (z + 1) * NFR / Z - lo;
+#pragma unroll
+    for (int k = 0; k < NO; ++k)
+      if (k < n) pieces[z * per_range + (lo + k) * 64] = own[k];
+  });
+  float* my_sums = sums + wn * ROWS + wm * WTM * 16 + (lane & 15);
+  // (its own share first, while that is in registers)
+  for (int sh = z; shares; sh = __builtin_ctz(shares | 1u << Z)) {
+    const int lo = sh * NFR / Z, hi = (sh + 1) * NFR / Z;
+    shares &= ~(1u << sh);
+    if (lane < 16) {
+#pragma unroll
+      for (int j = 0; j < WTM; ++j) my_sums[j * 16] = 0.f;
+    }
+    if (sh != z) {   // (the share of a block that has gone: this block's piece of it is in memory)
+#pragma unroll
+      for (int k = 0; k < NO; ++k) own[k] = pieces[z * per_range + min(lo + k, hi - 1) * 64];
+    }
+#pragma unroll
+    for (int b0 = 0; b0 < NO; b0 += NB) {
+      f32x4 p[NB][Z - 1];   // the pieces of the other ranges, in their order
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int y = 0; y < Z - 1; ++y)
+          if ((lo + b0 + k) % WTM < rows_j) p[k][y] = pieces[(y + (y >= z)) * per_range + min(lo + b0 + k, hi - 1) * 64];
+      if (sh != z || b0 > 0) fetch_h(lo + b0, hi);
+#pragma unroll
+      for (int k = 0; k < NB && b0 + k < NO; ++k) {
+        const int f = lo + b0 + k, m = row_of(f), vt = tile_of(f);
+        f32x4 v = z == 0 ? own[b0 + k] : p[k][0];
+#pragma unroll
+        for (int y = 1; y < Z; ++y) v += y == z ? own[b0 + k] : y < z ? p[k][y < Z - 1 ? y : 0] : p[k][y - 1];
+        float part = 0.f;
+        if (f < hi && m < e.M && vt < total_nt) part = epi_resid_pre(e, m, vt, q4, v, h[k], g[k]);
+        part += other_row(part);
+        part += other_half(part);
+        if (lane < 16) my_sums[f % WTM * 16] += part;
+      }
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r < ROWS; r += WM * WN * 64) {
+      float s = sums[r];
+#pragma unroll
+      for (int w = 1; w < WN; ++w) s += sums[w * ROWS + r];
+      const int m = mt0 * 16 + r;
+      const unsigned long long fx = sumsq_to_fixed(s);
+      if (fx && m < e.M)
+        atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)((tile + sh) & (kSumSlots - 1)) * e.sum_stride + m), fx);
+    }
+    if (shares) __syncthreads();
+  }
+}
+
+// Residual epilogue of a whole K: D row tiles of the residual stream are on their way while one is finished
+// (the epilogue of a round of 256 x 256 blocks then moves its bytes at 7 TB/s, most of them through the
+// last-level cache), and a block adds each row's sum of squares once, through LDS (`sums`: WN x rows floats).
+template <int WM, int WN, int WTM, int WTN>
+__device__ __forceinline__ void tiled_resid(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt0, int nt0,
+                                            int total_nt, int wave, int lane, float* sums) {
+  constexpr int ROWS = WM * WTM * 16, D = 14 / WTN < 2 ? 2 : 14 / WTN < WTM ? 14 / WTN : WTM;
+  const int wm = wave / WN, wn = wave % WN, q4 = lane >> 4;
+  const int vt0 = nt0 + wn * WTN, r0 = (mt0 + wm * WTM) * 16 + (lane & 15);
+  u32x2 g[WTN];
+  int n[WTN];
+#pragma unroll
+  for (int i = 0; i < WTN; ++i) {
+    n[i] = min(vt0 + i, total_nt - 1) * 16 + q4 * 4;
+    g[i] = *(const u32x2*)(e.gain_next + n[i]);
+  }
+  float4 h[D][WTN];
+  auto fetch = [&](float4 (&to)[WTN], int j) {
+    const float* row = e.h + (size_t)min(r0 + j * 16, e.M - 1) * e.d;
+#pragma unroll
+    for (int i = 0; i < WTN; ++i) to[i] = *(const float4*)(row + n[i]);
+  };
+#pragma unroll
+  for (int j = 0; j < D - 1; ++j) fetch(h[j], j);
+  __syncthreads();   // (the LDS is no longer read)
+  float* my_sums = sums + wn * ROWS + wm * WTM * 16 + (lane & 15);
+#pragma unroll
+  for (int j = 0; j < WTM; ++j) {
+    if (j + D - 1 < WTM) fetch(h[(j + D - 1) % D], j + D - 1);
+    const int m = r0 + j * 16;
+    float part = 0.f;
+#pragma unroll
+    for (int i = 0; i < WTN; ++i)
+      if (m < e.M && vt0 + i < total_nt) part += epi_resid_pre(e, m, vt0 + i, q4, acc[i][j], h[j % D][i], g[i]);
+    part += other_row(part);
+    part += other_half(part);
+    if (lane < 16) my_sums[j * 16] = part;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < ROWS; r += WM * WN * 64) {
+    float s = sums[r];
+#pragma unroll
+    for (int w = 1; w < WN; ++w) s += sums[w * ROWS + r];
+    const int m = mt0 * 16 + r;
+    const unsigned long long fx = sumsq_to_fixed(s);
+    if (fx && m < e.M)
+      atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)((nt0 / (WN * WTN)) & (kSumSlots - 1)) * e.sum_stride + m), fx);
   }
 }
 
@@ -829,7 +982,7 @@ __device__ __forceinline__ void tiled_block_xy(int& bx, int& by) {
 // tiled, 4 waves (2x2): wave tile = WTM x WTN fragments, K step 32.  Operands are double-buffered
 // in LDS; global loads run through four register sets, four k-steps ahead.  This variant is the
 // faster one for block tiles up to 192 x 192 (one wave per SIMD, nothing to overlap with).
-// grid = (ceil(n-tiles / (2*WTN)), ceil(m-tiles / (2*WTM)), k splits)
+// grid = (ceil(n-tiles / (2*WTN)), ceil(m-tiles / (2*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
 #define EC_TILED_GLOAD(REGS, KBV)                                                   \
   {                                                                                 \
@@ -854,7 +1007,7 @@ __device__ __forceinline__ void tiled_block_xy(int& bx, int& by) {
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf_[i], af_[j], acc[i][j], 0, 0, 0); \
   }
 
-template <int EPI, int WTM, int WTN, bool WS>
+template <int EPI, int WTM, int WTN, bool WS, int Z>
 __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __restrict__ Ap,
                                                               const u32x4* __restrict__ Wp,
                                                               int total_nt, int KB_all, int MT,
@@ -863,13 +1016,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __re
   constexpr int LF = (NF + 3) / 4;                             // fragments loaded per wave
   __shared__ u32x4 lds[2][NF][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int bx, by;
-  tiled_block_xy(bx, by);
+  int bx, by, tile = 0, z = 0;
+  if constexpr (Z > 1) {
+    const int gy = (e.M + 16 * BMT - 1) / (16 * BMT);   // (m fastest: the tiles that share weights meet on an XCD)
+    if (!meet_place<Z>((total_nt + BNT - 1) / BNT * gy, tile, z)) return;
+    bx = tile / gy; by = tile - bx * gy;
+  } else {
+    tiled_block_xy(bx, by);
+  }
   const int mt0 = by * BMT, nt0 = bx * BNT;
   const int wm = wave >> 1, wn = wave & 1;
-  // blockIdx.z picks one of gridDim.z contiguous K ranges (EPI_PARTIAL; otherwise gridDim.z = 1)
-  const int kb_first = (int)(((long)blockIdx.z * KB_all) / gridDim.z);
-  const int KB = (int)(((long)(blockIdx.z + 1) * KB_all) / gridDim.z) - kb_first;
+  // the block's range of K
+  const int kb_first = z * KB_all / Z, KB = (z + 1) * KB_all / Z - kb_first;
 
   // Fragment f of the block (0..BMT-1 activations, BMT.. weights) is loaded by wave f % 4.
   // A fragment outside the matrix streams fragment 0 instead (valid memory); what it produces
@@ -928,17 +1086,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __re
 #undef EC_TILED_STEP
 
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
-  tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane, blockIdx.z);
+  if constexpr (Z > 1)
+    tiled_meet_resid<2, 2, WTM, WTN, Z>(e, acc, mt0, nt0, total_nt, wave, lane, tile, z, (float*)lds);
+  else if constexpr (EPI == EPI_RESID)
+    tiled_resid<2, 2, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
+  else
+    tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane);
 }
 #undef EC_TILED_GLOAD
 #undef EC_TILED_LSTORE
 #undef EC_TILED_COMPUTE
 
-template <int EPI, int WTM, int WTN, bool WS>
+template <int EPI, bool WS, int Z, int WTM, int WTN>
 static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                           const GemmEpi& e, hipStream_t s, int ksplit) {
-  dim3 grid((total_nt + 2 * WTN - 1) / (2 * WTN), (MT + 2 * WTM - 1) / (2 * WTM), ksplit);
-  gemm_bf16_tiled4_kernel<EPI, WTM, WTN, WS><<<grid, 256, 0, s>>>((const u32x4*)Ap, (const u32x4*)Wp,
+                           const GemmEpi& e, hipStream_t s) {
+  dim3 grid((total_nt + 2 * WTN - 1) / (2 * WTN), (e.M + 32 * WTM - 1) / (32 * WTM));
+  if (Z > 1) grid = dim3(meet_grid(grid.x * grid.y, Z));
+  gemm_bf16_tiled4_kernel<EPI, WTM, WTN, WS, Z><<<grid, 256, 0, s>>>((const u32x4*)Ap, (const u32x4*)Wp,
                                                                  total_nt, KB, MT, e);
 }
 
@@ -947,15 +1111,12 @@ static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // K step 32.  Operand fragments go from global memory straight into LDS (global_load_lds_dwordx4:
 // lane l's 16 bytes land at base + 16 l, so a 1 KiB fragment keeps its order), NSTAGE stages deep,
 // no staging registers; one barrier per k-step.
-// grid = (ceil(n-tiles / (WN*WTN)), ceil(m-tiles / (WM*WTM)), k splits)
+// grid = (ceil(n-tiles / (WN*WTN)), ceil(m-tiles / (WM*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// (With the plain store epilogue of a K split, blocks of at most 192 x 192 fit two to a CU: the
-// register count is pinned to the 128 VGPRs that allows.  The fused epilogues need more.)
-//
 // ROLL: the fragments of k-step k+1 are read from LDS while the MFMAs of k-step k run, a few after
 // each row of them: a weight fragment goes back to the registers its last MFMA has just freed, the
 // activation fragments and the last weight fragment have a second set.  Reads and MFMAs of a
@@ -966,15 +1127,8 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // us per launch on MI355X at 768 rows, d 4096, F 12288:
 //   gate/up  192 x 384        141 -> 127     q k v  192 x 192            89 -> 84
 //   O, down  192 x 256 x 4 K   55 -> 52 (mean of the two; the read-ahead of whole k-steps before)
-template <int EPI, int WTM, int WTN>
-constexpr bool tiled8_roll() { return EPI != EPI_PARTIAL || WTM * WTN > 18; }
-template <int EPI, int WTM, int WTN>
-constexpr int tiled8_waves_per_eu() { return tiled8_roll<EPI, WTM, WTN>() ? 2 : 4; }
-
-template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool WS>
-__global__ __launch_bounds__(WM * WN * 64)
-__attribute__((amdgpu_waves_per_eu(tiled8_waves_per_eu<EPI, WTM, WTN>(),
-                                   tiled8_waves_per_eu<EPI, WTM, WTN>())))
+template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool WS, int Z>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_tiled8_kernel(
     const u32x4* __restrict__ Ap, const u32x4* __restrict__ Wp, int total_nt, int KB_all, int MT,
     GemmEpi e) {
@@ -985,13 +1139,18 @@ void gemm_bf16_tiled8_kernel(
   static_assert(WTN > 1, "the rolling reads need two weight fragments a wave");
   extern __shared__ u32x4 lds[];  // [NSTAGE][NF][64]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int bx, by;
-  tiled_block_xy(bx, by);
+  int bx, by, tile = 0, z = 0;
+  if constexpr (Z > 1) {
+    const int gy = (e.M + 16 * BMT - 1) / (16 * BMT);   // (m fastest: the tiles that share weights meet on an XCD)
+    if (!meet_place<Z>((total_nt + BNT - 1) / BNT * gy, tile, z)) return;
+    bx = tile / gy; by = tile - bx * gy;
+  } else {
+    tiled_block_xy(bx, by);
+  }
   const int mt0 = by * BMT, nt0 = bx * BNT;
   const int wm = wave / WN, wn = wave % WN;
-  // blockIdx.z picks one of gridDim.z contiguous K ranges (EPI_PARTIAL; otherwise gridDim.z = 1)
-  const int kb_first = (int)(((long)blockIdx.z * KB_all) / gridDim.z);
-  const int KB = (int)(((long)(blockIdx.z + 1) * KB_all) / gridDim.z) - kb_first;
+  // the block's range of K
+  const int kb_first = z * KB_all / Z, KB = (z + 1) * KB_all / Z - kb_first;
 
   // Fragment f of the block (0..BMT-1 activations, BMT.. weights) is loaded by wave f % NW.
   // A fragment outside the matrix streams fragment 0 instead (valid memory); what it produces
@@ -1034,27 +1193,7 @@ void gemm_bf16_tiled8_kernel(
     for (int j = 0; j < WTM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
   int slot_r = 0;
-  if constexpr (!tiled8_roll<EPI, WTM, WTN>()) {
-#pragma unroll
-    for (int sgl = 0; sgl < NSTAGE - 1; ++sgl) { EC_T8_ISSUE(0, LF) EC_T8_FILLED }
-    for (int kb = 0; kb < KB; ++kb) {
-      EC_T8_WAIT(NSTAGE - 2)    // this wave's loads of k-step kb have landed
-      block_barrier_nofence();  // ... and so have everyone else's; the slot read last iteration is free
-      EC_T8_ISSUE(0, LF) EC_T8_FILLED
-      const u32x4* st = lds + (size_t)slot_r * NF * 64;
-      slot_r = slot_r == NSTAGE - 1 ? 0 : slot_r + 1;
-      bf16x8 af[WTM], wf[WTN];
-#pragma unroll
-      for (int j = 0; j < WTM; ++j) af[j] = v4_as_bf16x8(st[(wm * WTM + j) * 64 + lane]);
-#pragma unroll
-      for (int i = 0; i < WTN; ++i) wf[i] = v4_as_bf16x8(st[(BMT + wn * WTN + i) * 64 + lane]);
-#pragma unroll
-      for (int i = 0; i < WTN; ++i)
-#pragma unroll
-        for (int j = 0; j < WTM; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], af[j], acc[i][j], 0, 0, 0);
-    }
-  } else {
+  {
     // All NSTAGE slots are kept in flight.  Step k: this wave has finished reading slot k (its
     // fragments sit in registers) and its loads of k-step k+1 have landed; after the barrier that
     // holds for every wave, so slot k is refilled with k-step k + NSTAGE while slot k+1 is read.
@@ -1116,29 +1255,33 @@ void gemm_bf16_tiled8_kernel(
 
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
   // (the read-ahead QKV epilogue needs registers that only the smaller wave tiles leave free)
-  tiled_epilogue<EPI, WTM, WTN, (WTM * WTN <= 18)>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane,
-                                                   blockIdx.z);
+  if constexpr (Z > 1)
+    tiled_meet_resid<WM, WN, WTM, WTN, Z>(e, acc, mt0, nt0, total_nt, wave, lane, tile, z, (float*)lds);
+  else if constexpr (EPI == EPI_RESID)
+    tiled_resid<WM, WN, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
+  else
+    tiled_epilogue<EPI, WTM, WTN, (WTM * WTN <= 18)>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane);
 }
 
-template <int EPI, bool WS, int WM, int WN, int WTM, int WTN, int NSTAGE>
+template <int EPI, bool WS, int Z, int WM, int WN, int WTM, int WTN, int NSTAGE>
 static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s, int ksplit) {
+                            const GemmEpi& e, hipStream_t s) {
   constexpr int NF = WM * WTM + WN * WTN;
   const size_t smem = (size_t)NSTAGE * NF * 1024;
-  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS>;
+  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS, Z>;
   static bool attr_set = false;
   if (!attr_set && smem > 48 * 1024) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)smem);
     attr_set = true;
   }
-  dim3 grid((total_nt + WN * WTN - 1) / (WN * WTN), (MT + WM * WTM - 1) / (WM * WTM), ksplit);
+  dim3 grid((total_nt + WN * WTN - 1) / (WN * WTN), (e.M + 16 * WM * WTM - 1) / (16 * WM * WTM));
+  if (Z > 1) grid = dim3(meet_grid(grid.x * grid.y, Z));
   kern<<<grid, WM * WN * 64, smem, s>>>((const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT, e);
 }
 
 // Block shapes of the tiled kernels (rows x weight rows) and what one k-step costs on MI355X
-// with all 256 CUs busy (us, measured): alone on its CU, and - for the shapes small enough that
-// two blocks share a CU's LDS and registers - per k-step of such a pair.
+// with all 256 CUs busy (us, measured).
 //   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128   8: 192 x 320   9: 256 x 256
 //   4 waves: 4: 192 x 192   5: 192 x 128   6: 128 x 128   7: 96 x 128
 // What a whole launch loses most by is its last round: shapes 8 and 9 are there for the sizes at which
@@ -1149,35 +1292,37 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 //   1280 rows  down     18944 -> 3584      3 x 70 of 0, 3 x 84 of 8              187 -> 161
 //   3552 rows  O + down                    209 of 0, 247 of 8                    480 -> 436
 //   24576 rows O + down                    2048 of 1, 1536 of 9                  2965 -> 2717
-// Two waves per SIMD overlap one wave's LDS reads and barrier waits with the other's MFMAs, four
-// (two 8-wave blocks) do so better still.  The wider the block the fewer operand bytes per flop
-// cross L2 and LDS.  A grid that does not fill the 256 CUs in whole rounds wastes the
-// remainder, so narrow outputs (N = d_model) are also split along K into partial products that
-// a small second kernel sums.  Two blocks to a CU need the 128-register kernels, which only the
-// plain store epilogue of a K split fits.
+// Two waves per SIMD overlap one wave's LDS reads and barrier waits with the other's MFMAs.  The wider
+// the block the fewer operand bytes per flop cross L2 and LDS.  A grid that does not fill the 256 CUs in
+// whole rounds wastes the remainder, so narrow outputs (N = d_model) are also split along K over blocks
+// that meet.
 struct TilePick { int tile, ksplit; };
 constexpr int kNumTiles = 10;
 static const int kTileM[kNumTiles] = {12, 12, 12, 12, 12, 12, 8, 6, 12, 16};
 static const int kTileN[kNumTiles] = {24, 16, 12, 8, 12, 8, 8, 8, 20, 16};
-static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.41f, 0.78f, 0.80f};
-static const float kTileUsPair[kNumTiles] = {0.f, 0.f, 0.93f, 0.75f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.45f, 0.78f, 0.80f};
+
+// floats of the pieces that the blocks of K split ks exchange
+static size_t meet_floats(const TilePick& t, int MT, int total_nt) {
+  return (size_t)((MT + kTileM[t.tile] - 1) / kTileM[t.tile]) * ((total_nt + kTileN[t.tile] - 1) / kTileN[t.tile]) *
+         t.ksplit * kTileM[t.tile] * kTileN[t.tile] * 256;
+}
 
 // epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
-// cache stores of q k v, the residual stream's read and write; partial products are plain stores.
-static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit, int M, int N) {
-  const float epi_us = epi == EPI_QKV || epi == EPI_RESID ? 0.064f : 0.f;
+// cache stores of q k v, the residual stream's read and write, the exchange of a K split (whose blocks run
+// in one round).  Over 104 residual products (112 - 4000 rows, 12 pairs of widths from 512 to 18944) the
+// pick is within 13 % of the best of all shapes and splits, 2 % on average.
+static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit, size_t piece_floats) {
   TilePick best{1, 1};
   float best_t = 1e30f;
   for (int i = 0; i < kNumTiles; ++i) {
-    long gm = (MT + kTileM[i] - 1) / kTileM[i], gn = (total_nt + kTileN[i] - 1) / kTileN[i];
-    for (int ks = 1; ks <= max_ksplit; ++ks) {
-      const long blocks = gm * gn * ks, per_cu = (blocks + 255) / 256;
-      const float ksteps = (float)((KB + ks - 1) / ks);
-      const long pairs = (kTileUsPair[i] > 0.f && ks > 1) ? per_cu / 2 : 0;
-      const long singles = per_cu - 2 * pairs;
-      const float edge = 5.0f + (ks > 1 ? 0.02f : epi_us) * kTileM[i] * kTileN[i];
-      float t = ksteps * (pairs * kTileUsPair[i] + singles * kTileUsAlone[i]) + edge * (pairs + singles);
-      if (ks > 1) t += 2.5f + (float)M * N * (ks + 4) * 4.0f / 5.0e6f;  // finish kernel
+    const int gm = (MT + kTileM[i] - 1) / kTileM[i], gn = (total_nt + kTileN[i] - 1) / kTileN[i], tiles = gm * gn;
+    for (int ks = 1; ks <= max_ksplit && ks <= KB; ++ks) {
+      if (ks > 1 && (tiles > kMeetSlots || meet_floats(TilePick{i, ks}, MT, total_nt) > piece_floats)) break;
+      const int rounds = (tiles * ks + 255) / 256;
+      if (ks > 1 && rounds > 1) break;
+      const float epi_us = ks > 1 ? 0.07f : epi == EPI_QKV ? 0.064f : epi == EPI_RESID ? 0.008f : 0.f;
+      const float t = rounds * ((KB + ks - 1) / ks * kTileUsAlone[i] + 5.0f + epi_us * kTileM[i] * kTileN[i]);
       if (t < best_t) { best_t = t; best = TilePick{i, ks}; }
     }
   }
@@ -1186,36 +1331,56 @@ static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit,
 
 // WS: the matrix carries per-row scales (it came as e4m3 codes): a variant of its own, so that
 // the kernels of plain bf16 models are compiled exactly as they were tuned
-template <int EPI, bool WS>
+template <int EPI, bool WS, int Z>
 static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                                 const GemmEpi& e, hipStream_t s, int tile, int ksplit) {
+                                 const GemmEpi& e, hipStream_t s, int tile) {
   switch (tile) {
-    case 0: launch_tiled8_t<EPI, WS, 2, 4, 6, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 1: launch_tiled8_t<EPI, WS, 2, 4, 6, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 2: launch_tiled8_t<EPI, WS, 2, 4, 6, 3, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 3: launch_tiled8_t<EPI, WS, 2, 4, 6, 2, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 4: launch_tiled4_t<EPI, 6, 6, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 5: launch_tiled4_t<EPI, 6, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 6: launch_tiled4_t<EPI, 4, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 7: launch_tiled4_t<EPI, 3, 4, WS>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    case 8: launch_tiled8_t<EPI, WS, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
-    default: launch_tiled8_t<EPI, WS, 2, 4, 8, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s, ksplit); break;
+    case 0: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 1: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 2: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 3, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 3: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 2, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 4: launch_tiled4_t<EPI, WS, Z, 6, 6>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 5: launch_tiled4_t<EPI, WS, Z, 6, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 6: launch_tiled4_t<EPI, WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 7: launch_tiled4_t<EPI, WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 8: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    default: launch_tiled8_t<EPI, WS, Z, 2, 4, 8, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
   }
 }
 
-template <int EPI>
-static void launch_tiled_pick(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                              const GemmEpi& e, hipStream_t s, int tile, int ksplit) {
-  if (e.wscale) launch_tiled_pick_ws<EPI, true>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
-  else launch_tiled_pick_ws<EPI, false>(Ap, MT, Wp, total_nt, KB, e, s, tile, ksplit);
+template <int EPI, bool WS>
+static void launch_tiled_pick_z(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
+                                const GemmEpi& e, hipStream_t s, const TilePick& tp) {
+  if constexpr (EPI == EPI_RESID) {
+    switch (tp.ksplit) {
+      case 4: launch_tiled_pick_ws<EPI, WS, 4>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile); return;
+      case 3: launch_tiled_pick_ws<EPI, WS, 3>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile); return;
+      case 2: launch_tiled_pick_ws<EPI, WS, 2>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile); return;
+      default: break;
+    }
+  }
+  launch_tiled_pick_ws<EPI, WS, 1>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile);
+}
+
+// The row tiles that the shape is picked for: those of the padded row list, unless it is mostly padding
+// (272 rows in a list of 512, down projection of 4096: 192 x 256 x 4 65.8 us, 192 x 128 x 4 55.7).  Only tiles that hold
+// rows are computed either way.
+static int pick_rows(int M_src, int M) {
+  const int padded = (M_src + 15) / 16, rows = (M + 15) / 16;
+  return 3 * rows <= 2 * padded ? rows : padded;
 }
 
 // row tiles up to which a product goes to the weight-streaming kernels (gathered LM-head rows: 64 at most)
 static bool streams_weights(int epi, int MT) { return MT <= (epi == EPI_LOGITS ? 4 : 6); }
 
-bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, int max_ksplit, int shape[3]) {
+// K ranges that a residual product may be divided into, as far as the caller has room for it
+static int max_ksplit(int epi, const GemmEpi& e) {
+  return epi == EPI_RESID && e.partial && e.meet ? kMaxKSplit : 1;
+}
+
+bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, size_t piece_floats, int shape[3]) {
   if (streams_weights(epi, (M + 15) / 16)) return false;
-  const TilePick tp = pick_tile(epi, (M_src + 15) / 16, N / 16, K / 32, epi == EPI_RESID ? max_ksplit : 1, M, N);
+  const TilePick tp = pick_tile(epi, pick_rows(M_src, M), N / 16, K / 32, epi == EPI_RESID ? kMaxKSplit : 1, piece_floats);
   shape[0] = kTileM[tp.tile] * 16; shape[1] = kTileN[tp.tile] * 16; shape[2] = tp.ksplit;
   return true;
 }
@@ -1248,16 +1413,11 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
       default: launch_skinny_mt<EPI, 6>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
     }
   } else {
-    // the tiled kernel reads its activation rows in place (no gather) and walks every m-tile of
-    // the buffer; rows from e.M on are dropped in the epilogue
-    const int max_ks = (EPI == EPI_RESID && e.partial) ? e.max_ksplit : 1;
-    TilePick tp = pick_tile(EPI, MT_src, total_nt, KB, max_ks, e.M, N);
-    if (tp.ksplit > 1) {
-      launch_tiled_pick<EPI_PARTIAL>(Ap, MT_src, Wp, total_nt, KB, e, s, tp.tile, tp.ksplit);
-      launch_resid_finish(e, tp.ksplit, N, s);
-    } else {
-      launch_tiled_pick<EPI>(Ap, MT_src, Wp, total_nt, KB, e, s, tp.tile, 1);
-    }
+    // the tiled kernel reads its activation rows in place (no gather); only the tiles that hold rows
+    // below e.M are computed (the buffer is padded to 256 rows), and rows from e.M on are dropped
+    const TilePick tp = pick_tile(EPI, pick_rows(M_src, e.M), total_nt, KB, max_ksplit(EPI, e), e.partial_floats);
+    if (e.wscale) launch_tiled_pick_z<EPI, true>(Ap, MT_src, Wp, total_nt, KB, e, s, tp);
+    else launch_tiled_pick_z<EPI, false>(Ap, MT_src, Wp, total_nt, KB, e, s, tp);
   }
 }
 

@@ -90,6 +90,7 @@ __global__ __launch_bounds__(256) void step_prologue_bf16_kernel(
   if (threadIdx.x == 0)
     sumsq[r] = sumsq_to_fixed<62>(ss);
   for (int b = 1 + threadIdx.x; b < nbuf; b += 256) sumsq[(size_t)b * sumsq_stride + r] = 0ull;
+  for (int i = r * 256 + threadIdx.x; i < L.n_meet; i += gridDim.x * 256) L.meet[i] = make_int4(0, 0, 0, 0);
 }
 
 void launch_step_prologue_bf16(const StepLists& L, const bf16_t* emb, int d, const bf16_t* gain,

@@ -635,6 +635,38 @@ def test_partial_step_with_split_down_projection(dtype, hq, d, f, block, k):
     assert s["modes"][eco.PARTIAL] == 5 and s["rows_stat"] > 0
 
 
+@pytest.mark.parametrize("dtype,d,f,P,block,down", [
+    ("bf16", 4128, 4096, 520, 40, (192, 320, 4)),   # 52 tiles of 4: four of them over several XCDs
+    ("bf16", 4128, 6176, 1089, 80, (256, 256, 3)),  # 85 tiles of 3
+    ("fp8w", 4160, 4096, 520, 60, (192, 320, 4)),
+    ("bf16", 96, 4128, 150, 70, None),              # one column of tiles, few k-steps to a range
+])
+def test_blocks_that_meet_give_the_same_bits(dtype, d, f, P, block, down):
+    """K split over blocks, full and partial steps: the same logits whether the blocks wait for each
+    other, give up at once (the last one finishes everything) or take each other to be on different XCDs.
+    Their values are checked against the oracle by the tests above, which run the default."""
+    cfg = small_cfg(dtype, 4, 4, 64, d=d, f=f, vocab=512, scale=4.0)
+    if down:
+        assert block_shape(cfg, ec.EC_K_DOWN, P + 2 * block) == down
+    w = ec_inputs.make_weights(cfg, 101, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=2 * block, block=block, k_recent=2, tokens_per_step=1, tau=1e9)
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, ec_inputs.make_prompt(cfg.vocab, P, 6))
+    g.keep_logits(True)
+    want = None
+    few = [(p, a) for p in (0, 1, 2, 3, 5, 8) for a in (False, True)]   # (who gives up depends on the moment)
+    for polls, apart in [(20000, False), (20000, True)] + few + [(20000, False)]:
+        g.debug_meeting(polls, apart)
+        got = []
+        for mode in (ec.EC_FULL, ec.EC_PARTIAL, ec.EC_PARTIAL):
+            g.step_forced(mode, [], [])
+            got.append(g.debug_read(ec.EC_DBG_LOGITS, count=block))
+        if want is None:
+            want = got
+            assert all(np.isfinite(z).all() and z.std() > 0 for z in want)
+        assert all(np.array_equal(a, b) for a, b in zip(want, got)), (polls, apart)
+    g.close()
+
+
 @pytest.mark.parametrize("N,block,k,n,sliding", [
     (512, 128, 30, 30, 0),     # the most slots the waves count for themselves, the largest block
     (513, 100, 3, 32, 1),      # one more; sliding window
