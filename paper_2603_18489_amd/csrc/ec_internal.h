@@ -118,9 +118,9 @@ void launch_attention_f32(const float* q, const float* kc, const float* vc, int 
                           int Hkv, int hd, float* out, hipStream_t s);
 
 // bf16 path
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_PARTIAL = 4 };
 constexpr int kMaxKSplit = 4;
-constexpr int kMeetSlots = 256;  // groups of blocks per launch that can exchange pieces of a K split
+constexpr int kMeetSlots = 128;  // groups of blocks per launch that can exchange pieces of a K split
 // A row's sum of squares is accumulated by many blocks at once.  Atomics on one address
 // serialise, so each row has kSumSlots counters (a block adds to the one its index selects) and
 // the reader adds them up; integer addition keeps the total independent of the order.
@@ -154,7 +154,8 @@ struct GemmEpi {
   float4* vparts;                 // EPI_LOGITS, skinny kernel: [row][blocks] partial tuples of
                                   // the vocabulary reduction (k_vtuple.h), one per block
   float* h; int d;                // EPI_RESID: residual stream [M, d]
-  float* partial; size_t partial_floats;  // EPI_RESID, nullable: room for the pieces of a K split
+  float* partial; size_t partial_floats;  // EPI_RESID, nullable: room for the pieces of a K split (few rows:
+                                          // its partial products [4][M][d])
   MeetSlot* meet;                 // nullable: [kMeetSlots], zero, this launch's own (k_meet.h)
   int meet_limit, meet_apart;     // polls before a block stops waiting; blocks taken as on different XCDs
   const bf16_t* gain_next;        // gain of the norm that follows

@@ -142,8 +142,8 @@ __device__ __forceinline__ size_t vcache_index(int key, int c, int Tpad) {
 // addition is associative, so the total does not depend on the order).  Format 44.20: one unit
 // is 2^-20 (a contribution is rounded to it: absolute error below 5e-7).  A contribution
 // saturates at 2^CAP units, CAP chosen by the caller so that all contributions of a row cannot
-// wrap the 64-bit total: 52 where up to 2^10 blocks add to a row (4.3e9 each), 62 for the
-// prologue's single store.  Rows whose sum of squares exceeds about 4e12 therefore saturate (their
+// wrap the 64-bit total: 52 where up to 2^10 blocks add to a row (4.3e9 each), 58 for the few
+// adds of the few-row K split's finish, 62 for the prologue's single store.  Rows whose sum of squares exceeds about 4e12 therefore saturate (their
 // 1/rms comes out too large) instead of wrapping.
 constexpr double kSumsqUnit = 1048576.0;  // 2^20
 template <int CAP = 52>

@@ -58,6 +58,9 @@ __device__ __forceinline__ bf16x8 e4m3x8_as_bf16x8(uint32_t a, uint32_t b) {
   c.h[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 1.0f, true);
   return c.v;
 }
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return pack2_bf16(a, b); }
 // x * sigmoid(x) with the hardware exp2 and reciprocal (about 1 ulp each; the result is rounded
 // to bf16 anyway).  exp overflow gives rcp(inf) = 0, the right limit.
@@ -205,36 +208,6 @@ __device__ __forceinline__ void epi_qkv(const GemmEpi& e, int m, int vt, int q4,
   }
 }
 
-// Which tile and range of K a block works on where K is split over Z blocks, on a one-dimensional grid.  An XCD
-// gets a run of whole tiles, the Z blocks of a tile one after the other, so that they run at the same time
-// and meet in one L2.  If the XCDs' runs, up to a tile of different length, fit its 32 compute units, the
-// grid has room for the longest on each (meet_grid) and the blocks it has too many find no tile: false.
-// Otherwise the grid is Z blocks a tile, and what is left over on the XCDs (up to Z - 1 blocks each) makes up
-// the last tiles, whose blocks have to fence.
-template <int Z>
-__device__ __forceinline__ bool meet_place(int tiles, int& tile, int& z) {
-  const int n = gridDim.x, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  if (n != tiles * Z) {
-    tile = xcd * tiles / 8 + j / Z;
-    z = j % Z;
-    return tile < (xcd + 1) * tiles / 8;
-  }
-  const int few = n >> 3, more = n & 7;   // blocks of an XCD: few + 1 on the first `more` of them
-  const int q = (few + (xcd < more)) / Z, above = min(xcd, more), below = xcd - above;
-  int at = (above * ((few + 1) / Z) + below * (few / Z)) * Z + j;
-  if (j >= q * Z) {
-    const int whole = (more * ((few + 1) / Z) + (8 - more) * (few / Z)) * Z;
-    at = whole + above * ((few + 1) % Z) + below * (few % Z) + j - q * Z;
-  }
-  tile = at / Z;
-  z = at - tile * Z;
-  return true;
-}
-static int meet_grid(int tiles, int Z) {
-  const int longest = (tiles + 7) / 8 * Z;
-  return longest <= 32 ? 8 * longest : tiles * Z;
-}
-
 // ---------------------------------------------------------------------------------------------
 // skinny: grid = ceil(n-tiles / NTW) blocks of KS*64 threads
 // ---------------------------------------------------------------------------------------------
@@ -242,10 +215,7 @@ static int meet_grid(int tiles, int Z) {
 // 64 k per weight tile and k-step; a lane's 16 bytes are turned into two bf16 MFMA operands in
 // registers (exact), so a k-step is two MFMAs per (weight tile, m-tile) on two activation
 // fragments, KB counts 64-wide steps, and the per-row scales multiply the K-reduced sums.
-// Z > 1: K is also divided over Z blocks, which exchange the sums of each other's shares of
-// the (tile, m-tile) units and finish their own (k_meet.h).  A block then owns Z times the weight tiles
-// and pulls a Z-th of the activations.
-template <int EPI, int MT, int NTW, int KS, int U, bool W8 = false, int Z = 1>
+template <int EPI, int MT, int NTW, int KS, int U, bool W8 = false>
 __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* __restrict__ Ap,
                                                                    const u32x4* __restrict__ Wp,
                                                                    int total_nt, int KB,
@@ -256,15 +226,13 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // provably wave-uniform: MFMA ignores the EXEC mask, so it must never sit under a condition
   // the compiler could treat as divergent
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int bx = blockIdx.x, bz = 0;
-  if constexpr (Z > 1) {
-    if (!meet_place<Z>((total_nt + NTW - 1) / NTW, bx, bz)) return;
-  }
-  const int nt0 = bx * NTW;
+  const int nt0 = blockIdx.x * NTW;
+  // EPI_PARTIAL: blockIdx.y picks one of gridDim.y contiguous K ranges.  (The others are not charged the
+  // division and the load of the grid's size ahead of their first operand: about 0.4 us a launch.)
   int kr_lo = 0, kr_n = KB;
-  if constexpr (Z > 1) {
-    kr_lo = bz * KB / Z;
-    kr_n = (bz + 1) * KB / Z - kr_lo;
+  if constexpr (EPI == EPI_PARTIAL) {
+    kr_lo = (int)((blockIdx.y * KB) / gridDim.y);
+    kr_n = (int)(((blockIdx.y + 1) * KB) / gridDim.y) - kr_lo;
   }
   const int kb_lo = kr_lo + (wave * kr_n) / KS, kb_hi = kr_lo + ((wave + 1) * kr_n) / KS;
 
@@ -347,14 +315,12 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
   // still counts outstanding loads exactly.
   // Epilogue operands of the thread's first output unit are fetched here too: the residual
   // stream and gains (EPI_RESID) so that the epilogue does not start with a round trip to memory.
-  constexpr int NU = NTW * MT, UNITS = NU * 64;  // whole waves: the wave's 64 lanes share (tile, m-tile)
-  // Z > 1: the block of range z finishes units z NU / Z .. (z + 1) NU / Z - 1
-  const int u_lo = bz * NU / Z, u_hi = (bz + 1) * NU / Z;
+  constexpr int UNITS = NTW * MT * 64;  // whole waves: the wave's 64 lanes share (tile, m-tile)
   float4 pre_h = make_float4(0.f, 0.f, 0.f, 0.f);
   u32x2 pre_g = {0u, 0u};
   if constexpr (EPI == EPI_RESID) {
-    const int unit = u_lo + wave < u_hi ? u_lo + wave : u_lo;
-    const int l = lane, iu = unit / MT, j = unit - iu * MT;
+    const int o = threadIdx.x < UNITS ? threadIdx.x : 0;
+    const int l = o & 63, unit = o >> 6, iu = unit / MT, j = unit - iu * MT;
     const int m = j * 16 + (l & 15), vt = nt0 + iu;
     const int mm = m < e.M ? m : 0, n = (vt < total_nt ? vt : 0) * 16 + (l >> 4) * 4;
     pre_h = *(const float4*)(e.h + (size_t)mm * e.d + n);
@@ -489,72 +455,78 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
     }
     return;
   }
-  // the epilogue on the sums of one unit
-  auto finish = [&](int unit, f32x4 v, bool pre) {
-    const int iu = unit / MT, j = unit - iu * MT, q4 = lane >> 4;
-    const int m = j * 16 + (lane & 15), vt = nt0 + iu;
+  for (int o = threadIdx.x; o < UNITS; o += KS * 64) {
+    const int l = o & 63, unit = o >> 6, iu = unit / MT, j = unit - iu * MT;
+    const int m = j * 16 + (l & 15), q4 = l >> 4;
     const bool mvalid = m < e.M;
+    const int vt = nt0 + iu;
+    f32x4 v = ksum((iu * MT + j) * 64 + l, iu, q4);
     if constexpr (EPI == EPI_RESID) {
       float part = 0.f;
       if (mvalid && vt < total_nt)
-        part = pre ? epi_resid_pre(e, m, vt, q4, v, pre_h, pre_g) : epi_resid(e, m, vt, q4, v);
+        part = o < KS * 64 ? epi_resid_pre(e, m, vt, q4, v, pre_h, pre_g) : epi_resid(e, m, vt, q4, v);
       epi_add_sumsq(e, m, mvalid, part);
     } else if (mvalid && vt < total_nt) {
-      if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
+      if constexpr (EPI == EPI_PARTIAL)
+        *(float4*)(e.partial + ((size_t)blockIdx.y * e.M + m) * e.d + vt * 16 + q4 * 4) =
+            make_float4(v[0], v[1], v[2], v[3]);
+      else if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, v, rstd_s[m]);
       else epi_qkv(e, m, vt, q4, v, rstd_s[m]);
-    }
-  };
-  if constexpr (Z == 1) {
-    for (int unit = wave; unit < NU; unit += KS) finish(unit, ksum(unit * 64 + lane, unit / MT, lane >> 4), unit == wave);
-  } else {
-    const int z = bz;
-    f32x4* mine = (f32x4*)e.partial + ((size_t)bx * Z + z) * UNITS + lane;
-    const f32x4* all = (const f32x4*)e.partial + (size_t)bx * Z * UNITS + lane;
-    for (int unit = wave; unit < NU; unit += KS)
-      if (unit < u_lo || unit >= u_hi) mine[unit * 64] = ksum(unit * 64 + lane, unit / MT, lane >> 4);
-    unsigned shares = meet_blocks(e.meet + bx, Z, z, e.meet_limit, e.meet_apart, [&] {
-      for (int unit = u_lo + wave; unit < u_hi; unit += KS) mine[unit * 64] = ksum(unit * 64 + lane, unit / MT, lane >> 4);
-    });
-    constexpr int MU = ((NU + Z - 1) / Z + KS - 1) / KS;  // units of a share to a wave
-    while (shares) {
-      const int sh = __builtin_ctz(shares), lo = sh * NU / Z + wave, hi = (sh + 1) * NU / Z;
-      shares &= shares - 1;
-      f32x4 p[MU][Z];   // every piece is requested before the first is used
-#pragma unroll
-      for (int i = 0; i < MU; ++i)
-#pragma unroll
-        for (int y = 0; y < Z; ++y)
-          if (y != z) p[i][y] = all[((size_t)y * NU + (lo + i * KS < hi ? lo + i * KS : hi - 1)) * 64];
-#pragma unroll
-      for (int i = 0; i < MU; ++i) {
-        const int unit = lo + i * KS;
-        if (unit >= hi) break;
-        const f32x4 own = ksum(unit * 64 + lane, unit / MT, lane >> 4);
-        f32x4 v = z == 0 ? own : p[i][0];
-#pragma unroll
-        for (int y = 1; y < Z; ++y) v += y == z ? own : p[i][y];
-        finish(unit, v, i == 0 && sh == z);
-      }
     }
   }
 }
 
-template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false, int Z = 1>
+constexpr int kSkinnySplit = 4;   // K ranges of a split few-row residual GEMM
+
+// Second half of such a GEMM: h += sum over the ranges (fixed order), then what EPI_RESID does: next
+// operand bf16(h * gain) and the row's sum of squares.  Every load is requested before the first is used.
+// (Blocks that meet as those of the tiled kernels do, k_meet.h, save the launch but end later one by one: the product and
+// this kernel 23.6 us, with a meeting 23.1 at 34 rows of 12288 -> 4096, and the next kernel starts slower: whole
+// partial steps 0.2 % faster to 1 % slower.)
+// grid (ceil(d / 1024), M), 256 threads, 4 columns per thread.
+__global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
+  __shared__ float red[4];
+  const int m = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;
+  float part = 0.f;
+  if (n < e.d) {
+    f32x4 p[kSkinnySplit];
+#pragma unroll
+    for (int z = 0; z < kSkinnySplit; ++z)
+      p[z] = *(const f32x4*)(e.partial + ((size_t)z * e.M + m) * e.d + n);
+    const float4 h = *(const float4*)(e.h + (size_t)m * e.d + n);
+    const u32x2 g4 = *(const u32x2*)(e.gain_next + n);
+    f32x4 v = p[0];
+#pragma unroll
+    for (int z = 1; z < kSkinnySplit; ++z) v += p[z];
+    part = epi_resid_pre(e, m, n >> 4, (n >> 2) & 3, v, h, g4);
+  }
+  part = block_sum<4>(part, red);
+  if (threadIdx.x == 0) {
+    unsigned long long fx = sumsq_to_fixed<58>(part);
+    if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)(blockIdx.x & (kSumSlots - 1)) * e.sum_stride + m), fx);
+  }
+}
+
+static void launch_resid_finish(const GemmEpi& e, int N, hipStream_t s) {
+  resid_finish_kernel<<<dim3((N + 1023) / 1024, e.M), 256, 0, s>>>(e);
+}
+
+template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false>
 static void launch_skinny_t(const bf16_t* Ap, int MT_src, const void* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s) {
-  const int groups = (total_nt + NTW - 1) / NTW, grid = Z > 1 ? meet_grid(groups, Z) : groups;
+                            const GemmEpi& e, hipStream_t s, int ksplit = 1) {
+  dim3 grid((total_nt + NTW - 1) / NTW, ksplit);
   size_t smem = (size_t)KS * NTW * MT * 64 * sizeof(float4) + MT * 16 * sizeof(float);
   if (EPI == EPI_LOGITS) smem += (size_t)NTW * MT * 16 * sizeof(float4);  // per-tile row tuples
   if (W8) smem += NTW * 16 * sizeof(float);                               // weight scales
   if (smem > 48 * 1024) {
     static bool once = false;
     if (!once) {
-      (void)hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8, Z>,
+      (void)hipFuncSetAttribute((const void*)gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
       once = true;
     }
   }
-  gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8, Z><<<grid, KS * 64, smem, s>>>(
+  gemm_bf16_skinny_kernel<EPI, MT, NTW, KS, U, W8><<<grid, KS * 64, smem, s>>>(
       (const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT_src, e);
 }
 
@@ -575,23 +547,20 @@ int skinny_tiles_per_block(int epi, int total_nt) {
 
 // A residual GEMM has only d_model / 16 weight tiles, one to a block, and every block pulls the
 // whole [rows, K] operand beside its 16 rows of weights: 1.2 MB beside 0.4 at 48 rows of 12288.  Four
-// neighbouring tiles and a quarter of K to a block pull a quarter of that; the meeting of the four
-// blocks costs about 2 us.  us on MI355X with weights from memory, whole K -> split, d 4096:
-//   row tiles   K 4096         K 8192         K 12288        K 18944        e4m3: K 4096, 12288
-//       1     8.7 -> 10.5   14.9 -> 16.6   19.9 -> 20.6   28.9 -> 28.1     6.9 ->  8.1  14.1 -> 13.1
-//       2    10.5 -> 11.3   17.5 -> 17.6   25.0 -> 21.9   36.9 -> 29.9     8.5 ->  8.9  18.9 -> 14.4
-//       3    11.5 -> 11.7   19.2 -> 17.9   27.8 -> 22.6   41.4 -> 31.0     9.5 ->  9.9  21.8 -> 15.7
-//       4    13.6 -> 12.5   23.2 -> 19.1   33.8 -> 24.2   51.6 -> 34.2    11.4 -> 10.6  26.9 -> 17.8
-//       6    16.3 -> 14.8   28.5 -> 21.5   42.3 -> 27.7   66.0 -> 38.9    14.7 -> 13.1  36.1 -> 22.4
-// so the line lies at MT * K = 16000.  (Two tiles and half of K lie in between; the wider products gain
-// nothing from a split: q k v 20.9 -> 21.3, gate/up 33.8 -> 38.9 at 3 row tiles.)  It holds at every width, since a
-// block's bytes do not depend on it: d 1024, 3 row tiles, K 12288 24.6 -> 17.4.
-constexpr int kSkinnySplit = 4;
-static int max_ksplit(int epi, const GemmEpi& e);
-static bool skinny_splits(int MT, int total_nt, int K, const GemmEpi& e) {
-  return max_ksplit(EPI_RESID, e) >= kSkinnySplit && (total_nt + kSkinnySplit - 1) / kSkinnySplit <= kMeetSlots &&
-         (size_t)(total_nt + kSkinnySplit - 1) / kSkinnySplit * kSkinnySplit * kSkinnySplit * MT * 256 <= e.partial_floats &&
-         (long)MT * K >= 16000;
+// neighbouring tiles and a quarter of K to a block pull a quarter of that; the partial products
+// are summed by resid_finish_kernel (4.8 us and the gap before it).  us on MI355X, whole K -> split
+// and finish, d 4096:
+//   3 row tiles  K 12288  30.5 -> 21.3 + 4.8   (e4m3 23.5 -> 15.4 + 4.0)   K 4096  11.2 ->  8.2 + 4.8
+//   6 row tiles  K 12288  44.4 -> 27.0 + 5.1                               K 4096  16.6 -> 11.0 + 5.1
+// which is a gain of about MT * K * 2.4e-4 - 5.5 us.  Two tiles and half of K: 23 and 33 at K 12288.
+// The line holds at every width, since a block's bytes do not depend on it and the few blocks of a narrow
+// matrix leave as much of the chip idle split or not.  us of a down projection with its finish, by
+// events, just above the line (MT K 23808 - 24576, 2 to 6 row tiles) and at 3 row tiles of 12288:
+//   d  128   17.1 -> 14.9, 22.7 -> 18.5     d 2048   20.4 -> 18.3, 28.0 -> 23.5
+//   d  512   18.7 -> 15.5, 26.1 -> 19.7     d 4096   23.8 -> 21.1, 32.0 -> 26.5 (6 x 3968: 20.1 -> 20.3)
+//   d 1024   19.5 -> 16.1, 26.7 -> 20.3     d 8192   38.7 -> 32.8, 56.8 -> 44.1
+static bool skinny_splits(int MT, int K, const GemmEpi& e) {
+  return e.partial && (size_t)kSkinnySplit * e.M * e.d <= e.partial_floats && (long)MT * K >= 23000;
 }
 
 // e4m3 weights: KB counts 64-wide k-steps; fewer steps per register set, because a step holds
@@ -602,9 +571,12 @@ static void launch_skinny_mt_w8(const bf16_t* Ap, int MT_src, const void* Wq, in
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
-    if (skinny_splits(MT, total_nt, KB * 64, e)) {
-      launch_skinny_t<EPI, MT, kSkinnySplit, 4, 1, true, kSkinnySplit>(Ap, MT_src, Wq, total_nt, KB, e, s);
-      return;
+    if constexpr (MT > 1) {
+      if (skinny_splits(MT, KB * 64, e)) {
+        launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s, kSkinnySplit);
+        launch_resid_finish(e, total_nt * 16, s);
+        return;
+      }
     }
     launch_skinny_t<EPI, MT, 1, 8, (MT > 3 ? 1 : 2), true>(Ap, MT_src, Wq, total_nt, KB, e, s);
   } else {
@@ -624,9 +596,18 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
   if constexpr (EPI == EPI_LOGITS) {
     launch_skinny_t<EPI, MT, kLmTiles, 4, (MT > 2 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else if constexpr (EPI == EPI_RESID) {
-    if (skinny_splits(MT, total_nt, KB * 32, e)) {
-      launch_skinny_t<EPI, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 2), false, kSkinnySplit>(Ap, MT_src, Wp, total_nt, KB, e, s);
-      return;
+    if constexpr (MT > 1) {
+      if (skinny_splits(MT, KB * 32, e)) {
+        // three k-steps to a register set where the two sets divide a wave's range: more in flight and no
+        // step loaded twice (3 row tiles, with a finish: K 12288, 24 steps, 22.6 -> 22.1 us; 16 and 37 steps lose, 17.9 -> 18.4
+        // and 31.0 -> 31.8)
+        if (MT <= 4 && KB % (6 * 4 * kSkinnySplit) == 0)
+          launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 3)>(Ap, MT_src, Wp, total_nt, KB, e, s, kSkinnySplit);
+        else
+          launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s, kSkinnySplit);
+        launch_resid_finish(e, total_nt * 16, s);
+        return;
+      }
     }
     launch_skinny_t<EPI, MT, 1, 8, 2>(Ap, MT_src, Wp, total_nt, KB, e, s);
   } else {
@@ -642,11 +623,11 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// QKV epilogue of the tiled kernels.  The rotation factors come from a table in global memory;
+// QKV epilogue of the 4-wave tiled kernels.  The rotation factors come from a table in global memory;
 // a load issued between two stores cannot be moved up by the compiler (the stores might alias
 // it), so one m-tile's factors are fetched while the previous m-tile is rotated and stored:
-// one exposed load latency per wave instead of one per accumulator tile.  (Needs registers the
-// 8-wave kernels do not have; they rotate tile by tile.)
+// one exposed load latency per wave instead of one per accumulator tile.  (The 8-wave kernels have no
+// registers for that: tiled_qkv.)
 // ---------------------------------------------------------------------------------------------
 template <int WTM, int WTN>
 __device__ __forceinline__ void tiled_epilogue_qkv(const GemmEpi& e, f32x4 (&acc)[WTN][WTM],
@@ -743,22 +724,24 @@ __device__ __forceinline__ void tiled_epilogue_qkv(const GemmEpi& e, f32x4 (&acc
 #undef EC_QKV_STORE
 }
 
-template <int EPI, int WTM, int WTN, bool PIPE = true>
-__device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WTN][WTM],
-                                               int mt_base, int nt_base, int total_nt, int lane) {
-  if constexpr (EPI == EPI_QKV && PIPE) {
+// rstd_s: 1/rms of the rows from row tile mt_base on, in LDS (null: from the counters, by every lane)
+template <int EPI, int WTM, int WTN>
+__device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt_base,
+                                               int nt_base, int total_nt, int lane, const float* rstd_s) {
+  if constexpr (EPI == EPI_QKV) {
     tiled_epilogue_qkv<WTM, WTN>(e, acc, mt_base, nt_base, total_nt, lane);
     return;
   }
   const int q4 = lane >> 4;
   // every row's 1/rms first: these loads must not be strung out between the stores below
   float rsj[WTM];
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS || EPI == EPI_QKV) {
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) {
 #pragma unroll
     for (int j = 0; j < WTM; ++j) {
       const int m = (mt_base + j) * 16 + (lane & 15);
       const int mm = m < e.M ? m : 0;
-      rsj[j] = rstd_of(e, (EPI == EPI_LOGITS && e.row_sel) ? e.row_sel[mm] : mm);
+      rsj[j] = rstd_s ? rstd_s[j * 16 + (lane & 15)]
+                      : rstd_of(e, (EPI == EPI_LOGITS && e.row_sel) ? e.row_sel[mm] : mm);
     }
   }
 #pragma unroll
@@ -780,13 +763,108 @@ __device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WT
 #pragma unroll
         for (int i = 0; i < WTN; ++i) {
           int vt = nt_base + i;
-          if constexpr (EPI == EPI_SWIGLU && WTN % 2 == 0) {
+          if constexpr (WTN % 2 == 0) {
             if (i & 1) continue;
             if (vt + 1 < total_nt) epi_swiglu2(e, m, vt, q4, acc[i][j], acc[i + 1][j], rs);
             else if (vt < total_nt) epi_swiglu(e, m, vt, q4, acc[i][j], rs);
           } else if (vt < total_nt) {
-            if constexpr (EPI == EPI_SWIGLU) epi_swiglu(e, m, vt, q4, acc[i][j], rs);
-            else epi_qkv(e, m, vt, q4, acc[i][j], rs);
+            epi_swiglu(e, m, vt, q4, acc[i][j], rs);
+          }
+        }
+      }
+    }
+  }
+}
+
+// Where a block keeps what its epilogue needs of its rows (tiled, 8 waves): behind the operand ring, 1/rms of
+// each row and, for q k v, the row's entry of the row list.  q k v also stages its rows' rotation factors in
+// the ring's place once the products are done.
+template <int EPI, int ROWS> constexpr int tiled_row_bytes() {
+  return EPI == EPI_RESID ? 0 : ROWS * (EPI == EPI_QKV ? 20 : 4);
+}
+
+// q k v epilogue of the 8-wave kernels.  The rotation factors of the block's rows (hd / 2 pairs each, the
+// same for every head) come to LDS in one go instead of 32 bytes a lane and fragment from memory, each time
+// waited for.  A row's 16-byte chunks are stored at their number XOR the row's low bits: 16 rows read at the
+// same column hit all banks.  Two row tiles are rotated together: after a swap of lane rows a lane
+// holds 8 consecutive columns of one row, stored as 16 bytes.
+//   us per launch, 4096 -> 3 x 4096, before -> after:  768 rows 192 x 192    79.3 -> 74.8
+//   4096 rows 192 x 384    405 -> 360                 4096 rows 256 x 256   386 -> 328
+template <int WM, int WN, int WTM, int WTN>
+__device__ __forceinline__ void tiled_qkv(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt0, int nt0,
+                                          int total_nt, int wave, int lane, u32x4* lds,
+                                          const int4* row_s, const float* rstd_s) {
+  static_assert(WTM % 2 == 0, "row tiles are taken in pairs");
+  constexpr int ROWS = WM * WTM * 16, NW = WM * WN;
+  const int wm = wave / WN, wn = wave % WN, q4 = lane >> 4, r16 = lane & 15;
+  const int hd = e.hd, tph = hd >> 4, half = hd >> 1, chunks = hd >> 2;  // 16-byte chunks of a row's factors
+  const int nqt = e.Hq * tph, nkt = e.Hkv * tph;
+  __syncthreads();   // (the ring is no longer read, and its last loads have landed)
+  for (int c = wave * 64; c < ROWS * chunks; c += NW * 64) {
+    const int row = (c + lane) / chunks, at = (c + lane) % chunks;
+    const int pos = max(row_s[row].x, 0);
+    const char* src = (const char*)(e.cs + (size_t)pos * half) + ((at ^ (row & 15)) * 16);
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)src,
+                                     (void __attribute__((address_space(3)))*)(lds + c), 16, 0, 0);
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+  const bool hi = q4 >= 2;
+  const unsigned sin_sign = hi ? 0u : 0x80000000u;  // first half: x cos - y sin; second: x cos + y sin
+#pragma unroll
+  for (int j = 0; j < WTM; j += 2) {
+    const int row0 = (wm * WTM + j) * 16 + r16, row1 = row0 + 16;
+    const float rs[2] = {rstd_s[row0], rstd_s[row1]};
+    // the row whose 8 columns the lane stores, and the rows whose values it holds
+    const int srow = (q4 & 1) ? row1 : row0;
+    const int4 ri = row_s[srow];   // position (-1: padding), -, cache offset, keys per slab
+    const int m = mt0 * 16 + srow, pos = max(ri.x, 0);
+    const bool valid = m < e.M && ri.x >= 0;
+    bf16_t* const q_row = e.q_out + (size_t)m * (e.Hq * hd) + (hi ? half : 0);
+    bf16_t* const k_row = e.kc + ri.z;
+    // V stays as the products left it: four columns of the lane's own two rows
+    const int4 va = row_s[row0], vb = row_s[row1];
+    const bool va_ok = mt0 * 16 + row0 < e.M && va.x >= 0, vb_ok = mt0 * 16 + row1 < e.M && vb.x >= 0;
+#pragma unroll
+    for (int i = 0; i < WTN; ++i) {
+      const int vt = nt0 + wn * WTN + i;
+      if (vt < nqt + nkt) {
+        const bool is_q = vt < nqt;
+        const int t = is_q ? vt : vt - nqt, head = t / tph, w = t - head * tph;
+        unsigned pk[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 v = acc[i][j + u];
+          const u32x4* cs = lds + (u ? row1 : row0) * chunks;
+          union { u32x4 q[2]; float f[8]; } c;   // (cos, sin) x 4 columns
+          c.q[0] = cs[(w * 4 + (q4 & 1) * 2) ^ r16];
+          c.q[1] = cs[(w * 4 + (q4 & 1) * 2 + 1) ^ r16];
+          float out[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float sn = __uint_as_float(__float_as_uint(c.f[2 * r + 1]) ^ sin_sign);
+            out[r] = (v[r] * c.f[2 * r] + other_half(v[r]) * sn) * rs[u];
+          }
+          pk[u][0] = pack2(out[0], out[1]);
+          pk[u][1] = pack2(out[2], out[3]);
+        }
+        // lanes with even q4 end with both halves of row tile j's 8 columns, the others with j + 1's
+        const auto s0 = __builtin_amdgcn_permlane16_swap(pk[0][0], pk[1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane16_swap(pk[0][1], pk[1][1], false, false);
+        const u32x4 o = {s0[0], s1[0], s0[1], s1[1]};
+        if (valid) {
+          if (is_q) *(u32x4*)(q_row + head * hd + w * 8) = o;
+          else *(u32x4*)(k_row + (size_t)head * ri.w * hd + kcache_index(pos, w * 8 + (hi ? half : 0), hd)) = o;
+        }
+      } else if (vt < total_nt) {
+        const int t = vt - nqt - nkt, head = t / tph, c0 = (t - head * tph) * 16 + q4 * 4;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int4 rv = u ? vb : va;
+          if (u ? vb_ok : va_ok) {
+            bf16_t* dst = e.vc + rv.z + (size_t)head * rv.w * hd + vcache_index(rv.x, c0, rv.w);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[r * 8] = f32_to_bf16(acc[i][j + u][r] * rs[u]);
           }
         }
       }
@@ -978,6 +1056,36 @@ __device__ __forceinline__ void tiled_block_xy(int& bx, int& by) {
   }
 }
 
+// Which tile and range of K a block works on where K is split over Z blocks, on a one-dimensional grid.  An XCD
+// gets a run of whole tiles, the Z blocks of a tile one after the other, so that they run at the same time
+// and meet in one L2.  If the XCDs' runs, up to a tile of different length, fit its 32 compute units, the
+// grid has room for the longest on each (meet_grid) and the blocks it has too many find no tile: false.
+// Otherwise the grid is Z blocks a tile, and what is left over on the XCDs (up to Z - 1 blocks each) makes up
+// the last tiles, whose blocks have to fence.
+template <int Z>
+__device__ __forceinline__ bool meet_place(int tiles, int& tile, int& z) {
+  const int n = gridDim.x, xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  if (n != tiles * Z) {
+    tile = xcd * tiles / 8 + j / Z;
+    z = j % Z;
+    return tile < (xcd + 1) * tiles / 8;
+  }
+  const int few = n >> 3, more = n & 7;   // blocks of an XCD: few + 1 on the first `more` of them
+  const int q = (few + (xcd < more)) / Z, above = min(xcd, more), below = xcd - above;
+  int at = (above * ((few + 1) / Z) + below * (few / Z)) * Z + j;
+  if (j >= q * Z) {
+    const int whole = (more * ((few + 1) / Z) + (8 - more) * (few / Z)) * Z;
+    at = whole + above * ((few + 1) % Z) + below * (few % Z) + j - q * Z;
+  }
+  tile = at / Z;
+  z = at - tile * Z;
+  return true;
+}
+static int meet_grid(int tiles, int Z) {
+  const int longest = (tiles + 7) / 8 * Z;
+  return longest <= 32 ? 8 * longest : tiles * Z;
+}
+
 // ---------------------------------------------------------------------------------------------
 // tiled, 4 waves (2x2): wave tile = WTM x WTN fragments, K step 32.  Operands are double-buffered
 // in LDS; global loads run through four register sets, four k-steps ahead.  This variant is the
@@ -1091,7 +1199,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __re
   else if constexpr (EPI == EPI_RESID)
     tiled_resid<2, 2, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
   else
-    tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane);
+    tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane, nullptr);
 }
 #undef EC_TILED_GLOAD
 #undef EC_TILED_LSTORE
@@ -1113,10 +1221,6 @@ static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // no staging registers; one barrier per k-step.
 // grid = (ceil(n-tiles / (WN*WTN)), ceil(m-tiles / (WM*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // ROLL: the fragments of k-step k+1 are read from LDS while the MFMAs of k-step k run, a few after
 // each row of them: a weight fragment goes back to the registers its last MFMA has just freed, the
 // activation fragments and the last weight fragment have a second set.  Reads and MFMAs of a
@@ -1127,6 +1231,13 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // us per launch on MI355X at 768 rows, d 4096, F 12288:
 //   gate/up  192 x 384        141 -> 127     q k v  192 x 192            89 -> 84
 //   O, down  192 x 256 x 4 K   55 -> 52 (mean of the two; the read-ahead of whole k-steps before)
+// bytes of LDS: the operand ring or, if larger, the rotation factors of the rows (hd 128) in its place, and the rows
+template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE>
+constexpr int tiled8_lds() {
+  constexpr int ring = NSTAGE * (WM * WTM + WN * WTN) * 1024, factors = EPI == EPI_QKV ? WM * WTM * 16 * 512 : 0;
+  return (ring > factors ? ring : factors) + tiled_row_bytes<EPI, WM * WTM * 16>();
+}
+
 template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool WS, int Z>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_tiled8_kernel(
@@ -1192,6 +1303,10 @@ void gemm_bf16_tiled8_kernel(
 #pragma unroll
     for (int j = 0; j < WTM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
+  constexpr int ROWS = BMT * 16;
+  static_assert(ROWS % 64 == 0, "whole waves fetch the rows' sums");
+  int4* row_s = (int4*)((char*)lds + tiled8_lds<EPI, WM, WN, WTM, WTN, NSTAGE>() - tiled_row_bytes<EPI, ROWS>());
+  float* rstd_s = (float*)(row_s + (EPI == EPI_QKV ? ROWS : 0));
   int slot_r = 0;
   {
     // All NSTAGE slots are kept in flight.  Step k: this wave has finished reading slot k (its
@@ -1223,8 +1338,32 @@ void gemm_bf16_tiled8_kernel(
     }                                                                                        \
     EC_T8_FILLED                                                                             \
   }
+    // The rows' sums of squares are requested ahead of the first operands, by one lane a row, and turned
+    // into 1/rms while those are on their way, instead of in the epilogue by every lane for each of its
+    // row tiles (eight loads and a division in 64 bits): gate/up, 768 rows 126.2 -> 123.4 us, 4096 rows
+    // in 256 x 256 blocks 666 -> 631.
+    constexpr bool HAS_ROWS = EPI != EPI_RESID;
+    unsigned long long ssq[kSumSlots];
+    int4 ri = make_int4(0, 0, 0, 0);
+    const int my_row = wave * 64 + lane;
+    if (HAS_ROWS && wave < ROWS / 64) {
+      const int m = min(mt0 * 16 + my_row, e.M - 1);
+      const int src_row = (EPI == EPI_LOGITS && e.row_sel) ? e.row_sel[m] : m;
+#pragma unroll
+      for (int sl = 0; sl < kSumSlots; ++sl) ssq[sl] = e.sumsq_in[(size_t)sl * e.sum_stride + src_row];
+      if constexpr (EPI == EPI_QKV) ri = e.rowinfo[m];
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int sgl = 0; sgl < NSTAGE; ++sgl) { EC_T8_ISSUE(0, LF) EC_T8_FILLED }
+    __builtin_amdgcn_sched_barrier(0);
+    if (HAS_ROWS && wave < ROWS / 64) {
+      unsigned long long fx = 0;
+#pragma unroll
+      for (int sl = 0; sl < kSumSlots; ++sl) fx += ssq[sl];
+      rstd_s[my_row] = rstd_from_sum(e, fx);
+      if constexpr (EPI == EPI_QKV) row_s[my_row] = ri;
+    }
     EC_T8_WAIT(NSTAGE - 1)
     block_barrier_nofence();
 #pragma unroll
@@ -1254,20 +1393,20 @@ void gemm_bf16_tiled8_kernel(
   wait_vmcnt<0>();  // drain the clamped tail loads before the LDS goes away
 
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
-  // (the read-ahead QKV epilogue needs registers that only the smaller wave tiles leave free)
   if constexpr (Z > 1)
     tiled_meet_resid<WM, WN, WTM, WTN, Z>(e, acc, mt0, nt0, total_nt, wave, lane, tile, z, (float*)lds);
   else if constexpr (EPI == EPI_RESID)
     tiled_resid<WM, WN, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
+  else if constexpr (EPI == EPI_QKV)
+    tiled_qkv<WM, WN, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, lds, row_s, rstd_s);
   else
-    tiled_epilogue<EPI, WTM, WTN, (WTM * WTN <= 18)>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane);
+    tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane, rstd_s + wm * WTM * 16);
 }
 
 template <int EPI, bool WS, int Z, int WM, int WN, int WTM, int WTN, int NSTAGE>
 static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
                             const GemmEpi& e, hipStream_t s) {
-  constexpr int NF = WM * WTM + WN * WTN;
-  const size_t smem = (size_t)NSTAGE * NF * 1024;
+  const size_t smem = tiled8_lds<EPI, WM, WN, WTM, WTN, NSTAGE>();
   auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS, Z>;
   static bool attr_set = false;
   if (!attr_set && smem > 48 * 1024) {

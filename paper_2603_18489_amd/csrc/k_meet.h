@@ -1,5 +1,5 @@
 // Blocks that compute the same output tile over different ranges of K meet here, exchange pieces
-// through memory and each finish a share of the tile.
+// through memory and each finish a share of the tile (the many-row residual GEMMs).
 //
 // The pieces are small and short-lived, so what the exchange costs is what keeping them coherent
 // costs.  An agent-scope release writes back an XCD's whole L2 and the acquire invalidates it (5 us a
