@@ -223,3 +223,7 @@ def test_block_shape_query(lib):
     assert q(C.byref(mc), ec.EC_K_QKV, 96, 96) == ec.EC_ERR_ARG      # weight-streaming kernels
     f32, _, _ = _cfgs("tiny_f32")
     assert q(C.byref(f32), ec.EC_K_QKV, 768, 768) == ec.EC_ERR_ARG
+
+
+def test_debug_meeting_arguments(lib):
+    assert lib.ec_debug_meeting(None, 0, 0) == ec.EC_ERR_ARG

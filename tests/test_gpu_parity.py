@@ -635,11 +635,44 @@ def test_partial_step_with_split_down_projection(dtype, hq, d, f, block, k):
     assert s["modes"][eco.PARTIAL] == 5 and s["rows_stat"] > 0
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,hd,d,T,shape", [
+    ("bf16", 32, 32, 64, 96, 523, (192, 128, 1)),     # head_dim 64: 16 chunks of factors to a row
+    ("bf16", 48, 16, 64, 96, 1700, (192, 256, 1)),
+    ("fp8w", 32, 32, 64, 128, 771, (192, 192, 1)),    # three tiles a wave: they straddle heads and q | k | v
+    ("bf16", 16, 16, 128, 96, 771, (192, 192, 1)),
+    ("bf16", 40, 8, 128, 96, 1030, (192, 256, 1)),    # grouped queries, the last row block 70 rows
+    ("bf16", 32, 32, 128, 96, 1300, (192, 384, 1)),
+])
+def test_rotation_and_cache_stores_of_wide_blocks(dtype, hq, hkv, hd, d, T, shape):
+    """The q / k / v epilogue that stages its rows' rotation factors in LDS, at every block shape and both
+    head dimensions (192 x 320 and 256 x 256: above)."""
+    cfg = small_cfg(dtype, hq, hkv, hd, d=d, f=256, vocab=512, layers=1, scale=4.0)
+    assert block_shape(cfg, ec.EC_K_QKV, T) == shape
+    w = ec_inputs.make_weights(cfg, 107, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=11, block=4, k_recent=2, tokens_per_step=1, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, T - 11, 6), TOL[dtype], max_steps=2)
+    print(s)
+    assert s["rows_stat"] > 0
+
+
+@pytest.mark.parametrize("block", [30, 44])
+def test_split_down_projection_three_steps_ahead(block):
+    """Few-row down projection (split from 3 row tiles on) whose K ranges are whole pairs of sets of three
+    k-steps: 9216 = 3 x 3072."""
+    cfg = small_cfg("bf16", 4, 2, 64, d=288, f=9216, vocab=512, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 103, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=2 * block, block=block, k_recent=4, tokens_per_step=4, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 30, 6), TOL["bf16"], max_steps=6)
+    print(s)
+    assert s["modes"][eco.PARTIAL] == 5 and s["rows_stat"] > 0
+
+
 @pytest.mark.parametrize("dtype,d,f,P,block,down", [
     ("bf16", 4128, 4096, 520, 40, (192, 320, 4)),   # 52 tiles of 4: four of them over several XCDs
     ("bf16", 4128, 6176, 1089, 80, (256, 256, 3)),  # 85 tiles of 3
     ("fp8w", 4160, 4096, 520, 60, (192, 320, 4)),
     ("bf16", 96, 4128, 150, 70, None),              # one column of tiles, few k-steps to a range
+    ("bf16", 1056, 1024, 2060, 20, (192, 128, 2)),  # two ranges; a row block with few rows
 ])
 def test_blocks_that_meet_give_the_same_bits(dtype, d, f, P, block, down):
     """K split over blocks, full and partial steps: the same logits whether the blocks wait for each
