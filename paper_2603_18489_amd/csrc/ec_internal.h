@@ -125,6 +125,14 @@ constexpr int kMeetSlots = 128;  // groups of blocks per launch that can exchang
 // serialise, so each row has kSumSlots counters (a block adds to the one its index selects) and
 // the reader adds them up; integer addition keeps the total independent of the order.
 constexpr int kSumSlots = 8;
+// The largest contribution (a power of two) with which no counter of a row can wrap, where `blocks` blocks
+// whose indexes go through the counters in turn add to the row, each of them `adds` times.
+constexpr unsigned long long sumsq_cap(long blocks, long adds = 1) {
+  long per_slot = (blocks + kSumSlots - 1) / kSumSlots * adds;
+  unsigned long long cap = 1ull << 63;
+  for (; per_slot > 1; per_slot = (per_slot + 1) / 2) cap >>= 1;
+  return cap;
+}
 enum { REPACK_PLAIN = 0, REPACK_ROPE_HALVES = 1, REPACK_LO8 = 2, REPACK_HI8 = 3 };
 
 struct MeetSlot;   // k_meet.h
@@ -161,6 +169,7 @@ struct GemmEpi {
   const bf16_t* gain_next;        // gain of the norm that follows
   bf16_t* a_next;                 // packed bf16(h * gain_next)
   unsigned long long* sumsq_out;  // [kSumSlots][sum_stride], accumulated with integer atomics
+  unsigned long long sum_cap;     // most that one addition brings (sumsq_cap; set by the launch)
   bf16_t* act;                    // EPI_SWIGLU: packed activations, K = d_ffn
   const int4* rowinfo;            // EPI_QKV: per row (position or -1 for a padding row, index
                                   // into x, offset and keys per slab of its sequence's cache)

@@ -75,7 +75,7 @@ __device__ __forceinline__ float rstd_from_sum(const GemmEpi& e, unsigned long l
 __device__ __forceinline__ float rstd_of(const GemmEpi& e, int row) {
   unsigned long long fx = 0;
 #pragma unroll
-  for (int sl = 0; sl < kSumSlots; ++sl) fx += e.sumsq_in[(size_t)sl * e.sum_stride + row];
+  for (int sl = 0; sl < kSumSlots; ++sl) fx = sumsq_add(fx, e.sumsq_in[(size_t)sl * e.sum_stride + row]);
   return rstd_from_sum(e, fx);
 }
 
@@ -123,8 +123,8 @@ __device__ __forceinline__ void epi_add_sumsq(const GemmEpi& e, int m, bool vali
   part += __shfl_xor(part, 16, 64);
   part += __shfl_xor(part, 32, 64);
   if (valid && (threadIdx.x & 63) < 16) {
-    unsigned long long fx = sumsq_to_fixed(part);
-    const int slot = (blockIdx.x + blockIdx.y) & (kSumSlots - 1);
+    unsigned long long fx = sumsq_to_fixed(part, e.sum_cap);
+    const int slot = blockIdx.x & (kSumSlots - 1);
     // (the padding rows of the row list are all zeros: nothing to add)
     if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)slot * e.sum_stride + m), fx);
   }
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
     for (int sl = 0; sl < kSumSlots; ++sl) {
       // keeps the compiler from adding the counters up (and waiting for them) before the loop
       asm volatile("" : "+v"(ssq[sl]));
-      fx += ssq[sl];
+      fx = sumsq_add(fx, ssq[sl]);
     }
     if (threadIdx.x < MT * 16) rstd_s[threadIdx.x] = rstd_from_sum(e, fx);
   }
@@ -502,19 +502,22 @@ __global__ __launch_bounds__(256) void resid_finish_kernel(GemmEpi e) {
   }
   part = block_sum<4>(part, red);
   if (threadIdx.x == 0) {
-    unsigned long long fx = sumsq_to_fixed<58>(part);
+    unsigned long long fx = sumsq_to_fixed(part, e.sum_cap);
     if (fx) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)(blockIdx.x & (kSumSlots - 1)) * e.sum_stride + m), fx);
   }
 }
 
-static void launch_resid_finish(const GemmEpi& e, int N, hipStream_t s) {
-  resid_finish_kernel<<<dim3((N + 1023) / 1024, e.M), 256, 0, s>>>(e);
+static void launch_resid_finish(GemmEpi e, int N, hipStream_t s) {
+  const dim3 grid((N + 1023) / 1024, e.M);
+  e.sum_cap = sumsq_cap(grid.x);
+  resid_finish_kernel<<<grid, 256, 0, s>>>(e);
 }
 
 template <int EPI, int MT, int NTW, int KS, int U = 4, bool W8 = false>
 static void launch_skinny_t(const bf16_t* Ap, int MT_src, const void* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s, int ksplit = 1) {
+                            GemmEpi e, hipStream_t s, int ksplit = 1) {
   dim3 grid((total_nt + NTW - 1) / NTW, ksplit);
+  if (EPI == EPI_RESID) e.sum_cap = sumsq_cap(grid.x, NTW);
   size_t smem = (size_t)KS * NTW * MT * 64 * sizeof(float4) + MT * 16 * sizeof(float);
   if (EPI == EPI_LOGITS) smem += (size_t)NTW * MT * 16 * sizeof(float4);  // per-tile row tuples
   if (W8) smem += NTW * 16 * sizeof(float);                               // weight scales
@@ -963,9 +966,9 @@ __device__ __forceinline__ void tiled_meet_resid(const GemmEpi& e, f32x4 (&acc)[
 #pragma unroll
       for (int w = 1; w < WN; ++w) s += sums[w * ROWS + r];
       const int m = mt0 * 16 + r;
-      const unsigned long long fx = sumsq_to_fixed(s);
-      if (fx && m < e.M)
-        atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)((tile + sh) & (kSumSlots - 1)) * e.sum_stride + m), fx);
+      const unsigned long long fx = sumsq_to_fixed(s, e.sum_cap);
+      const int slot = (nt0 / (WN * WTN) * Z + sh) & (kSumSlots - 1);
+      if (fx && m < e.M) atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)slot * e.sum_stride + m), fx);
     }
     if (shares) __syncthreads();
   }
@@ -1015,7 +1018,7 @@ __device__ __forceinline__ void tiled_resid(const GemmEpi& e, f32x4 (&acc)[WTN][
 #pragma unroll
     for (int w = 1; w < WN; ++w) s += sums[w * ROWS + r];
     const int m = mt0 * 16 + r;
-    const unsigned long long fx = sumsq_to_fixed(s);
+    const unsigned long long fx = sumsq_to_fixed(s, e.sum_cap);
     if (fx && m < e.M)
       atomicAdd((unsigned long long*)(e.sumsq_out + (size_t)((nt0 / (WN * WTN)) & (kSumSlots - 1)) * e.sum_stride + m), fx);
   }
@@ -1207,8 +1210,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __re
 
 template <int EPI, bool WS, int Z, int WTM, int WTN>
 static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                           const GemmEpi& e, hipStream_t s) {
+                           GemmEpi e, hipStream_t s) {
   dim3 grid((total_nt + 2 * WTN - 1) / (2 * WTN), (e.M + 32 * WTM - 1) / (32 * WTM));
+  e.sum_cap = sumsq_cap((long)grid.x * Z);
   if (Z > 1) grid = dim3(meet_grid(grid.x * grid.y, Z));
   gemm_bf16_tiled4_kernel<EPI, WTM, WTN, WS, Z><<<grid, 256, 0, s>>>((const u32x4*)Ap, (const u32x4*)Wp,
                                                                  total_nt, KB, MT, e);
@@ -1360,7 +1364,7 @@ void gemm_bf16_tiled8_kernel(
     if (HAS_ROWS && wave < ROWS / 64) {
       unsigned long long fx = 0;
 #pragma unroll
-      for (int sl = 0; sl < kSumSlots; ++sl) fx += ssq[sl];
+      for (int sl = 0; sl < kSumSlots; ++sl) fx = sumsq_add(fx, ssq[sl]);
       rstd_s[my_row] = rstd_from_sum(e, fx);
       if constexpr (EPI == EPI_QKV) row_s[my_row] = ri;
     }
@@ -1405,7 +1409,7 @@ void gemm_bf16_tiled8_kernel(
 
 template <int EPI, bool WS, int Z, int WM, int WN, int WTM, int WTN, int NSTAGE>
 static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
-                            const GemmEpi& e, hipStream_t s) {
+                            GemmEpi e, hipStream_t s) {
   const size_t smem = tiled8_lds<EPI, WM, WN, WTM, WTN, NSTAGE>();
   auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS, Z>;
   static bool attr_set = false;
@@ -1415,6 +1419,7 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
     attr_set = true;
   }
   dim3 grid((total_nt + WN * WTN - 1) / (WN * WTN), (e.M + 16 * WM * WTM - 1) / (16 * WM * WTM));
+  e.sum_cap = sumsq_cap((long)grid.x * Z);
   if (Z > 1) grid = dim3(meet_grid(grid.x * grid.y, Z));
   kern<<<grid, WM * WN * 64, smem, s>>>((const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT, e);
 }

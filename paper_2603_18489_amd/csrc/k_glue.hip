@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void step_prologue_bf16_kernel(
   }
   ss = block_sum<4>(ss, red);
   if (threadIdx.x == 0)
-    sumsq[r] = sumsq_to_fixed<62>(ss);
+    sumsq[r] = sumsq_to_fixed(ss, sumsq_cap(1));
   for (int b = 1 + threadIdx.x; b < nbuf; b += 256) sumsq[(size_t)b * sumsq_stride + r] = 0ull;
   for (int i = r * 256 + threadIdx.x; i < L.n_meet; i += gridDim.x * 256) L.meet[i] = make_int4(0, 0, 0, 0);
 }

@@ -700,6 +700,32 @@ def test_blocks_that_meet_give_the_same_bits(dtype, d, f, P, block, down):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,d,f,P,block,k,down", [
+    ("bf16", 4128, 4096, 520, 40, 8, (192, 320, 4)),   # K split over blocks that meet; few rows: over the grid
+    ("fp8w", 4160, 4096, 520, 40, 8, (192, 320, 4)),
+    ("bf16", 1056, 1024, 260, 20, 2, (96, 128, 4)),    # the 4-wave kernels meet; few rows: K whole
+    ("bf16", 4128, 64, 520, 20, 2, (128, 128, 1)),     # K whole, 4 waves and 8
+    ("bf16", 4128, 64, 860, 20, 2, (192, 128, 1)),
+])
+def test_one_large_residual_channel(dtype, d, f, P, block, k, down):
+    """A residual channel of 3e5, as trained models have them in a few columns: its square, 9e10, is one
+    block's contribution to the row's sum of squares, which must not saturate it.  The gains of the channel are small,
+    so that the other channels decide the logits."""
+    cfg = small_cfg(dtype, 4, 4, 64, d=d, f=f, vocab=512, layers=2, scale=1000.0)
+    assert block_shape(cfg, ec.EC_K_DOWN, P + 2 * block) == down
+    w = ec_inputs.make_weights(cfg, 109, gain_jitter=0.1)
+    # (tensors are bfloat16 bit patterns: 0x4892 is 299008, 0x3880 is 2^-14)
+    emb = (w["tok_emb"].astype(np.uint32) << np.uint32(16)).view(np.float32) * np.float32(64)   # exact
+    w["tok_emb"] = (emb.view(np.uint32) >> np.uint32(16)).astype(np.uint16)
+    w["tok_emb"][:, d // 2 + 5] = 0x4892
+    for gain in [w["final_norm"], *w["attn_norm"], *w["mlp_norm"]]:
+        gain[d // 2 + 5] = 0x3880
+    dec = ec_inputs.DecodeCfg(gen_len=2 * block, block=block, k_recent=k, tokens_per_step=4, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, P, 6), TOL[dtype], max_steps=3)
+    print(s)
+    assert s["modes"][eco.PARTIAL] == 2 and s["rows_stat"] > 0
+
+
 @pytest.mark.parametrize("N,block,k,n,sliding", [
     (512, 128, 30, 30, 0),     # the most slots the waves count for themselves, the largest block
     (513, 100, 3, 32, 1),      # one more; sliding window
