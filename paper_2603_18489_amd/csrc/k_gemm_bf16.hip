@@ -1091,8 +1091,9 @@ static int meet_grid(int tiles, int Z) {
 
 // ---------------------------------------------------------------------------------------------
 // tiled, 4 waves (2x2): wave tile = WTM x WTN fragments, K step 32.  Operands are double-buffered
-// in LDS; global loads run through four register sets, four k-steps ahead.  This variant is the
-// faster one for block tiles up to 192 x 192 (one wave per SIMD, nothing to overlap with).
+// in LDS; global loads run through four register sets, four k-steps ahead.  For the blocks that are
+// too small to keep eight waves busy (128 x 128 and 96 x 128; at 192 x 192 and 192 x 128 eight waves take 0.53 and 0.46
+// us a k-step, four 0.64 and 0.55).
 // grid = (ceil(n-tiles / (2*WTN)), ceil(m-tiles / (2*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
 #define EC_TILED_GLOAD(REGS, KBV)                                                   \
@@ -1426,25 +1427,25 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 
 // Block shapes of the tiled kernels (rows x weight rows) and what one k-step costs on MI355X
 // with all 256 CUs busy (us, measured).
-//   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128   8: 192 x 320   9: 256 x 256
-//   4 waves: 4: 192 x 192   5: 192 x 128   6: 128 x 128   7: 96 x 128
-// What a whole launch loses most by is its last round: shapes 8 and 9 are there for the sizes at which
-// the others leave compute units or rows idle.  us per launch, best of 0 - 7 -> with 8 and 9:
-//   544 rows   gate/up  4096 -> 2 x 12288  192 blocks of 0, 231 of 8             122 -> 107
-//   512 rows   LM head  4096 -> 126464     990 of 0 in 576 rows, 988 of 9        543 -> 481
-//   1280 rows  gate/up  3584 -> 2 x 18944  693 of 0, 740 of 9 (in three rounds)  344 -> 314
-//   1280 rows  down     18944 -> 3584      3 x 70 of 0, 3 x 84 of 8              187 -> 161
-//   3552 rows  O + down                    209 of 0, 247 of 8                    480 -> 436
-//   24576 rows O + down                    2048 of 1, 1536 of 9                  2965 -> 2717
+//   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128   6: 192 x 320   7: 256 x 256
+//   4 waves: 4: 128 x 128   5: 96 x 128
+// What a whole launch loses most by is its last round: shapes 6 and 7 are there for the sizes at which
+// the others leave compute units or rows idle.  us per launch, best of 0 - 5 -> with 6 and 7:
+//   544 rows   gate/up  4096 -> 2 x 12288  192 blocks of 0, 231 of 6             122 -> 107
+//   512 rows   LM head  4096 -> 126464     990 of 0 in 576 rows, 988 of 7        543 -> 481
+//   1280 rows  gate/up  3584 -> 2 x 18944  693 of 0, 740 of 7 (in three rounds)  344 -> 314
+//   1280 rows  down     18944 -> 3584      3 x 70 of 0, 3 x 84 of 6              187 -> 161
+//   3552 rows  O + down                    209 of 0, 247 of 6                    480 -> 436
+//   24576 rows O + down                    2048 of 1, 1536 of 7                  2965 -> 2717
 // Two waves per SIMD overlap one wave's LDS reads and barrier waits with the other's MFMAs.  The wider
 // the block the fewer operand bytes per flop cross L2 and LDS.  A grid that does not fill the 256 CUs in
 // whole rounds wastes the remainder, so narrow outputs (N = d_model) are also split along K over blocks
 // that meet.
 struct TilePick { int tile, ksplit; };
-constexpr int kNumTiles = 10;
-static const int kTileM[kNumTiles] = {12, 12, 12, 12, 12, 12, 8, 6, 12, 16};
-static const int kTileN[kNumTiles] = {24, 16, 12, 8, 12, 8, 8, 8, 20, 16};
-static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.64f, 0.55f, 0.53f, 0.45f, 0.78f, 0.80f};
+constexpr int kNumTiles = 8;
+static const int kTileM[kNumTiles] = {12, 12, 12, 12, 8, 6, 12, 16};
+static const int kTileN[kNumTiles] = {24, 16, 12, 8, 8, 8, 20, 16};
+static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.53f, 0.45f, 0.78f, 0.80f};
 
 // floats of the pieces that the blocks of K split ks exchange
 static size_t meet_floats(const TilePick& t, int MT, int total_nt) {
@@ -1483,11 +1484,9 @@ static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int
     case 1: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 2: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 3, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 3: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 2, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 4: launch_tiled4_t<EPI, WS, Z, 6, 6>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 5: launch_tiled4_t<EPI, WS, Z, 6, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 6: launch_tiled4_t<EPI, WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 7: launch_tiled4_t<EPI, WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 8: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 4: launch_tiled4_t<EPI, WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 5: launch_tiled4_t<EPI, WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 6: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
     default: launch_tiled8_t<EPI, WS, Z, 2, 4, 8, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
   }
 }
