@@ -581,7 +581,7 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     # gate/up with row scales
     ("fp8w", 4, 4, 64, 128, 6016, 760, {"GATEUP": (192, 320, 1)}),
     ("fp8w", 4, 4, 64, 128, 8128, 760, {"GATEUP": (256, 256, 1)}),
-    # residual products, K whole and split (partial products, finish)
+    # residual products, K whole and split over blocks that meet
     ("bf16", 4, 4, 64, 4640, 64, 2538, {"OPROJ": (192, 320, 1), "DOWN": (192, 320, 1)}),
     ("fp8w", 4, 4, 64, 4672, 64, 2538, {"OPROJ": (192, 320, 1), "DOWN": (192, 320, 1)}),
     ("bf16", 4, 4, 64, 6176, 64, 2538, {"OPROJ": (256, 256, 1), "DOWN": (256, 256, 1)}),
@@ -671,16 +671,16 @@ def test_split_down_projection_three_steps_ahead(block):
     ("bf16", 4128, 4096, 520, 40, (192, 320, 4)),   # 52 tiles of 4: four of them over several XCDs
     ("bf16", 4128, 6176, 1089, 80, (256, 256, 3)),  # 85 tiles of 3
     ("fp8w", 4160, 4096, 520, 60, (192, 320, 4)),
-    ("bf16", 96, 4128, 150, 70, None),              # one column of tiles, few k-steps to a range
+    ("bf16", 96, 4128, 150, 70, (96, 128, 4)),      # 4 waves; one column of tiles, few k-steps to a range
     ("bf16", 1056, 1024, 2060, 20, (192, 128, 2)),  # two ranges; a row block with few rows
 ])
 def test_blocks_that_meet_give_the_same_bits(dtype, d, f, P, block, down):
-    """K split over blocks, full and partial steps: the same logits whether the blocks wait for each
-    other, give up at once (the last one finishes everything) or take each other to be on different XCDs.
+    """K split over blocks, full steps and the few-row steps behind them (which stream their weights and
+    read what the full step left): the same logits whether the blocks wait for each other, give up at once (the
+    last one finishes everything) or take each other to be on different XCDs.
     Their values are checked against the oracle by the tests above, which run the default."""
     cfg = small_cfg(dtype, 4, 4, 64, d=d, f=f, vocab=512, scale=4.0)
-    if down:
-        assert block_shape(cfg, ec.EC_K_DOWN, P + 2 * block) == down
+    assert block_shape(cfg, ec.EC_K_DOWN, P + 2 * block) == down
     w = ec_inputs.make_weights(cfg, 101, gain_jitter=0.1)
     dec = ec_inputs.DecodeCfg(gen_len=2 * block, block=block, k_recent=2, tokens_per_step=1, tau=1e9)
     g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, ec_inputs.make_prompt(cfg.vocab, P, 6))
@@ -698,6 +698,80 @@ def test_blocks_that_meet_give_the_same_bits(dtype, d, f, P, block, down):
             assert all(np.isfinite(z).all() and z.std() > 0 for z in want)
         assert all(np.array_equal(a, b) for a, b in zip(want, got)), (polls, apart)
     g.close()
+
+
+@pytest.mark.parametrize("dtype,d,partial,mixed", [
+    ("bf16", 4128, (192, 128, 4), (192, 320, 4)),
+    ("bf16", 1056, (96, 128, 4), (96, 128, 4)),
+    ("fp8w", 1088, (96, 128, 4), (96, 128, 4)),
+])
+def test_blocks_of_a_batch_that_meet(dtype, d, partial, mixed):
+    """Six ragged sequences whose partial steps (30 rows each, back to back) and mixed steps (two segments
+    padded to 256 rows before them) split K over blocks that meet: against the oracle, and the same bits
+    however the blocks find each other."""
+    B, block = 6, 30
+    cfg = small_cfg(dtype, 4, 4, 64, d=d, f=4096, vocab=512, scale=4.0)
+    assert ec.block_shape(cfg, ec.EC_K_DOWN, 192, 192) == partial
+    assert ec.block_shape(cfg, ec.EC_K_DOWN, 640, 640) == mixed
+    w = ec_inputs.make_weights(cfg, 113, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(batch=B, gen_len=2 * block, block=block, k_recent=2, tokens_per_step=1, tau=1e9)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, 130 + 3 * b, 6 + b) for b in range(B)]
+    s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL[dtype], max_steps=3, check_cache_every=3)
+    print(s)
+    assert s["modes"][eco.PARTIAL] == 2 * B and s["rows_stat"] > 0
+
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, prompts)
+    g.keep_logits(True)
+    full, part, none = [ec.EC_FULL] * B, [ec.EC_PARTIAL] * B, [[]] * B
+    want = None
+    for polls, apart in [(20000, False), (20000, True), (0, False), (0, True), (2, False), (5, True), (20000, False)]:
+        g.debug_meeting(polls, apart)
+        got = []
+        for modes in (full, part, full[:2] + part[2:]):
+            g.step_forced_batch(modes, none, none)
+            got += [g.debug_read(ec.EC_DBG_LOGITS, count=block, seq=b) for b in range(B)]
+        if want is None:
+            want = got
+            assert all(np.isfinite(z).all() and z.std() > 0 for z in want)
+        assert all(np.array_equal(a, b) for a, b in zip(want, got)), (polls, apart)
+    g.close()
+
+
+def test_blocks_meet_while_another_context_runs():
+    """Two contexts stepping at once on two streams: their blocks take each other's compute units, so those of a
+    tile need not run at the same time.  Every step's logits are those of the context alone."""
+    import threading
+
+    import torch
+    cfgs = [small_cfg("bf16", 4, 4, 64, d=d, f=4096, vocab=512, scale=4.0) for d in (4128, 1056)]
+    assert [block_shape(c, ec.EC_K_DOWN, 600) for c in cfgs] == [(192, 320, 4), (128, 128, 4)]
+    dec = ec_inputs.DecodeCfg(gen_len=40, block=20, k_recent=2, tokens_per_step=1, tau=1e9)
+    ctx, want, bad = [], [], []
+
+    def step(g):
+        g.step_forced(ec.EC_FULL, [], [])
+        return g.debug_read(ec.EC_DBG_LOGITS, count=20)
+
+    for i, cfg in enumerate(cfgs):
+        dw = ec.weights_to_device(cfg, ec_inputs.make_weights(cfg, 127 + i, gain_jitter=0.1))
+        torch.cuda.synchronize()
+        g = ec.EntropyCache(cfg, dw, dec, ec_inputs.make_prompt(cfg.vocab, 560, 6), stream=torch.cuda.Stream())
+        g.keep_logits(True)
+        ctx.append(g)
+        want.append(step(g))
+    gate = threading.Barrier(2)
+
+    def work(i):
+        gate.wait(timeout=30)
+        for _ in range(60):
+            if not np.array_equal(step(ctx[i]), want[i]):
+                bad.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    [t.start() for t in threads]
+    [t.join(timeout=60) for t in threads]
+    assert not any(t.is_alive() for t in threads) and not bad
+    [g.close() for g in ctx]
 
 
 @pytest.mark.parametrize("dtype,d,f,P,block,k,down", [
