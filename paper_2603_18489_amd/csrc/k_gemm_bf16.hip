@@ -602,8 +602,13 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
     if constexpr (MT > 1) {
       if (skinny_splits(MT, KB * 32, e)) {
         // three k-steps to a register set where the two sets divide a wave's range: more in flight and no
-        // step loaded twice (3 row tiles, with a finish: K 12288, 24 steps, 22.6 -> 22.1 us; 16 and 37 steps lose, 17.9 -> 18.4
-        // and 31.0 -> 31.8)
+        // step loaded twice.  us of the product and its finish, by events, two steps to a set -> three:
+        //   d 4096  K  9216  3 row tiles 22.4 -> 21.5   4: 24.5 -> 23.9      K 6144  4: 20.1 -> 20.1
+        //           K 12288  2: 24.2 -> 23.8   3: 26.0 -> 25.6   4: 28.5 -> 28.5
+        //           K 15360  2: 28.0 -> 27.3   3: 30.1 -> 29.2   4: 32.9 -> 32.2
+        //           K 18432  2: 31.8 -> 31.1   3: 33.9 -> 33.3   4: 36.9 -> 36.9
+        //   d 1024  0 - 0.9 shorter at the same sizes
+        // and longer where a range ends inside a set: 16 and 37 steps a wave, 17.9 -> 18.4 and 31.0 -> 31.8.
         if (MT <= 4 && KB % (6 * 4 * kSkinnySplit) == 0)
           launch_skinny_t<EPI_PARTIAL, MT, kSkinnySplit, 4, (MT > 4 ? 1 : 3)>(Ap, MT_src, Wp, total_nt, KB, e, s, kSkinnySplit);
         else
@@ -879,9 +884,11 @@ __device__ __forceinline__ void tiled_qkv(const GemmEpi& e, f32x4 (&acc)[WTN][WT
 // are shared out by their number in the wave, WTM * i + j: every wave stores those of the other blocks'
 // shares (1 KiB each, as the registers hold them), and after the meeting adds the others' pieces to its
 // own share in the order of the ranges and finishes it.  Rows' sums of squares go through LDS (`sums`: the
-// block's WN x rows floats), one addition to memory per row and share.
-// Against partial products and a second kernel that reads them all back (768 rows, d 4096, 192 x 256 x 4):
-// O 46.7 -> 38.1 us, down 89 -> 80; of that 14 us are the exchange and the residual stream's read and write.
+// block's WN x rows floats: added in float32, rounded to fixed point once), one addition to memory per row and
+// share.
+// Against partial products and a second kernel that reads them all back, in whole steps by events (768 rows,
+// d 4096, 192 x 256 x 4): O 49.1 -> 44.3 us, down (K 12288) 87.6 -> 81.6; kernel trace 43.3 and 83.2.  About 14 us of
+// that are the exchange and the residual stream's read and write.
 template <int WM, int WN, int WTM, int WTN, int Z>
 __device__ __forceinline__ void tiled_meet_resid(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt0,
                                                  int nt0, int total_nt, int wave, int lane, int tile,
@@ -976,7 +983,8 @@ __device__ __forceinline__ void tiled_meet_resid(const GemmEpi& e, f32x4 (&acc)[
 
 // Residual epilogue of a whole K: D row tiles of the residual stream are on their way while one is finished
 // (the epilogue of a round of 256 x 256 blocks then moves its bytes at 7 TB/s, most of them through the
-// last-level cache), and a block adds each row's sum of squares once, through LDS (`sums`: WN x rows floats).
+// last-level cache), and a block adds each row's sum of squares once, through LDS (`sums`: WN x rows floats, added
+// in float32 and rounded to fixed point once).
 template <int WM, int WN, int WTM, int WTN>
 __device__ __forceinline__ void tiled_resid(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt0, int nt0,
                                             int total_nt, int wave, int lane, float* sums) {
@@ -1455,8 +1463,10 @@ static size_t meet_floats(const TilePick& t, int MT, int total_nt) {
 
 // epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
 // cache stores of q k v, the residual stream's read and write, the exchange of a K split (whose blocks run
-// in one round).  Over 104 residual products (112 - 4000 rows, 12 pairs of widths from 512 to 18944) the
-// pick is within 13 % of the best of all shapes and splits, 2 % on average.
+// in one round); it does not count the ranges, though two exchange less than four.
+// Against the best of all shapes and splits, by events in whole steps (64 sizes: 112 - 3000 rows, d 512 - 4096,
+// F 2048 - 18944), the pick takes 3 % longer on average for residual products (24 % at most: O, 368
+// rows, pick_rows), 6 % for q k v (21 %: narrow ones, where 192 x 128 beats 96 x 128) and 6 % for gate/up (52 %: 368 rows again).
 static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit, size_t piece_floats) {
   TilePick best{1, 1};
   float best_t = 1e30f;
@@ -1505,9 +1515,13 @@ static void launch_tiled_pick_z(const bf16_t* Ap, int MT, const bf16_t* Wp, int 
   launch_tiled_pick_ws<EPI, WS, 1>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile);
 }
 
-// The row tiles that the shape is picked for: those of the padded row list, unless it is mostly padding
-// (272 rows in a list of 512, down projection of 4096: 192 x 256 x 4 65.8 us, 192 x 128 x 4 55.7).  Only tiles that hold
-// rows are computed either way.
+// The row tiles that the shape is picked for: those of the padded row list, unless a third of it or more is
+// padding (272 rows in a list of 512, down projection of 4096: 192 x 256 x 4 65.8 us, 192 x 128 x 4 55.7).  Only tiles
+// that hold rows are computed either way, so below that third the shape can be one for rows that are not there.
+// us of a layer's four products, by events in whole steps, as picked -> picked for the rows themselves:
+//   d 4096, F 12288   368 rows 270 -> 234   528 290 -> 285   848 426 -> 403   944 437 -> 416
+//   d 3584, F 18944   368 rows 319 -> 265   528 357 -> 331   848 462 -> 431   1328 618 -> 591
+// and the same at multiples of 256.
 static int pick_rows(int M_src, int M) {
   const int padded = (M_src + 15) / 16, rows = (M + 15) / 16;
   return 3 * rows <= 2 * padded ? rows : padded;
@@ -1544,8 +1558,8 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
     return;
   }
   // Up to 96 rows (a block of 32 plus the paper's default budget of 64 recent tokens) the GEMMs
-  // are weight-streaming: 3.7 ms a step at 64 rows, 4.5 ms at 96, against 7.8 ms through the
-  // tiled kernels.
+  // are weight-streaming: eight layers of d 4096, F 12288 take 0.93 ms a step at 64 rows and 1.10 at 96, against 1.76
+  // and 1.85 through the tiled kernels.
   if (streams_weights(EPI, MT)) {
     switch (MT) {
       case 1: launch_skinny_mt<EPI, 1>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
