@@ -32,7 +32,7 @@
 //     order, then the epilogue runs on the sums.
 //   tiled (M > 96): block tile chosen per shape so that the grid fills the 256 CUs.  4 waves:
 //     LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384, 256x256): operands
-//     loaded from global memory directly into a 3-stage LDS ring.
+//     loaded from global memory directly into an LDS ring of four k-steps.
 #include "ec_internal.h"
 #include "k_meet.h"
 #include "k_vtuple.h"
@@ -1229,39 +1229,45 @@ static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 
 // ---------------------------------------------------------------------------------------------
 // tiled, 8 waves (WM x WN): wave tile = WTM x WTN fragments of 16 rows (activations x weights),
-// K step 32.  Operand fragments go from global memory straight into LDS (global_load_lds_dwordx4:
-// lane l's 16 bytes land at base + 16 l, so a 1 KiB fragment keeps its order), NSTAGE stages deep,
+// K step 32.  Operand fragments go from global memory straight into LDS (buffer loads of 16 bytes a lane:
+// lane l's land at base + 16 l, so a 1 KiB fragment keeps its order), into a ring of four k-steps,
 // no staging registers; one barrier per k-step.
 // grid = (ceil(n-tiles / (WN*WTN)), ceil(m-tiles / (WM*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
-// ROLL: the fragments of k-step k+1 are read from LDS while the MFMAs of k-step k run, a few after
+// The fragments of k-step k+1 are read from LDS while the MFMAs of k-step k run, a few after
 // each row of them: a weight fragment goes back to the registers its last MFMA has just freed, the
 // activation fragments and the last weight fragment have a second set.  Reads and MFMAs of a
 // k-step one after the other leave the matrix cores idle for the reads (96 KiB at 128 B a clock
-// for 192 x 384) and all of a step's reads ahead of its MFMAs hold up the issue of the latter.  What
-// is left at 192 x 384 is mostly the delivery of the operands from L2: without the loads (on
-// whatever the LDS holds) the gate/up launch below takes 89 us, with all of them hitting in L2 125.
-// us per launch on MI355X at 768 rows, d 4096, F 12288:
-//   gate/up  192 x 384        141 -> 127     q k v  192 x 192            89 -> 84
-//   O, down  192 x 256 x 4 K   55 -> 52 (mean of the two; the read-ahead of whole k-steps before)
+// for 192 x 384) and all of a step's reads ahead of its MFMAs hold up the issue of the latter.
+// What bounds the loop is power: products of random operands alone hold 1.94 GHz and 1.94 PFLOP/s, with the reads
+// and loads the clock settles at 1.7 - 1.8.  So what a k-step costs in cycles matters (256 x 256: 1024 of
+// MFMAs, 1160 in all) and what it moves.  Against a ring of three that the barrier drains of LDS reads, with an uneven
+// number of loads a wave and their addresses in vector registers: 1252 -> 1160 cycles a k-step for 256 x 256, 1564 ->
+// 1410 for 192 x 384, 1165 -> 1124 for 192 x 320.  Kernel alone, 4096 -> 2 x 12288: 4096 rows 604 -> 583 us, 24576 rows 3520 ->
+// 3390; whole full steps take 2.3 - 3.8 % less.
+// Measured and left out, as slower: weights straight to registers, 8 waves side by side (less LDS traffic; 5 - 15 %); 4
+// waves of 128 x 128 (a third less LDS traffic, 1.90 GHz, but 1270 cycles and a longer epilogue); s_setprio around the MFMAs
+// (5 % more cycles); v_mfma_f32_32x32x16 (1.70 PFLOP/s alone).
+constexpr int kRing = 4;   // k-steps in LDS
 // bytes of LDS: the operand ring or, if larger, the rotation factors of the rows (hd 128) in its place, and the rows
-template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE>
+template <int EPI, int WM, int WN, int WTM, int WTN>
 constexpr int tiled8_lds() {
-  constexpr int ring = NSTAGE * (WM * WTM + WN * WTN) * 1024, factors = EPI == EPI_QKV ? WM * WTM * 16 * 512 : 0;
+  constexpr int ring = kRing * (WM * WTM + WN * WTN) * 1024, factors = EPI == EPI_QKV ? WM * WTM * 16 * 512 : 0;
   return (ring > factors ? ring : factors) + tiled_row_bytes<EPI, WM * WTM * 16>();
 }
 
-template <int EPI, int WM, int WN, int WTM, int WTN, int NSTAGE, bool WS, int Z>
+template <int EPI, int WM, int WN, int WTM, int WTN, bool WS, int Z>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_tiled8_kernel(
     const u32x4* __restrict__ Ap, const u32x4* __restrict__ Wp, int total_nt, int KB_all, int MT,
     GemmEpi e) {
   constexpr int NW = WM * WN, BMT = WM * WTM, BNT = WN * WTN, NF = BMT + BNT;
-  constexpr int LF = (NF + NW - 1) / NW;  // loads per stage of the waves with wave < NF - (LF-1)*NW,
-                                          // one less for the others
-  static_assert(LF * NSTAGE <= 63, "vmcnt counts at most 63 outstanding loads");
+  // A wave loads FULL whole fragments a k-step and, where they do not divide over the waves, half of one more,
+  // so that all waves have the same number of loads in flight.
+  constexpr int FULL = NF / NW, LF = FULL + (NF % NW != 0);
+  static_assert(NF % NW == 0 || NF % NW == NW / 2, "the fragments left over are shared by two waves each");
   static_assert(WTN > 1, "the rolling reads need two weight fragments a wave");
-  extern __shared__ u32x4 lds[];  // [NSTAGE][NF][64]
+  extern __shared__ u32x4 lds[];  // [kRing][NF][64]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int bx, by, tile = 0, z = 0;
   if constexpr (Z > 1) {
@@ -1276,39 +1282,34 @@ void gemm_bf16_tiled8_kernel(
   // the block's range of K
   const int kb_first = z * KB_all / Z, KB = (z + 1) * KB_all / Z - kb_first;
 
-  // Fragment f of the block (0..BMT-1 activations, BMT.. weights) is loaded by wave f % NW.
+  // Fragment f of the block: 0..BMT-1 activations, BMT.. weights.
   // A fragment outside the matrix streams fragment 0 instead (valid memory); what it produces
   // lands in rows / columns that are never stored.  The addresses are wave-uniform.
   const char* src[LF];
-  size_t step[LF];  // bytes per k-step
-  const bool more = wave < NF - (LF - 1) * NW;
+  unsigned step[LF];  // bytes per k-step
+  int frag[LF];
 #pragma unroll
   for (int l = 0; l < LF; ++l) {
-    const int f = wave + NW * l;
+    const int f = l < FULL ? wave + NW * l : NW * FULL + (wave >> 1);
     const int mt = f < BMT && mt0 + f < MT ? mt0 + f : 0;
-    const int nt = f >= BMT && f < NF && nt0 + f - BMT < total_nt ? nt0 + f - BMT : 0;
-    step[l] = (f < BMT ? (size_t)MT : (size_t)e.w_grp) * 1024;
+    const int nt = f >= BMT && nt0 + f - BMT < total_nt ? nt0 + f - BMT : 0;
+    frag[l] = f;
+    step[l] = (unsigned)(f < BMT ? MT : e.w_grp) * 1024;
     src[l] = (f < BMT ? (const char*)Ap + (size_t)mt * 1024
                       : (const char*)Wp + packed_w_frag(nt, 0, KB_all, e.w_grp) * 1024) +
-             kb_first * step[l];
+             (size_t)kb_first * step[l];
   }
   const unsigned voff = lane * 16;
-  int fill = 0, slot_w = 0;  // k-step requested next (its operands are those of the last one once
-                             // the range is through), and the slot it goes to
-#define EC_T8_LOAD(L)                                                                        \
-  __builtin_amdgcn_global_load_lds(                                                          \
-      (const void __attribute__((address_space(1)))*)(src[L] + voff),                        \
-      (void __attribute__((address_space(3)))*)(lds + ((size_t)slot_w * NF + wave + NW * (L)) * 64), 16, 0, 0);
-#define EC_T8_ISSUE(LO, HI)                                                                  \
-  _Pragma("unroll") for (int l = (LO); l < (HI); ++l) {                                      \
-    if (NF % NW == 0 || l < LF - 1) { EC_T8_LOAD(l) }                                        \
-    else if (more) { EC_T8_LOAD(l) }                                                         \
-    src[l] += fill + 1 < KB ? step[l] : 0;                                                   \
+  const bool my_half = (lane >> 5) == (wave & 1);
+  // load L of a k-step into the slot at byte SLOT of the ring; the next one's source is STEP bytes on
+#define EC_T8_LOAD(L, SLOT, STEP)                                                            \
+  {                                                                                          \
+    const auto rs_ = __builtin_amdgcn_make_buffer_rsrc((void*)src[L], 0, 0xffffffff, 0x00027000);  \
+    const auto to_ = (void __attribute__((address_space(3)))*)((char*)lds + (SLOT) + frag[L] * 1024);  \
+    if ((L) < FULL) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, to_, 16, voff, 0, 0, 0);   \
+    else if (my_half) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, to_, 16, voff, 0, 0, 0); \
+    src[L] += (STEP);                                                                        \
   }
-#define EC_T8_FILLED ++fill; slot_w = slot_w == NSTAGE - 1 ? 0 : slot_w + 1;
-  // waits until at most the loads of the newest STEPS k-steps of this wave are in flight
-#define EC_T8_WAIT(STEPS)                                                                    \
-  if (NF % NW == 0 || more) wait_vmcnt<LF*(STEPS)>(); else wait_vmcnt<(LF - 1)*(STEPS)>();
 
   f32x4 acc[WTN][WTM];
 #pragma unroll
@@ -1318,39 +1319,10 @@ void gemm_bf16_tiled8_kernel(
 
   constexpr int ROWS = BMT * 16;
   static_assert(ROWS % 64 == 0, "whole waves fetch the rows' sums");
-  int4* row_s = (int4*)((char*)lds + tiled8_lds<EPI, WM, WN, WTM, WTN, NSTAGE>() - tiled_row_bytes<EPI, ROWS>());
+  int4* row_s = (int4*)((char*)lds + tiled8_lds<EPI, WM, WN, WTM, WTN>() - tiled_row_bytes<EPI, ROWS>());
   float* rstd_s = (float*)(row_s + (EPI == EPI_QKV ? ROWS : 0));
-  int slot_r = 0;
   {
-    // All NSTAGE slots are kept in flight.  Step k: this wave has finished reading slot k (its
-    // fragments sit in registers) and its loads of k-step k+1 have landed; after the barrier that
-    // holds for every wave, so slot k is refilled with k-step k + NSTAGE while slot k+1 is read.
     bf16x8 afa[WTM], afb[WTM], wf[WTN - 1], wla, wlb;
-#define EC_T8_WF(I, WL) ((I) < WTN - 1 ? wf[(I) < WTN - 1 ? (I) : 0] : WL)
-#define EC_T8_STEP(AF, WL, AFN, WLN)                                                         \
-  {                                                                                          \
-    EC_T8_WAIT(NSTAGE - 2)                                                                   \
-    block_barrier_nofence();                                                                 \
-    slot_r = slot_r == NSTAGE - 1 ? 0 : slot_r + 1;                                          \
-    const u32x4* sa_ = lds + ((size_t)slot_r * NF + wm * WTM) * 64 + lane;                   \
-    const u32x4* sw_ = lds + ((size_t)slot_r * NF + BMT + wn * WTN) * 64 + lane;             \
-    _Pragma("unroll") for (int i = 0; i < WTN; ++i) {                                        \
-      _Pragma("unroll") for (int j = 0; j < WTM; ++j)                                        \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(EC_T8_WF(i, WL), AF[j],          \
-                                                            acc[i][j], 0, 0, 0);             \
-      __builtin_amdgcn_sched_barrier(0);                                                     \
-      if (i < WTN - 1) {                                                                     \
-        if (i == 0) WLN = v4_as_bf16x8(sw_[(WTN - 1) * 64]);                                 \
-        _Pragma("unroll")                                                                    \
-        for (int j = i * WTM / (WTN - 1); j < (i + 1) * WTM / (WTN - 1); ++j)                \
-          AFN[j] = v4_as_bf16x8(sa_[j * 64]);                                                \
-        wf[i < WTN - 1 ? i : 0] = v4_as_bf16x8(sw_[i * 64]);                                 \
-      }                                                                                      \
-      EC_T8_ISSUE(i * LF / WTN, (i + 1) * LF / WTN)                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                     \
-    }                                                                                        \
-    EC_T8_FILLED                                                                             \
-  }
     // The rows' sums of squares are requested ahead of the first operands, by one lane a row, and turned
     // into 1/rms while those are on their way, instead of in the epilogue by every lane for each of its
     // row tiles (eight loads and a division in 64 bits): gate/up, 768 rows 126.2 -> 123.4 us, 4096 rows
@@ -1367,8 +1339,12 @@ void gemm_bf16_tiled8_kernel(
       if constexpr (EPI == EPI_QKV) ri = e.rowinfo[m];
     }
     __builtin_amdgcn_sched_barrier(0);
+    // k-step k sits in slot k % kRing; past the range the last one is requested again
+    constexpr int SLOT = NF * 1024;
 #pragma unroll
-    for (int sgl = 0; sgl < NSTAGE; ++sgl) { EC_T8_ISSUE(0, LF) EC_T8_FILLED }
+    for (int k = 0; k < kRing - 1; ++k)
+#pragma unroll
+      for (int l = 0; l < LF; ++l) EC_T8_LOAD(l, k * SLOT, k + 1 < KB ? step[l] : 0u)
     __builtin_amdgcn_sched_barrier(0);
     if (HAS_ROWS && wave < ROWS / 64) {
       unsigned long long fx = 0;
@@ -1377,18 +1353,55 @@ void gemm_bf16_tiled8_kernel(
       rstd_s[my_row] = rstd_from_sum(e, fx);
       if constexpr (EPI == EPI_QKV) row_s[my_row] = ri;
     }
-    EC_T8_WAIT(NSTAGE - 1)
+    wait_vmcnt<LF * (kRing - 2)>();
     block_barrier_nofence();
+    typedef const __attribute__((address_space(3))) u32x4* lds_ptr;
+    const unsigned la = (unsigned)(size_t)(lds_ptr)lds + (unsigned)(wm * WTM * 1024 + lane * 16);
+    const unsigned lw = (unsigned)(size_t)(lds_ptr)lds + (unsigned)((BMT + wn * WTN) * 1024 + lane * 16);
 #pragma unroll
-    for (int j = 0; j < WTM; ++j) afa[j] = v4_as_bf16x8(lds[(wm * WTM + j) * 64 + lane]);
+    for (int j = 0; j < WTM; ++j) afa[j] = v4_as_bf16x8(((lds_ptr)(size_t)la)[j * 64]);
 #pragma unroll
-    for (int i = 0; i < WTN - 1; ++i) wf[i] = v4_as_bf16x8(lds[(BMT + wn * WTN + i) * 64 + lane]);
-    wla = v4_as_bf16x8(lds[(BMT + wn * WTN + WTN - 1) * 64 + lane]);
+    for (int i = 0; i < WTN - 1; ++i) wf[i] = v4_as_bf16x8(((lds_ptr)(size_t)lw)[i * 64]);
+    wla = v4_as_bf16x8(((lds_ptr)(size_t)lw)[(WTN - 1) * 64]);
+    // Step k: this wave's loads of k-step k+1 have landed; after the barrier that holds for every wave, and
+    // every wave is through with the MFMAs of k-step k-1, whose slot is then refilled with k-step k+3 while slot
+    // k+1 is read.  (The reads of slot k may still be under way: nothing is written there.)  Two loads
+    // follow each of the first rows of MFMAs: the sooner they are out, the less the barrier two steps on
+    // has to wait for them.
+#define EC_T8_WF(I, WL) ((I) < WTN - 1 ? wf[(I) < WTN - 1 ? (I) : 0] : WL)
+#define EC_T8_STEP(NEXT, REFILL, AF, WL, AFN, WLN, MORE)                                     \
+  {                                                                                          \
+    wait_vmcnt<LF>();                                                                        \
+    asm volatile("s_barrier" ::: "memory");                                                  \
+    unsigned va_ = la + (NEXT), vw_ = lw + (NEXT);                                           \
+    asm volatile("" : "+v"(va_), "+v"(vw_)); /* (one address each, the rest are offsets) */  \
+    const lds_ptr sa_ = (lds_ptr)(size_t)va_, sw_ = (lds_ptr)(size_t)vw_;                    \
+    _Pragma("unroll") for (int i = 0; i < WTN; ++i) {                                        \
+      _Pragma("unroll") for (int j = 0; j < WTM; ++j)                                        \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(EC_T8_WF(i, WL), AF[j],          \
+                                                            acc[i][j], 0, 0, 0);             \
+      __builtin_amdgcn_sched_barrier(0);                                                     \
+      if (i < WTN - 1) {                                                                     \
+        _Pragma("unroll")                                                                    \
+        for (int j = i * WTM / (WTN - 1); j < (i + 1) * WTM / (WTN - 1); ++j)                \
+          AFN[j] = v4_as_bf16x8(sa_[j * 64]);                                                \
+        wf[i < WTN - 1 ? i : 0] = v4_as_bf16x8(sw_[i * 64]);                                 \
+        if (i == WTN - 2) WLN = v4_as_bf16x8(sw_[(WTN - 1) * 64]);                           \
+      }                                                                                      \
+      _Pragma("unroll")                                                                      \
+      for (int l = i * 2 < LF ? i * 2 : LF; l < (i + 1 == WTN || i * 2 + 2 > LF ? LF : i * 2 + 2); ++l)  \
+        EC_T8_LOAD(l, REFILL, (MORE) ? step[l] : 0u)                                         \
+      __builtin_amdgcn_sched_barrier(0);                                                     \
+    }                                                                                        \
+  }
+    int odd = SLOT, even = 2 * SLOT;   // slots of the odd and the even k-step that follow
     for (int kb = 0; kb + 1 < KB; kb += 2) {
-      EC_T8_STEP(afa, wla, afb, wlb)
-      EC_T8_STEP(afb, wlb, afa, wla)
+      EC_T8_STEP(odd, 4 * SLOT - odd, afa, wla, afb, wlb, kb + 4 < KB)
+      EC_T8_STEP(even, 2 * SLOT - even, afb, wlb, afa, wla, kb + 5 < KB)
+      odd = 4 * SLOT - odd;     // 1, 3, 1, ...
+      even = 2 * SLOT - even;   // 2, 0, 2, ...
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    static_assert(kRing == 4, "the slots follow each other as above");
     if (KB & 1) {  // (an odd trip count: the last k-step's fragments are in the first set)
 #pragma unroll
       for (int i = 0; i < WTN; ++i)
@@ -1399,10 +1412,8 @@ void gemm_bf16_tiled8_kernel(
 #undef EC_T8_STEP
 #undef EC_T8_WF
   }
-#undef EC_T8_WAIT
-#undef EC_T8_FILLED
-#undef EC_T8_ISSUE
 #undef EC_T8_LOAD
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   wait_vmcnt<0>();  // drain the clamped tail loads before the LDS goes away
 
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
@@ -1416,11 +1427,11 @@ void gemm_bf16_tiled8_kernel(
     tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane, rstd_s + wm * WTM * 16);
 }
 
-template <int EPI, bool WS, int Z, int WM, int WN, int WTM, int WTN, int NSTAGE>
+template <int EPI, bool WS, int Z, int WM, int WN, int WTM, int WTN>
 static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
                             GemmEpi e, hipStream_t s) {
-  const size_t smem = tiled8_lds<EPI, WM, WN, WTM, WTN, NSTAGE>();
-  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, NSTAGE, WS, Z>;
+  const size_t smem = tiled8_lds<EPI, WM, WN, WTM, WTN>();
+  auto kern = gemm_bf16_tiled8_kernel<EPI, WM, WN, WTM, WTN, WS, Z>;
   static bool attr_set = false;
   if (!attr_set && smem > 48 * 1024) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1490,14 +1501,14 @@ template <int EPI, bool WS, int Z>
 static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
                                  const GemmEpi& e, hipStream_t s, int tile) {
   switch (tile) {
-    case 0: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 1: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 2: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 3, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 3: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 2, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 0: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 6>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 1: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 2: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 3: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 2>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 4: launch_tiled4_t<EPI, WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 5: launch_tiled4_t<EPI, WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 6: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    default: launch_tiled8_t<EPI, WS, Z, 2, 4, 8, 4, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 6: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    default: launch_tiled8_t<EPI, WS, Z, 2, 4, 8, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
   }
 }
 

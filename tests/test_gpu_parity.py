@@ -572,6 +572,18 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 160, 192])
+def test_tiled_gemm_ranges_around_the_operand_ring(d):
+    """One to six k-steps through the 8-wave kernels, whose ring holds four and is filled three ahead."""
+    cfg = small_cfg("bf16", 4, 4, 64, d=d, f=4128, vocab=512, layers=1, scale=4.0)
+    assert block_shape(cfg, ec.EC_K_GATEUP, 911) == (192, 256, 1)
+    w = ec_inputs.make_weights(cfg, 131, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=11, block=4, k_recent=2, tokens_per_step=1, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 900, 6), TOL["bf16"], max_steps=2)
+    print(s)
+    assert s["rows_stat"] > 0
+
+
 @pytest.mark.parametrize("dtype,hq,hkv,hd,d,f,P,blocks", [
     # q/k/v with rotation and cache stores, the last row and column block ragged
     ("bf16", 32, 32, 128, 96, 256, 760, {"QKV": (192, 320, 1)}),
