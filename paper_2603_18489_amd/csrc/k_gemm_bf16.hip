@@ -30,8 +30,8 @@
 //     across its waves; each weight byte is read from HBM exactly once while the small
 //     activation fragments come from L2.  The KS partial tiles are summed in LDS in a fixed
 //     order, then the epilogue runs on the sums.
-//   tiled (M > 96): block tile chosen per shape so that the grid fills the 256 CUs.  4 waves:
-//     LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384, 256x256): operands
+//   tiled (M > 96): block tile chosen per shape so that the grid fills the 256 CUs.  4 waves
+//     (residual products): LDS double buffer fed through four register sets.  8 waves (192x128 .. 192x384, 256x256): operands
 //     loaded from global memory directly into an LDS ring of four k-steps.
 #include "ec_internal.h"
 #include "k_meet.h"
@@ -72,13 +72,6 @@ __device__ __forceinline__ float rstd_from_sum(const GemmEpi& e, unsigned long l
   double ss = sumsq_from_fixed(fx);
   return 1.0f / sqrtf((float)(ss / (double)e.d_in) + e.eps);
 }
-__device__ __forceinline__ float rstd_of(const GemmEpi& e, int row) {
-  unsigned long long fx = 0;
-#pragma unroll
-  for (int sl = 0; sl < kSumSlots; ++sl) fx = sumsq_add(fx, e.sumsq_in[(size_t)sl * e.sum_stride + row]);
-  return rstd_from_sum(e, fx);
-}
-
 // ---- epilogues on one lane's values -----------------------------------------------------------
 // (m: activation row, < M;  vt: virtual weight tile;  q4: lane>>4, so the lane's 4 values are
 // output features vt*16 + q4*4 + 0..3.)
@@ -630,128 +623,15 @@ static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// QKV epilogue of the 4-wave tiled kernels.  The rotation factors come from a table in global memory;
-// a load issued between two stores cannot be moved up by the compiler (the stores might alias
-// it), so one m-tile's factors are fetched while the previous m-tile is rotated and stored:
-// one exposed load latency per wave instead of one per accumulator tile.  (The 8-wave kernels have no
-// registers for that: tiled_qkv.)
-// ---------------------------------------------------------------------------------------------
-template <int WTM, int WTN>
-__device__ __forceinline__ void tiled_epilogue_qkv(const GemmEpi& e, f32x4 (&acc)[WTN][WTM],
-                                                   int mt_base, int nt_base, int total_nt,
-                                                   int lane) {
-  const int q4 = lane >> 4, hd = e.hd, tph = hd >> 4, half = hd >> 1;
-  const int nqt = e.Hq * tph, nkt = e.Hkv * tph;
-  const bool hi = q4 >= 2;
-  // wave-uniform description of the WTN weight tiles: kind 0 = q, 1 = k, 2 = v, 3 = past the end
-  int kind[WTN], head[WTN], w[WTN];
-#pragma unroll
-  for (int i = 0; i < WTN; ++i) {
-    const int vt = nt_base + i;
-    kind[i] = vt >= total_nt ? 3 : vt < nqt ? 0 : vt < nqt + nkt ? 1 : 2;
-    const int t = kind[i] == 0 ? vt : kind[i] == 1 ? vt - nqt : kind[i] == 2 ? vt - nqt - nkt : 0;
-    head[i] = t / tph;
-    w[i] = t - head[i] * tph;
-  }
-  // Addresses split into a row part (per m-tile j) and a column part (per weight tile i): the
-  // cache index functions are sums of a function of the key and a function of the column.
-  //   q:  row m * Hq*hd            + head*hd + col
-  //   K:  slab(head) + K(key)      + C(col)       (k_common.h: kcache_index)
-  //   V:  slab(head) + Vk(key)     + w * Vs + (q4*4 + r) * 8,  Vs = keys/32 * 512 per hd tile
-  int pos[WTM], krow[WTM], vrow[WTM], vstep[WTM], slab[WTM];
-  size_t qrow[WTM];
-  float rs[WTM];
-  bool mvalid[WTM];
-#pragma unroll
-  for (int j = 0; j < WTM; ++j) {
-    const int m = (mt_base + j) * 16 + (lane & 15);
-    const int mm = m < e.M ? m : 0;
-    const int4 ri = e.rowinfo[mm];
-    mvalid[j] = m < e.M && ri.x >= 0;  // not a padding row
-    pos[j] = ri.x >= 0 ? ri.x : 0;
-    qrow[j] = (size_t)mm * (e.Hq * hd);
-    krow[j] = ri.z + (int)kcache_index(pos[j], 0, hd);
-    vrow[j] = ri.z + (int)vcache_index(pos[j], 0, ri.w);
-    vstep[j] = (ri.w >> 5) * 512;
-    slab[j] = ri.w * hd;  // elements per kv head
-    rs[j] = rstd_of(e, mm);
-  }
-  const int colq = (q4 & 1) * 4 + (hi ? half : 0);  // the lane's first column within a head, tile 0
-  int qcol[WTN], kcol[WTN];
-#pragma unroll
-  for (int i = 0; i < WTN; ++i) {
-    qcol[i] = head[i] * hd + w[i] * 8 + colq;
-    kcol[i] = (int)kcache_index(0, w[i] * 8 + colq, hd);
-  }
-  const unsigned sin_sign = hi ? 0u : 0x80000000u;  // first half: x cos - y sin; second: x cos + y sin
-  float4 ca[WTN][2], cb[WTN][2];  // (cos, sin) x 4 columns for each rotary tile of one m-tile
-#define EC_QKV_LOADC(C, J)                                                                   \
-  _Pragma("unroll") for (int i = 0; i < WTN; ++i) if (kind[i] < 2) {                           \
-    const float4* src_ = (const float4*)(e.cs + (size_t)pos[J] * half + w[i] * 8 + (q4 & 1) * 4); \
-    C[i][0] = src_[0];                                                                       \
-    C[i][1] = src_[1];                                                                       \
-  }
-#define EC_QKV_STORE(C, J)                                                                   \
-  _Pragma("unroll") for (int i = 0; i < WTN; ++i) {                                            \
-    const f32x4 v = acc[i][J];                                                               \
-    if (kind[i] < 2) {                                                                       \
-      float out_[4];                                                                         \
-      const float cc_[4] = {C[i][0].x, C[i][0].z, C[i][1].x, C[i][1].z};                      \
-      const float ss_[4] = {C[i][0].y, C[i][0].w, C[i][1].y, C[i][1].w};                      \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) {                                          \
-        const float y_ = other_half(v[r]);                                                   \
-        const float s_ = __uint_as_float(__float_as_uint(ss_[r]) ^ sin_sign);                \
-        out_[r] = (v[r] * cc_[r] + y_ * s_) * rs[J];                                         \
-      }                                                                                      \
-      u32x2 pk_;                                                                             \
-      pk_[0] = pack2(out_[0], out_[1]);                                                      \
-      pk_[1] = pack2(out_[2], out_[3]);                                                      \
-      if (mvalid[J]) {                                                                       \
-        if (kind[i] == 0)                                                                    \
-          *(u32x2*)(e.q_out + qrow[J] + qcol[i]) = pk_;                                      \
-        else                                                                                 \
-          *(u32x2*)(e.kc + (size_t)head[i] * slab[J] + krow[J] + kcol[i]) = pk_;             \
-      }                                                                                      \
-    } else if (kind[i] == 2 && mvalid[J]) {                                                  \
-      bf16_t* dst_ = e.vc + (size_t)head[i] * slab[J] + vrow[J] + w[i] * vstep[J] + q4 * 32; \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r) dst_[r * 8] = f32_to_bf16(v[r] * rs[J]);   \
-    }                                                                                        \
-  }
-  EC_QKV_LOADC(ca, 0)
-#pragma unroll
-  for (int j = 0; j < WTM; j += 2) {
-    if (j + 1 < WTM) { EC_QKV_LOADC(cb, j + 1) }
-    EC_QKV_STORE(ca, j)
-    if (j + 1 < WTM) {
-      if (j + 2 < WTM) { EC_QKV_LOADC(ca, j + 2) }
-      EC_QKV_STORE(cb, j + 1)
-    }
-  }
-#undef EC_QKV_LOADC
-#undef EC_QKV_STORE
-}
-
-// rstd_s: 1/rms of the rows from row tile mt_base on, in LDS (null: from the counters, by every lane)
+// gate/up and LM head; rstd_s: 1/rms of the rows from row tile mt_base on, in LDS
 template <int EPI, int WTM, int WTN>
 __device__ __forceinline__ void tiled_epilogue(const GemmEpi& e, f32x4 (&acc)[WTN][WTM], int mt_base,
                                                int nt_base, int total_nt, int lane, const float* rstd_s) {
-  if constexpr (EPI == EPI_QKV) {
-    tiled_epilogue_qkv<WTM, WTN>(e, acc, mt_base, nt_base, total_nt, lane);
-    return;
-  }
   const int q4 = lane >> 4;
   // every row's 1/rms first: these loads must not be strung out between the stores below
   float rsj[WTM];
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) {
 #pragma unroll
-    for (int j = 0; j < WTM; ++j) {
-      const int m = (mt_base + j) * 16 + (lane & 15);
-      const int mm = m < e.M ? m : 0;
-      rsj[j] = rstd_s ? rstd_s[j * 16 + (lane & 15)]
-                      : rstd_of(e, (EPI == EPI_LOGITS && e.row_sel) ? e.row_sel[mm] : mm);
-    }
-  }
+  for (int j = 0; j < WTM; ++j) rsj[j] = rstd_s[j * 16 + (lane & 15)];
 #pragma unroll
   for (int j = 0; j < WTM; ++j) {
     const int m = (mt_base + j) * 16 + (lane & 15);
@@ -1099,8 +979,8 @@ static int meet_grid(int tiles, int Z) {
 
 // ---------------------------------------------------------------------------------------------
 // tiled, 4 waves (2x2): wave tile = WTM x WTN fragments, K step 32.  Operands are double-buffered
-// in LDS; global loads run through four register sets, four k-steps ahead.  For the blocks that are
-// too small to keep eight waves busy (128 x 128 and 96 x 128; at 192 x 192 and 192 x 128 eight waves take 0.53 and 0.46
+// in LDS; global loads run through four register sets, four k-steps ahead.  For the blocks of
+// residual products that are too small to keep eight waves busy (128 x 128 and 96 x 128; at 192 x 192 and 192 x 128 eight waves take 0.53 and 0.46
 // us a k-step, four 0.64 and 0.55).
 // grid = (ceil(n-tiles / (2*WTN)), ceil(m-tiles / (2*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
@@ -1127,7 +1007,7 @@ static int meet_grid(int tiles, int Z) {
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf_[i], af_[j], acc[i][j], 0, 0, 0); \
   }
 
-template <int EPI, int WTM, int WTN, bool WS, int Z>
+template <int WTM, int WTN, bool WS, int Z>
 __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __restrict__ Ap,
                                                               const u32x4* __restrict__ Wp,
                                                               int total_nt, int KB_all, int MT,
@@ -1208,22 +1088,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_tiled4_kernel(const u32x4* __re
   if constexpr (WS) scale_acc<WTM, WTN>(e, acc, nt0 + wn * WTN, total_nt, lane);
   if constexpr (Z > 1)
     tiled_meet_resid<2, 2, WTM, WTN, Z>(e, acc, mt0, nt0, total_nt, wave, lane, tile, z, (float*)lds);
-  else if constexpr (EPI == EPI_RESID)
-    tiled_resid<2, 2, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
   else
-    tiled_epilogue<EPI, WTM, WTN>(e, acc, mt0 + wm * WTM, nt0 + wn * WTN, total_nt, lane, nullptr);
+    tiled_resid<2, 2, WTM, WTN>(e, acc, mt0, nt0, total_nt, wave, lane, (float*)lds);
 }
 #undef EC_TILED_GLOAD
 #undef EC_TILED_LSTORE
 #undef EC_TILED_COMPUTE
 
-template <int EPI, bool WS, int Z, int WTM, int WTN>
+template <bool WS, int Z, int WTM, int WTN>
 static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int total_nt, int KB,
                            GemmEpi e, hipStream_t s) {
   dim3 grid((total_nt + 2 * WTN - 1) / (2 * WTN), (e.M + 32 * WTM - 1) / (32 * WTM));
   e.sum_cap = sumsq_cap((long)grid.x * Z);
   if (Z > 1) grid = dim3(meet_grid(grid.x * grid.y, Z));
-  gemm_bf16_tiled4_kernel<EPI, WTM, WTN, WS, Z><<<grid, 256, 0, s>>>((const u32x4*)Ap, (const u32x4*)Wp,
+  gemm_bf16_tiled4_kernel<WTM, WTN, WS, Z><<<grid, 256, 0, s>>>((const u32x4*)Ap, (const u32x4*)Wp,
                                                                  total_nt, KB, MT, e);
 }
 
@@ -1444,27 +1322,24 @@ static void launch_tiled8_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
   kern<<<grid, WM * WN * 64, smem, s>>>((const u32x4*)Ap, (const u32x4*)Wp, total_nt, KB, MT, e);
 }
 
-// Block shapes of the tiled kernels (rows x weight rows) and what one k-step costs on MI355X
-// with all 256 CUs busy (us, measured).
+// Block shapes of the tiled kernels (rows x weight rows).
 //   8 waves: 0: 192 x 384   1: 192 x 256   2: 192 x 192   3: 192 x 128   6: 192 x 320   7: 256 x 256
-//   4 waves: 4: 128 x 128   5: 96 x 128
+//   4 waves: 4: 128 x 128   5: 96 x 128   (residual products only: q k v and gate/up of d 512 and 1536 take 15 - 25 %
+//   longer with them than with 192 x 128 at 112 - 3000 rows, and no less at any other size)
 // What a whole launch loses most by is its last round: shapes 6 and 7 are there for the sizes at which
-// the others leave compute units or rows idle.  us per launch, best of 0 - 5 -> with 6 and 7:
-//   544 rows   gate/up  4096 -> 2 x 12288  192 blocks of 0, 231 of 6             122 -> 107
-//   512 rows   LM head  4096 -> 126464     990 of 0 in 576 rows, 988 of 7        543 -> 481
-//   1280 rows  gate/up  3584 -> 2 x 18944  693 of 0, 740 of 7 (in three rounds)  344 -> 314
-//   1280 rows  down     18944 -> 3584      3 x 70 of 0, 3 x 84 of 6              187 -> 161
-//   3552 rows  O + down                    209 of 0, 247 of 6                    480 -> 436
-//   24576 rows O + down                    2048 of 1, 1536 of 7                  2965 -> 2717
-// Two waves per SIMD overlap one wave's LDS reads and barrier waits with the other's MFMAs.  The wider
-// the block the fewer operand bytes per flop cross L2 and LDS.  A grid that does not fill the 256 CUs in
-// whole rounds wastes the remainder, so narrow outputs (N = d_model) are also split along K over blocks
-// that meet.
+// the others leave compute units or rows idle.  Two waves per SIMD overlap one wave's LDS reads and barrier
+// waits with the other's MFMAs.  The wider the block the fewer operand bytes per flop cross L2 and LDS.  A grid
+// that does not fill the 256 CUs in whole rounds wastes the remainder, so narrow outputs (N = d_model) are
+// also split along K over blocks that meet.
 struct TilePick { int tile, ksplit; };
 constexpr int kNumTiles = 8;
 static const int kTileM[kNumTiles] = {12, 12, 12, 12, 8, 6, 12, 16};
 static const int kTileN[kNumTiles] = {24, 16, 12, 8, 8, 8, 20, 16};
+static const int kTileWaves[kNumTiles] = {8, 8, 8, 8, 4, 4, 8, 8};
+// What a k-step is taken to cost with all 256 CUs busy (us): for residual products as it was measured alone with an
+// earlier main loop (tile_cost), for the others as fitted in whole steps with the present one.
 static const float kTileUsAlone[kNumTiles] = {0.89f, 0.66f, 0.53f, 0.46f, 0.53f, 0.45f, 0.78f, 0.80f};
+static const float kTileUs[kNumTiles] = {0.762f, 0.557f, 0.470f, 0.423f, 0.f, 0.f, 0.651f, 0.656f};
 
 // floats of the pieces that the blocks of K split ks exchange
 static size_t meet_floats(const TilePick& t, int MT, int total_nt) {
@@ -1472,23 +1347,33 @@ static size_t meet_floats(const TilePick& t, int MT, int total_nt) {
          t.ksplit * kTileM[t.tile] * kTileN[t.tile] * 256;
 }
 
-// epi_us: what the epilogue adds per 16 x 16 output fragment of a block (us): the rotation and the
-// cache stores of q k v, the residual stream's read and write, the exchange of a K split (whose blocks run
-// in one round); it does not count the ranges, though two exchange less than four.
-// Against the best of all shapes and splits, by events in whole steps (64 sizes: 112 - 3000 rows, d 512 - 4096,
-// F 2048 - 18944), the pick takes 3 % longer on average for residual products (24 % at most: O, 368
-// rows, pick_rows), 6 % for q k v (21 %: narrow ones, where 192 x 128 beats 96 x 128) and 6 % for gate/up (52 %: 368 rows again).
+// What a launch of block shape i is expected to take beside what all shapes share (us); a K split's blocks run in
+// one round.
+//   Residual products: kTileUsAlone and the epilogue per 16 x 16 output fragment of a block, the residual stream's
+// read and write or the exchange of a K split (the ranges are not counted, though two exchange less than four).
+//   The others: kTileUs, a last round that costs the less the fewer of its compute units work, and the
+// epilogue.  Fitted to every shape's time by events in whole steps (60 sizes: 112 - 24576 rows, d 512 - 4096, F 2048 - 18944).
+// Against the best of all shapes and splits there, the picks take 1.6 % longer on average for residual
+// products (24 % at most: O of 1536 -> 1536 at 1536 rows, where 192 x 128 x 2 beats 192 x 192 x 4), 0.0 % for q k v
+// (1.3 % at most) and 0.2 % for gate/up (7 %).  With the residual products' costs the latter two took 5.7 and 6.1 % (50 %).
+static float tile_cost(int epi, int i, int tiles, int KB, int ks) {
+  const int frags = kTileM[i] * kTileN[i], full = tiles * ks / 256, rest = tiles * ks % 256;
+  if (epi == EPI_RESID)
+    return (full + (rest > 0)) * ((KB + ks - 1) / ks * kTileUsAlone[i] + 5.0f + (ks > 1 ? 0.07f : 0.008f) * frags);
+  const float loop = KB * kTileUs[i], ends = epi == EPI_QKV ? 1.1f + 0.045f * frags : 0.026f * frags;
+  return full * (loop + ends) + (rest ? loop * (0.76f + 0.24f / 256 * rest) + ends : 0.f);
+}
+
 static TilePick pick_tile(int epi, int MT, int total_nt, int KB, int max_ksplit, size_t piece_floats) {
   TilePick best{1, 1};
   float best_t = 1e30f;
   for (int i = 0; i < kNumTiles; ++i) {
+    if (kTileWaves[i] == 4 && epi != EPI_RESID) continue;
     const int gm = (MT + kTileM[i] - 1) / kTileM[i], gn = (total_nt + kTileN[i] - 1) / kTileN[i], tiles = gm * gn;
     for (int ks = 1; ks <= max_ksplit && ks <= KB; ++ks) {
       if (ks > 1 && (tiles > kMeetSlots || meet_floats(TilePick{i, ks}, MT, total_nt) > piece_floats)) break;
-      const int rounds = (tiles * ks + 255) / 256;
-      if (ks > 1 && rounds > 1) break;
-      const float epi_us = ks > 1 ? 0.07f : epi == EPI_QKV ? 0.064f : epi == EPI_RESID ? 0.008f : 0.f;
-      const float t = rounds * ((KB + ks - 1) / ks * kTileUsAlone[i] + 5.0f + epi_us * kTileM[i] * kTileN[i]);
+      if (ks > 1 && tiles * ks > 256) break;
+      const float t = tile_cost(epi, i, tiles, KB, ks);
       if (t < best_t) { best_t = t; best = TilePick{i, ks}; }
     }
   }
@@ -1505,8 +1390,8 @@ static void launch_tiled_pick_ws(const bf16_t* Ap, int MT, const bf16_t* Wp, int
     case 1: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 2: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 3>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 3: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 2>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 4: launch_tiled4_t<EPI, WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
-    case 5: launch_tiled4_t<EPI, WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 4: if constexpr (EPI == EPI_RESID) launch_tiled4_t<WS, Z, 4, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
+    case 5: if constexpr (EPI == EPI_RESID) launch_tiled4_t<WS, Z, 3, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
     case 6: launch_tiled8_t<EPI, WS, Z, 2, 4, 6, 5>(Ap, MT, Wp, total_nt, KB, e, s); break;
     default: launch_tiled8_t<EPI, WS, Z, 2, 4, 8, 4>(Ap, MT, Wp, total_nt, KB, e, s); break;
   }
@@ -1526,16 +1411,14 @@ static void launch_tiled_pick_z(const bf16_t* Ap, int MT, const bf16_t* Wp, int 
   launch_tiled_pick_ws<EPI, WS, 1>(Ap, MT, Wp, total_nt, KB, e, s, tp.tile);
 }
 
-// The row tiles that the shape is picked for: those of the padded row list, unless a third of it or more is
-// padding (272 rows in a list of 512, down projection of 4096: 192 x 256 x 4 65.8 us, 192 x 128 x 4 55.7).  Only tiles
-// that hold rows are computed either way, so below that third the shape can be one for rows that are not there.
-// us of a layer's four products, by events in whole steps, as picked -> picked for the rows themselves:
-//   d 4096, F 12288   368 rows 270 -> 234   528 290 -> 285   848 426 -> 403   944 437 -> 416
-//   d 3584, F 18944   368 rows 319 -> 265   528 357 -> 331   848 462 -> 431   1328 618 -> 591
-// and the same at multiples of 256.
-static int pick_rows(int M_src, int M) {
+// The row tiles that the shape is picked for.  Only tiles that hold rows are computed, so it is the rows' own, from
+// 16 k-steps on: 368 rows, gate/up of d 4096 88 -> 72 us, of 3584 132 -> 88; 848 rows 167 -> 147 and 222 -> 185.
+// Residual products, whose costs were fitted to the padded row list, and the few microseconds of a shorter K keep to
+// that, unless a third of it or more is padding (272 rows in a list of 512, down projection of 4096: 192 x 256 x 4
+// 65.8 us, 192 x 128 x 4 55.7).
+static int pick_rows(int epi, int M_src, int M, int KB) {
   const int padded = (M_src + 15) / 16, rows = (M + 15) / 16;
-  return 3 * rows <= 2 * padded ? rows : padded;
+  return (epi != EPI_RESID && KB >= 16) || 3 * rows <= 2 * padded ? rows : padded;
 }
 
 // row tiles up to which a product goes to the weight-streaming kernels (gathered LM-head rows: 64 at most)
@@ -1548,7 +1431,7 @@ static int max_ksplit(int epi, const GemmEpi& e) {
 
 bool gemm_bf16_block_shape(int epi, int M_src, int M, int N, int K, size_t piece_floats, int shape[3]) {
   if (streams_weights(epi, (M + 15) / 16)) return false;
-  const TilePick tp = pick_tile(epi, pick_rows(M_src, M), N / 16, K / 32, epi == EPI_RESID ? kMaxKSplit : 1, piece_floats);
+  const TilePick tp = pick_tile(epi, pick_rows(epi, M_src, M, K / 32), N / 16, K / 32, epi == EPI_RESID ? kMaxKSplit : 1, piece_floats);
   shape[0] = kTileM[tp.tile] * 16; shape[1] = kTileN[tp.tile] * 16; shape[2] = tp.ksplit;
   return true;
 }
@@ -1583,7 +1466,7 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
   } else {
     // the tiled kernel reads its activation rows in place (no gather); only the tiles that hold rows
     // below e.M are computed (the buffer is padded to 256 rows), and rows from e.M on are dropped
-    const TilePick tp = pick_tile(EPI, pick_rows(M_src, e.M), total_nt, KB, max_ksplit(EPI, e), e.partial_floats);
+    const TilePick tp = pick_tile(EPI, pick_rows(EPI, M_src, e.M, KB), total_nt, KB, max_ksplit(EPI, e), e.partial_floats);
     if (e.wscale) launch_tiled_pick_z<EPI, true>(Ap, MT_src, Wp, total_nt, KB, e, s, tp);
     else launch_tiled_pick_z<EPI, false>(Ap, MT_src, Wp, total_nt, KB, e, s, tp);
   }
