@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
           if (ok[u] && d == 0.f && pi < v.idx) v.idx = pi;       // lowest index among equal maxima
         }
       }
-      v = vt_merge_half(v);
+      v = vt_merge_lanes<32>(v);
       if (live && l32 == 0) {
         float conf, H;
         vt_finish(v, conf, H);

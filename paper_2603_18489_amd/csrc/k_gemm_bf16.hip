@@ -208,8 +208,12 @@ __device__ __forceinline__ void epi_qkv(const GemmEpi& e, int m, int vt, int q4,
 // 64 k per weight tile and k-step; a lane's 16 bytes are turned into two bf16 MFMA operands in
 // registers (exact), so a k-step is two MFMAs per (weight tile, m-tile) on two activation
 // fragments, KB counts 64-wide steps, and the per-row scales multiply the K-reduced sums.
+// The LM head of up to 32 rows keeps to 256 registers, with one k-step to a register set: two blocks to a compute unit, one
+// streaming while the other is in its epilogue.  (8 tiles with two steps to a set take 264 and run alone, four rounds of
+// blocks one after the other.)  us by events: 32 rows, 4096 -> 126464 186 -> 179; 3584 -> 152064 207 -> 195.
+constexpr int skinny_waves(int epi, int MT) { return epi == EPI_LOGITS && MT <= 2 ? 2 : 1; }
 template <int EPI, int MT, int NTW, int KS, int U, bool W8 = false>
-__global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* __restrict__ Ap,
+__global__ __launch_bounds__(KS * 64, skinny_waves(EPI, MT)) void gemm_bf16_skinny_kernel(const u32x4* __restrict__ Ap,
                                                                    const u32x4* __restrict__ Wp,
                                                                    int total_nt, int KB,
                                                                    int MT_src, GemmEpi e) {
@@ -406,10 +410,9 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
     // sit in the 4 lanes l, l^16, l^32, l^48 (4 columns each): maximum and lowest index holding
     // it through two lane swaps, then sum e^(z-max) and sum e^(z-max)(z-max) relative to that
     // maximum (added pairwise, the same pairs in all four lanes, so they agree bit for bit);
-    // after a barrier one thread per row merges the NTW tiles in tile order and stores the
-    // block's tuple.
+    // after a barrier a row's NTW tuples are merged by as many lanes into the block's.
     float4* tup = (float4*)(rstd_s + MT * 16);  // [NTW][MT*16]
-    for (int o = threadIdx.x; o < UNITS; o += KS * 64) {  // UNITS is a multiple of the block size
+    for (int o = threadIdx.x; o < UNITS; o += KS * 64) {  // (UNITS is a multiple of the wave)
       const int l = o & 63, unit = o >> 6, iu = unit / MT, j = unit - iu * MT;
       const int m = j * 16 + (l & 15), q4 = l >> 4, vt = nt0 + iu;
       const f32x4 v = ksum((iu * MT + j) * 64 + l, iu, q4);
@@ -440,11 +443,11 @@ __global__ __launch_bounds__(KS * 64) void gemm_bf16_skinny_kernel(const u32x4* 
                                                 : vt_pack(vt_identity());
     }
     __syncthreads();
-    if (threadIdx.x < MT * 16 && (int)threadIdx.x < e.M) {
-      VTuple t = vt_unpack(tup[threadIdx.x]);
-#pragma unroll
-      for (int iu = 1; iu < NTW; ++iu) t = vt_merge(t, vt_unpack(tup[iu * (MT * 16) + threadIdx.x]));
-      e.vparts[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = vt_pack(t);
+    // (a lane for every tuple; whole waves, so that a row's lanes are there together)
+    for (int o = threadIdx.x; o < MT * 16 * NTW; o += KS * 64) {
+      const int m = o / NTW;
+      const VTuple t = vt_merge_lanes<NTW>(vt_unpack(tup[o % NTW * (MT * 16) + m]));
+      if (o % NTW == 0 && m < e.M) e.vparts[(size_t)m * gridDim.x + blockIdx.x] = vt_pack(t);
     }
     return;
   }
@@ -529,13 +532,17 @@ static void launch_skinny_t(const bf16_t* Ap, int MT_src, const void* Wp, int to
 // Tile counts per block were chosen by timing on MI355X: the kernels are bound by what the L2
 // delivers (weights once + the activation fragments once per block), so more weight tiles per
 // block (fewer re-reads of the activations) win as long as the grid still covers the 256 CUs.
+// Weight tiles (of 16 vocabulary columns) to a block of the skinny LM head: eight, whose activations are
+// then read the fewest times, where that fills the chip, fewer where it leaves compute units without a block.  us by events,
+// 32 rows: vocabulary 126464, d 4096: 4 tiles 191, 8 179;  152064 of 3584: 207, 195;  4096 of 256 (32 blocks of eight):
+// 8 tiles 8.5, 4 tiles 7.3, 2 tiles 6.5.
+static int lm_tiles(int total_nt) { return total_nt >= 8 * 256 ? 8 : total_nt >= 4 * 256 ? 4 : 2; }
 // blocks (= partial tuples per row) of the skinny LM-head GEMM over a vocabulary of V columns
-constexpr int kLmTiles = 8;  // weight tiles (of 16 vocabulary columns) per LM-head block
-int lm_head_parts(int V) { return (V / 16 + kLmTiles - 1) / kLmTiles; }
+int lm_head_parts(int V) { const int t = lm_tiles(V / 16); return (V / 16 + t - 1) / t; }
 
 int skinny_tiles_per_block(int epi, int total_nt) {
   if (epi == EPI_RESID) return 1;
-  if (epi == EPI_LOGITS) return kLmTiles;
+  if (epi == EPI_LOGITS) return lm_tiles(total_nt);
   if (total_nt >= 6 * 256) return 6;
   if (total_nt >= 3 * 256) return 3;
   return total_nt >= 2 * 256 ? 2 : 1;
@@ -565,7 +572,11 @@ template <int EPI, int MT>
 static void launch_skinny_mt_w8(const bf16_t* Ap, int MT_src, const void* Wq, int total_nt,
                                 int KB, const GemmEpi& e, hipStream_t s) {
   if constexpr (EPI == EPI_LOGITS) {
-    launch_skinny_t<EPI, MT, kLmTiles, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s);
+    switch (lm_tiles(total_nt)) {
+      case 8: launch_skinny_t<EPI, MT, 8, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s); break;
+      case 4: launch_skinny_t<EPI, MT, 4, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s); break;
+      default: launch_skinny_t<EPI, MT, 2, 4, 1, true>(Ap, MT_src, Wq, total_nt, KB, e, s); break;
+    }
   } else if constexpr (EPI == EPI_RESID) {
     if constexpr (MT > 1) {
       if (skinny_splits(MT, KB * 64, e)) {
@@ -590,7 +601,11 @@ template <int EPI, int MT>
 static void launch_skinny_mt(const bf16_t* Ap, int MT_src, const bf16_t* Wp, int total_nt, int KB,
                              const GemmEpi& e, hipStream_t s) {
   if constexpr (EPI == EPI_LOGITS) {
-    launch_skinny_t<EPI, MT, kLmTiles, 4, (MT > 2 ? 1 : 2)>(Ap, MT_src, Wp, total_nt, KB, e, s);
+    switch (lm_tiles(total_nt)) {
+      case 8: launch_skinny_t<EPI, MT, 8, 4, 1>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
+      case 4: launch_skinny_t<EPI, MT, 4, 4, 2>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
+      default: launch_skinny_t<EPI, MT, 2, 4, 2>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
+    }
   } else if constexpr (EPI == EPI_RESID) {
     if constexpr (MT > 1) {
       if (skinny_splits(MT, KB * 32, e)) {
@@ -1446,8 +1461,8 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
       case 2: launch_skinny_mt_w8<EPI, 2>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
       case 3: launch_skinny_mt_w8<EPI, 3>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
       case 4: launch_skinny_mt_w8<EPI, 4>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
-      case 5: launch_skinny_mt_w8<EPI, 5>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
-      default: launch_skinny_mt_w8<EPI, 6>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
+      case 5: if constexpr (EPI != EPI_LOGITS) launch_skinny_mt_w8<EPI, 5>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
+      default: if constexpr (EPI != EPI_LOGITS) launch_skinny_mt_w8<EPI, 6>(Ap, MT_src, Wq, total_nt, K / 64, e, s); break;
     }
     return;
   }
@@ -1460,8 +1475,8 @@ static void launch_epi(const bf16_t* Ap, int M_src, const bf16_t* Wp, const void
       case 2: launch_skinny_mt<EPI, 2>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
       case 3: launch_skinny_mt<EPI, 3>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
       case 4: launch_skinny_mt<EPI, 4>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
-      case 5: launch_skinny_mt<EPI, 5>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
-      default: launch_skinny_mt<EPI, 6>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
+      case 5: if constexpr (EPI != EPI_LOGITS) launch_skinny_mt<EPI, 5>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
+      default: if constexpr (EPI != EPI_LOGITS) launch_skinny_mt<EPI, 6>(Ap, MT_src, Wp, total_nt, KB, e, s); break;
     }
   } else {
     // the tiled kernel reads its activation rows in place (no gather); only the tiles that hold rows

@@ -89,24 +89,33 @@ __device__ __forceinline__ VTuple vt_shfl_down(const VTuple& v, int o) {
   return r;
 }
 
-// The 32 tuples of a half wave merged at once: every lane re-bases its own to the common maximum
-// (one exponential), then the sums go through lane exchanges.  All lanes of the half return the result.
-__device__ __forceinline__ VTuple vt_merge_half(const VTuple& v) {
+// The tuples of N neighbouring lanes (2, 4, 8, 16 or 32) merged at once: every lane re-bases its own to the
+// common maximum (one exponential), then the sums go through lane exchanges.  All N lanes return the result.
+template <int N> __device__ __forceinline__ VTuple vt_merge_lanes(const VTuple& v) {
   VTuple r;
   float m = v.m;
-  m = fmaxf(m, dpp_f<0xB1>(m)); m = fmaxf(m, dpp_f<0x4E>(m));
-  m = fmaxf(m, dpp_f<0x141>(m)); m = fmaxf(m, dpp_f<0x140>(m));
-  r.m = fmaxf(m, other_row(m));
+  m = fmaxf(m, dpp_f<0xB1>(m));
+  if (N > 2) m = fmaxf(m, dpp_f<0x4E>(m));
+  if (N > 4) m = fmaxf(m, dpp_f<0x141>(m));
+  if (N > 8) m = fmaxf(m, dpp_f<0x140>(m));
+  if (N > 16) m = fmaxf(m, other_row(m));
+  r.m = m;
   int idx = v.s != 0.f && v.m == r.m ? v.idx : INT_MAX;
-  idx = min(idx, dpp_i<0xB1>(idx)); idx = min(idx, dpp_i<0x4E>(idx));
-  idx = min(idx, dpp_i<0x141>(idx)); idx = min(idx, dpp_i<0x140>(idx));
-  r.idx = min(idx, __float_as_int(other_row(__int_as_float(idx))));
+  idx = min(idx, dpp_i<0xB1>(idx));
+  if (N > 2) idx = min(idx, dpp_i<0x4E>(idx));
+  if (N > 4) idx = min(idx, dpp_i<0x141>(idx));
+  if (N > 8) idx = min(idx, dpp_i<0x140>(idx));
+  if (N > 16) idx = min(idx, __float_as_int(other_row(__int_as_float(idx))));
+  r.idx = idx;
   const float d = v.m - r.m, e = expf(d);
   float s = v.s != 0.f ? v.s * e : 0.f, t = v.s != 0.f ? e * (v.t + d * v.s) : 0.f;
-  s += dpp_f<0xB1>(s); s += dpp_f<0x4E>(s); s += dpp_f<0x141>(s); s += dpp_f<0x140>(s);
-  t += dpp_f<0xB1>(t); t += dpp_f<0x4E>(t); t += dpp_f<0x141>(t); t += dpp_f<0x140>(t);
-  r.s = s + other_row(s);
-  r.t = t + other_row(t);
+  s += dpp_f<0xB1>(s); t += dpp_f<0xB1>(t);
+  if (N > 2) { s += dpp_f<0x4E>(s); t += dpp_f<0x4E>(t); }
+  if (N > 4) { s += dpp_f<0x141>(s); t += dpp_f<0x141>(t); }
+  if (N > 8) { s += dpp_f<0x140>(s); t += dpp_f<0x140>(t); }
+  if (N > 16) { s += other_row(s); t += other_row(t); }
+  r.s = s;
+  r.t = t;
   return r;
 }
 __device__ __forceinline__ float4 vt_pack(const VTuple& v) {

@@ -572,6 +572,22 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
 
 
+@pytest.mark.parametrize("dtype,tiles,block", [
+    ("bf16", 33, 9), ("bf16", 1023, 20), ("fp8w", 1023, 40), ("bf16", 1023, 64),    # two weight tiles to a block
+    ("bf16", 1025, 9), ("fp8w", 1026, 20), ("bf16", 2047, 40), ("bf16", 1027, 64),  # four
+    ("bf16", 2049, 9), ("fp8w", 2051, 20), ("bf16", 2055, 40),                      # eight
+])
+def test_lm_head_tiles_to_a_block(dtype, tiles, block):
+    """The few-row LM head at each number of weight tiles to a block, the last block part empty, with one to four row
+    tiles: logits and the vocabulary reduction merged from the blocks' tiles."""
+    cfg = small_cfg(dtype, 4, 2, 64, d=64, f=64, vocab=16 * tiles, layers=1, scale=24.0)
+    w = ec_inputs.make_weights(cfg, 137, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=block + 3, block=block, k_recent=2, tokens_per_step=2, tau=1e9)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 12, 6), TOL[dtype], max_steps=3)
+    print(s)
+    assert s["rows_stat"] > 0
+
+
 @pytest.mark.parametrize("d", [32, 64, 96, 128, 160, 192])
 def test_tiled_gemm_ranges_around_the_operand_ring(d):
     """One to six k-steps through the 8-wave kernels, whose ring holds four and is filled three ahead."""
