@@ -46,8 +46,9 @@ struct Buffers {
   int* x; uint8_t* masked; int* hist; DevState* st; int* mb_pos; int* rows_partial; int* mb_idx;
   float* row_stats; int* prompt;
   // the step's row list (bf16 path)
-  SeqDesc* seqs; int4* rowinfo; int4* tileinfo; int* lm_sel;
-  int4* pairs;  // (row tile, sequence) visits of the few-row sequences, [rmax/16 + B]
+  SeqDesc* seqs; int4* rowinfo; int* lm_sel;
+  int4* pairs;  // [B] few-row sequences, their (row tile, sequence) visits and the many-row sequences' groups of row
+                // tiles, [rmax/16 + B] together
   float2* rope_cs;
   char* kv;  // [L][2] planes; a plane holds every sequence's [Hkv][keys][hd] slabs, storage type
   size_t kv_plane;  // elements per plane
@@ -122,7 +123,7 @@ void carve(Carver& c, const ec_model_cfg& m, const ec_decode_cfg& d, const Geome
   static_assert(sizeof(SeqDesc) % sizeof(int4) == 0, "pairs follow seqs");
   char* tab = c.take<char>((size_t)B * sizeof(SeqDesc) + (R / 16 + 2 * B) * sizeof(int4));
   b.seqs = (SeqDesc*)tab; b.pairs = tab ? (int4*)(tab + (size_t)B * sizeof(SeqDesc)) : nullptr;
-  b.rowinfo = c.take<int4>(R); b.tileinfo = c.take<int4>(R / 16);
+  b.rowinfo = c.take<int4>(R);
   b.lm_sel = c.take<int>(BL);
   b.rope_cs = c.take<float2>((size_t)g.tmax * (m.head_dim / 2));
   b.kv_plane = g.kv_plane;
@@ -405,10 +406,11 @@ int upload_and_init_state(ec_ctx* c, const int32_t* prompt_ids) {
 // What the host worked out for one step.
 struct StepPlan {
   int R = 0, n_lm = 0;                      // rows of the list (with padding), masked block rows
-  bool has_small = false, has_large = false;
+  bool has_small = false;
   int max_T_small = 1;
   int npairs = 0;                           // (row tile, sequence) visits of few-row sequences
   int nsmall = 0, max_visits = 0;           // few-row sequences; most visits of one of them
+  int rows_shape = 0, groups = 0;           // many-row sequences: blocks of their attention, groups of row tiles
   bool single = false;                      // one sequence takes part: one_seq is its tile entry
   int4 one_seq = make_int4(0, 0, 32, 0);
   int64_t rows = 0;                         // sum of the sequences' own row counts
@@ -491,7 +493,7 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
     sl.rows_partial = b.rows_partial; sl.mb_pos = b.mb_pos; sl.mb_idx = b.mb_idx;
     sl.vocab = m.vocab;
     sl.meet = b.meet; sl.n_meet = 2 * L * kMeetSlots;
-    sl.block = c->d.block; sl.rowinfo = b.rowinfo; sl.tileinfo = b.tileinfo; sl.lm_sel = b.lm_sel;
+    sl.block = c->d.block; sl.rowinfo = b.rowinfo; sl.lm_sel = b.lm_sel;
     launch_step_prologue_bf16(sl, G(c->w.tok_emb), d, G(c->attn_norm[0]), b.h, u, b.sumsq,
                               (2 * L + 1) * kSumSlots, b.sumsq_stride, s); }
   for (int l = 0; l < L; ++l) {
@@ -503,10 +505,10 @@ int forward_bf16(ec_ctx* c, const StepPlan& sp) {
       e.w_grp = skinny_tiles_per_block(EPI_QKV, nqkv / 16); e.wscale = b.pl[l].sqkv;
       launch_gemm_bf16(EPI_QKV, u, R, b.pl[l].wqkv, b.pl[l].qqkv, nqkv, d, e, s); }
     { Scope p(c, EC_K_ATTN);
-      launch_attention_mfma(q, kc, vc, R, b.rowinfo, sp.single ? nullptr : b.tileinfo,
-                            sp.single ? nullptr : b.pairs + c->B, sp.npairs,
+      launch_attention_mfma(q, kc, vc, R, b.rowinfo, sp.single ? nullptr : b.pairs + c->B + sp.npairs,
+                            sp.rows_shape, sp.groups, sp.single ? nullptr : b.pairs + c->B, sp.npairs,
                             sp.single ? nullptr : b.pairs, sp.nsmall, sp.max_visits, sp.one_seq,
-                            sp.has_small, sp.has_large, sp.max_T_small, m.n_heads, m.n_kv_heads, hd,
+                            sp.has_small, sp.max_T_small, m.n_heads, m.n_kv_heads, hd,
                             attn, b.ksplit_part, b.ksplit_floats, b.attn_tickets, s); }
     { Scope p(c, EC_K_OPROJ);
       GemmEpi e{}; e.M = M; e.MT = MT; e.h = b.h; e.d = d; e.gain_next = G(c->mlp_norm[l]);
@@ -590,6 +592,7 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
   }
   // ---- the step's row list: many-row sequences first -------------------------------------------
   StepPlan sp;
+  std::vector<AttnSeq> many;
   for (int pass = 0; pass < 2; ++pass) {
     foff = 0;
     for (int b = 0; b < B; ++b) {
@@ -615,7 +618,8 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
         if (sp.npairs - first > sp.max_visits) sp.max_visits = sp.npairs - first;
       }
       sp.R += sd.seg_rows; sp.rows += n_rows;
-      (large ? sp.has_large : sp.has_small) = true;
+      if (large) many.push_back(AttnSeq{(n_rows + 15) / 16, c->g.T[b]});
+      else sp.has_small = true;
       if (!large && c->g.T[b] > sp.max_T_small) sp.max_T_small = c->g.T[b];
       (mode[b] == EC_FULL ? sp.n_full : sp.n_partial) += 1;
       if (fn > 0) {
@@ -633,9 +637,26 @@ int run_step(ec_ctx* c, const int32_t* modes, int modes_n, const int32_t* forced
     }
   sp.single = sp.n_full + sp.n_partial == 1;
   sp.R = (sp.R + 15) / 16 * 16;
+  if (!many.empty()) {
+    sp.rows_shape = pick_attn_rows(many.data(), (int)many.size(), c->m.n_heads);
+    const int per = attn_rows_tiles(sp.rows_shape);
+    if (sp.single) {
+      sp.groups = (many[0].tiles + per - 1) / per;
+    } else {
+      // behind the visits: every many-row sequence's tiles, then those of its padding that no group of them takes along
+      int4* tab = c->host_pairs + B + sp.npairs;
+      for (int b = 0; b < B; ++b) {
+        const SeqDesc& sd = c->host_seqs[b];
+        if (mode[b] < 0 || sd.n_rows <= kSmallRows) continue;
+        const int used = (sd.n_rows + 15) / 16;
+        for (int t = 0; t < sd.seg_rows / 16; t += per)
+          tab[sp.groups++] = make_int4(sd.row0 / 16 + t, sd.kv_off, t < used ? sd.T : 0, sd.tpad);
+      }
+    }
+  }
   if (B > 1) {
-    const size_t npairs = !sp.single && sp.npairs > 0 ? B + sp.npairs : 0;
-    EC_HIP(c, hipMemcpyAsync(c->b.seqs, c->host_seqs, B * sizeof(SeqDesc) + npairs * sizeof(int4),
+    const size_t entries = !sp.single ? B + sp.npairs + sp.groups : 0;
+    EC_HIP(c, hipMemcpyAsync(c->b.seqs, c->host_seqs, B * sizeof(SeqDesc) + entries * sizeof(int4),
                              hipMemcpyHostToDevice, c->stream));
   }
   // ---- forward, vocabulary reduction, decision ---------------------------------------------------

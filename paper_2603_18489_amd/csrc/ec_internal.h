@@ -180,8 +180,7 @@ struct GemmEpi {
 };
 
 // First kernel of a step.  From the sequence table it writes the step's row list (rowinfo, one
-// int4 per row as GemmEpi describes; tileinfo, one int4 per 16 rows: cache offset, positions,
-// keys per slab, 1 if the sequence has more than kSmallRows rows) and lm_sel (for each masked
+// int4 per row as GemmEpi describes) and lm_sel (for each masked
 // row of a current block, its row in the list); then, per row, h = Emb[x], packed bf16(h * gain)
 // for the first GEMM, the row's sum of squares into sumsq[0..R) and zeros into the nbuf-1
 // further sum buffers (stride sumsq_stride) of the step.  Padding rows get zeros.
@@ -195,7 +194,7 @@ struct StepLists {
   const int* mb_pos;            // stride block
   const int* mb_idx;            // stride block
   int block;
-  int4* rowinfo; int4* tileinfo; int* lm_sel;
+  int4* rowinfo; int* lm_sel;
   int4* meet; int n_meet;       // the step's MeetSlots: zeroed (as int4)
 };
 void launch_step_prologue_bf16(const StepLists& L, const bf16_t* emb, int d, const bf16_t* gain,
@@ -239,17 +238,21 @@ void launch_repack_rows_f32(const float* src, int N, float* dst, int mode, int h
 // q row-major [M, Hq*hd]; packed caches of one layer; out packed bf16 (K = Hq*hd).
 // part / tickets: scratch for splitting the keys over blocks when there are few query rows
 // (part_floats floats; 256 counters, zero on entry and again on exit); null = never split.
-// R rows (rowinfo / tileinfo as the step prologue wrote them), kc / vc: one layer's planes.
+// R rows (rowinfo as the step prologue wrote it), kc / vc: one layer's planes.
+// Sequences with more than kSmallRows rows: `groups` groups of attn_rows_tiles(rows_shape) row tiles; grouptab has an entry
+// for each (first row tile, cache offset, positions or 0 for nothing but padding rows, keys per slab).
 // Sequences with at most kSmallRows rows are served through `pairs`: npairs entries (row tile,
 // cache offset, positions, keys per slab), one for every sequence a row tile holds rows of.
-// pairs (and tileinfo) may be NULL when the step has a single sequence: then one_seq (cache
-// offset, positions, keys per slab, many-rows flag) describes every tile.  has_small /
-// has_large: whether any sequence of the step has at most / more than kSmallRows rows; max_T:
-// most positions of any few-row sequence taking part.
-void launch_attention_mfma(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int R,
-                           const int4* rowinfo, const int4* tileinfo, const int4* pairs,
+// grouptab and pairs may be NULL when the step has a single sequence: then one_seq (cache
+// offset, positions, keys per slab, many-rows flag) describes every tile.  has_small: whether any sequence of the step
+// has at most kSmallRows rows; max_T: most positions of any few-row sequence taking part.
+struct AttnSeq { int tiles, keys; };   // a many-row sequence: row tiles that hold rows, positions
+int pick_attn_rows(const AttnSeq* seqs, int n, int Hq);   // the block shape for these sequences
+int attn_rows_tiles(int shape);
+void launch_attention_mfma(const bf16_t* q, const bf16_t* kc, const bf16_t* vc, int R, const int4* rowinfo,
+                           const int4* grouptab, int rows_shape, int groups, const int4* pairs,
                            int npairs, const int4* seqtab, int nsmall, int max_visits,
-                           int4 one_seq, bool has_small, bool has_large, int max_T,
+                           int4 one_seq, bool has_small, int max_T,
                            int Hq, int Hkv, int hd, bf16_t* out, float* part, size_t part_floats,
                            int* tickets, hipStream_t s);
 

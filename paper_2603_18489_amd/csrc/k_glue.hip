@@ -43,7 +43,6 @@ __global__ __launch_bounds__(256) void step_prologue_bf16_kernel(
   const int r = blockIdx.x;
   if (threadIdx.x == 0) {
     int4 ri = make_int4(-1, -1, 0, 32);
-    int4 ti = make_int4(0, 0, 32, 0);
     for (int b = 0; b < L.B; ++b) {
       const SeqDesc sd = L.seqs ? L.seqs[b] : L.seq0;
       if (sd.mode < 0 || r < sd.row0 || r >= sd.row0 + sd.seg_rows) continue;
@@ -51,10 +50,8 @@ __global__ __launch_bounds__(256) void step_prologue_bf16_kernel(
       int pos = -1;
       if (i < sd.n_rows) pos = sd.mode == EC_FULL ? i : L.rows_partial[sd.x_off + i];
       ri = make_int4(pos, pos >= 0 ? sd.x_off + pos : -1, sd.kv_off, sd.tpad);
-      ti = make_int4(sd.kv_off, sd.T, sd.tpad, sd.n_rows > kSmallRows ? 1 : 0);
     }
     L.rowinfo[r] = ri;
-    if ((r & 15) == 0) L.tileinfo[r >> 4] = ti;
     sh_xidx = ri.y;
     if (r < L.n_lm) {
       for (int b = 0; b < L.B; ++b) {

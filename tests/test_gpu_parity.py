@@ -572,6 +572,26 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
 
 
+@pytest.mark.parametrize("hq,hkv,hd,plens", [
+    # eight tiles to a block: sequences of 7 to 17 row tiles, one of whole groups
+    (4, 2, 64, [72, 88, 216, 217, 90]),
+    (4, 4, 128, [231, 56, 200]),
+    # twelve, from enough blocks on: groups that end in the next sequence or in padding, and whole ones
+    (16, 16, 64, [530, 537, 520, 471, 536, 529, 344, 535, 530, 533]),
+    (16, 4, 128, [530, 472, 537, 520, 535, 529, 536, 504, 530, 533]),
+])
+def test_many_row_attention_of_ragged_batches(hq, hkv, hd, plens):
+    """Attention of full steps, whose blocks take eight or twelve row tiles of one sequence: the tiles of a sequence's last block
+    that belong to the next one or hold padding rows only."""
+    cfg = small_cfg("bf16", hq, hkv, hd, d=64, f=64, vocab=512, layers=2, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 139, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(batch=len(plens), gen_len=40, block=20, k_recent=2, tokens_per_step=1, tau=1e9)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, P, 20 + i) for i, P in enumerate(plens)]
+    s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL["bf16"], max_steps=2)
+    print(s)
+    assert s["modes"][eco.FULL] == len(plens) and s["rows_stat"] > 0
+
+
 @pytest.mark.parametrize("dtype,tiles,block", [
     ("bf16", 33, 9), ("bf16", 1023, 20), ("fp8w", 1023, 40), ("bf16", 1023, 64),    # two weight tiles to a block
     ("bf16", 1025, 9), ("fp8w", 1026, 20), ("bf16", 2047, 40), ("bf16", 1027, 64),  # four
