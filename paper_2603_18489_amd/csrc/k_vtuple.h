@@ -35,16 +35,27 @@ __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
   return r;
 }
 
+// e^d for -200 <= d <= 0, to about an ulp: 2^t for the rounded product t = d log2 e, times 1 + (d - t ln 2).
+__device__ __forceinline__ float exp_of_negative(float d) {
+  const float t = d * 1.44269502f;
+  const float r = fmaf(t, -1.90465421e-9f, fmaf(t, -0.693147182f, d));   // (ln 2 = 0.693147182 + 1.90465e-9 - ...)
+  const float e = __builtin_amdgcn_exp2f(t);
+  return fmaf(e, r, e);
+}
+
 // Tuple of NE * 64 consecutive logits held by one wave (lane l: elements first + 64 u + l, -inf for
-// those past the end).  The maximum and its lowest index come first, so every logit then costs one
-// exponential and no branch.  A logit of -inf has probability 0 and contributes 0 (0 ln 0 := 0); a
+// those past the end).  The maximum comes first, so every logit then costs one exponential and no branch.  A logit of -inf has probability 0 and contributes 0 (0 ln 0 := 0); a
 // NaN makes the sums NaN.  All lanes return the same tuple.
 template <int NE>
 __device__ __forceinline__ VTuple vt_of_wave(const float (&z)[NE], int first) {
+  static_assert(NE % 4 == 0, "taken four at a time");
   const int lane = threadIdx.x & 63;
-  float m = z[0];
+  float four[NE / 4], m = -INFINITY;
 #pragma unroll
-  for (int u = 1; u < NE; ++u) m = fmaxf(m, z[u]);
+  for (int g = 0; g < NE / 4; ++g) {
+    four[g] = fmaxf(fmaxf(z[4 * g], z[4 * g + 1]), fmaxf(z[4 * g + 2], z[4 * g + 3]));
+    m = fmaxf(m, four[g]);
+  }
   VTuple v;
   v.m = wave_max_dpp(fmaxf(m, -INFINITY));   // (a lane of NaNs must not hand one on)
   if (!(fabsf(v.m) < INFINITY)) {
@@ -65,28 +76,35 @@ __device__ __forceinline__ VTuple vt_of_wave(const float (&z)[NE], int first) {
     v.t = n_other > 0 || n_inf > 1 ? __builtin_nanf("") : 0.f;
     return v;
   }
-  int u_first = NE;
   float s = 0.f, t = 0.f;
+  unsigned long long nan = 0;
 #pragma unroll
   for (int u = NE - 1; u >= 0; --u) {
-    u_first = z[u] == v.m ? u : u_first;
-    const float d = z[u] - v.m, e = expf(d);
+    if (u & 1) nan |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(z[u], z[u - 1]));
+    const float d = fmaxf(z[u] - v.m, -200.f), e = exp_of_negative(d);   // (-inf: e = 0; a NaN is seen above)
     s += e;
-    t = fmaf(e, fmaxf(d, -1e30f), t);        // (-inf: e = 0; a NaN is in e)
+    t = fmaf(e, d, t);
   }
-  v.idx = wave_min_dpp(u_first < NE ? first + u_first * 64 + lane : INT_MAX);
+  // The lowest index that holds the maximum: the lowest four of the lanes' elements that have it, then the lowest of these.
+  int at = 0;
+#pragma unroll
+  for (int g = NE / 4 - 1; g >= 0; --g)
+    if (__builtin_amdgcn_ballot_w64(four[g] == v.m)) {
+#pragma unroll
+      for (int u = 4 * g + 3; u >= 4 * g; --u) {
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(z[u] == v.m);
+        at = has ? u * 64 + __builtin_ctzll(has) : at;
+      }
+    }
+  v.idx = first + at;
   v.s = wave_sum_dpp(s);
   v.t = wave_sum_dpp(t);
+  if (nan) v.s = v.t = __builtin_nanf("");
   return v;
 }
 
-__device__ __forceinline__ VTuple vt_shfl_down(const VTuple& v, int o) {
-  VTuple r;
-  r.m = __shfl_down(v.m, o, 64);
-  r.idx = __shfl_down(v.idx, o, 64);
-  r.s = __shfl_down(v.s, o, 64);
-  r.t = __shfl_down(v.t, o, 64);
-  return r;
+__device__ __forceinline__ VTuple vt_of_lane(const VTuple& v, int l) {
+  return VTuple{__shfl(v.m, l, 64), __shfl(v.idx, l, 64), __shfl(v.s, l, 64), __shfl(v.t, l, 64)};
 }
 
 // The tuples of N neighbouring lanes (2, 4, 8, 16 or 32) merged at once: every lane re-bases its own to the

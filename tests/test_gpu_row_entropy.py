@@ -137,3 +137,26 @@ def test_row_entropy_calls_on_two_streams_at_once(side_first):
         assert np.array_equal(late.cpu().numpy(), ref_b)
         assert np.array_equal(more.cpu().numpy(), ref_a)
         del busy
+
+
+@pytest.mark.parametrize("V", [2048, 4099, 40961])
+def test_row_entropy_ties_nan_and_wide_ranges(V):
+    """Each row holds its maximum twice, at elements of every distance a wave tells apart (lanes, loads, groups of four
+    loads, parts): the lower one is the token.  Logits far below the maximum count nothing, as far as float32 reaches; a
+    single NaN among finite logits leaves the maximum and takes the sums."""
+    rng = np.random.default_rng(V)
+    at = [(i, i + gap) for i in (0, 63, 64, 190, 255, 256, 1983, 2047 - 256) for gap in (1, 64, 128, 256) if i + gap < V]
+    z = (rng.standard_normal((len(at) + 3, V)) * 3.0).astype(np.float32)
+    for row, (i, j) in enumerate(at):
+        z[row, i] = z[row, j] = 40.0
+    z[-3] *= np.float32(30.0)                     # differences of hundreds
+    z[-2] = -3.0e38
+    z[-2, 7], z[-2, V - 2] = 3.0e38, 2.9e38      # a difference past the type's range
+    z[-1, V // 2] = np.nan
+    got = ec.row_entropy(torch.from_numpy(z).cuda()).cpu().numpy().astype(np.float64)
+    ref = oracle_stats(z[:-1])
+    assert np.array_equal(got[:-1, 0], ref[:, 0])
+    assert np.array_equal(got[:-1, 3], ref[:, 3])
+    assert np.allclose(got[:-1, 1], ref[:, 1], rtol=2e-6, atol=0)
+    assert np.allclose(got[:-1, 2], ref[:, 2], rtol=1e-5, atol=1e-6)
+    assert got[-1, 3] == np.nanmax(z[-1]) and np.isnan(got[-1, 1:3]).any()
