@@ -920,3 +920,16 @@ def test_attention_weights_sum_to_one(hq, hkv, hd, P, batch, gain):
         g.close()
         got.append(np.stack(z))
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("plens", [[5, 9, 3], [3 + 5 * (i % 7) for i in range(64)], [97, 4, 113, 30, 6]])
+def test_row_lists_of_batches(plens):
+    """Row lists of under and over 128 rows, from few sequences and from the most a batch can have (a lane looks for
+    each), some of which recompute everything where others do not, with a last row tile that is not full."""
+    cfg = small_cfg("bf16", 4, 2, 64, d=64, f=64, vocab=512, layers=1, scale=8.0)
+    w = ec_inputs.make_weights(cfg, 149, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(batch=len(plens), gen_len=12, block=6, k_recent=2, tokens_per_step=1, tau=2.5)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, P, 40 + i) for i, P in enumerate(plens)]
+    s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL["bf16"], max_steps=4)
+    print(s)
+    assert s["modes"][eco.FULL] >= len(plens) and s["rows_stat"] > 0
