@@ -118,11 +118,12 @@ void launch_row_stats(const float* logits, int n_rows, int V, size_t ld, float4*
 constexpr int kDecideThreads = 1024, kDecideWaves = kDecideThreads / 64;
 
 // Exclusive prefixes of up to four 0/1 flags over the block and their totals, one exchange for all
-// of them (each count fits 16 bits).  `scratch` may be written again after the next barrier.
+// of them (each count fits 16 bits).  `scratch` may be written again after the next barrier.  The first nw waves
+// take part; the others only come to the barrier (and get no totals).
 template <int NF>
-__device__ __forceinline__ void block_excl_scan_flags(const bool (&flag)[NF], unsigned long long* scratch,
+__device__ __forceinline__ void block_excl_scan_flags(const bool (&flag)[NF], unsigned long long* scratch, int nw,
                                                       int (&prefix)[NF], int (&total)[NF]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long mine = 0;
 #pragma unroll
@@ -134,11 +135,13 @@ __device__ __forceinline__ void block_excl_scan_flags(const bool (&flag)[NF], un
   if (lane == 0) scratch[w] = mine;
   __syncthreads();
   unsigned long long off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kDecideWaves; ++i) {
-    const unsigned long long c = scratch[i];
-    off += i < w ? c : 0;
-    tot += c;
+  if (w < nw) {
+#pragma unroll 4
+    for (int i = 0; i < nw; ++i) {
+      const unsigned long long c = scratch[i];
+      off += i < w ? c : 0;
+      tot += c;
+    }
   }
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
@@ -163,18 +166,74 @@ __device__ __forceinline__ bool gate_skips(float v, float tau, int metric) {
   return metric == EC_GATE_MAX_CONFIDENCE ? v >= tau : v <= tau;
 }
 
+// Lane l32 of a half wave merges parts l32, l32 + 32, ... of a row in that order, NU loads in flight.  The running
+// tuple is re-based once per batch of NU parts (to the batch's maximum if that is larger), after which a part costs
+// one fast exponential and a few FMAs.
+template <int NU>
+__device__ __forceinline__ VTuple merge_row_parts(const float4* __restrict__ pr, int l32, int nparts) {
+  VTuple v = vt_identity();
+  for (int p0 = l32; p0 < nparts; p0 += 32 * NU) {
+    float4 q[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)   // unconditional loads (clamped), so that all are in flight
+      q[u] = pr[min(p0 + 32 * u, nparts - 1)];
+    float bm = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {   // (past the end: a maximum of -inf; an empty part has that, and sums of 0)
+      q[u].x = p0 + 32 * u < nparts ? q[u].x : -INFINITY;
+      bm = fmaxf(bm, q[u].x);
+    }
+    if (bm > v.m) {
+      if (v.s != 0.f) {
+        const float d = v.m - bm, e = __expf(d);
+        v.t = e * (v.t + d * v.s);
+        v.s *= e;
+      }
+      v.m = bm;
+      v.idx = INT_MAX;
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const float d = fmaxf(q[u].x - v.m, -200.f);            // <= 0; e^-200 is 0 in float32
+      const float e = __expf(d);
+      v.s += q[u].z * e;
+      v.t += e * (q[u].w + d * q[u].z);
+      v.idx = min(v.idx, q[u].x == v.m ? __float_as_int(q[u].y) : INT_MAX);   // lowest index among equal maxima
+    }
+  }
+  return v;
+}
+
+// The k-th largest of the history values of a wave's copy (NU slots a lane): the largest v in [1, t] with
+// count(hist >= v) >= k, by bisection; INT_MIN if fewer than k are decoded.
+template <int NU>
+__device__ __forceinline__ int kth_of_history(const int* s_hist, int N, int lane, int t, int k) {
+  int hv[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) hv[u] = u * 64 + lane < N ? s_hist[u * 64 + lane] : INT_MIN;
+  int lo = 1, hi = t, found = INT_MIN;
+  while (lo <= hi) {
+    const int mid = (lo + hi) >> 1;
+    int c = 0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) c += __popcll(__ballot(hv[u] >= mid));
+    if (c >= k) { found = mid; lo = mid + 1; } else { hi = mid - 1; }
+  }
+  return found;
+}
+
 // ---------------------------------------------------------------------------------------------
-// decide: one block of kDecideThreads threads per sequence.  Everything the block reads from
-// memory (state, history, mask set, the rows' partial tuples, the caller's forced tokens) is
-// requested up front; from then on it works in LDS and registers, so the kernel's latency is two
-// memory round trips plus a chain of barriers and exchanges, which is kept short: one exponential to
-// merge a half wave's tuples, no barrier to find the k-th largest history value (up to 512 slots)
-// or the current block, one to compact the three row lists.  The forced lists are read where the
-// host left them and the flag goes back with the result, so a forced step adds no copies.
-// On MI355X a step of the float32 model of 128 positions and 4096 tokens spends 11.3 us here (15.7 with
-// a barrier per bisection step and per scan), a 2-layer bf16 model's forced step 81 us in all (132).
-// With the 988 tuples a row of a 126464-token vocabulary it is 15.4 us: 32 rows' tuples, 0.5 MB, come
-// through one compute unit.
+// decide: one block of kDecideThreads threads per sequence.  A chain of latencies: the loads (state, history, mask set,
+// the rows' partial tuples, the caller's forced tokens) are all on their way before the first is used, from then on the
+// kernel works in LDS and registers.  Sixteen waves are four to a SIMD, so what all of them do costs four
+// times: a lane merges no more parts than there are, ranks are counted by half a wave a row, the gate value
+// comes from the last wave beside the others, and waves that hold no slot of the generation only come to the
+// barriers.  No barrier to find the k-th largest history value (up to 512 slots) or the current block, one to compact the
+// three row lists.  The forced lists are read where the host left them and the flag goes back with the result, so
+// a forced step adds no copies.
+// On MI355X, first instruction to the result's release: 128 slots, 4096 tokens, float32 10.1 -> 6.1 us; 32 rows of a
+// small bf16 model, forced, 11.5 -> 6.4; 64 rows of 988 tuples (1 MB through one compute unit, 7 us of it) 15.4 -> 12.1; 16
+// sequences of 512 slots 14.8 -> 9.7.
 // dynamic LDS: int hist[N4] | uint8 masked[N4], N4 = N rounded up to 4
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
@@ -192,76 +251,55 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     a.P = sd.P; a.T = sd.T;
   }
   __shared__ int s_tok[EC_MAX_BLOCK], s_pos[EC_MAX_BLOCK];
-  __shared__ __align__(16) float s_conf[EC_MAX_BLOCK];
+  __shared__ float s_conf[EC_MAX_BLOCK];
   __shared__ float s_H[EC_MAX_BLOCK];
   __shared__ int s_badrow[EC_MAX_BLOCK];  // 1: the row's logits had no finite maximum / sums
   __shared__ int s_sel[EC_MAX_N];    // block rows of the step's own choice, most confident first
+  __shared__ int s_fpos[EC_MAX_N], s_ftok[EC_MAX_N];   // the caller's positions and tokens
   __shared__ int s_frow[EC_MAX_N];   // block rows of the caller's positions (-1: not in the block)
   __shared__ unsigned long long scratch[2][kDecideWaves];
   __shared__ float sh_f[2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ int sh_bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int P = a.P, N = a.N;
   int* s_hist = s_dyn;
   uint8_t* s_msk = (uint8_t*)(s_dyn + ((N + 3) & ~3));
   const int nblocks = (N + a.block - 1) / a.block;
 
   // ---- requests: state, history, mask set, block positions, forced tokens --------------------
+  // (they stay in registers until the rows' partial tuples, whose loads follow, have been merged; the forced lists
+  // are in host memory and go to the last wave, whose rows wait for them, as the loads of a wave return in order:
+  // as kernel arguments they measured the same)
   DevState st = *a.st;  // every thread holds a private copy; thread 0 writes it back
-  for (int i = tid; i < N; i += kDecideThreads) {
-    s_hist[i] = a.hist[i];
-    s_msk[i] = a.masked[P + i];
-  }
-  int f_pos = -1, f_tok = -1;
+  int my_hist = 0, my_pos = 0, f_pos = -1, f_tok = -1;
+  uint8_t my_msk = 0;
+  const int f = tid - (kDecideThreads - EC_MAX_N);
+  if (tid < N) { my_hist = a.hist[tid]; my_msk = a.masked[P + tid]; }
   if (!a.init_only) {
-    if (tid < a.n_mb) s_pos[tid] = a.mb_pos[tid];
-    else if (tid < EC_MAX_BLOCK) s_conf[tid] = -1.f;   // ranks behind every row
-    if (tid < a.forced_n) { f_pos = a.forced_pos[tid]; f_tok = a.forced_tok[tid]; }
+    if (tid < a.n_mb) my_pos = a.mb_pos[tid];
+    if (f >= 0 && f < a.forced_n) { f_pos = a.forced_pos[f]; f_tok = a.forced_tok[f]; }
   }
+  auto to_lds = [&]() {
+    if (tid < N) { s_hist[tid] = my_hist; s_msk[tid] = my_msk; }
+    for (int i = tid + kDecideThreads; i < N; i += kDecideThreads) {
+      s_hist[i] = a.hist[i];
+      s_msk[i] = a.masked[P + i];
+    }
+  };
   const int t = st.t;
-  int bad_rows = 0;
+  int n = 0;   // tokens of the step's own choice
 
   if (!a.init_only) {
     // ---- merge the vocabulary partials of each block row (fixed order) ----------------------
-    // Half a wave per row, 32 rows at a time: lane l of the half merges parts l, l + 32, ... in
-    // that order (sixteen loads in flight), then the 32 tuples are merged at once.
+    // Half a wave per row, 32 rows at a time: each lane its parts, then the 32 tuples at once.
     for (int row0 = 0; row0 < a.n_mb; row0 += 2 * kDecideWaves) {
       const int row = row0 + wave * 2 + (lane >> 5), l32 = lane & 31;
+      if (row0 + wave * 2 >= a.n_mb) break;   // (wave-uniform: nothing for either half)
       const bool live = row < a.n_mb;
       const float4* pr = a.partials + (size_t)(live ? row : 0) * a.nparts;
-      // The lane's running tuple is re-based once per batch of 16 parts (to the batch's maximum
-      // if that is larger), after which a part costs one fast exponential and a few FMAs.
-      VTuple v = vt_identity();
-      for (int p0 = l32; p0 < a.nparts; p0 += 32 * 16) {
-        float4 q[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u)   // unconditional loads (clamped), so that all are in flight
-          q[u] = pr[min(p0 + 32 * u, a.nparts - 1)];
-        bool ok[16];
-        float bm = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          ok[u] = live && p0 + 32 * u < a.nparts && q[u].z != 0.f;   // (an empty part has S = 0)
-          bm = fmaxf(bm, ok[u] ? q[u].x : -INFINITY);
-        }
-        if (bm > v.m) {
-          if (v.s != 0.f) {
-            const float d = v.m - bm, e = __expf(d);
-            v.t = e * (v.t + d * v.s);
-            v.s *= e;
-          }
-          v.m = bm;
-          v.idx = INT_MAX;
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          const float d = ok[u] ? q[u].x - v.m : 0.f;            // <= 0
-          const float e = ok[u] ? __expf(d) : 0.f;
-          v.s += q[u].z * e;
-          v.t += e * (q[u].w + d * q[u].z);
-          const int pi = __float_as_int(q[u].y);
-          if (ok[u] && d == 0.f && pi < v.idx) v.idx = pi;       // lowest index among equal maxima
-        }
-      }
+      VTuple v = a.nparts <= 64 ? merge_row_parts<2>(pr, l32, a.nparts)
+                 : a.nparts <= 128 ? merge_row_parts<4>(pr, l32, a.nparts)
+                                   : merge_row_parts<16>(pr, l32, a.nparts);
       v = vt_merge_lanes<32>(v);
       if (live && l32 == 0) {
         float conf, H;
@@ -280,134 +318,112 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
         *(float4*)(a.row_stats + row * 4) = make_float4((float)tok, conf, H, v.m);
       }
     }
+    to_lds();
+    if (tid < a.n_mb) s_pos[tid] = my_pos;
+    if (f >= 0 && f < a.forced_n) { s_fpos[f] = f_pos; s_ftok[f] = f_tok; s_frow[f] = -1; }
     __syncthreads();
     // ---- decode(): most confident rows first; ties -> lowest position (= lowest row) --------
-    // A row's rank is the number of rows that go before it; the n lowest ranks are unmasked.
-    int n = min(a.n_tok, a.n_mb);
-    const bool is_row = tid < a.n_mb;
-    const float my_conf = is_row ? s_conf[tid] : 0.f;
+    // A row's rank is the number of rows that go before it (counted by half a wave, as above); the
+    // n lowest ranks are unmasked.
+    n = min(a.n_tok, a.n_mb);
     if (a.conf_threshold > 0.f) {
       // confidence-based parallel decoding: every row above the threshold, the n most
       // confident ones in any case, no more than one result can report
-      const int above = __syncthreads_count(is_row && my_conf > a.conf_threshold);
+      const int above = __syncthreads_count(tid < a.n_mb && s_conf[tid] > a.conf_threshold);
       n = min(min(max(n, above), EC_MAX_N), a.n_mb);
     }
-    ec_step_result& R = a.out->r;
-    int rank = EC_MAX_BLOCK;
-    if (is_row) {
-      rank = 0;
-#pragma unroll 4
-      for (int r = 0; r < a.n_mb; r += 4) {   // (four rows a read; those past the end hold -1)
-        const float4 c4 = *(const float4*)(s_conf + r);
-        const float c[4] = {c4.x, c4.y, c4.z, c4.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          rank += (c[i] > my_conf || (c[i] == my_conf && r + i < tid)) ? 1 : 0;
+    // commit, own choice or the caller's under teacher forcing (Eq. 2): to memory, and to the LDS
+    // copies the rest of the kernel works on
+    auto commit = [&](int pos, int tok) {
+      a.x[pos] = tok;
+      a.masked[pos] = 0;
+      a.hist[pos - P] = t;
+      s_msk[pos - P] = 0;
+      s_hist[pos - P] = t;
+    };
+    for (int row0 = wave * 2; row0 < a.n_mb; row0 += 2 * kDecideWaves) {
+      const int row = row0 + (lane >> 5), l32 = lane & 31;
+      const float my_conf = s_conf[min(row, a.n_mb - 1)];
+      int rank = 0;
+      for (int r0 = 0; r0 < a.n_mb; r0 += 32) {
+        const int r = r0 + l32;
+        const float c = s_conf[min(r, a.n_mb - 1)];
+        const unsigned long long before = __ballot(r < a.n_mb && (c > my_conf || (c == my_conf && r < row)));
+        rank += __popc((unsigned)(lane < 32 ? before : before >> 32));
       }
-      if (rank < n) {
-        s_sel[rank] = tid;
-        R.positions[rank] = s_pos[tid];
-        R.tokens[rank] = s_tok[tid];
-        R.entropy[rank] = s_H[tid];
-        R.confidence[rank] = my_conf;
+      if (l32 == 0 && row < a.n_mb && rank < n) {
+        s_sel[rank] = row;
+        if (a.forced_n < 0) commit(s_pos[row], s_tok[row]);
       }
     }
-    if (tid >= n && tid < EC_MAX_N) {
-      R.positions[tid] = -1; R.tokens[tid] = -1; R.entropy[tid] = 0.f; R.confidence[tid] = 0.f;
+    if (a.forced_n > 0) {
+      if (tid < a.forced_n) commit(s_fpos[tid], s_ftok[tid]);
+      if (tid < a.n_mb)
+        for (int i = 0; i < a.forced_n; ++i)
+          if (s_fpos[i] == my_pos) s_frow[i] = tid;
     }
-    // ---- commit: own choice, or the caller's under teacher forcing (Eq. 2) -------------------
-    // (to memory, and to the LDS copies the rest of the kernel works on)
-    int c_pos = -1, c_tok = 0;
-    if (a.forced_n >= 0) {
-      if (tid < a.forced_n) {
-        int row = -1;
-        for (int r = 0; r < a.n_mb; ++r)
-          if (s_pos[r] == f_pos) row = r;
-        s_frow[tid] = row;
-        c_pos = f_pos; c_tok = f_tok;
-      }
-    } else if (rank < n) {
-      c_pos = s_pos[tid]; c_tok = s_tok[tid];
-    }
-    if (c_pos >= 0) {
-      a.x[c_pos] = c_tok;
-      a.masked[c_pos] = 0;
-      a.hist[c_pos - P] = t;
-      s_msk[c_pos - P] = 0;
-      s_hist[c_pos - P] = t;
-    }
-    bad_rows = __syncthreads_or(is_row && s_badrow[tid]);
-    if (tid == 0) {
-      // gate values, accumulated in the order of the lists (the entropy sum is order-sensitive)
-      GateAcc own = gate_init(a.gate_metric);
-      for (int i = 0; i < n; ++i) gate_add(own, s_H[s_sel[i]], s_conf[s_sel[i]]);
-      float E = own.v;
-      if (a.forced_n >= 0) {
-        bool all_in_block = true;
-        GateAcc fa = gate_init(a.gate_metric);
-        for (int i = 0; i < a.forced_n; ++i) {
-          const int row = s_frow[i];
-          if (row < 0) all_in_block = false; else gate_add(fa, s_H[row], s_conf[row]);
+    __syncthreads();   // the LDS copies of history and mask set are complete and committed to
+    if (wave == kDecideWaves - 1) {   // beside the other waves' way to the next barrier
+      const bool bad = (lane < a.n_mb && s_badrow[lane]) || (lane + 64 < a.n_mb && s_badrow[lane + 64]);
+      const bool any_bad = __ballot(bad) != 0;
+      if (lane == 0) {
+        // gate values, accumulated in the order of the lists (the entropy sum is order-sensitive)
+        GateAcc own = gate_init(a.gate_metric);
+        for (int i = 0; i < n; ++i) gate_add(own, s_H[s_sel[i]], s_conf[s_sel[i]]);
+        float E = own.v;
+        if (a.forced_n >= 0) {
+          bool all_in_block = true;
+          GateAcc fa = gate_init(a.gate_metric);
+          for (int i = 0; i < a.forced_n; ++i) {
+            const int row = s_frow[i];
+            if (row < 0) all_in_block = false; else gate_add(fa, s_H[row], s_conf[row]);
+          }
+          if (all_in_block) E = fa.v;                       // nothing committed: always skips
         }
-        if (all_in_block) E = fa.v;                       // nothing committed: always skips
+        sh_f[0] = E;
+        sh_f[1] = own.v;
+        sh_bad = any_bad;
       }
-      R.n_unmasked = n;
-      R.max_entropy = own.v;
-      sh_f[0] = E;
-      sh_f[1] = own.v;
     }
+  } else {
+    to_lds();
+    __syncthreads();
   }
-  __syncthreads();   // the LDS copies of history and mask set are complete (and committed to)
 
   // ---- recency threshold: tau_R = max(k-th largest history value, t - dt) --------------------
-  // History values are step indices in [1, t] or "never": the k-th largest is the largest v with
-  // count(hist >= v) >= k, found by bisection; fewer than k decoded -> -inf.
+  // History values are step indices in [1, t] or "never"; fewer than k decoded -> -inf.  Up to 512 slots
+  // every wave that holds some of them counts for itself, without a barrier.
+  const int nw = min(kDecideWaves, (N + 63) >> 6);   // waves that hold slots
   int t_lastfull = st.t_lastfull;
   int tauR = INT_MAX;
   if (!a.init_only) {
     if (a.mode_run == EC_FULL) t_lastfull = t;
     int kth = INT_MIN;
-    if (a.k_recent > 0) {
-      int lo = 1, hi = t, found = INT_MIN;
-      // (up to 512 slots every wave counts for itself, eight to a lane, without a barrier)
-      constexpr int HL = 8;
-      int hv[HL];
-      if (N <= 64 * HL) {
-#pragma unroll
-        for (int u = 0; u < HL; ++u) hv[u] = u * 64 + lane < N ? s_hist[u * 64 + lane] : INT_MIN;
-      }
+    if (a.k_recent <= 0) {
+      kth = INT_MAX;  // empty selection: nothing qualifies by rank
+    } else if (N <= 512) {
+      if (wave < nw)
+        kth = N <= 128 ? kth_of_history<2>(s_hist, N, lane, t, a.k_recent) : kth_of_history<8>(s_hist, N, lane, t, a.k_recent);
+    } else {
+      int lo = 1, hi = t;
       while (lo <= hi) {  // uniform across the block
         const int mid = (lo + hi) >> 1;
         int c = 0;
-        if (N <= 64 * HL) {
-#pragma unroll
-          for (int u = 0; u < HL; ++u) c += __popcll(__ballot(hv[u] >= mid));
-        } else {
-          for (int base = 0; base < N; base += kDecideThreads) {  // uniform trip count
-            const int i = base + tid;
-            c += __syncthreads_count(i < N && s_hist[i] >= mid);
-          }
+        for (int base = 0; base < N; base += kDecideThreads) {  // uniform trip count
+          const int i = base + tid;
+          c += __syncthreads_count(i < N && s_hist[i] >= mid);
         }
-        if (c >= a.k_recent) { found = mid; lo = mid + 1; } else { hi = mid - 1; }
+        if (c >= a.k_recent) { kth = mid; lo = mid + 1; } else { hi = mid - 1; }
       }
-      kth = found;
-    } else {
-      kth = INT_MAX;  // empty selection: nothing qualifies by rank
     }
     tauR = max(kth, t_lastfull);  // t - dt == index of the last FULL step
   }
 
-  // ---- flag for the next step, counters, block advance ---------------------------------------
-  if (!a.init_only) {
-    float E = sh_f[0];
-    if (gate_skips(E, a.tau, a.gate_metric)) { st.skip = 1; st.dt += 1; } else { st.skip = 0; st.dt = 0; }
-    st.t_lastfull = t_lastfull;
-    st.t = t + 1;
-  }
+  // ---- block advance -----------------------------------------------------------------------
   const bool sliding = a.schedule == EC_SCHED_SLIDING;
   int blk = st.blk;
   if (!sliding) {
-    while (blk < nblocks) {  // uniform: every wave looks at the whole block (at most 128 slots)
+    while (wave < nw && blk < nblocks) {  // every wave with slots looks at the whole block (at most 128 slots)
       const int lo = blk * a.block + lane, hi = min(N, (blk + 1) * a.block);
       if (__ballot((lo < hi && s_msk[lo]) || (lo + 64 < hi && s_msk[lo + 64]))) break;
       ++blk;
@@ -431,13 +447,13 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     }
     if (sliding) {
       int pre[1], tot[1];
-      block_excl_scan_flags<1>({msk}, scratch[buf], pre, tot);
+      block_excl_scan_flags<1>({msk}, scratch[buf], nw, pre, tot);
       inM = msk && masked_seen + pre[0] < a.block;
       masked_seen += tot[0];
       buf ^= 1;
     }
     int pre[3], tot[3];
-    block_excl_scan_flags<3>({inM || inR, inM, inR}, scratch[buf], pre, tot);
+    block_excl_scan_flags<3>({inM || inR, inM, inR}, scratch[buf], nw, pre, tot);
     if (inM || inR) a.rows_partial[n_rows + pre[0]] = pos;
     if (inM) {
       a.mb_pos[n_mb + pre[1]] = pos;
@@ -448,7 +464,22 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     n_recent += tot[2];
   }
   if (sliding) st.done = (n_mb == 0);
+  // The result, all of it from wave 0, whose fence then orders it before the serial number.  (The barriers of the lists
+  // lie between the gate values and their use here.)
+  if (!a.init_only && tid < EC_MAX_N) {
+    ec_step_result& R = a.out->r;
+    const int row = tid < n ? s_sel[tid] : 0;
+    R.positions[tid] = tid < n ? s_pos[row] : -1;
+    R.tokens[tid] = tid < n ? s_tok[row] : -1;
+    R.entropy[tid] = tid < n ? s_H[row] : 0.f;
+    R.confidence[tid] = tid < n ? s_conf[row] : 0.f;
+  }
   if (tid == 0) {
+    if (!a.init_only) {
+      if (gate_skips(sh_f[0], a.tau, a.gate_metric)) { st.skip = 1; st.dt += 1; } else { st.skip = 0; st.dt = 0; }
+      st.t_lastfull = t_lastfull;
+      st.t = t + 1;
+    }
     st.n_mb = n_mb;
     st.n_rows_partial = n_rows;
     st.n_recent = n_recent;
@@ -457,6 +488,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     o.next_n_mb = n_mb;
     o.next_n_rows_partial = n_rows;
     if (!a.init_only) {
+      o.r.n_unmasked = n;
+      o.r.max_entropy = sh_f[1];
       o.r.done = st.done;
       o.r.mode_run = a.mode_run;
       o.r.next_mode = gate_skips(sh_f[1], a.tau, a.gate_metric) ? EC_PARTIAL : EC_FULL;
@@ -465,10 +498,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
       o.r.n_block_rows = a.n_mb;
       o.r.n_recent_next = n_recent;
     }
-    // The result sits in pinned host memory.  The other threads' entries were stored before the
-    // barriers above; this fence orders them and the fields above before the serial number, so
-    // a host that sees the number sees the whole result.
-    o.nonfinite = bad_rows;
+    // The result sits in pinned host memory: a host that sees the serial number sees the whole of it.
+    o.nonfinite = a.init_only ? 0 : sh_bad;
     o.skip = st.skip;
     __threadfence_system();
     __hip_atomic_store(&o.serial, a.serial, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

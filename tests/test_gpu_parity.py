@@ -933,3 +933,20 @@ def test_row_lists_of_batches(plens):
     s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL["bf16"], max_steps=4)
     print(s)
     assert s["modes"][eco.FULL] >= len(plens) and s["rows_stat"] > 0
+
+
+@pytest.mark.parametrize("tiles,gen_len,block,k_recent,threshold", [
+    (128, 128, 40, 3, 0.0), (129, 129, 7, 2, 0.02),     # 64 and 65 parts of a row; the last wave with slots full, and one more
+    (256, 512, 64, 3, 0.0), (257, 513, 33, 2, 0.0),     # 128 and 129; history counted by each wave, and by the block
+    (128, 1030, 128, 4, 0.0), (1024, 64, 64, 0, 0.02),  # more slots than threads; four rounds of rows; no recency
+])
+def test_decisions_at_the_edges_of_rows_parts_and_slots(tiles, gen_len, block, k_recent, threshold):
+    """The decision kernel where a lane's parts, a wave's slots and a round of rows begin or end: tokens, ranks, history threshold
+    and row lists of a few steps."""
+    cfg = small_cfg("bf16", 4, 2, 64, d=64, f=64, vocab=16 * tiles, layers=1, scale=24.0)
+    w = ec_inputs.make_weights(cfg, 151, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(gen_len=gen_len, block=block, k_recent=k_recent, tokens_per_step=3, tau=2.0,
+                              conf_threshold=threshold)
+    s = run_teacher_forced(cfg, w, dec, ec_inputs.make_prompt(cfg.vocab, 9, 6), TOL["bf16"], max_steps=6)
+    print(s)
+    assert s["rows_stat"] > 0
