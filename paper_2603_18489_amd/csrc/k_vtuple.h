@@ -8,6 +8,7 @@
 #include <limits.h>
 
 #include "k_common.h"
+#include "k_exp.h"
 
 namespace ec {
 
@@ -33,14 +34,6 @@ __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
   r.s = a.s * ea + b.s * eb;
   r.t = ea * (a.t + da * a.s) + eb * (b.t + db * b.s);
   return r;
-}
-
-// e^d for -200 <= d <= 0, to about an ulp: 2^t for the rounded product t = d log2 e, times 1 + (d - t ln 2).
-__device__ __forceinline__ float exp_of_negative(float d) {
-  const float t = d * 1.44269502f;
-  const float r = fmaf(t, -1.90465421e-9f, fmaf(t, -0.693147182f, d));   // (ln 2 = 0.693147182 + 1.90465e-9 - ...)
-  const float e = __builtin_amdgcn_exp2f(t);
-  return fmaf(e, r, e);
 }
 
 // Tuple of NE * 64 consecutive logits held by one wave (lane l: elements first + 64 u + l, -inf for

@@ -160,3 +160,21 @@ def test_row_entropy_ties_nan_and_wide_ranges(V):
     assert np.allclose(got[:-1, 1], ref[:, 1], rtol=2e-6, atol=0)
     assert np.allclose(got[:-1, 2], ref[:, 2], rtol=1e-5, atol=1e-6)
     assert got[-1, 3] == np.nanmax(z[-1]) and np.isnan(got[-1, 1:3]).any()
+
+
+@pytest.mark.parametrize("V", [16384, 131072])
+def test_row_entropy_errors_have_no_side(V):
+    """Rows whose parts of 2048 logits hold one maximum and logits 5 to 8 below it, which make four fifths of the sum, in the
+    one-launch and the two-launch form: the errors of 4096 confidences against 64 bits average out.  About a dozen roundings are
+    common to all of a row (lane exchanges, merges, the quotient; the sums before them differ from lane to lane): 2^-24 *
+    sqrt(12 / 3) = 1.2e-7 r.m.s. at most, 1.9e-9 in the mean; the hardware's 2^t is 3.4e-9 low on average, 2.8e-9 here; four
+    times the one and the other make 1e-8.  (An exponential that takes ln 2 for 3.8e-9 more than it is: 2e-8.)"""
+    rows, gen, err = 128, torch.Generator(device="cuda").manual_seed(V), []
+    for _ in range(32):
+        z = torch.empty((rows, V), device="cuda").uniform_(-8.0, -5.0, generator=gen)
+        z[:, 77::2048] = 0.0
+        exact = 1.0 / torch.exp(z.double()).sum(dim=1)
+        err.append(ec.row_entropy(z)[:, 1].double() / exact - 1.0)
+    err = torch.cat(err)
+    print(err.mean().item(), err.square().mean().sqrt().item(), err.abs().max().item())
+    assert abs(err.mean().item()) < 1e-8
