@@ -304,11 +304,11 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
       if (live && l32 == 0) {
         float conf, H;
         vt_finish(v, conf, H);
-        // A row of NaNs has no maximum: its index is still the sentinel, its sums are NaN.  The
-        // token becomes an index into the embedding table at the next step, so it must be a
-        // token; such a row counts as least confident and of infinite entropy, and is reported.
+        // A row of NaNs has no maximum: its index is still the sentinel, its sums are NaN.  One of +inf has no
+        // finite maximum.  The token becomes an index into the embedding table at the next step, so it must be a
+        // token, 0 for both; such a row counts as least confident and of infinite entropy, and is reported.
         int tok = v.idx, bad = 0;
-        if ((unsigned)tok >= (unsigned)a.vocab) { tok = 0; bad = 1; }
+        if ((unsigned)tok >= (unsigned)a.vocab || !(fabsf(v.m) < INFINITY)) { tok = 0; bad = 1; }
         if (!(v.s > 0.f) || !(conf >= 0.f) || !(v.t == v.t) || !(H >= 0.f)) bad = 1;
         if (bad) { conf = 0.f; H = INFINITY; }  // (the clamp in vt_finish turns a NaN entropy into 0)
         s_badrow[row] = bad;

@@ -516,6 +516,28 @@ def test_rows_of_nan_logits_are_reported_and_nothing_leaves_its_buffers(dtype, b
     assert s["steps"] == 4
 
 
+@pytest.mark.parametrize("dtype,batch,block", [
+    ("bf16", 1, 24), ("f32", 1, 24), ("bf16", 2, 48),   # reduced in the LM head; over 64 rows, from stored logits
+])
+def test_rows_with_an_infinite_maximum_take_token_0(dtype, batch, block):
+    """Two vocabulary rows with an infinite weight each, of either sign for the same feature: one of their logits is +inf.  Such
+    rows have no finite maximum: they take token 0, confidence 0 and infinite entropy, and the step reports them."""
+    cfg = small_cfg(dtype, 4, 2, 64)
+    w = ec_inputs.make_weights(cfg, 61, gain_jitter=0.1)
+    w["lm_head"] = w["lm_head"].copy()
+    w["lm_head"][[1234, 2345], 7] = (np.inf, -np.inf) if dtype == "f32" else (0x7F80, 0xFF80)
+    dec = ec_inputs.DecodeCfg(gen_len=block, block=block, k_recent=2, tokens_per_step=2, tau=2.5, batch=batch)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, 9 + 5 * b, 70 + b) for b in range(batch)]
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, prompts if batch > 1 else prompts[0])
+    with pytest.raises(ec.EcError) as e:
+        g.step(ec.EC_FULL)
+    assert e.value.code == ec.EC_ERR_NONFINITE
+    s = np.concatenate([g.debug_read(ec.EC_DBG_ROW_STATS, seq=b) for b in range(batch)])
+    g.close()
+    assert (s[:, 3] == np.inf).all()
+    assert not s[:, :2].any() and np.isinf(s[:, 2]).all()
+
+
 @pytest.mark.parametrize("hq,hkv,hd,d,f,vocab,P,shift", [
     (2, 1, 64, 136, 200, 1003, 19, 0),     # K = 136 and 200: half-filled last k-chunks, odd tile counts
     (3, 3, 128, 264, 1032, 4099, 40, 0),   # K just above 256: eight waves to a block
