@@ -464,17 +464,18 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
     n_recent += tot[2];
   }
   if (sliding) st.done = (n_mb == 0);
-  // The result, all of it from wave 0, whose fence then orders it before the serial number.  (The barriers of the lists
-  // lie between the gate values and their use here.)
-  if (!a.init_only && tid < EC_MAX_N) {
+  // The result, all of it from wave 0.  (The barriers of the lists lie between the gate values and their use here.)
+  if (wave > 0) return;
+  static_assert(EC_MAX_N <= kWave, "the result's lists are stored by one wave");
+  if (!a.init_only && lane < EC_MAX_N) {
     ec_step_result& R = a.out->r;
-    const int row = tid < n ? s_sel[tid] : 0;
-    R.positions[tid] = tid < n ? s_pos[row] : -1;
-    R.tokens[tid] = tid < n ? s_tok[row] : -1;
-    R.entropy[tid] = tid < n ? s_H[row] : 0.f;
-    R.confidence[tid] = tid < n ? s_conf[row] : 0.f;
+    const int row = lane < n ? s_sel[lane] : 0;
+    R.positions[lane] = lane < n ? s_pos[row] : -1;
+    R.tokens[lane] = lane < n ? s_tok[row] : -1;
+    R.entropy[lane] = lane < n ? s_H[row] : 0.f;
+    R.confidence[lane] = lane < n ? s_conf[row] : 0.f;
   }
-  if (tid == 0) {
+  if (lane == 0) {
     if (!a.init_only) {
       if (gate_skips(sh_f[0], a.tau, a.gate_metric)) { st.skip = 1; st.dt += 1; } else { st.skip = 0; st.dt = 0; }
       st.t_lastfull = t_lastfull;
@@ -498,12 +499,14 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(DecideArgs a) {
       o.r.n_block_rows = a.n_mb;
       o.r.n_recent_next = n_recent;
     }
-    // The result sits in pinned host memory: a host that sees the serial number sees the whole of it.
     o.nonfinite = a.init_only ? 0 : sh_bad;
     o.skip = st.skip;
-    __threadfence_system();
-    __hip_atomic_store(&o.serial, a.serial, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+  // The result sits in pinned host memory: a host that sees the serial number sees the whole of it.  Each lane's fence
+  // orders what that lane stored, the wave barrier keeps all of them ahead of the number.
+  __threadfence_system();
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) __hip_atomic_store(&a.out->serial, a.serial, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 void launch_decide(const DecideArgs& a, int B, hipStream_t s) {

@@ -538,6 +538,34 @@ def test_rows_with_an_infinite_maximum_take_token_0(dtype, batch, block):
     assert not s[:, :2].any() and np.isinf(s[:, 2]).all()
 
 
+@pytest.mark.parametrize("batch,gen_len,n", [(1, 1024, 32), (16, 512, 32), (64, 96, 7)])
+def test_every_result_is_whole_when_its_step_returns(batch, gen_len, n):
+    """A step returns as soon as the host sees its serial number in pinned memory.  The lists that it hands over then are the step's
+    own: the tokens that the device holds at their positions in the end, each position once, in order of confidence."""
+    cfg = small_cfg("bf16", 4, 2, 64, d=64, f=64, vocab=512, layers=1, scale=24.0)
+    w = ec_inputs.make_weights(cfg, 157, gain_jitter=0.1)
+    dec = ec_inputs.DecodeCfg(batch=batch, gen_len=gen_len, block=64, k_recent=0, tokens_per_step=n, tau=1e9)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, 3 + b % 5, 80 + b) for b in range(batch)]
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, prompts if batch > 1 else prompts[0])
+    x = [{} for _ in range(batch)]
+    done = [False] * batch
+    while not all(done):
+        r = g.step(ec.EC_AUTO)
+        for b, q in enumerate(r if batch > 1 else [r]):
+            if done[b]:
+                continue
+            assert 0 < q["n_unmasked"] == len(q["positions"]) <= n
+            assert not set(q["positions"]) & set(x[b])
+            assert q["confidence"] == sorted(q["confidence"], reverse=True) and min(q["confidence"]) > 0
+            x[b].update(zip(q["positions"], q["tokens"]))
+            done[b] = q["done"]
+    for b in range(batch):
+        P = len(prompts[b])
+        got = g.debug_read(ec.EC_DBG_X, seq=b)
+        assert [x[b][p] for p in range(P, P + gen_len)] == got[P:].tolist()
+    g.close()
+
+
 @pytest.mark.parametrize("hq,hkv,hd,d,f,vocab,P,shift", [
     (2, 1, 64, 136, 200, 1003, 19, 0),     # K = 136 and 200: half-filled last k-chunks, odd tile counts
     (3, 3, 128, 264, 1032, 4099, 40, 0),   # K just above 256: eight waves to a block
