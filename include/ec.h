@@ -291,6 +291,12 @@ int ec_debug_read_seq(ec_ctx *ctx, int seq, int what, int layer, void *host_dst,
 int ec_debug_block_shape(const ec_model_cfg *model, int product, int32_t list_rows, int32_t rows,
                          int32_t shape[3] /*HOST*/);
 
+/* How many 16-row tiles of query rows a block of the many-row attention of a bfloat16 or e4m3 model takes, in
+ * a step in which these n sequences recompute rows[i] rows (more than 96) of positions[i] each (test and diagnosis
+ * aid; pure host computation; HOST arrays).  Results do not depend on it.  Errors: EC_ERR_ARG. */
+int ec_debug_attn_tiles(const ec_model_cfg *model, int32_t n, const int32_t *rows, const int32_t *positions,
+                        int32_t *tiles /*HOST*/);
+
 /* The O(V) reduction behind the method's decision (Eq. 1 and the complexity discussion of the
  * Method section) as a call of its own, for logits that already sit on the device: for each row
  * of a float32 matrix, stats[row] = (argmax token id as a float, lowest id on ties; confidence =

@@ -31,7 +31,8 @@ KERNEL_CLASS_NAMES = ["embed", "norm", "qkv", "rope_kv", "attn", "oproj", "gateu
 
 EXPORTS = ["ec_workspace_bytes", "ec_init", "ec_reset", "ec_step", "ec_step_forced", "ec_debug_keep_logits",
            "ec_step_forced_batch", "ec_generate", "ec_profile_enable", "ec_profile_read",
-           "ec_debug_read", "ec_debug_read_seq", "ec_debug_block_shape", "ec_debug_meeting", "ec_destroy", "ec_strerror", "ec_last_error",
+           "ec_debug_read", "ec_debug_read_seq", "ec_debug_block_shape", "ec_debug_attn_tiles", "ec_debug_meeting",
+           "ec_destroy", "ec_strerror", "ec_last_error",
            "ec_row_entropy_workspace_bytes", "ec_row_entropy", "ec_row_entropy_noalloc"]
 
 
@@ -131,6 +132,8 @@ def load_library() -> C.CDLL:
     lib.ec_debug_block_shape.restype = C.c_int
     lib.ec_debug_block_shape.argtypes = [C.POINTER(ec_model_cfg), C.c_int, C.c_int32, C.c_int32,
                                          C.POINTER(C.c_int32 * 3)]
+    lib.ec_debug_attn_tiles.restype = C.c_int
+    lib.ec_debug_attn_tiles.argtypes = [C.POINTER(ec_model_cfg), C.c_int32, i32p, i32p, i32p]
     lib.ec_row_entropy_workspace_bytes.restype = C.c_size_t
     lib.ec_row_entropy_workspace_bytes.argtypes = [C.c_int32, C.c_int32]
     lib.ec_row_entropy.restype = C.c_int
@@ -203,6 +206,16 @@ def block_shape(cfg, product: int, list_rows: int, rows: int):
     if rc != EC_OK:
         raise EcError(rc, load_library().ec_last_error(None).decode())
     return tuple(shape)
+
+
+def attn_tiles(cfg, rows: Sequence[int], positions: Sequence[int]) -> int:
+    """ec_debug_attn_tiles: row tiles to a block of the attention of sequences with so many rows and positions."""
+    mc, tiles = model_cfg_struct(cfg), C.c_int32()
+    rc = load_library().ec_debug_attn_tiles(C.byref(mc), len(rows), _i32p(_i32(rows)), _i32p(_i32(positions)),
+                                            C.byref(tiles))
+    if rc != EC_OK:
+        raise EcError(rc, load_library().ec_last_error(None).decode())
+    return tiles.value
 
 
 def _raw_stream(torch, stream, device: int) -> int:

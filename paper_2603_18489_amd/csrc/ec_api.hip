@@ -1076,6 +1076,23 @@ int ec_debug_block_shape(const ec_model_cfg* m, int product, int32_t list_rows, 
   return EC_OK;
 }
 
+int ec_debug_attn_tiles(const ec_model_cfg* m, int32_t n, const int32_t* rows, const int32_t* positions,
+                        int32_t* tiles) {
+  if (!m || !rows || !positions || !tiles)
+    return fail(nullptr, EC_ERR_ARG, "model, rows, positions and tiles must not be NULL");
+  if (!bf16_path(m->dtype)) return fail(nullptr, EC_ERR_ARG, "float32 models have no such blocks");
+  if (m->n_heads < 1) return fail(nullptr, EC_ERR_ARG, "n_heads must be at least 1");
+  if (n < 1 || n > EC_MAX_BATCH) return fail(nullptr, EC_ERR_ARG, "n must be in [1, EC_MAX_BATCH]");
+  AttnSeq seqs[EC_MAX_BATCH];
+  for (int i = 0; i < n; ++i) {
+    if (rows[i] <= kSmallRows || positions[i] < rows[i])
+      return fail(nullptr, EC_ERR_ARG, "rows must be more than 96 and at most the positions");
+    seqs[i] = AttnSeq{(rows[i] + 15) / 16, positions[i]};
+  }
+  *tiles = attn_rows_tiles(pick_attn_rows(seqs, n, m->n_heads));
+  return EC_OK;
+}
+
 int ec_debug_read(ec_ctx* ctx, int what, int layer, void* host_dst, size_t bytes) {
   return ec_debug_read_seq(ctx, 0, what, layer, host_dst, bytes);
 }

@@ -225,5 +225,25 @@ def test_block_shape_query(lib):
     assert q(C.byref(f32), ec.EC_K_QKV, 768, 768) == ec.EC_ERR_ARG
 
 
+def test_attn_tiles_query(lib):
+    mc, _, wl = _cfgs("llada8b_l2")
+    i32 = lambda *v: (C.c_int32 * len(v))(*v)
+    tiles = C.c_int32()
+    q = lambda m, n, rows, pos: lib.ec_debug_attn_tiles(m, n, rows, pos, C.byref(tiles))
+    for rows in ([768], [1536] * 16, [97, 4000], [700] * ec.EC_MAX_BATCH):
+        assert q(C.byref(mc), len(rows), i32(*rows), i32(*rows)) == ec.EC_OK and tiles.value in (8, 12)
+    assert q(C.byref(mc), 1, i32(97), i32(4096)) == ec.EC_OK      # a partial step of many rows
+    assert q(None, 1, i32(768), i32(768)) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), 1, None, i32(768)) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), 1, i32(768), None) == ec.EC_ERR_ARG
+    assert lib.ec_debug_attn_tiles(C.byref(mc), 1, i32(768), i32(768), None) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), 0, i32(768), i32(768)) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), ec.EC_MAX_BATCH + 1, i32(768), i32(768)) == ec.EC_ERR_ARG
+    assert q(C.byref(mc), 1, i32(96), i32(768)) == ec.EC_ERR_ARG      # few rows: no such blocks
+    assert q(C.byref(mc), 2, i32(768, 768), i32(768, 767)) == ec.EC_ERR_ARG
+    f32, _, _ = _cfgs("tiny_f32")
+    assert q(C.byref(f32), 1, i32(768), i32(768)) == ec.EC_ERR_ARG
+
+
 def test_debug_meeting_arguments(lib):
     assert lib.ec_debug_meeting(None, 0, 0) == ec.EC_ERR_ARG

@@ -28,6 +28,12 @@ def block_shape(cfg, product, T):
     return ec.block_shape(cfg, product, (T + 255) // 256 * 256, T)
 
 
+def full_step_attn_tiles(cfg, lengths):
+    """row tiles to a block of the attention in a full step of sequences of these lengths (those of up to 96 rows go elsewhere)"""
+    many = [T for T in lengths if T > 96]
+    return ec.attn_tiles(cfg, many, many)
+
+
 def test_tiny_f32_whole_generation():
     wl = ec_inputs.WORKLOADS["tiny_f32"]
     cfg = wl.model.replace(logit_scale=16.0)      # both modes occur (about half the steps FULL)
@@ -622,22 +628,28 @@ def test_tiled_gemm_k_steps_and_ragged_tiles(hq, hkv, hd, d, f, P, gate_up):
     assert s["rows_stat"] > 0    # (d = 32 gives logits too flat for exact tokens)
 
 
-@pytest.mark.parametrize("hq,hkv,hd,plens", [
-    # eight tiles to a block: sequences of 7 to 17 row tiles, one of whole groups
-    (4, 2, 64, [72, 88, 216, 217, 90]),
-    (4, 4, 128, [231, 56, 200]),
+@pytest.mark.parametrize("hq,hkv,hd,plens,tiles", [
+    # eight tiles to a block: sequences of 7 to 17 row tiles, one of whole groups; one of few rows among them; ten of 24 to 37 tiles
+    (4, 2, 64, [72, 88, 216, 217, 90], 8),
+    (4, 4, 128, [231, 56, 200], 8),
+    (16, 16, 64, [530, 537, 520, 471, 536, 529, 344, 535, 530, 533], 8),
     # twelve, from enough blocks on: groups that end in the next sequence or in padding, and whole ones
-    (16, 16, 64, [530, 537, 520, 471, 536, 529, 344, 535, 530, 533]),
-    (16, 4, 128, [530, 472, 537, 520, 535, 529, 536, 504, 530, 533]),
+    (16, 16, 64, [530, 537, 520, 471, 536, 529, 504, 535, 530, 533], 12),
+    (16, 4, 128, [530, 472, 537, 520, 535, 529, 536, 504, 530, 533], 12),
+    # one sequence alone, without a table of groups: 81 and 67 tiles, the last blocks part empty
+    (48, 16, 128, [1250], 12),
+    (64, 64, 64, [1021], 12),
 ])
-def test_many_row_attention_of_ragged_batches(hq, hkv, hd, plens):
+def test_many_row_attention_of_ragged_batches(hq, hkv, hd, plens, tiles):
     """Attention of full steps, whose blocks take eight or twelve row tiles of one sequence: the tiles of a sequence's last block
     that belong to the next one or hold padding rows only."""
     cfg = small_cfg("bf16", hq, hkv, hd, d=64, f=64, vocab=512, layers=2, scale=8.0)
     w = ec_inputs.make_weights(cfg, 139, gain_jitter=0.1)
     dec = ec_inputs.DecodeCfg(batch=len(plens), gen_len=40, block=20, k_recent=2, tokens_per_step=1, tau=1e9)
+    assert full_step_attn_tiles(cfg, [P + 40 for P in plens]) == tiles
     prompts = [ec_inputs.make_prompt(cfg.vocab, P, 20 + i) for i, P in enumerate(plens)]
-    s = run_teacher_forced_batch(cfg, w, dec, prompts, TOL["bf16"], max_steps=2)
+    s = (run_teacher_forced(cfg, w, dec, prompts[0], TOL["bf16"], max_steps=2) if len(plens) == 1 else
+         run_teacher_forced_batch(cfg, w, dec, prompts, TOL["bf16"], max_steps=2))
     print(s)
     assert s["modes"][eco.FULL] == len(plens) and s["rows_stat"] > 0
 
@@ -942,12 +954,13 @@ def test_attention_scores_that_keep_growing(P, gain):
     assert s["tokens_exact"] > 0
 
 
-@pytest.mark.parametrize("hq,hkv,hd,P,batch", [
-    (4, 2, 64, 70, 1), (4, 4, 128, 900, 1), (8, 2, 128, 2600, 1),   # one visit, key slices over blocks
-    (16, 4, 64, 300, 16),                                           # a batch: one block per (sequence, head)
+@pytest.mark.parametrize("hq,hkv,hd,P,batch,tiles", [
+    (4, 2, 64, 70, 1, 8), (4, 4, 128, 900, 1, 8), (8, 2, 128, 2600, 1, 8),   # one visit, key slices over blocks
+    (16, 4, 64, 300, 16, 8),                        # a batch: one block per (sequence, head)
+    (32, 8, 128, 2100, 1, 12), (64, 8, 64, 1060, 1, 12),   # full steps with three tiles a wave
 ])
 @pytest.mark.parametrize("gain", [4.0, 30.0, 300.0])
-def test_attention_weights_sum_to_one(hq, hkv, hd, P, batch, gain):
+def test_attention_weights_sum_to_one(hq, hkv, hd, P, batch, tiles, gain):
     """With one and the same embedding for every token all values are equal, and attention returns that
     value whatever the scores are: the weights' sum is one to float32 rounding (at most T + 32 roundings
     of 2^-24, far inside half a bf16 step), so the logits are those of a model with zero queries, bit
@@ -958,6 +971,7 @@ def test_attention_weights_sum_to_one(hq, hkv, hd, P, batch, gain):
     w["tok_emb"][:] = w["tok_emb"][0]
     dec = ec_inputs.DecodeCfg(batch=batch, gen_len=48, block=20, k_recent=2, tokens_per_step=1, tau=1e9)
     prompts = [ec_inputs.make_prompt(cfg.vocab, P + b, 7) for b in range(batch)]
+    assert full_step_attn_tiles(cfg, [P + b + 48 for b in range(batch)]) == tiles
     got = []
     for c in (0.0, gain):
         wc = dict(w, wq=[ec_inputs.f32_to_bf16_bits(bf16_bits_to_f32(w["wq"][0]) * np.float32(c))])
