@@ -443,7 +443,8 @@ __global__ __launch_bounds__(KS * 64, skinny_waves(EPI, MT)) void gemm_bf16_skin
                                                 : vt_pack(vt_identity());
     }
     __syncthreads();
-    // (a lane for every tuple; whole waves, so that a row's lanes are there together)
+    // (a lane for every tuple; a row's are neighbours and NTW divides the lanes there are - a multiple of 64, or 32 with one
+    // row tile and two weight tiles - so they are there together)
     for (int o = threadIdx.x; o < MT * 16 * NTW; o += KS * 64) {
       const int m = o / NTW;
       const VTuple t = vt_merge_lanes<NTW>(vt_unpack(tup[o % NTW * (MT * 16) + m]));
@@ -995,8 +996,8 @@ static int meet_grid(int tiles, int Z) {
 // ---------------------------------------------------------------------------------------------
 // tiled, 4 waves (2x2): wave tile = WTM x WTN fragments, K step 32.  Operands are double-buffered
 // in LDS; global loads run through four register sets, four k-steps ahead.  For the blocks of
-// residual products that are too small to keep eight waves busy (128 x 128 and 96 x 128; at 192 x 192 and 192 x 128 eight waves take 0.53 and 0.46
-// us a k-step, four 0.64 and 0.55).
+// residual products that are too small to keep eight waves busy (128 x 128 and 96 x 128; at 192 x 192 and 192 x 128
+// eight waves take 0.53 and 0.46 us a k-step, four 0.64 and 0.55).
 // grid = (ceil(n-tiles / (2*WTN)), ceil(m-tiles / (2*WTM))); K split over Z > 1 blocks: meet_grid()
 // ---------------------------------------------------------------------------------------------
 #define EC_TILED_GLOAD(REGS, KBV)                                                   \
@@ -1132,7 +1133,7 @@ static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // activation fragments and the last weight fragment have a second set.  Reads and MFMAs of a
 // k-step one after the other leave the matrix cores idle for the reads (96 KiB at 128 B a clock
 // for 192 x 384) and all of a step's reads ahead of its MFMAs hold up the issue of the latter.
-// What bounds the loop is power: products of random operands alone hold 1.94 GHz and 1.94 PFLOP/s, with the reads
+// What bounds the loop is power: products of random operands alone hold 1.94 GHz and 1.95 PFLOP/s, with the reads
 // and loads the clock settles at 1.7 - 1.8.  So what a k-step costs in cycles matters (256 x 256: 1024 of
 // MFMAs, 1160 in all) and what it moves.  Against a ring of three that the barrier drains of LDS reads, with an uneven
 // number of loads a wave and their addresses in vector registers: 1252 -> 1160 cycles a k-step for 256 x 256, 1564 ->
@@ -1140,7 +1141,7 @@ static void launch_tiled4_t(const bf16_t* Ap, int MT, const bf16_t* Wp, int tota
 // 3390; whole full steps take 2.3 - 3.8 % less.
 // Measured and left out, as slower: weights straight to registers, 8 waves side by side (less LDS traffic; 5 - 15 %); 4
 // waves of 128 x 128 (a third less LDS traffic, 1.90 GHz, but 1270 cycles and a longer epilogue); s_setprio around the MFMAs
-// (5 % more cycles); v_mfma_f32_32x32x16 (1.70 PFLOP/s alone).
+// (5 % more cycles); v_mfma_f32_32x32x16 (1.78 PFLOP/s alone).
 constexpr int kRing = 4;   // k-steps in LDS
 // bytes of LDS: the operand ring or, if larger, the rotation factors of the rows (hd 128) in its place, and the rows
 template <int EPI, int WM, int WN, int WTM, int WTN>

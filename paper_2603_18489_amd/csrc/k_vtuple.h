@@ -37,8 +37,8 @@ __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
 }
 
 // Tuple of NE * 64 consecutive logits held by one wave (lane l: elements first + 64 u + l, -inf for
-// those past the end).  The maximum comes first, so every logit then costs one exponential and no branch.  A logit of -inf has probability 0 and contributes 0 (0 ln 0 := 0); a
-// NaN makes the sums NaN.  All lanes return the same tuple.
+// those past the end).  The maximum comes first, so every logit then costs one exponential and no branch.  A logit of
+// -inf has probability 0 and contributes 0 (0 ln 0 := 0); a NaN makes the sums NaN.  All lanes return the same tuple.
 template <int NE>
 __device__ __forceinline__ VTuple vt_of_wave(const float (&z)[NE], int first) {
   static_assert(NE % 4 == 0, "taken four at a time");
