@@ -186,7 +186,7 @@ __device__ __forceinline__ VTuple merge_row_parts(const float4* __restrict__ pr,
     if (bm > v.m) {
       if (v.s != 0.f) {
         const float d = v.m - bm, e = __expf(d);
-        v.t = e * (v.t + d * v.s);
+        v.t = vt_rebased_t(v.s, v.t, d, e);
         v.s *= e;
       }
       v.m = bm;

@@ -21,6 +21,10 @@ struct VTuple {
 
 __device__ __forceinline__ VTuple vt_identity() { return {-INFINITY, INT_MAX, 0.f, 0.f}; }
 
+// sum e^(z-m') (z-m') of a tuple for a maximum m' = m - d no smaller than its own, e = e^d.  Where e is 0 so is the sum, also when d
+// times s is past the type's range (parts of a row at its lowest value, as masks leave them); -200 is past the last e that is not.
+__device__ __forceinline__ float vt_rebased_t(float s, float t, float d, float e) { return e * (t + fmaxf(d, -200.f) * s); }
+
 // Associative merge: re-base both sides to the common maximum.
 __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
   if (b.s == 0.f) return a;
@@ -32,7 +36,7 @@ __device__ __forceinline__ VTuple vt_merge(const VTuple& a, const VTuple& b) {
   float da = a.m - r.m, db = b.m - r.m;  // <= 0
   float ea = expf(da), eb = expf(db);
   r.s = a.s * ea + b.s * eb;
-  r.t = ea * (a.t + da * a.s) + eb * (b.t + db * b.s);
+  r.t = vt_rebased_t(a.s, a.t, da, ea) + vt_rebased_t(b.s, b.t, db, eb);
   return r;
 }
 
@@ -119,7 +123,7 @@ template <int N> __device__ __forceinline__ VTuple vt_merge_lanes(const VTuple& 
   if (N > 16) idx = min(idx, __float_as_int(other_row(__int_as_float(idx))));
   r.idx = idx;
   const float d = v.m - r.m, e = expf(d);
-  float s = v.s != 0.f ? v.s * e : 0.f, t = v.s != 0.f ? e * (v.t + d * v.s) : 0.f;
+  float s = v.s != 0.f ? v.s * e : 0.f, t = v.s != 0.f ? vt_rebased_t(v.s, v.t, d, e) : 0.f;
   s += dpp_f<0xB1>(s); t += dpp_f<0xB1>(t);
   if (N > 2) { s += dpp_f<0x4E>(s); t += dpp_f<0x4E>(t); }
   if (N > 4) { s += dpp_f<0x141>(s); t += dpp_f<0x141>(t); }

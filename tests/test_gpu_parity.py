@@ -544,6 +544,33 @@ def test_rows_with_an_infinite_maximum_take_token_0(dtype, batch, block):
     assert not s[:, :2].any() and np.isinf(s[:, 2]).all()
 
 
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("dtype,batch,block", [
+    ("bf16", 1, 24), ("f32", 1, 24), ("bf16", 2, 48),   # reduced in the LM head; over 64 rows, from stored logits
+])
+def test_logits_far_apart_are_a_distribution(dtype, batch, block, sign):
+    """Half of the vocabulary at logits around 1e36, either sign, with the other half near 0: finite logits, of which the lower half counts
+    nothing.  The decision's statistics are those of the step's own logits in 64 bits, but for the float32 sums, a fast exponential of
+    4e-6 at most (arguments down to -87) and their rounding: under 1e-5."""
+    cfg = small_cfg(dtype, 4, 2, 64, vocab=8192)
+    w = ec_inputs.make_weights(cfg, 61, gain_jitter=0.1)
+    w["lm_head"] = w["lm_head"].copy()
+    w["lm_head"][2048:6144, 7] = sign * 1e36 if dtype == "f32" else (0x7B41 if sign > 0 else 0xFB41)   # 1.002e36
+    dec = ec_inputs.DecodeCfg(gen_len=block, block=block, k_recent=2, tokens_per_step=2, tau=2.5, batch=batch)
+    prompts = [ec_inputs.make_prompt(cfg.vocab, 9 + 5 * b, 70 + b) for b in range(batch)]
+    g = ec.EntropyCache(cfg, ec.weights_to_device(cfg, w), dec, prompts if batch > 1 else prompts[0])
+    g.keep_logits(True)
+    g.step(ec.EC_FULL)
+    for b in range(batch):
+        z = g.debug_read(ec.EC_DBG_LOGITS, seq=b, count=block).astype(np.float64)
+        assert np.isfinite(z).all() and np.ptp(z, axis=1).min() > 1e34
+        s = g.debug_read(ec.EC_DBG_ROW_STATS, seq=b, count=block)
+        ref = np.array([eco.softmax_stats(r) for r in z])
+        assert np.array_equal(s[:, 0], ref[:, 0])
+        assert np.allclose(s[:, 1], ref[:, 1], rtol=1e-5) and np.allclose(s[:, 2], ref[:, 2], rtol=1e-5, atol=1e-5)
+    g.close()
+
+
 @pytest.mark.parametrize("batch,gen_len,n", [(1, 1024, 32), (16, 512, 32), (64, 96, 7)])
 def test_every_result_is_whole_when_its_step_returns(batch, gen_len, n):
     """A step returns as soon as the host sees its serial number in pinned memory.  The lists that it hands over then are the step's

@@ -179,3 +179,21 @@ def test_row_entropy_errors_have_no_side(V):
     err = torch.cat(err)
     print(err.mean().item(), err.square().mean().sqrt().item(), err.abs().max().item())
     assert abs(err.mean().item()) < 1e-8
+
+
+@pytest.mark.parametrize("V", [4096, 16384, 50000, 163840])
+def test_row_entropy_of_logits_masked_with_the_lowest_value(V):
+    """Whole parts of 2048 logits at the type's lowest finite value (a vocabulary mask), before, behind and around the others, in the
+    one-launch and the two-launch form: they have probability 0 and contribute nothing.  Bounds as above."""
+    rng = np.random.default_rng(V)
+    z = (rng.standard_normal((4, V)) * 2.0).astype(np.float32)
+    low = np.finfo(np.float32).min
+    z[0, 2048:] = low
+    z[1, :V - 1000] = low
+    z[2, :V // 4] = z[2, V // 2:] = low
+    z[3, :V // 2] = -3.0e37                    # (times 2048 it is past the type's range)
+    got = ec.row_entropy(torch.from_numpy(z).cuda()).cpu().numpy().astype(np.float64)
+    ref = oracle_stats(z)
+    assert np.array_equal(got[:, 0], ref[:, 0]) and np.array_equal(got[:, 3], ref[:, 3])
+    assert np.abs(got[:, 1] / ref[:, 1] - 1.0).max() <= 4e-6
+    assert np.abs(got[:, 2] - ref[:, 2]).max() <= 4e-6 * math.log(V)
